@@ -31,12 +31,13 @@ if ROOT not in sys.path:
 # MI355X: 256 CUs x 64 lanes x 2.4 GHz of 32-bit / non-packed FP64 VALU issue
 # (each CU issues one 64-lane VALU instruction per clock: 4 SIMDs, 4 clocks each).
 PEAK_LANE_OPS = 256 * 64 * 2.4e9
-# MI355X dense int8 matrix-core peak (v_mfma_i32_*_i8), ops/s (a multiply-add is 2).
-PEAK_INT8_OPS = 5.0e15
-# int8 ops of the split path's linear part per (element, neighbour) term: one
-# multiply-add per digit of the quantized coefficient (8 digits).
-LIN_OPS_PER_TERM = 2 * 8
-# Shortest walk the split evaluation takes, and the fewest nominal updates of a
+# MI355X dense FP4/FP6 matrix-core peak (v_mfma_f32_*_f8f6f4), FLOP/s (a multiply-add is 2).
+PEAK_FP4_OPS = 1.0e16
+# FLOPs of the matrix path per nominal C_k-update: an element j takes two products per
+# both-neighbour shift and one per one-neighbour shift, 2 min(j, L-1-j) + |L-1-2j| = L-1 in
+# all, each with 16 digit columns.
+MX_OPS_PER_UPDATE = 2 * 16
+# Shortest walk the matrix path takes, and the fewest nominal updates of a
 # launch that takes it by default.
 SPLIT_MIN_L = 2048
 SPLIT_MIN_WORK = 1 << 34
@@ -126,7 +127,7 @@ def parse():
     ap.add_argument("--autotune", action="store_true",
                     help="time every evaluation launch shape on the batch first and keep the fastest")
     ap.add_argument("--split", type=int, default=-1, choices=[-1, 0, 1, 2],
-                    help="split evaluation (linear part on the matrix cores): -1 the library default "
+                    help="matrix path of the evaluation: -1 the library default "
                          "(2: for launches of at least 2^34 nominal updates), 0 off (table evaluation), "
                          "1 wherever L >= 2048")
     ap.add_argument("--tune-file", default="", help="evaluation launch shapes to load (psl_tune_load)")
@@ -670,17 +671,17 @@ def main():
                      "basis": "no SQ_INSTS_VALU record for these kernel sources and this workload"}
     roof_lin = None
     if split_on and lin_avg_s > 0:
-        # algorithmic int8 ops of one launch: every (element, neighbour) term
-        # of the evaluated elements of the split walks, 8 digit products each
-        ops = LIN_OPS_PER_TERM * split_work
-        roof_lin = {"kernel": "k_lin", "bound": "mfma", "achieved": ops / lin_avg_s / 1e12,
-                    "peak": PEAK_INT8_OPS / 1e12, "unit": "TOP/s", "frac": ops / lin_avg_s / PEAK_INT8_OPS,
-                    "traffic": measured_traffic(tag, "k_lin"), "traffic_unit": "B/launch",
+        # digit products of one launch over the evaluated elements of the matrix walks
+        ops = MX_OPS_PER_UPDATE * split_work
+        roof_lin = {"kernel": "k_mx", "bound": "mfma", "achieved": ops / lin_avg_s / 1e12,
+                    "peak": PEAK_FP4_OPS / 1e12, "unit": "TFLOP/s", "frac": ops / lin_avg_s / PEAK_FP4_OPS,
+                    "traffic": measured_traffic(tag, "k_mx"), "traffic_unit": "B/launch",
                     "ops_per_launch": ops,
-                    "basis": "16 int8 ops (8 digit multiply-adds) per (element, neighbour) term of the "
-                             "linear part / the launch time measured here, against the dense int8 peak"}
+                    "basis": "32 FLOPs (16 digit multiply-adds) per element and coefficient / the launch "
+                             "time measured here, against the dense FP4/FP6 peak"}
     roofline = roof_eval if roof_lin is None or eval_avg_s >= lin_avg_s else roof_lin
-    direct = OPS_PER_UPDATE_DIRECT * updates_per_step / eval_avg_s
+    eval_s = eval_avg_s + lin_avg_s       # table evaluation and matrix products
+    direct = OPS_PER_UPDATE_DIRECT * updates_per_step / eval_s
     tiles, ks = ctx.eval_shape(L, n_lmt, nw)
     names = {"batched": "batched uniform", "single": "single walk", "large": "large single instance",
              "uneven": "uneven batch", "paper": "paper settings (Table 4)"}
@@ -710,20 +711,21 @@ def main():
         "C_k_updates_per_s": updates_per_step * args.steps / el,
         "C_k_updates_explicit": explicit_updates(groups, wl, args.n_lmt, updates_per_step, args.steps, el),
         "eval_kernel": {"avg_ms": eval_avg_s * 1e3, "launches": tm["eval_launches"],
-                        "updates_per_s": updates_per_step / eval_avg_s,
+                        "updates_per_s": updates_per_step / eval_s,
                         "split": split_on,
-                        "split_prep_avg_ms": prep_avg_s * 1e3, "lin_avg_ms": lin_avg_s * 1e3,
+                        "split_prep_avg_ms": prep_avg_s * 1e3, "matrix_avg_ms": lin_avg_s * 1e3,
                         "rest_of_step_avg_ms": tm["rest_ms"] / max(1, tm["steps"])},
         "roofline": roofline,
         "roofline_by_kernel": [r for r in (roof_eval, roof_lin) if r is not None],
         "vs_direct_form": {"direct_lane_ops_per_update": OPS_PER_UPDATE_DIRECT,
-                           "nominal_updates_per_s": updates_per_step / eval_avg_s,
+                           "nominal_updates_per_s": updates_per_step / eval_s,
                            "ceiling_updates_per_s": PEAK_LANE_OPS / OPS_PER_UPDATE_DIRECT,
                            "ratio": direct / PEAK_LANE_OPS,
                            "lane_ops_per_nominal_update": (valu * 64 / updates_per_step) if valu else None,
                            "note": "nominal C_k-updates/s of the evaluation against the ceiling of the "
-                                   "direct form (4 VALU lane-ops per update); above 1 because the kernel "
-                                   "skips the unchanged shifts and resolves 2 or 4 shifts per table lookup"},
+                                   "direct form (4 VALU lane-ops per update); above 1 because the kernels "
+                                   "skip the unchanged shifts and take the rest in table lookups of 2 or 4 "
+                                   "shifts or in matrix products"},
         "walk0_after": {"t": st["t"], "psl_best": st["psl_best"], "alpha": st["alpha"]},
     }
     if whole is not None:

@@ -326,8 +326,8 @@ typedef struct {
     uint64_t eval_launches;
     double   rest_ms;        /* total time of the rest of each step               */
     uint64_t steps;
-    double   prep_ms;        /* split evaluation: its per-step preparation        */
-    double   lin_ms;         /* split evaluation: the matrix-core linear sums     */
+    double   prep_ms;        /* matrix path: its per-step preparation             */
+    double   lin_ms;         /* matrix path: the matrix products                  */
 } psl_timing;
 
 /* on != 0: start recording (counters reset); on == 0: stop. */
@@ -392,11 +392,11 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
  * relative, and of an exact summation). Only the flags change: the moves are
  * the band rule's whatever the margin. Errors: PSL_E_INVAL outside the range. */
 #define PSL_OPT_AMBIG_MARGIN 3
-/* PSL_OPT_SPLIT: the split evaluation (Eq. (5) expanded exactly in the +-1
- * neighbours of Section 3's one-element flip: the linear part of F_j as exact
- * integer sums on the matrix cores, the both-neighbour remainder on the
- * vector units) for walks of L >= 2048, in the steps that allow it (the
- * near-peak list holds the PSL and the quantization bound of the linear part
+/* PSL_OPT_SPLIT: the matrix path of the evaluation (Eq. (5) over the
+ * neighbours as 0/1 matrices, the XOR and AND of the two neighbours of
+ * Section 3's one-element flip, times fixed-point coefficients, summed exactly
+ * on the matrix cores) for walks of L >= 2048, in the steps that allow it (the
+ * near-peak list holds the PSL and the quantization bound of the coefficients
  * is below 1e-14 of every neighbour's F). 2 (default; -1 restores it): in
  * batches and evaluations whose walks of L >= 2048 hold at least 2^34
  * nominal updates (N_lmt x (L-1) summed), below which its fixed cost exceeds

@@ -121,17 +121,4 @@ __device__ __forceinline__ void seg_of(const SegMap &m, uint32_t i, uint32_t &b,
     seg = i - m.off[lo];
 }
 
-
-// The last both-neighbour shift of the aligned 64-element block holding j:
-// min over j' of the block of min(j', L-1-j') (a tent function, so the
-// minimum over an interval is at one of its ends). A 32-shift chunk
-// 1+32c .. 32+32c is "covered" for the block when it ends at or below this
-// bound; the linear items then use B_k for it instead of B'_k (psl_split.hip
-// makes the same choice per block and chunk).
-__device__ __forceinline__ int split_block_bound(int j, int L)
-{
-    const int j0 = j & ~63, j1 = min(j0 + 63, L - 1);
-    return min(min(j0, L - 1 - j0), min(j1, L - 1 - j1));
-}
-
 }  // namespace psl

@@ -116,11 +116,12 @@ struct BatchPlan {
     SegMap seg{};
     // split evaluation (walks with BatchEntry.lsplit > 0)
     bool split = false;               // some walk of the plan can take the split path
-    int8_t *d_limbs = nullptr;
-    double *d_dq = nullptr, *d_pre = nullptr, *d_lpart = nullptr;
+    uint8_t *d_dig = nullptr;
+    double *d_pre = nullptr, *d_lpart = nullptr;
     SplitState *d_ss = nullptr;
-    EvalItem *d_litems = nullptr;     // linear items
-    uint32_t n_litems = 0;
+    EvalItem *d_mitems = nullptr;     // matrix items
+    uint32_t n_mitems = 0;
+    uint32_t *d_tab = nullptr;        // walks left to the table evaluation in this step
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -131,8 +132,8 @@ constexpr uint32_t kEvalItemsMax = 1u << 18;    // and its largest value
 constexpr int64_t kAmbigMarginMax = 1000000000000000ll;  // PSL_OPT_AMBIG_MARGIN: 1.0 in units of 1e-15
 constexpr uint32_t kSplitMinL = 2048;          // shortest walk the split evaluation takes
 constexpr uint64_t kSplitMinWork = 1ull << 34; // fewest nominal updates of a launch that takes it
-constexpr uint32_t kLinItemsTarget = 8192;     // linear items per launch the k-splits aim for
-constexpr uint32_t kLinMinChunks = 256;         // fewest shift chunks per k-split of a linear item
+constexpr uint32_t kMxItemsTarget = 4096;      // matrix items per launch the k-splits aim for
+constexpr uint32_t kMxMinChunks = 32;           // fewest shift chunks per k-split of a matrix item
 
 
 struct Server;   // serving loop (psl_serve.hip)

@@ -426,11 +426,13 @@ __device__ __forceinline__ void chunk_octs(const BatchEntry &be, const WalkDev &
 // Mode 0 (step, with the near list) and 2 (init): one block per segment of
 // the map.
 __global__ __launch_bounds__(kChunkThreads) void k_chunks(const WalkDev *walks, const BatchEntry *batch,
-                                                          Tables tabs, int mode, SegMap map, uint32_t *pend)
+                                                          Tables tabs, int mode, SegMap map, uint32_t *pend,
+                                                          uint32_t *tab)
 {
     // the previous step's pending list has been consumed; this step's
     // bookkeeping (in the selection) refills it
     if (pend && blockIdx.x == 0 && threadIdx.x == 0) pend[0] = 0;
+    if (tab && blockIdx.x == 0 && threadIdx.x == 0) tab[0] = 0;
     const int wave = (int)threadIdx.x >> 6;
     constexpr int kWaves = kChunkThreads / 64;
     uint32_t b, seg;
@@ -938,6 +940,26 @@ __device__ __forceinline__ void bookkeep_walk(WalkDev &w, uint32_t bi, uint32_t 
     }
 }
 
+// The largest |C'_k| of element j's flip over the near-peak shifts list[g],
+// list[g + G], ..
+__device__ __forceinline__ uint32_t near_peak(const uint32_t *__restrict__ list, uint32_t n, const int32_t *__restrict__ C,
+                                              const uint32_t *__restrict__ w32, int L, int j, uint32_t g, uint32_t G)
+{
+    const uint32_t sj = (w32[j >> 5] >> (j & 31)) & 1u;
+    int peak = 0;
+#pragma unroll 4
+    for (uint32_t q = g; q < n; q += G) {
+        const int k = (int)list[q];
+        int c = C[k];
+        const int pr = j + k, pl = j - k;            // the guard words hold every index
+        const uint32_t wr = w32[pr >> 5], wl = w32[pl >> 5];
+        if (pr < L) c += (((wr >> (pr & 31)) & 1u) ^ sj) ? 2 : -2;
+        if (pl >= 0) c += (((wl >> (pl & 31)) & 1u) ^ sj) ? 2 : -2;
+        peak = max(peak, c < 0 ? -c : c);
+    }
+    return (uint32_t)peak;
+}
+
 // F and PSL per candidate from the k-split partials, spread over gridDim.x
 // blocks per walk (blockIdx.y = batch position); each block leaves its
 // smallest F and its first smallest PSL in be.red. A group of G lanes
@@ -970,12 +992,13 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
     static_assert(kCombThreads == 256, "four wavefronts per combine block");
     __shared__ double s_wf[4][32];
     __shared__ uint32_t s_wm[4][32];
-    // split path: the partials hold the VALU terms only; the prefix sums and
-    // the linear sums (psl_split.hip) supply the rest of F_j
+    // matrix path: F_j from the prefix sums and the matrix sums (psl_split.hip),
+    // PSL_j from the near-peak shifts here
     const bool split = be.lsplit != 0 && be.ss->use != 0;
     const double U = split ? be.ss->U : 0.0;
     const uint32_t start = be.fixed ? be.start : step_start(w);
     const uint32_t L = w.L;
+    const uint32_t n_near = split ? be.near[0] : 0;
 
     double fmin = INFINITY;
     int32_t pmin = INT_MAX;
@@ -986,7 +1009,14 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
         const uint32_t i = i0 + ci;
         double f = 0.0;
         uint32_t m = 0;
-        if (i < hi) {
+        if (split) {
+            if (i < hi) {
+                const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
+                for (uint32_t x = g; x < be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
+                m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
+                              (uint32_t)G);
+            }
+        } else if (i < hi) {
             // up to kCombBatch of this lane's splits are loaded before they
             // are added (in split order)
             for (uint32_t x0 = g; x0 < ks; x0 += (uint32_t)G * kCombBatch) {
@@ -1040,16 +1070,12 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
             // because |C'_{L-1}| = 1 for every sequence
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
             if (split) {
-                // F_j = sum_{k<=m} A_k + sum_{m<k<=M} A'_k + sum_{k>M} T(|C_k|)
-                //       - s_j U (linear sums) + the VALU terms, m = min(j, L-1-j)
+                // F_j = sum_{k<=m} T(|C_k-4|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
+                //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
                 const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
-                const double *pa = be.pre, *pa1 = be.pre + L, *pt = be.pre + 2 * (size_t)L;
-                const double cst = pa[mj] + (pa1[Mj] - pa1[mj]) + (pt[L - 1] - pt[Mj]);
-                double lin = 0.0;
-                for (uint32_t x = 0; x < be.lsplit; ++x) lin += be.lpart[(size_t)x * L + j];
-                const double sgn = get_bit(w.pivot, j) ? U : -U;     // -s_j U
-                f = cst + sgn * lin + f;
+                const double *p1 = be.pre + (size_t)L * (get_bit(w.pivot, j) ? 2 : 1), *pt = be.pre + 3 * (size_t)L;
+                f = be.pre[mj] + (p1[Mj] - p1[mj]) + (pt[L - 1] - pt[Mj]) + U * f;
             }
             be.F[i] = f;
             be.P[i] = p;
@@ -1248,7 +1274,8 @@ hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, 
 }
 
 hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan, hipStream_t s)
+                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan, uint32_t *tab,
+                         hipStream_t s)
 {
     if (mode != 0 && mode != 2) return hipErrorInvalidValue;
     if (!map || map->total == 0 || map->nb != nb || map->shift < kSegShiftMin || map->shift > kSegShiftMax)
@@ -1257,7 +1284,7 @@ hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, u
     if (scan && (!map->tot || !map->tmax)) return hipErrorInvalidValue;
     SegMap m = *map;
     if (!scan) m.tot = nullptr, m.tmax = nullptr;
-    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, mode, m, mode == 0 ? pend : nullptr);
+    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, mode, m, mode == 0 ? pend : nullptr, tab);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (scan) {

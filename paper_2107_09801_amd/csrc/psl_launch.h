@@ -20,17 +20,19 @@ hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, 
                           const Tables &tabs, const uint32_t *pend, hipStream_t s);
 hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
                           int mode, hipStream_t s);
+// tab (batches with a matrix path): the number of the batch's walks left to
+// this evaluation in this step; with none, its blocks return at once.
 hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items,
                        uint32_t n_items, const Tables &tabs, const EvalShape &shape,
-                       EvalQueues *queues, hipStream_t s);
+                       EvalQueues *queues, const uint32_t *tab, uint32_t n_cu, hipStream_t s);
 // mode 0: the step's chunk arrays and near-peak list (and, with pend, the
-// step's pending list emptied), turned into suffix values when scan != 0 (the
+// step's pending list emptied; with tab, *tab zeroed), turned into suffix values when scan != 0 (the
 // evaluation in 16-wavefront blocks reads those; smaller blocks add the chunk
 // values themselves); mode 2: the initial fitness (value_local, F_pivot,
 // psl_pivot, psl_best) of every walk.
 hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
                          const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan,
-                         hipStream_t s);
+                         uint32_t *tab, hipStream_t s);
 // Zero the near-peak counts of a batch, its pending count and its combine
 // counters (done, nb entries; may be null) after its scratch is allocated.
 hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done, hipStream_t s);
@@ -55,13 +57,13 @@ hipError_t launch_flip_bit(WalkDev *walks, const BatchEntry *batch, uint32_t j, 
 // Units of launch_pending for walks of length L.
 inline uint64_t pending_units(uint32_t L) { return (L - 1 + kPendUnit - 1) / kPendUnit; }
 
-// Split evaluation (psl_split.hip): the step's coefficients, digits, prefix
-// sums, scale and path choice of the batch's split walks (after the suffix
-// pass, before the evaluation), and the matrix-core linear sums (items:
-// walk, 512-element block, k-split).
+// Matrix path (psl_split.hip): the step's coefficients, digits, prefix sums,
+// scale and path choice of the batch's split walks (after the suffix pass,
+// before the evaluation; *tab counts the walks left to the table evaluation),
+// and the matrix products (items: walk, kMxTile-element tile, k-split).
 hipError_t launch_split_prep(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                             const SegMap &map, hipStream_t s);
-hipError_t launch_lin(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
-                      hipStream_t s);
+                             const SegMap &map, uint32_t *tab, hipStream_t s);
+hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
+                     hipStream_t s);
 
 }  // namespace psl

@@ -138,12 +138,12 @@ void plan_free(psl_ctx *ctx, BatchPlan &pl)
     dev_free(ctx, pl.d_segmax, false);
     dev_free(ctx, pl.d_near, false);
     dev_free(ctx, pl.d_queues, false);
-    dev_free(ctx, pl.d_limbs, false);
-    dev_free(ctx, pl.d_dq, false);
+    dev_free(ctx, pl.d_dig, false);
     dev_free(ctx, pl.d_pre, false);
     dev_free(ctx, pl.d_lpart, false);
     dev_free(ctx, pl.d_ss, false);
-    dev_free(ctx, pl.d_litems, false);
+    dev_free(ctx, pl.d_mitems, false);
+    dev_free(ctx, pl.d_tab, false);
     pl = BatchPlan();
 }
 
@@ -332,6 +332,93 @@ EvalShape pick_shape(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl,
     return sh;
 }
 
+// Selection: a group of G lanes per candidate with about 16 splits per lane,
+// about 2048 partials per combine block, at most one block per block-pass of
+// candidates.
+static void comb_shape(const uint32_t *ks, const uint32_t *nl, uint32_t n, uint32_t *blocks, uint32_t *group)
+{
+    uint64_t work = 0, nmax = 0, ksmax = 1;
+    for (uint32_t b = 0; b < n; ++b) {
+        work = std::max<uint64_t>(work, (uint64_t)ks[b] * nl[b]);
+        nmax = std::max<uint64_t>(nmax, nl[b]);
+        ksmax = std::max<uint64_t>(ksmax, ks[b]);
+    }
+    uint32_t G = 1;
+    while (G < 64 && (uint64_t)G * 16 < ksmax) G <<= 1;
+    *group = G;
+    const uint64_t cpb = 256 / G;
+    // up to two blocks' worth of partials per walk: one block, which then
+    // also makes the selection (no separate selection launch)
+    *blocks = work <= 16384 ? 1u
+                            : (uint32_t)std::max<uint64_t>(
+                                  1, std::min<uint64_t>({(work + 2047) / 2048, (nmax + cpb - 1) / cpb,
+                                                         (uint64_t)kCombMaxBlocks}));
+}
+
+// Bytes of a walk's digit records.
+static size_t dig_bytes(uint32_t L)
+{
+    return (size_t)kRecBytes * (split_chunks(L) + kRecPad + 2 * (split_both_chunks(L) + kRecPad));
+}
+
+// The matrix path's k-splits per walk (0: none) and items in launch order.
+static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl, uint32_t n, std::vector<uint32_t> &lsp,
+                      std::vector<EvalItem> &items)
+{
+    uint64_t work = 0, tiles = 0;
+    std::vector<uint32_t> nq(n, 0);
+    for (uint32_t b = 0; b < n; ++b) {
+        if (Ls[b] < kSplitMinL) continue;
+        work += (uint64_t)nl[b] * (Ls[b] - 1);
+        // tiles that nl[b] consecutive elements can touch, the last tile of
+        // the sequence possibly short
+        nq[b] = std::min<uint32_t>((Ls[b] + kMxTile - 1) / kMxTile, (nl[b] + kMxTile - 1) / kMxTile + 2);
+        tiles += nq[b];
+    }
+    if (!tiles || !(ctx->split_mode == 1 || (ctx->split_mode == 2 && work >= kSplitMinWork))) return;
+    struct Piece {
+        uint32_t b, first, count;   // items first .. first+count-1 of walk b (tile-major, k-split minor)
+        uint64_t cost;
+    };
+    std::vector<Piece> pieces;
+    std::vector<uint64_t> item_cost(n, 0);
+    uint64_t total = 0;
+    for (uint32_t b = 0; b < n; ++b) {
+        if (!nq[b]) continue;
+        const uint32_t nco = split_chunks(Ls[b]);
+        const uint64_t want = (kMxItemsTarget + tiles - 1) / tiles;
+        lsp[b] = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, nco / kMxMinChunks));
+        item_cost[b] = (nco + lsp[b] - 1) / lsp[b];
+        total += item_cost[b] * nq[b] * lsp[b];
+    }
+    const uint64_t cap = std::max<uint64_t>(1, total / 16);
+    for (uint32_t b = 0; b < n; ++b) {
+        if (!nq[b]) continue;
+        const uint32_t cnt = nq[b] * lsp[b];
+        const uint64_t cost = item_cost[b] * cnt;
+        const uint32_t np = (uint32_t)std::min<uint64_t>(cnt, (cost + cap - 1) / cap);
+        for (uint32_t p = 0; p < np; ++p) {
+            const uint32_t lo = (uint32_t)((uint64_t)cnt * p / np), hi = (uint32_t)((uint64_t)cnt * (p + 1) / np);
+            pieces.push_back(Piece{b, lo, hi - lo, item_cost[b] * (hi - lo)});
+        }
+    }
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &c) { return a.cost > c.cost; });
+    std::vector<EvalItem> xq[kXcds];
+    uint64_t load[kXcds] = {};
+    for (const Piece &pc : pieces) {
+        const int x = (int)(std::min_element(load, load + kXcds) - load);
+        for (uint32_t i = pc.first; i < pc.first + pc.count; ++i)
+            xq[x].push_back(EvalItem{pc.b, i / lsp[pc.b], i % lsp[pc.b], 0});
+        load[x] += pc.cost;
+    }
+    size_t rounds = 0;
+    for (int x = 0; x < kXcds; ++x) rounds = std::max(rounds, xq[x].size());
+    items.reserve(rounds * kXcds);
+    for (size_t r = 0; r < rounds; ++r)
+        for (int x = 0; x < kXcds; ++x)
+            items.push_back(r < xq[x].size() ? xq[x][r] : EvalItem{kMxNoWalk, 0, 0, 0});
+}
+
 void eval_layout(const uint32_t *Ls, const uint32_t *nl, uint32_t n, const EvalShape &shape,
                  uint32_t min_items, EvalLayout &out)
 {
@@ -375,25 +462,7 @@ void eval_layout(const uint32_t *Ls, const uint32_t *nl, uint32_t n, const EvalS
         std::stable_sort(sg.begin(), sg.end(), [](const C &a, const C &b) { return a.cost > b.cost; });
         cmax = std::max(cmax, sg.size());
     }
-    // selection: a group of G lanes per candidate with about 16 splits per
-    // lane, about 2048 partials per combine block, at most one block per
-    // block-pass of candidates
-    uint64_t work = 0, nmax = 0, ksmax = 1;
-    for (uint32_t b = 0; b < n; ++b) {
-        work = std::max<uint64_t>(work, (uint64_t)out.ks[b] * nl[b]);
-        nmax = std::max<uint64_t>(nmax, nl[b]);
-        ksmax = std::max<uint64_t>(ksmax, out.ks[b]);
-    }
-    uint32_t G = 1;
-    while (G < 64 && (uint64_t)G * 16 < ksmax) G <<= 1;
-    out.comb_group = G;
-    const uint64_t cpb = 256 / G;
-    // up to two blocks' worth of partials per walk: one block, which then
-    // also makes the selection (no separate selection launch)
-    out.comb_blocks = work <= 16384 ? 1u
-                                    : (uint32_t)std::max<uint64_t>(
-                                          1, std::min<uint64_t>({(work + 2047) / 2048, (nmax + cpb - 1) / cpb,
-                                                                 (uint64_t)kCombMaxBlocks}));
+    comb_shape(out.ks.data(), nl, n, &out.comb_blocks, &out.comb_group);
     out.items.reserve(shape.persistent ? all.size() : 8 * cmax);
     for (int q = 0; q < 8; ++q) {
         auto &sg = seg[q];
@@ -446,6 +515,16 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
                 force_items ? force_items : items_for(ctx, Ls.data(), n_l.data(), n), lay);
     const std::vector<uint32_t> &tiles = lay.tiles, &ks = lay.ks;
     std::vector<EvalItem> &items = lay.items;
+    std::vector<uint32_t> lsp(n, 0);
+    std::vector<EvalItem> mitems;
+    if (!mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, mitems);
+    if (!mitems.empty()) {
+        // the combine adds a matrix walk's own partials
+        std::vector<uint32_t> cs(ks);
+        for (uint32_t b = 0; b < n; ++b)
+            if (lsp[b]) cs[b] = lsp[b];
+        comb_shape(cs.data(), n_l.data(), n, &lay.comb_blocks, &lay.comb_group);
+    }
     pl.shape = lay.shape;
     pl.comb_blocks = lay.comb_blocks;
     pl.comb_group = lay.comb_group;
@@ -514,100 +593,45 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         pl.seg.tot = pl.d_segtot;
         pl.seg.tmax = pl.d_segmax;
     }
-    // split evaluation: per walk of at least kSplitMinL elements (not for
-    // plans carved from fixed scratch, nor for launches with less work than
-    // kSplitMinWork nominal updates, where its fixed cost exceeds what it
-    // saves): its coefficient arrays, linear partials and linear items (walk,
-    // kLinBlockElems-element block, k-split). Workgroup i runs on XCD i mod 8:
-    // each walk's items (cost: the chunks of its k-split) form one piece, or
-    // several of consecutive items when the walk holds more than 1/16 of the
-    // launch's cost; the pieces are dealt to 8 queues (costliest first, each
-    // to the least loaded queue) and the launch order interleaves the queues,
-    // so XCD x takes queue x. A batch of many walks keeps each walk's items
-    // (and its digits in L2) on one XCD, and one long walk spreads over all
-    // eight; short queues are padded with kLinNoWalk items.
-    std::vector<uint32_t> lsp(n, 0);
-    std::vector<EvalItem> litems;
-    size_t n_limb = 0, n_dq = 0, n_pre = 0, n_lp = 0;
-    uint64_t split_work = 0;
-    for (uint32_t b = 0; b < n; ++b)
-        if (Ls[b] >= kSplitMinL) split_work += (uint64_t)n_l[b] * (Ls[b] - 1);
-    if (!mem && (ctx->split_mode == 1 || (ctx->split_mode == 2 && split_work >= kSplitMinWork))) {
-        uint64_t blocks = 0;
-        std::vector<uint32_t> nq(n, 0);
-        for (uint32_t b = 0; b < n; ++b) {
-            if (Ls[b] < kSplitMinL) continue;
-            const uint32_t nblk = (Ls[b] + kLinBlockElems - 1) / kLinBlockElems;
-            nq[b] = std::min<uint32_t>(nblk, (n_l[b] + kLinBlockElems - 1) / kLinBlockElems + 1);
-            blocks += nq[b];
-        }
-        struct Piece {
-            uint32_t b, first, count;   // items first .. first+count-1 of walk b (q-major, k-split minor)
-            uint64_t cost;
-        };
-        std::vector<Piece> pieces;
-        std::vector<uint64_t> item_cost(n, 0);
-        uint64_t total = 0;
-        for (uint32_t b = 0; b < n; ++b) {
-            if (!nq[b]) continue;
-            const uint32_t nchunks = (Ls[b] - 1 + 31) / 32;
-            const uint64_t want = (kLinItemsTarget + blocks - 1) / std::max<uint64_t>(blocks, 1);
-            lsp[b] = (uint32_t)std::max<uint64_t>(
-                1, std::min<uint64_t>(want, std::max<uint32_t>(1, nchunks / kLinMinChunks)));
-            item_cost[b] = (nchunks + lsp[b] - 1) / lsp[b];
-            total += item_cost[b] * nq[b] * lsp[b];
-            n_limb += 2 * (size_t)kLimbs * split_row(Ls[b]);
-            n_dq += 2 * (size_t)Ls[b];
-            n_pre += 3 * (size_t)Ls[b];
-            n_lp += (size_t)lsp[b] * Ls[b];
-        }
-        const uint64_t cap = std::max<uint64_t>(1, total / 16);
-        for (uint32_t b = 0; b < n; ++b) {
-            if (!nq[b]) continue;
-            const uint32_t items = nq[b] * lsp[b];
-            const uint64_t cost = item_cost[b] * items;
-            const uint32_t np = (uint32_t)std::min<uint64_t>(items, (cost + cap - 1) / cap);
-            for (uint32_t p = 0; p < np; ++p) {
-                const uint32_t lo = (uint32_t)((uint64_t)items * p / np), hi = (uint32_t)((uint64_t)items * (p + 1) / np);
-                pieces.push_back(Piece{b, lo, hi - lo, item_cost[b] * (hi - lo)});
-            }
-        }
-        std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &c) { return a.cost > c.cost; });
-        std::vector<EvalItem> xq[kXcds];
-        uint64_t load[kXcds] = {};
-        for (const Piece &pc : pieces) {
-            const int x = (int)(std::min_element(load, load + kXcds) - load);
-            for (uint32_t i = pc.first; i < pc.first + pc.count; ++i)
-                xq[x].push_back(EvalItem{pc.b, i / lsp[pc.b], i % lsp[pc.b], 0});
-            load[x] += pc.cost;
-        }
-        size_t rounds = 0;
-        for (int x = 0; x < kXcds; ++x) rounds = std::max(rounds, xq[x].size());
-        for (size_t r = 0; r < rounds; ++r)
-            for (int x = 0; x < kXcds; ++x)
-                litems.push_back(r < xq[x].size() ? xq[x][r] : EvalItem{kLinNoWalk, 0, 0, 0});
+    // matrix path: per walk of at least kSplitMinL elements (not for plans
+    // carved from fixed scratch, nor for launches with less work than
+    // kSplitMinWork nominal updates): its digit records, prefix and partial
+    // sums and matrix items (walk, tile, k-split). Workgroup i runs on XCD
+    // i mod 8: each walk's items (cost: the chunks of its k-split) form one
+    // piece, or several of consecutive items when the walk holds more than
+    // 1/16 of the launch's cost; the pieces are dealt to 8 queues (costliest
+    // first, each to the least loaded queue) and the launch order interleaves
+    // the queues, so XCD x takes queue x. A batch of many walks keeps each
+    // walk's items (and its digits in L2) on one XCD, and one long walk spreads
+    // over all eight; short queues are padded with kMxNoWalk items.
+    size_t n_dig = 0, n_pre = 0, n_lp = 0;
+    for (uint32_t b = 0; b < n; ++b) {
+        if (!lsp[b]) continue;
+        n_dig += dig_bytes(Ls[b]);
+        n_pre += 4 * (size_t)Ls[b];
+        n_lp += (size_t)lsp[b] * Ls[b];
     }
-    pl.split = !litems.empty();
+    pl.split = !mitems.empty();
     if (pl.split) {
-        if ((st = get(&p, n_limb))) return st;
-        pl.d_limbs = (int8_t *)p;
-        if ((st = get(&p, sizeof(double) * n_dq))) return st;
-        pl.d_dq = (double *)p;
+        if ((st = get(&p, n_dig))) return st;
+        pl.d_dig = (uint8_t *)p;
         if ((st = get(&p, sizeof(double) * n_pre))) return st;
         pl.d_pre = (double *)p;
         if ((st = get(&p, sizeof(double) * n_lp))) return st;
         pl.d_lpart = (double *)p;
         if ((st = get(&p, sizeof(SplitState) * n))) return st;
         pl.d_ss = (SplitState *)p;
-        if ((st = get(&p, sizeof(EvalItem) * litems.size()))) return st;
-        pl.d_litems = (EvalItem *)p;
-        pl.n_litems = (uint32_t)litems.size();
-        HIP_TRY(ctx, hipMemcpy(pl.d_litems, litems.data(), sizeof(EvalItem) * litems.size(),
+        if ((st = get(&p, sizeof(EvalItem) * mitems.size()))) return st;
+        pl.d_mitems = (EvalItem *)p;
+        if ((st = get(&p, sizeof(uint32_t)))) return st;
+        pl.d_tab = (uint32_t *)p;
+        pl.n_mitems = (uint32_t)mitems.size();
+        HIP_TRY(ctx, hipMemcpy(pl.d_mitems, mitems.data(), sizeof(EvalItem) * mitems.size(),
                                hipMemcpyHostToDevice));
     }
     std::vector<BatchEntry> be(n);
     size_t op = 0, oc = 0, os = 0;
-    size_t o_limb = 0, o_dq = 0, o_pre = 0, o_lp = 0;
+    size_t o_dig = 0, o_pre = 0, o_lp = 0;
     for (uint32_t b = 0; b < n; ++b) {
         BatchEntry &e = be[b];
         memset(&e, 0, sizeof e);
@@ -628,16 +652,14 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         e.near_lim = near_limit_for(ctx, ctx->walks[ids[b]].L);
         e.fixed = fixed ? 1 : 0;
         if (lsp[b]) {
-            const size_t K = split_row(Ls[b]);
             e.lsplit = lsp[b];
-            e.limbs = pl.d_limbs + o_limb;
-            e.dq = pl.d_dq + o_dq;
+            e.dig_one = pl.d_dig + o_dig;
+            e.dig_both = e.dig_one + (size_t)kRecBytes * (split_chunks(Ls[b]) + kRecPad);
             e.pre = pl.d_pre + o_pre;
             e.lpart = pl.d_lpart + o_lp;
             e.ss = pl.d_ss + b;
-            o_limb += 2 * (size_t)kLimbs * K;
-            o_dq += 2 * (size_t)Ls[b];
-            o_pre += 3 * (size_t)Ls[b];
+            o_dig += dig_bytes(Ls[b]);
+            o_pre += 4 * (size_t)Ls[b];
             o_lp += (size_t)lsp[b] * Ls[b];
         }
         op += (size_t)ks[b] * n_l[b];
@@ -716,14 +738,14 @@ psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, ui
 {
     psl_status st;
     HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, n, pl.max_L, tabs, 0, &pl.seg, pl.d_pend,
-                               pl.shape.waves >= kEvalWavesMax, ctx->stream));
+                               pl.shape.waves >= kEvalWavesMax, pl.d_tab, ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
-    if (pl.split) HIP_TRY(ctx, launch_split_prep(ctx->d_walks, pl.d_batch, n, tabs, pl.seg, ctx->stream));
+    if (pl.split) HIP_TRY(ctx, launch_split_prep(ctx->d_walks, pl.d_batch, n, tabs, pl.seg, pl.d_tab, ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
     HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues,
-                             ctx->stream));
+                             pl.d_tab, ctx->n_cu, ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
-    if (pl.split) HIP_TRY(ctx, launch_lin(ctx->d_walks, pl.d_batch, pl.d_litems, pl.n_litems, ctx->stream));
+    if (pl.split) HIP_TRY(ctx, launch_mx(ctx->d_walks, pl.d_batch, pl.d_mitems, pl.n_mitems, ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
                                pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
@@ -967,7 +989,7 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         hipError_t e = launch_init_bits(ctx->d_walks, tmp.d_batch, (const uint32_t *)dw, n, nw, ctx->stream);
         if (e == hipSuccess) e = launch_corr(ctx->d_walks, tmp.d_batch, n, L, 0, ctx->stream);
         const SegMap sm = seg_uniform(n, L);
-        if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, ctx->stream);
+        if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, nullptr, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         dev_free(ctx, dw, false);
         plan_free(ctx, tmp);
@@ -1026,15 +1048,15 @@ psl_status psl_eval_neighbourhood(psl_ctx *ctx, uint32_t walk, uint32_t start, u
     }
     const Tables tabs = tables_of(ctx);
     HIP_TRY(ctx, launch_suffix(ctx->d_walks, ctx->pure.d_batch, 1, h.L, tabs, 0, &ctx->pure.seg, nullptr,
-                               ctx->pure.shape.waves >= kEvalWavesMax,
-                               ctx->stream));
+                               ctx->pure.shape.waves >= kEvalWavesMax, ctx->pure.d_tab, ctx->stream));
     if (ctx->pure.split)
-        HIP_TRY(ctx, launch_split_prep(ctx->d_walks, ctx->pure.d_batch, 1, tabs, ctx->pure.seg, ctx->stream));
+        HIP_TRY(ctx, launch_split_prep(ctx->d_walks, ctx->pure.d_batch, 1, tabs, ctx->pure.seg, ctx->pure.d_tab,
+                                       ctx->stream));
     HIP_TRY(ctx, launch_eval(ctx->d_walks, ctx->pure.d_batch, ctx->pure.d_items, ctx->pure.n_items,
-                             tabs, ctx->pure.shape, ctx->pure.d_queues, ctx->stream));
+                             tabs, ctx->pure.shape, ctx->pure.d_queues, ctx->pure.d_tab, ctx->n_cu, ctx->stream));
     if (ctx->pure.split)
-        HIP_TRY(ctx, launch_lin(ctx->d_walks, ctx->pure.d_batch, ctx->pure.d_litems, ctx->pure.n_litems,
-                                ctx->stream));
+        HIP_TRY(ctx, launch_mx(ctx->d_walks, ctx->pure.d_batch, ctx->pure.d_mitems, ctx->pure.n_mitems,
+                               ctx->stream));
     HIP_TRY(ctx, launch_select(ctx->d_walks, ctx->pure.d_batch, 1, ctx->pure.comb_blocks, ctx->pure.comb_group, tabs, 1,
                                ctx->d_choice, nullptr, ctx->pure.d_done, ctx->amb_margin, ctx->stream));
     if (F_dev)
@@ -1084,9 +1106,9 @@ psl_status psl_eval_neighbourhood_noalloc(psl_ctx *ctx, uint32_t walk, uint32_t 
     }
     const Tables tabs = tables_of(ctx);
     HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, 1, h.L, tabs, 0, &pl.seg, nullptr,
-                               pl.shape.waves >= kEvalWavesMax, ctx->stream));
+                               pl.shape.waves >= kEvalWavesMax, nullptr, ctx->stream));
     HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues,
-                             ctx->stream));
+                             nullptr, ctx->n_cu, ctx->stream));
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, 1, pl.comb_blocks, pl.comb_group, tabs, 1, d_choice,
                                nullptr, pl.d_done, ctx->amb_margin, ctx->stream));
     alignas(16) unsigned char host[256];
@@ -1282,15 +1304,19 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
         psl_status s2 = make_plan(ctx, tmp, walk_ids, n, UINT32_MAX, 0, &c, items);
         if (s2) return s2;
         hipError_t e = launch_suffix(ctx->d_walks, tmp.d_batch, n, tmp.max_L, tabs, 0, &tmp.seg, nullptr,
-                                     tmp.shape.waves >= kEvalWavesMax, ctx->stream);
-        if (e == hipSuccess)   // warm-up
-            e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape,
-                            tmp.d_queues, ctx->stream);
+                                     tmp.shape.waves >= kEvalWavesMax, tmp.d_tab, ctx->stream);
+        if (e == hipSuccess && tmp.split)
+            e = launch_split_prep(ctx->d_walks, tmp.d_batch, n, tabs, tmp.seg, tmp.d_tab, ctx->stream);
+        auto launch = [&]() {
+            const hipError_t r = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape,
+                                             tmp.d_queues, tmp.d_tab, ctx->n_cu, ctx->stream);
+            if (r != hipSuccess || !tmp.split) return r;
+            return launch_mx(ctx->d_walks, tmp.d_batch, tmp.d_mitems, tmp.n_mitems, ctx->stream);
+        };
+        if (e == hipSuccess) e = launch();     // warm-up
         const int reps = 2;
         if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-        for (int r = 0; r < reps && e == hipSuccess; ++r)
-            e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape,
-                            tmp.d_queues, ctx->stream);
+        for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch();
         if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;

@@ -1,23 +1,22 @@
-// psl_split.hip -- the split evaluation of libpsl (gfx950).
+// psl_split.hip -- the matrix evaluation of libpsl (gfx950).
 //
-// Eq. (5) summed over the neighbours of Algorithm 1, regrouped. For shift k
-// with c = C_k and T(x) = T_alpha(|x|), the one-element flip of Section 3
-// changes C_k by 2a + 2b when both neighbours of j exist and by 2a when one
-// does (a, b = +-1: a = -s_j s_{j+k}, b = -s_j s_{j-k}). Because a and b
-// are +-1, each term is exactly a polynomial in them:
-//   T(|c + 2a + 2b|) = A + B (a + b) + D ab,
-//     A = (T(c+4) + 2T(c) + T(c-4))/4, B = (T(c+4) - T(c-4))/4,
-//     D = (T(c+4) + T(c-4) - 2T(c))/4;
-//   T(|c + 2a|) = A' + B' a, A' = (T(c+2) + T(c-2))/2, B' = (T(c+2) - T(c-2))/2.
-// So F_j = (prefix sums of A, A', T at j's region bounds)
-//        - s_j (sum_k beta_k s_{j+k} + sum_k beta_k s_{j-k})   [the linear part]
-//        + sum over both-neighbour shifts of D_k ab (+ (B_k - B'_k)(a + b)
-//          where the linear part used B'_k).
-// The linear part is a sum of products of +-1 elements and coefficients:
-// the matrix cores take it as exact integers (B and B' quantized to
-// multiples of a power of two U, kLimbs signed byte digits each). This file
-// holds the per-step preparation (coefficients, digits, prefix sums, scale
-// and path choice) and the matrix-core kernel of the linear part.
+// Eq. (5) summed over the neighbours of Algorithm 1, as products of 0/1
+// matrices with coefficient vectors. For shift k with c = C_k and
+// T(x) = T_alpha(|x|), the one-element flip of Section 3 gives
+// C'_k = c + 4(x_R + x_L - 1) where both neighbours of j exist
+// (k <= m_j = min(j, L-1-j)) and c + 2(2x - 1) where one does
+// (m_j < k <= M_j = max(j, L-1-j)); x_R = 1 where s_j s_{j+k} = -1, x_L = 1
+// where s_j s_{j-k} = -1. So
+//   both: T(c-4) + XOR(x_R, x_L) (T(c) - T(c-4)) + AND(x_R, x_L) (T(c+4) - T(c-4)),
+//   one:  T(c-2) + x (T(c+2) - T(c-2)),
+// and F_j is a sum of prefix sums of the constant parts plus three 0/1
+// matrices times coefficient vectors. The matrix cores take the matrices as
+// FP4 (a bit of the sequence is a nibble of 0.5 or 1.0 after one masking
+// operation) and the coefficients as exact fixed-point numbers in kDig
+// balanced base-32 digits, each exact in FP6: the FP32 accumulators then hold
+// exact integers, and only the rounding of a coefficient to the quantum U
+// enters. This file holds the per-step preparation (coefficients, digits,
+// prefix sums, scale and path choice) and the matrix kernel.
 #include "psl_dev_util.h"
 #include "psl_device.h"
 #include "psl_launch.h"
@@ -27,36 +26,68 @@
 
 namespace psl {
 
-// The scale of step's quantized coefficients: U = 2^e with every |B_k| and
-// |B'_k| below 2^62 U. Both grow with |c| (T is increasing and convex in
-// |c|), so their largest values are those at |c| = P, the pivot's PSL (the
-// maximum |C_k|).
+// The quantum of a step's coefficients: U = 2^e with every coefficient below
+// 2^67 U. They grow with |c| (T is increasing and convex in |c|), so the
+// largest is T(P+4) - T(P-4) at the pivot's PSL P (the maximum |C_k|).
 __device__ __forceinline__ double split_scale(const double *__restrict__ T, int P)
 {
     const int m4 = P >= 4 ? P - 4 : 4 - P, m2 = P >= 2 ? P - 2 : 2 - P;
-    const double b1 = (T[P + 4] - T[m4]) * 0.25, b2 = (T[P + 2] - T[m2]) * 0.5;
-    const double bmax = b1 > b2 ? b1 : b2;
-    return ldexp(1.0, ilogb(bmax) - 61);
+    const double c4 = T[P + 4] - T[m4], c2 = T[P + 2] - T[m2];
+    return ldexp(1.0, ilogb(c4 > c2 ? c4 : c2) - 66);
 }
 
-// The kLimbs balanced base-256 digits (each in [-128, 127]) of q.
-__device__ __forceinline__ void split_digits(int64_t q, int8_t *__restrict__ out, size_t stride)
+// The digits of one coefficient as FP6 codes, four per word (digit 4q + i in
+// byte i of out[q]; digits 14 and 15 are 0). v = coefficient / U in three
+// 30-bit words of six digits; adding 16 to every 5-bit field (kBias) turns
+// the balanced digits d in -16..15 into plain fields d + 16. The FP6 (E2M3)
+// code of n/8, n = 0..16, is n; of n/4 it is n + min(n, 8); 0x20 is the sign.
+// Odd shifts meet 1.0 in the FP4 matrix and take d/8, even ones 0.5 and d/4.
+constexpr int kBias = 0x21084210;
+
+__device__ __forceinline__ uint32_t digit_codes(uint32_t v, bool even)
 {
-#pragma unroll
-    for (int l = 0; l < kLimbs; ++l) {
-        const int d = (int)((q + 128) & 0xFF) - 128;
-        out[(size_t)l * stride] = (int8_t)d;
-        q = (q - d) >> 8;
-    }
+    const uint32_t neg = ~(v >> 4) & 0x01010101u;                   // d < 0
+    const uint32_t mag = ((v ^ ((neg << 4) - neg)) & 0x0F0F0F0Fu) + neg;   // |d|
+    const uint32_t big = ((mag >> 3) | (mag >> 4)) & 0x01010101u;   // |d| >= 8
+    const uint32_t dbl = mag + ((mag & ~((big << 5) - big)) | (big << 3));
+    return (even ? dbl : mag) | (neg << 5);
 }
 
-// Per shift k of every split walk of the batch (one block per segment of a
-// walk's shifts): the digits of B'_k and B_k, D_k and B_k - B'_k, and the
-// values A_k, A'_k, T(|C_k|) that k_split_scan turns into prefix sums.
+__device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out)[4])
+{
+    const double h2 = rint(v * 0x1p-60);
+    const double r1 = fma(h2, -0x1p60, v);
+    const double h1 = rint(r1 * 0x1p-30);
+    const double r0 = fma(h1, -0x1p30, r1);
+    int w0 = __double2int_rn(r0) + kBias, w1 = __double2int_rn(h1) + kBias, w2 = __double2int_rn(h2) + kBias;
+    w1 += w0 >> 30;                     // the carries out of the six-digit words
+    w0 &= 0x3FFFFFFF;
+    w2 += w1 >> 30;
+    w1 &= 0x3FFFFFFF;
+    const uint32_t a = (uint32_t)w0, b = (uint32_t)w1, c = (uint32_t)w2;
+    out[0] = (a & 31u) | ((a << 3) & 0x1F00u) | ((a << 6) & 0x1F0000u) | ((a << 9) & 0x1F000000u);
+    out[1] = ((a >> 20) & 31u) | ((a >> 17) & 0x1F00u) | ((b << 16) & 0x1F0000u) | ((b << 19) & 0x1F000000u);
+    out[2] = ((b >> 10) & 31u) | ((b >> 7) & 0x1F00u) | ((b >> 4) & 0x1F0000u) | ((b >> 1) & 0x1F000000u);
+    out[3] = (c & 31u) | ((c << 3) & 0x1F00u) | 0x10100000u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = digit_codes(out[q], even);
+}
+
+// Per shift k of every split walk (one block per segment of the walk's shifts,
+// in tiles of 256): the values T(|C_k - 4|), T(|C_k - 2|), T(|C_k + 2|),
+// T(|C_k|) that k_split_scan turns into prefix sums, and the digit records.
+// A record holds one 32-shift chunk (shifts 32c .. 32c+31) of one coefficient:
+// 16 columns (digits) of 32 FP6 codes, the first 16 bytes of each column, then
+// the last 8 of each (kRecBytes); slot 8 r + q of a column is shift 32c + 4q + r,
+// the order in which the matrix kernel's masks leave the bits of a word. The
+// threads leave the codes of a tile in LDS (one word per shift and four
+// columns); then one thread per (coefficient, chunk, four columns) packs them.
 constexpr int kPrepThreads = 256;
+constexpr int kPrepStride = 36;         // words per chunk and four columns in LDS (32 and padding)
 __global__ __launch_bounds__(kPrepThreads) void k_split_prep(const WalkDev *walks, const BatchEntry *batch,
                                                              Tables tabs, SegMap map)
 {
+    __shared__ __align__(16) uint32_t s_c[3][4][8 * kPrepStride];
     uint32_t b, seg;
     seg_of(map, blockIdx.x, b, seg);
     const BatchEntry be = batch[b];
@@ -64,35 +95,79 @@ __global__ __launch_bounds__(kPrepThreads) void k_split_prep(const WalkDev *walk
     const WalkDev &w = walks[be.slot];
     const int L = (int)w.L;
     const double *__restrict__ T = tabs.T[w.alpha];
-    const double U = split_scale(T, w.psl_pivot);
-    const double inv = 1.0 / U;                    // exact: U is a power of two
-    const size_t K = split_row((uint32_t)L);       // digits per (set, limb)
-    const int k0 = 1 + (int)(seg << map.shift);
-    const int k1 = min(L, k0 + (1 << map.shift));
-    for (int k = k0 + (int)threadIdx.x; k < k1; k += kPrepThreads) {
-        const int c = w.C[k];
+    const double inv = 1.0 / split_scale(T, w.psl_pivot);      // exact: U is a power of two
+    const int half = (L - 1) / 2;                              // the largest m_j
+    const int nbo = (int)split_both_chunks((uint32_t)L), nco = (int)split_chunks((uint32_t)L);
+    const int k_end = (int)seg + 1 == (int)seg_count((uint32_t)L, map.shift) ? 32 * nco : (int)((seg + 1) << map.shift);
+    const int t = (int)threadIdx.x;
+    const int slot = (t >> 5) * kPrepStride + 8 * (t & 3) + ((t & 31) >> 2);
+    double *__restrict__ pre = be.pre;
+    for (int k0 = (int)(seg << map.shift); k0 < k_end; k0 += kPrepThreads) {
+        const int k = k0 + t;
+        const bool in = k >= 1 && k < L;
+        const bool both = (k0 >> 5) < nbo;                     // some chunk of the tile has both-neighbour shifts
+        const int c = in ? w.C[k] : 0;
         const int a4 = c + 4 < 0 ? -(c + 4) : c + 4, m4 = c - 4 < 0 ? 4 - c : c - 4;
         const int a2 = c + 2 < 0 ? -(c + 2) : c + 2, m2 = c - 2 < 0 ? 2 - c : c - 2;
-        const int a0 = c < 0 ? -c : c;
-        const double tp4 = T[a4], tm4 = T[m4], tp2 = T[a2], tm2 = T[m2], t0 = T[a0];
-        const double A = (tp4 + 2.0 * t0 + tm4) * 0.25;
-        const double B = (tp4 - tm4) * 0.25;
-        const double D = (tp4 + tm4 - 2.0 * t0) * 0.25;
-        const double A1 = (tp2 + tm2) * 0.5;
-        const double B1 = (tp2 - tm2) * 0.5;
-        split_digits(__double2ll_rn(B1 * inv), be.limbs + (k - 1), K);
-        split_digits(__double2ll_rn(B * inv), be.limbs + (size_t)kLimbs * K + (k - 1), K);
-        be.dq[2 * (size_t)k] = D;
-        be.dq[2 * (size_t)k + 1] = B - B1;
-        be.pre[k] = A;
-        be.pre[(size_t)L + k] = A1;
-        be.pre[2 * (size_t)L + k] = t0;
-    }
-    if (k1 == L) {
-        // the shifts at and beyond L (the rest of the last chunk and the
-        // zero chunk): zero digits
-        for (int k = L + (int)threadIdx.x; k <= (int)K; k += kPrepThreads)
-            for (int s = 0; s < 2 * kLimbs; ++s) be.limbs[(size_t)s * K + (k - 1)] = 0;
+        const double t0 = T[c < 0 ? -c : c], tp2 = T[a2], tm2 = T[m2];
+        if (in) {
+            pre[(size_t)L + k] = tm2;
+            pre[2 * (size_t)L + k] = tp2;
+            pre[3 * (size_t)L + k] = t0;
+        }
+        uint32_t d[4];
+        split_digits(in ? (tp2 - tm2) * inv : 0.0, !(t & 1), d);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s_c[2][q][slot] = d[q];
+        if (both) {
+            const double tp4 = T[a4], tm4 = T[m4];
+            if (in && k <= half) pre[k] = tm4;
+            split_digits(in ? (t0 - tm4) * inv : 0.0, !(t & 1), d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s_c[0][q][slot] = d[q];
+            split_digits(in ? (tp4 - tm4) * inv : 0.0, !(t & 1), d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s_c[1][q][slot] = d[q];
+        }
+        __syncthreads();
+        // task e: coefficient e / 32, chunk (e / 4) % 8, columns 4 (e % 4) .. +3
+        const int set = t >> 5, cc = (t >> 2) & 7, q = t & 3;
+        const int ch = (k0 >> 5) + cc;
+        if (t < 96 && ch < (set == 2 ? nco : nbo)) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(&s_c[set][q][cc * kPrepStride]);
+            uint32_t o[4][6];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t x[4][4];                              // [column][4 codes in 24 bits]
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    const uint4 v = src[4 * h + y];
+                    // 16-bit lanes: columns 0 and 2, columns 1 and 3
+                    const uint32_t e01 = (v.x & 0x00FF00FFu) | ((v.y & 0x00FF00FFu) << 6);
+                    const uint32_t e23 = (v.z & 0x00FF00FFu) | ((v.w & 0x00FF00FFu) << 6);
+                    const uint32_t f01 = ((v.x >> 8) & 0x00FF00FFu) | (((v.y >> 8) & 0x00FF00FFu) << 6);
+                    const uint32_t f23 = ((v.z >> 8) & 0x00FF00FFu) | (((v.w >> 8) & 0x00FF00FFu) << 6);
+                    x[0][y] = (e01 & 0xFFFFu) | ((e23 & 0xFFFFu) << 12);
+                    x[1][y] = (f01 & 0xFFFFu) | ((f23 & 0xFFFFu) << 12);
+                    x[2][y] = (e01 >> 16) | ((e23 >> 16) << 12);
+                    x[3][y] = (f01 >> 16) | ((f23 >> 16) << 12);
+                }
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    o[y][3 * h] = x[y][0] | (x[y][1] << 24);
+                    o[y][3 * h + 1] = (x[y][1] >> 8) | (x[y][2] << 16);
+                    o[y][3 * h + 2] = (x[y][2] >> 16) | (x[y][3] << 8);
+                }
+            }
+            uint8_t *rec = set == 2 ? be.dig_one + (size_t)ch * kRecBytes
+                                    : be.dig_both + ((size_t)ch * 2 + (size_t)set) * kRecBytes;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                *reinterpret_cast<uint4 *>(rec + 16 * (4 * q + y)) = make_uint4(o[y][0], o[y][1], o[y][2], o[y][3]);
+                *reinterpret_cast<uint2 *>(rec + 256 + 8 * (4 * q + y)) = make_uint2(o[y][4], o[y][5]);
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -103,34 +178,39 @@ __global__ __launch_bounds__(kPrepThreads) void k_split_prep(const WalkDev *walk
 // wavefronts' totals before them, and the chunks' totals are carried with
 // Neumaier's compensation. Every summand is non-negative, so each prefix is
 // within a few dozen roundings of its exact value. Block (walk, 0) also
-// stores the step's scale and path choice: the split path is taken when the
-// near-peak list holds the PSL (sparse form) and the quantization error of
-// the linear part, at most (L-1) U, is below 1e-14 of a lower bound of every
-// neighbour's F (T(P-4) for the pivot's PSL P, and at least 1).
+// stores the step's scale and path choice: the matrix path is taken when the
+// near-peak list holds the PSL (sparse form) and the quantization error,
+// at most (L-1) U, is below 1e-14 of a lower bound of every neighbour's F
+// (T(P-4) for the pivot's PSL P, and at least 1); a walk that does not take
+// it is counted in *tab, which the table evaluation looks at first.
 constexpr int kScanThreads = 256;
 constexpr int kScanPer = 4;
 constexpr int kScanChunk = kScanThreads * kScanPer;
 __global__ __launch_bounds__(kScanThreads) void k_split_scan(const WalkDev *walks, const BatchEntry *batch,
-                                                             Tables tabs)
+                                                             Tables tabs, uint32_t *tab)
 {
-    const uint32_t wb = blockIdx.x / 3, x = blockIdx.x % 3;
+    const uint32_t wb = blockIdx.x / 4, x = blockIdx.x % 4;
     const BatchEntry be = batch[wb];
-    if (!be.lsplit) return;
+    if (!be.lsplit) {
+        if (x == 0 && threadIdx.x == 0) atomicAdd(tab, 1u);
+        return;
+    }
     const WalkDev &w = walks[be.slot];
     const int L = (int)w.L;
+    const int K = x == 0 ? (L - 1) / 2 + 1 : L;     // T(|C_k - 4|) is summed over both-neighbour shifts only
     double *__restrict__ v = be.pre + (size_t)x * L;
     __shared__ double s_tot[kScanThreads / 64];
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     auto load = [&](int base, double (&e)[kScanPer]) {
         const int k0 = base + (int)threadIdx.x * kScanPer;
 #pragma unroll
-        for (int i = 0; i < kScanPer; ++i) e[i] = k0 + i < L ? v[k0 + i] : 0.0;
+        for (int i = 0; i < kScanPer; ++i) e[i] = k0 + i < K ? v[k0 + i] : 0.0;
     };
     double carry = 0.0, ccomp = 0.0;
     double cur[kScanPer], nxt[kScanPer];
     load(1, cur);
-    for (int base = 1; base < L; base += kScanChunk) {
-        if (base + kScanChunk < L) load(base + kScanChunk, nxt);
+    for (int base = 1; base < K; base += kScanChunk) {
+        if (base + kScanChunk < K) load(base + kScanChunk, nxt);
 #pragma unroll
         for (int i = 1; i < kScanPer; ++i) cur[i] += cur[i - 1];
         // inclusive scan of the thread totals over the wavefront
@@ -154,7 +234,7 @@ __global__ __launch_bounds__(kScanThreads) void k_split_scan(const WalkDev *walk
         const int k0 = base + (int)threadIdx.x * kScanPer;
 #pragma unroll
         for (int i = 0; i < kScanPer; ++i)
-            if (k0 + i < L) v[k0 + i] = off + cur[i];
+            if (k0 + i < K) v[k0 + i] = off + cur[i];
         nsum_add(carry, ccomp, tot);
         __syncthreads();                           // s_tot is rewritten by the next chunk
 #pragma unroll
@@ -174,329 +254,404 @@ __global__ __launch_bounds__(kScanThreads) void k_split_scan(const WalkDev *walk
             st.use = exact_enough && sparse_psl ? 1u : 0u;
             st.pad = 0;
             *be.ss = st;
+            if (!st.use) atomicAdd(tab, 1u);
         }
     }
 }
 
 hipError_t launch_split_prep(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                             const SegMap &map, hipStream_t s)
+                             const SegMap &map, uint32_t *tab, hipStream_t s)
 {
-    if (map.shift < kSegShiftMin || map.shift > kSegShiftMax || map.nb != nb) return hipErrorInvalidValue;
+    if (map.shift < kSegShiftMin || map.shift > kSegShiftMax || map.nb != nb || !tab) return hipErrorInvalidValue;
     if (nb == 0 || map.total == 0) return hipSuccess;
     k_split_prep<<<map.total, kPrepThreads, 0, s>>>(walks, batch, tabs, map);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_split_scan<<<3 * nb, kScanThreads, 0, s>>>(walks, batch, tabs);
+    k_split_scan<<<4 * nb, kScanThreads, 0, s>>>(walks, batch, tabs, tab);
     return hipGetLastError();
 }
 
-// ------------------------------------------------------- linear part
+// ------------------------------------------------------- matrix kernel
 
-// The linear part of F_j on the matrix cores. For element j and shift k the
-// right sum takes beta_k s_{j+k} (j+k < L) and the left sum beta_k s_{j-k}
-// (j-k >= 0), beta_k = B_k where the chunk of k is covered for j's 64-element
-// block (split_block_bound) and B'_k elsewhere. Elements come in groups of 32
-// (group G: j = 32 G + a) and shifts in chunks of 32 (chunk c: k = 32 c + 1 +
-// kappa). For group G and chunk c the +-1 factors form a 32 x 32 matrix that
-// depends on G + c only on the right (entry (a, kappa) is s at position
-// 32 (G + c) + 1 + a + kappa: Hankel) and on G - c only on the left (position
-// 32 (G - c) - 1 + a - kappa: Toeplitz); positions outside 0..L-1 are 0.
+// One wavefront per work item (walk, tile of kMxTile = 256 consecutive
+// elements, k-split). The tile's elements J0 + 32 b + 16 p + r (b = 0..7,
+// p = 0..1, r = 0..15) are the rows of 16 products per step of
+// v_mfma_f32_16x16x128_f8f6f4: lane l has row r = l % 16 (FP4 matrix) or
+// column l % 16 (FP6 digits) and the 32 shifts of one chunk, lane group
+// g = l / 16 having a chunk of its own. Element j and chunk c read the right
+// window, bits j + 32c .. +31 of the sequence, and the left window, bits
+// j - 32c, j - 32c - 1, ..; the right one depends on b + c and p only, the
+// left one on b - c and p. So the four lane groups sweep four ranges of N
+// chunks each (chunk c0 + g N + s at step s): a step then needs one new right
+// and one new left window per p, kept in rings of eight, for its 16 products
+// of a 16 x 128 matrix. Per product the wavefront makes four words of eight
+// nibbles: (bits & 0x11111111) holds shifts 4q as 0.5, (bits & 0x22222222)
+// shifts 4q + 1 as 1.0, and the same of (bits >> 2) shifts 4q + 2 and 4q + 3;
+// the record's slot order and digit scales match.
 //
-// One v_mfma_i32_32x32x32_i8 multiplies such a matrix by 32 columns: 4
-// column sets x of the 8 signed byte digits of beta over one chunk each. A
-// wavefront owns 1024 elements (32 groups from G_w) in 8 accumulators:
-// accumulator b holds groups G_w + b + 8x, x = 0..3. On the right, the digit
-// tile of step c0 holds chunks c0 - 8x; accumulator b multiplies it by the
-// matrix of index c0 + G_w + b, which serves all four of its column sets. So
-// one tile load feeds 8 products, and consecutive steps share 7 of their 8
-// matrices (each step expands one new one from the sequence bits). The left
-// side runs the same way with chunks c0 + 8x and matrix index G_w + b - c0.
-// The int32 sums per digit (at most 128 (L-1) in magnitude per side) are
-// combined per element into the sum in units of U.
+// One-neighbour shifts come first, with the sequence's bits as they are (the
+// matrix of a window is the same for all b + c, so it is masked once); then
+// the rows with s_j = -1 change sign (their x is 1 minus the bit, and the
+// combine takes T(c+2) as their constant part), and the both-neighbour shifts
+// add XOR (which s_j does not change) and AND of the bits times s_j. Both go
+// into the same accumulators: |digit| <= 16 over at most L-1 shifts, one
+// coefficient each, stays within 2^24 units of 1/8, exact in FP32.
 //
-// Work item: (walk, 4096-element block q, k-split); a block of four
-// wavefronts, wavefront x taking elements 4096 q' + 1024 x .. + 1023, q' being
-// the block q positions past the one holding the neighbourhood's first
-// element. Items for the whole batch are laid out so that one walk's items run
-// on one XCD (workgroup i goes to XCD i mod 8), keeping its digits in that
-// XCD's L2; padding items carry walk kLinNoWalk.
+// Chunks in which some row of the tile has a bound (m_j) inside, and the up to
+// three that do not fill a step, are taken by mx_edge: four consecutive
+// chunks per step, every row's shifts outside its bounds masked.
+typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int kLinWaves = kLinBlockElems / kLinWaveElems;
-constexpr int kLinAcc = 8;                       // accumulators per wavefront
-constexpr int kLinPrefetch = 3;                  // steps between a load and its use
-static_assert(kLinWaveElems == 32 * 4 * kLinAcc, "a wavefront's groups are its accumulators' column sets");
+constexpr uint32_t kM0 = 0x11111111u, kM1 = 0x22222222u;
+constexpr int kBlk = kMxTile / 32;       // pairs of 16-row blocks of a tile
+constexpr int kPad = 256;                // words before the sequence that the word offsets start from
 
-__device__ __forceinline__ v4i ldg_v4i(const int8_t *p)
+__device__ __forceinline__ v4f mx_mfma(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, v8i B, v4f acc)
 {
-    return *(const __attribute__((address_space(1))) v4i *)(p);
+    const v8i A = {(int)x0, (int)x1, (int)x2, (int)x3, 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, acc, 4, 2, 0, 0, 0, 0);
 }
 
-__device__ __forceinline__ v2u ldg_v2u(const uint32_t *p)
+// (a ^ b) & m and (a ^ s) & (b ^ s), one operation each
+__device__ __forceinline__ uint32_t xor_and(uint32_t a, uint32_t b, uint32_t m)
 {
-    return *(const __attribute__((address_space(1))) v2u *)(p);
+    return __builtin_amdgcn_bitop3_b32(a, b, m, 0x28);
+}
+__device__ __forceinline__ uint32_t and_signed(uint32_t a, uint32_t b, uint32_t s)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, s, 0x42);
 }
 
-// Per-lane constants of k_lin. Operand layout of v_mfma_i32_32x32x32_i8:
-// lane l holds row (A) or column (B) l % 32 and the 16 bytes k = 16 (l / 32)
-// .. +15 of it.
-struct LinLane {
-    int x;                  // B: column set (column = 8 x + digit)
-    uint32_t off0, off1;    // B: byte offset of this lane's digit row in set 0 / set 1, plus its 16 k-bytes
-    uint32_t offz;          // B: the same in the zero chunk
-    int n[4];               // covered chunks (c < n) of the column set's four 64-element blocks
-    int lo, hi;             // min and max of n
-    int pb;                 // A: position of this lane's first entry is 32 (matrix index) + pb
-    int woff;               // A: first sequence word = matrix index + woff
-    uint32_t sh;            // A: bit offset in it
+// This lane's column of a digit record.
+__device__ __forceinline__ v8i mx_rec(const uint8_t *__restrict__ base, uint32_t off16, uint32_t off8)
+{
+    const v4i a = *(const __attribute__((address_space(1))) v4i *)(base + off16);
+    const v2i b = *(const __attribute__((address_space(1))) v2i *)(base + off8);
+    return v8i{a.x, a.y, a.z, a.w, b.x, b.y, 0, 0};
+}
+
+struct MxLane {
+    const uint32_t *w;      // kPad words before the sequence's first
+    int J32;                // first word of the tile
+    int r, g, col;
+    uint32_t S[2 * kBlk];   // all ones where s_j = -1, per 16-row block
+    __device__ __forceinline__ uint32_t word(int i) const
+    {
+        return *(const __attribute__((address_space(1))) uint32_t *)(w + (uint32_t)(i + kPad));
+    }
 };
 
-// The 32 x 32 +-1 matrix of index idx, this lane's 16 entries: bytes 0x01
-// (+1) and 0xFF (-1) from the sequence bits wv via a byte table (entry e:
-// byte t is -1 where bit t of e is set), 0 at positions outside 0..L-1 (only
-// matrices at the ends of the sequence have such entries: `edge`).
-template <bool RIGHT>
-__device__ __forceinline__ v4i lin_matrix(v2u wv, int idx, const LinLane &ln, int L,
-                                          const v2u *__restrict__ lut)
+// The both-neighbour products of chunks c0 + g N + s, s < N, all of whose
+// shifts are at most every row's m_j.
+__device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int c0,
+                                        int N)
 {
-    const uint32_t y = __builtin_amdgcn_alignbit(wv.y, wv.x, ln.sh);
-    const uint32_t x = RIGHT ? y : __builtin_bitreverse32(y) >> 16;   // bit t: entry t
-    const v2u e0 = lut[x & 0xFFu], e1 = lut[(x >> 8) & 0xFFu];
-    v4i r = {(int)e0.x, (int)e0.y, (int)e1.x, (int)e1.y};
-    // right: entries t at P + t (< L needed; P >= 1); left: at P - t (>= 0
-    // needed; P - t <= L - 2 for every real element)
-    const bool edge = RIGHT ? 32 * idx + 63 >= L : idx <= 0;
-    if (edge) {
-        const int P = 32 * idx + ln.pb;
-        const int valid = RIGHT ? L - P : P + 1;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int nv = min(4, max(0, valid - 4 * q));
-            const uint32_t m = nv >= 4 ? 0xFFFFFFFFu : ((1u << (8 * nv)) - 1u);
-            r[q] = (int)((uint32_t)r[q] & m);
-        }
-    }
-    return r;
-}
-
-__device__ __forceinline__ int lin_wave_min(int v)
-{
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) v = min(v, __shfl_xor(v, d));
-    return v;
-}
-
-__device__ __forceinline__ int lin_wave_max(int v)
-{
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) v = max(v, __shfl_xor(v, d));
-    return v;
-}
-
-// One side's products into acc over tiles c0 = cs .. ce-1. The main loop runs
-// whole 9-step rounds (the steps past ce multiply zero tiles or zero
-// matrices) and leaves out every lane's mixed chunks (those whose column
-// set's blocks disagree on coverage); a second pass visits the steps where
-// some lane's chunk is mixed and adds those products with the tile of each
-// block pair. The two passes add disjoint terms of the same sums.
-template <bool RIGHT>
-__device__ __forceinline__ void lin_side(v16i (&acc)[kLinAcc], const LinLane &ln,
-                                         const uint32_t *__restrict__ w32, const int8_t *__restrict__ limbs,
-                                         const v2u *__restrict__ lut, int L, int Gw, int c_lo, int c_hi, int cs,
-                                         int ce)
-{
-    // matrix index of accumulator b at step c0; the step's new matrix is that
-    // of accumulator kFresh
-    constexpr int kFresh = RIGHT ? kLinAcc - 1 : 0;
-    auto midx = [&](int c0, int b) { return RIGHT ? c0 + Gw + b : Gw + b - c0; };
-    auto chunk = [&](int c0) { return RIGHT ? c0 - 8 * ln.x : c0 + 8 * ln.x; };
-    // w32 points 32 words before the sequence (every index here is above -32)
-    auto fetch = [&](int idx) { return ldg_v2u(w32 + (uint32_t)(idx + ln.woff + 32)); };
-    // (bitwise, not short-circuit, so that the lane predicates stay selects)
-    auto in_range = [&](int c) { return (uint32_t)(c - c_lo) < (uint32_t)(c_hi - c_lo); };
-    auto mixed = [&](int c) { return (c >= ln.lo) & (c < ln.hi) & in_range(c); };
-    // this lane's 16 digit bytes of chunk c (the zero chunk unless `take`)
-    auto tile = [&](int c, bool take, bool set1) {
-        const uint32_t off = take ? (set1 ? ln.off1 : ln.off0) + 32u * (uint32_t)c : ln.offz;
-        return ldg_v4i(limbs + off);
-    };
-    auto tile_main = [&](int c) { return tile(c, in_range(c) & ((c < ln.lo) | (c >= ln.hi)), c < ln.lo); };
-    // Matrices in a ring of kRing = 9 slots: the matrix of accumulator b at
-    // step cs + v sits in slot (v + b) % 9 on the right and (v + 7 - b) % 9 on
-    // the left, so step v uses slots v .. v+7 and the matrix new at step v+1
-    // (slot (v + 8) % 9) is expanded during step v's products. The sequence
-    // words of that matrix and the digit tiles are loaded kLinPrefetch steps
-    // before their use.
-    constexpr int kRing = kLinAcc + 1;
-    static_assert(kRing % kLinPrefetch == 0, "the unrolled round holds whole prefetch cycles");
-    v4i A[kRing];
+    const int cb = c0 + ln.g * N;
+    const uint32_t shr = (uint32_t)ln.r, shl = (uint32_t)(31 - ln.r);
+    uint32_t R[8][2], R2[8][2], W[8][2], W2[8][2];        // right and left windows, and shifted by 2
+    uint32_t rprev, lprev, rq[4], lq[4];
+    v8i bx[2], ba[2];
+    uint32_t o16 = (uint32_t)cb * (2 * kRecBytes) + 16u * (uint32_t)ln.col;
+    uint32_t o8 = (uint32_t)cb * (2 * kRecBytes) + 256u + 8u * (uint32_t)ln.col;
+    bx[0] = mx_rec(dig, o16, o8);
+    ba[0] = mx_rec(dig + kRecBytes, o16, o8);
     {
-        v2u pw[kLinAcc];                        // all loads issued before the first use
+        uint32_t x[9], y[9];
 #pragma unroll
-        for (int b = 0; b < kLinAcc; ++b) pw[b] = fetch(midx(cs, b));
+        for (int i = 0; i < 9; ++i) {
+            x[i] = ln.word(ln.J32 + cb + i);
+            y[i] = ln.word(ln.J32 - cb - 1 + i);
+        }
 #pragma unroll
-        for (int b = 0; b < kLinAcc; ++b)
-            A[RIGHT ? b : kLinAcc - 1 - b] = lin_matrix<RIGHT>(pw[b], midx(cs, b), ln, L, lut);
-    }
-    // wq[k % P]: words of the new matrix of step k (k >= 1); tq[k % P]: tile of step k
-    v2u wq[kLinPrefetch];
-    v4i tq[kLinPrefetch];
+        for (int k = 0; k < 4; ++k) {
+            rq[k] = ln.word(ln.J32 + cb + k + 9);
+            lq[k] = ln.word(ln.J32 - cb - k - 2);
+        }
 #pragma unroll
-    for (int p = 0; p < kLinPrefetch; ++p) {
-        wq[(p + 1) % kLinPrefetch] = fetch(midx(cs + p + 1, kFresh));
-        tq[p] = tile_main(chunk(cs + p));
-    }
-    for (int c0b = cs; c0b < ce; c0b += kRing) {
+        for (int i = 0; i < 9; ++i) y[i] = __builtin_bitreverse32(y[i]);
 #pragma unroll
-        for (int v = 0; v < kRing; ++v) {
-            const int c0 = c0b + v;
-            const v4i T = tq[v % kLinPrefetch];
-            tq[v % kLinPrefetch] = tile_main(chunk(c0 + kLinPrefetch));
-            const v2u wn = wq[(v + 1) % kLinPrefetch];
-            wq[(v + 1) % kLinPrefetch] = fetch(midx(c0 + 1 + kLinPrefetch, kFresh));
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int b = 0; b < kLinAcc; ++b) {
-                const int slot = RIGHT ? (v + b) % kRing : (v + kLinAcc - 1 - b) % kRing;
-                acc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[slot], T, acc[b], 0, 0, 0);
+            for (int p = 0; p < 2; ++p) {
+                R[u][p] = __builtin_amdgcn_alignbit(x[u + 1], x[u], shr + 16u * p);
+                R2[u][p] = R[u][p] >> 2;
+                W[u][p] = __builtin_amdgcn_alignbit(y[u], y[u + 1], shl - 16u * p);
+                W2[u][p] = W[u][p] >> 2;
             }
-            A[(v + kLinAcc) % kRing] = lin_matrix<RIGHT>(wn, midx(c0 + 1, kFresh), ln, L, lut);
+        rprev = x[8];
+        lprev = y[0];
+    }
+    for (int s = 0;;) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            if (s >= N) return;
+            o16 += 2 * kRecBytes;
+            o8 += 2 * kRecBytes;
+            bx[(v + 1) & 1] = mx_rec(dig, o16, o8);
+            ba[(v + 1) & 1] = mx_rec(dig + kRecBytes, o16, o8);
+            const uint32_t rn = rq[v & 3], lw = lq[v & 3];
+            rq[v & 3] = ln.word(ln.J32 + cb + s + 13);
+            lq[v & 3] = ln.word(ln.J32 - cb - s - 6);
+#pragma unroll
+            for (int b = 0; b < kBlk; ++b) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int i = 2 * b + p, u = (v + b) & 7, x = (b - v) & 7;
+                    acc[i] = mx_mfma(xor_and(R[u][p], W[x][p], kM0), xor_and(R[u][p], W[x][p], kM1),
+                                     xor_and(R2[u][p], W2[x][p], kM0), xor_and(R2[u][p], W2[x][p], kM1), bx[v & 1],
+                                     acc[i]);
+                    const uint32_t t = and_signed(R[u][p], W[x][p], ln.S[i]);
+                    const uint32_t t2 = and_signed(R2[u][p], W2[x][p], ln.S[i]);
+                    acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba[v & 1], acc[i]);
+                }
+            }
+            const uint32_t ly = __builtin_bitreverse32(lw);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                R[v][p] = __builtin_amdgcn_alignbit(rn, rprev, shr + 16u * p);
+                R2[v][p] = R[v][p] >> 2;
+                W[7 - v][p] = __builtin_amdgcn_alignbit(ly, lprev, shl - 16u * p);
+                W2[7 - v][p] = W[7 - v][p] >> 2;
+            }
+            rprev = rn;
+            lprev = ly;
+            ++s;
         }
     }
-    // mixed chunks: lane chunk c in [lo, hi) at steps c0 = c +- 8x. The steps
-    // with a mixed lane are marked in 64-step masks first; each such step then
-    // issues all its loads (the 8 matrices' sequence words and the 4 block
-    // pairs' tiles) before it waits, and adds its 8 products.
-    const bool has = ln.lo < ln.hi;
-    const int z_lo = RIGHT ? ln.lo + 8 * ln.x : ln.lo - 8 * ln.x;
-    const int z0 = max(cs, lin_wave_min(has ? z_lo : INT_MAX));
-    const int z1 = min(ce, lin_wave_max(has ? z_lo + (ln.hi - ln.lo) : INT_MIN));
-    for (int zb = z0; zb < z1; zb += 64) {
-        uint64_t steps = 0;
-        for (int i = 0; i < 64 && zb + i < z1; ++i)
-            if (__any(mixed(chunk(zb + i)))) steps |= 1ull << i;
-        while (steps) {
-            const int c0 = zb + __builtin_ctzll(steps);
-            steps &= steps - 1;
-            const int c = chunk(c0);
-            const bool mx = mixed(c);
-            v2u wv[kLinAcc];
-            v4i T[4];
+}
+
+// The one-neighbour products (right or left side) of chunks c0 + g N + s,
+// s < N, all of whose shifts are past every row's m_j.
+template <bool RIGHT>
+__device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int c0,
+                                       int N)
+{
+    const int cb = c0 + ln.g * N;
+    const uint32_t sh = RIGHT ? (uint32_t)ln.r : (uint32_t)(31 - ln.r);
+    uint32_t A[8][2][4];                    // the matrices of eight windows
+    uint32_t prev, wq[4];
+    v8i bq[4];
+    uint32_t o16 = (uint32_t)cb * kRecBytes + 16u * (uint32_t)ln.col;
+    uint32_t o8 = (uint32_t)cb * kRecBytes + 256u + 8u * (uint32_t)ln.col;
 #pragma unroll
-            for (int b = 0; b < kLinAcc; ++b) wv[b] = fetch(midx(c0, b));
+    for (int k = 0; k < 2; ++k) {
+        bq[k] = mx_rec(dig, o16, o8);
+        o16 += kRecBytes;
+        o8 += kRecBytes;
+    }
+    auto make = [&](uint32_t hi, uint32_t lo, uint32_t(&a)[2][4]) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) T[p] = tile(c, mx, c < ln.n[p]);
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t win = __builtin_amdgcn_alignbit(hi, lo, RIGHT ? sh + 16u * p : sh - 16u * p);
+            a[p][0] = win & kM0;
+            a[p][1] = win & kM1;
+            a[p][2] = (win >> 2) & kM0;
+            a[p][3] = (win >> 2) & kM1;
+        }
+    };
+    {
+        uint32_t x[9];
 #pragma unroll
-            for (int b = 0; b < kLinAcc; ++b) {
-                const v4i Am = lin_matrix<RIGHT>(wv[b], midx(c0, b), ln, L, lut);
-                acc[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Am, T[b / 2], acc[b], 0, 0, 0);
+        for (int i = 0; i < 9; ++i) x[i] = ln.word(RIGHT ? ln.J32 + cb + i : ln.J32 - cb - 1 + i);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) wq[k] = ln.word(RIGHT ? ln.J32 + cb + k + 9 : ln.J32 - cb - k - 2);
+        if (!RIGHT) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) x[i] = __builtin_bitreverse32(x[i]);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) make(RIGHT ? x[u + 1] : x[u], RIGHT ? x[u] : x[u + 1], A[u]);
+        prev = RIGHT ? x[8] : x[0];
+    }
+    for (int s = 0;;) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            if (s >= N) return;
+            bq[(v + 2) & 3] = mx_rec(dig, o16, o8);
+            o16 += kRecBytes;
+            o8 += kRecBytes;
+            uint32_t wn = wq[v & 3];
+            wq[v & 3] = ln.word(RIGHT ? ln.J32 + cb + s + 13 : ln.J32 - cb - s - 6);
+#pragma unroll
+            for (int b = 0; b < kBlk; ++b) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int i = 2 * b + p;
+                    const uint32_t(&a)[4] = A[RIGHT ? (v + b) & 7 : (b - v) & 7][p];
+                    acc[i] = mx_mfma(a[0], a[1], a[2], a[3], bq[v & 3], acc[i]);
+                }
+            }
+            if (!RIGHT) wn = __builtin_bitreverse32(wn);
+            make(wn, prev, A[RIGHT ? v : 7 - v]);
+            prev = wn;
+            ++s;
+        }
+    }
+}
+
+// Chunks ca .. ce-1, four consecutive ones per step, with every row's shifts
+// outside its bounds masked: BOTH: shifts up to m_j; otherwise the shifts past
+// m_j, on the row's one-neighbour side (right for j <= half). Only a side that
+// some row uses is read: the other side's words can lie outside the guards.
+template <bool BOTH>
+__device__ __forceinline__ void mx_edge(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int L,
+                                        int ca, int ce, int nrec)
+{
+    const int half = (L - 1) / 2;
+    const uint32_t shr = (uint32_t)ln.r, shl = (uint32_t)(31 - ln.r);
+    constexpr uint32_t kStep = BOTH ? 2 * kRecBytes : kRecBytes;
+    const bool need_r = BOTH || 32 * ln.J32 <= half, need_l = BOTH || min(32 * ln.J32 + kMxTile, L) - 1 > half;
+#pragma unroll 1
+    for (int c4 = ca; c4 < ce; c4 += 4) {
+        const int c = c4 + ln.g;
+        const uint32_t cl = (uint32_t)min(c, nrec - 1);
+        const uint32_t o16 = cl * kStep + 16u * (uint32_t)ln.col, o8 = cl * kStep + 256u + 8u * (uint32_t)ln.col;
+        const v8i bx = mx_rec(dig, o16, o8);
+        v8i ba = bx;
+        if (BOTH) ba = mx_rec(dig + kRecBytes, o16, o8);
+        uint32_t x[kBlk + 1], y[kBlk + 1];
+#pragma unroll
+        for (int i = 0; i < kBlk + 1; ++i) {
+            x[i] = need_r ? ln.word(ln.J32 + c + i) : 0u;
+            y[i] = need_l ? __builtin_bitreverse32(ln.word(ln.J32 - c - 1 + i)) : 0u;
+        }
+#pragma unroll
+        for (int b = 0; b < kBlk; ++b) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int i = 2 * b + p;
+                const int j = 32 * (ln.J32 + b) + 16 * p + ln.r;
+                const int m = min(j, L - 1 - j);
+                // the shifts 32c + t of this row: t < n (BOTH) or t >= n
+                const int n = min(32, max(0, m + 1 - 32 * c));
+                const uint32_t lowm = n > 0 ? 0xFFFFFFFFu >> (32 - n) : 0u;
+                const uint32_t V = c >= ce ? 0u : BOTH ? lowm : ~lowm;
+                if (!__any(V != 0u)) continue;
+                const uint32_t R = __builtin_amdgcn_alignbit(x[b + 1], x[b], shr + 16u * p);
+                const uint32_t W = __builtin_amdgcn_alignbit(y[b], y[b + 1], shl - 16u * p);
+                if (BOTH) {
+                    const uint32_t q = xor_and(R, W, V), q2 = q >> 2;
+                    acc[i] = mx_mfma(q & kM0, q & kM1, q2 & kM0, q2 & kM1, bx, acc[i]);
+                    const uint32_t t = and_signed(R, W, ln.S[i]) & V, t2 = t >> 2;
+                    acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba, acc[i]);
+                } else {
+                    const uint32_t q = (j <= half ? R : W) & V, q2 = q >> 2;
+                    acc[i] = mx_mfma(q & kM0, q & kM1, q2 & kM0, q2 & kM1, bx, acc[i]);
+                }
             }
         }
     }
 }
 
-__global__ __launch_bounds__(64 * kLinWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_lin(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx(
     const WalkDev *__restrict__ walks, const BatchEntry *__restrict__ batch, const EvalItem *__restrict__ items)
 {
-    __shared__ v2u s_lut[256];
     const EvalItem it = items[blockIdx.x];
-    {
-        const uint32_t e = threadIdx.x;         // 256 threads, one entry each
-        uint32_t lo = 0, hi = 0;
-        for (int t = 0; t < 4; ++t) {
-            lo |= (((e >> t) & 1u) ? 0xFFu : 0x01u) << (8 * t);
-            hi |= (((e >> (t + 4)) & 1u) ? 0xFFu : 0x01u) << (8 * t);
-        }
-        s_lut[e] = v2u{lo, hi};
-    }
-    __syncthreads();
-    // no barrier from here on: wavefronts leave independently
-    if (it.walk == kLinNoWalk) return;
+    if (it.walk == kMxNoWalk) return;
     const BatchEntry be = batch[it.walk];
     if (!be.lsplit || !be.ss->use) return;
     const WalkDev &w = walks[be.slot];
     const int L = (int)w.L;
+    const uint32_t n_lmt = be.fixed ? be.n_lmt : w.n_lmt;
     const uint32_t start = be.fixed ? be.start : step_start(w);
-    // the sequence words from 32 words before the first (the guard words
-    // before it are zero and at least 2 nw + 4 >= 68 when L >= 2048)
-    const uint32_t *__restrict__ w32 = reinterpret_cast<const uint32_t *>(w.pivot) - 32;
-    const int nchunks = (L - 1 + 31) / 32;
-    const uint32_t K = split_row((uint32_t)L);
-    const int nblk = (L + kLinBlockElems - 1) / kLinBlockElems;
-    const int first = (int)(((start + 1u) % (uint32_t)L) / kLinBlockElems);
-    const int blk = (first + (int)it.tile) % nblk;
-    const int per = (nchunks + (int)be.lsplit - 1) / (int)be.lsplit;
-    const int c_lo = (int)it.ks * per, c_hi = min(nchunks, c_lo + per);
-    // the wavefront index read as a scalar: every matrix index, chunk bound
-    // and end-of-sequence test below is then uniform
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
-    const int jw = kLinBlockElems * blk + kLinWaveElems * wave;
-    if (jw >= L) return;
-    const int Gw = jw >> 5;
-    const int h = lane >> 5, row = lane & 31, dig = lane & 7;
+    // the tile: it.tile tiles past the one of the neighbourhood's first
+    // element; nothing to do when no candidate lies in it
+    const int ntile = (L + kMxTile - 1) / kMxTile;
+    const int j_first = (int)((start + 1u) % (uint32_t)L);
+    const int J0 = kMxTile * ((j_first / kMxTile + (int)it.tile) % ntile);
+    const int jt = min(J0 + kMxTile, L) - 1;
+    if (!(j_first >= J0 && j_first <= jt) && (J0 - j_first + (J0 < j_first ? L : 0)) >= (int)n_lmt) return;
+    const int half = (L - 1) / 2;
+    const int nco = (int)split_chunks((uint32_t)L), nbo = (int)split_both_chunks((uint32_t)L);
+    const int per = (nco + (int)be.lsplit - 1) / (int)be.lsplit;
+    const int c_lo = (int)it.ks * per, c_hi = min(nco, c_lo + per);
+    const int m0 = min(J0, L - 1 - J0), m1 = min(jt, L - 1 - jt);
+    const int m_min = min(m0, m1), m_max = J0 <= half && half <= jt ? half : max(m0, m1);
+    const int M_max = max(L - 1 - J0, jt);
 
-    LinLane ln;
-    ln.x = (lane & 31) >> 3;
-    ln.off0 = (uint32_t)dig * K + 16u * (uint32_t)h;
-    ln.off1 = (uint32_t)(kLimbs + dig) * K + 16u * (uint32_t)h;
-    ln.offz = ln.off0 + 32u * (uint32_t)nchunks;
-    ln.lo = INT_MAX;
-    ln.hi = INT_MIN;
+    const int lane = (int)threadIdx.x;
+    MxLane ln;
+    ln.w = reinterpret_cast<const uint32_t *>(w.pivot) - kPad;
+    ln.J32 = J0 >> 5;
+    ln.r = lane & 15;
+    ln.g = lane >> 4;
+    ln.col = lane & 15;
+    v4f acc[2 * kBlk];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        ln.n[p] = split_block_bound(min(jw + 256 * ln.x + 64 * p, L - 1), L) >> 5;
-        ln.lo = min(ln.lo, ln.n[p]);
-        ln.hi = max(ln.hi, ln.n[p]);
+    for (int i = 0; i < 2 * kBlk; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    {
+        // one neighbour: chunks o0 .. o1-1, those from f0 on past every m_j;
+        // a tile across the middle has both sides and is all edge
+        const int o0 = max(c_lo, (m_min + 1) >> 5), o1 = min(c_hi, (M_max >> 5) + 1);
+        int f0 = o1, N = 0;
+        if (jt <= half || J0 > half) {
+            f0 = max(o0, (m_max + 32) >> 5);
+            N = f0 < o1 ? (o1 - f0) / 4 : 0;
+        }
+        if (N > 0) {
+            if (jt <= half) mx_one<true>(acc, ln, be.dig_one, f0, N);
+            else            mx_one<false>(acc, ln, be.dig_one, f0, N);
+            mx_edge<false>(acc, ln, be.dig_one, L, f0 + 4 * N, o1, nco);
+        }
+        mx_edge<false>(acc, ln, be.dig_one, L, o0, N > 0 ? f0 : o1, nco);
     }
-    v16i acc[kLinAcc];
+    {
+        uint32_t sw[kBlk];
 #pragma unroll
-    for (int b = 0; b < kLinAcc; ++b) acc[b] = v16i{};
-    if (c_lo < c_hi) {
-        // right: position 32 t + 1 + row + 16 h for entries of matrix index t
-        const int tmax = (L - 2) >> 5;                   // the last index with a position below L
-        {
-            const int r0 = 1 + row + 16 * h;
-            ln.pb = r0;
-            ln.woff = r0 >> 5;
-            ln.sh = (uint32_t)r0 & 31u;
-            const int cs = c_lo, ce = min(c_hi + 24, tmax - Gw + 1);
-            if (cs < ce) lin_side<true>(acc, ln, w32, be.limbs, s_lut, L, Gw, c_lo, c_hi, cs, ce);
-        }
-        // left: entries t = 0..15 at positions P - t, P = 32 u - 1 + row - 16 h,
-        // read as the 32 bits from P - 15 on
-        {
-            const int q0 = row - 16 - 16 * h;
-            ln.pb = q0 + 15;
-            ln.woff = q0 >> 5;                           // arithmetic shift: floor
-            ln.sh = (uint32_t)q0 & 31u;
-            const int cs = c_lo - 24, ce = min(c_hi, Gw + kLinAcc);
-            if (cs < ce) lin_side<false>(acc, ln, w32, be.limbs, s_lut, L, Gw, c_lo, c_hi, cs, ce);
+        for (int b = 0; b < kBlk; ++b) sw[b] = ln.word(ln.J32 + b);
+        // rows with s_j = -1 change sign (accumulator register q: row 4 g + q)
+#pragma unroll
+        for (int i = 0; i < 2 * kBlk; ++i) {
+            const uint32_t bits = sw[i >> 1] >> (16 * (i & 1) + 4 * ln.g);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[i][q] = __uint_as_float(__float_as_uint(acc[i][q]) ^ ((bits << (31 - q)) & 0x80000000u));
+            ln.S[i] = (uint32_t)-(int)((sw[i >> 1] >> (16 * (i & 1) + ln.r)) & 1u);
         }
     }
-    // accumulator b, register r: row (r % 4) + 8 (r / 4) + 4 h of group
-    // G_w + b + 8 x, digit `dig`; the eight digits of an element sit in eight
-    // consecutive lanes
+    const int b1 = min(c_hi, (m_max >> 5) + 1);
+    if (c_lo < b1) {
+        const int fb = min(b1, (m_min + 1) >> 5);
+        const int N = fb > c_lo ? (fb - c_lo) / 4 : 0;
+        if (N > 0) mx_both(acc, ln, be.dig_both, c_lo, N);
+        mx_edge<true>(acc, ln, be.dig_both, L, c_lo + 4 * N, b1, nbo);
+    }
+
+    // digit column x weighs 32^x (in units of 8: the products are eighths);
+    // the 16 columns of a row sit in 16 lanes: each stage adds a partner's half
+    // of the values, until lane x of a group holds rows 4g .. 4g+3 of block x
+    const double wcol = ldexp(8.0, 5 * ln.col);
+    double v[32];
+    {
+        const bool up = ln.col & 8;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            const double lo = (double)acc[i >> 2][i & 3] * wcol, hi = (double)acc[8 + (i >> 2)][i & 3] * wcol;
+            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, 8);
+        }
+    }
+#pragma unroll
+    for (int n = 16, d = 4; n >= 4; n >>= 1, d >>= 1) {
+        const bool up = ln.col & d;
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + __shfl_xor(up ? v[i] : v[i + n], d);
+    }
     double *__restrict__ out = be.lpart + (size_t)it.ks * L;
+    const int j = J0 + 16 * ln.col + 4 * ln.g;
 #pragma unroll
-    for (int b = 0; b < kLinAcc; ++b) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            double v = ldexp((double)acc[b][r], 8 * dig);
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            const int j = 32 * (Gw + b + 8 * ln.x) + (r & 3) + 8 * (r >> 2) + 4 * h;
-            if (dig == 0 && j < L) out[j] = v;
-        }
-    }
+    for (int q = 0; q < 4; ++q)
+        if (j + q < L) out[j + q] = v[q];
 }
 
-hipError_t launch_lin(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
-                      hipStream_t s)
+hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
+                     hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    k_lin<<<n_items, 64 * kLinWaves, 0, s>>>(walks, batch, items);
+    k_mx<<<n_items, 64, 0, s>>>(walks, batch, items);
     return hipGetLastError();
 }
 

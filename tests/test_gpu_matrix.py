@@ -1,0 +1,69 @@
+"""The matrix path of the evaluation at the sizes where its tiling can go wrong
+(256-element tiles and a short last one, 32-shift chunks, k-splits, the tile
+across the middle, neighbourhoods that wrap past the end), against the table
+evaluation for every neighbour and the oracle for some. Both forms of F are
+sums of positive terms with at most a few hundred roundings (3e-14 relative)
+plus, here, the coefficients' quantization (1e-14): 1e-13 between them."""
+import numpy as np
+import pytest
+
+import oracle
+import seeded_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2107_09801_amd import libpsl
+    c = libpsl.Context(0)
+    yield c
+    c.close()
+
+
+def _eval(ctx, w, start, n, mode):
+    import torch
+    from paper_2107_09801_amd import libpsl
+    ctx.set_option(libpsl.OPT_SPLIT, mode)
+    try:
+        F = torch.empty(n, dtype=torch.float64, device="cuda:0")
+        P = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        return ctx.eval_neighbourhood(w, start, n, F, P), F.cpu().numpy(), P.cpu().numpy()
+    finally:
+        ctx.set_option(libpsl.OPT_SPLIT, -1)
+
+
+CASES = [(2048, 4, 0, 2048), (2303, 1, 2302, 2303), (2304, 2, 255, 257), (2305, 3, 256, 256), (2305, 13, 2303, 1),
+         (4096, 16, 2047, 4096), (4351, 4, 4095, 255), (8191, 10, 4000, 300), (8193, 4, 8190, 4099),
+         # the neighbourhood's 4099 elements start at the end of one 4096-element block, pass the
+         # sequence's last (one element long) and reach a fourth block
+         (12289, 13, 12286, 4099), (16640, 11, 16639, 16640), (30011, 4, 15000, 6912)]
+
+
+@pytest.mark.parametrize("L,alpha,start,n", CASES)
+def test_matrix_equals_table_and_oracle(ctx, L, alpha, start, n):
+    bits = si.random_bits(L, 1000 * L + alpha)
+    (w,) = ctx.init_walks(L, 1, 1, alpha1=alpha, alpha2=4, init_bits=[bits])
+    ch, F, P = _eval(ctx, w, start, n, 1)
+    ct, Ft, Pt = _eval(ctx, w, start, n, 0)
+    assert np.array_equal(P, Pt)
+    assert np.max(np.abs(F - Ft) / Ft) <= 1e-13
+    assert all(ch[k] == ct[k] for k in ("i_best", "j_best", "j_psl", "psl_min", "psl_k", "flags"))
+    s = si.to_pm1(bits, L)
+    C = oracle.corr(s)
+    for i in np.unique(np.linspace(0, n - 1, 9).astype(int)):
+        Fo, Po = oracle.eval_neighbourhood(s, C, alpha, (start + int(i)) % L, 1)
+        assert P[i] == Po[0] and abs(F[i] - Fo[0]) <= 1e-12 * Fo[0]
+    ctx.free_walks([w])
+
+
+@pytest.mark.parametrize("p_minus", [0.0, 0.05, 0.3])
+def test_matrix_biased_sequences(ctx, p_minus):
+    """Large |C_k| (the largest table indices and digits)."""
+    L = 5001
+    bits = si.biased_bits(L, 3, p_minus)
+    (w,) = ctx.init_walks(L, 1, 1, alpha1=13, alpha2=4, init_bits=[bits])
+    _, F, P = _eval(ctx, w, 77, L, 1)
+    _, Ft, Pt = _eval(ctx, w, 77, L, 0)
+    assert np.array_equal(P, Pt) and np.max(np.abs(F - Ft) / Ft) <= 1e-13
+    ctx.free_walks([w])
