@@ -37,10 +37,10 @@ PEAK_FP4_OPS = 1.0e16
 # both-neighbour shift and one per one-neighbour shift, 2 min(j, L-1-j) + |L-1-2j| = L-1 in
 # all, each with 16 digit columns.
 MX_OPS_PER_UPDATE = 2 * 16
-# Shortest walk the matrix path takes, and the fewest nominal updates of a
-# launch that takes it by default.
-SPLIT_MIN_L = 2048
-SPLIT_MIN_WORK = 1 << 34
+# Shortest walk the matrix path takes, and the fewest candidates per shift (on
+# average over its walks) of a launch that takes it by default.
+SPLIT_MIN_L = 512
+SPLIT_MIN_CAND = 512
 # VALU lane-ops per C_k-update of the direct form of the one-element flip: form
 # C' (1), fold |C'| into the running max (1), select T(|C'|) (1), one FP64 add
 # (1). The evaluation kernel needs fewer (it skips the unchanged shifts and
@@ -128,8 +128,8 @@ def parse():
                     help="time every evaluation launch shape on the batch first and keep the fastest")
     ap.add_argument("--split", type=int, default=-1, choices=[-1, 0, 1, 2],
                     help="matrix path of the evaluation: -1 the library default "
-                         "(2: for launches of at least 2^34 nominal updates), 0 off (table evaluation), "
-                         "1 wherever L >= 2048")
+                         "(2: for launches of at least 512 candidates per walk on average), 0 off (table "
+                         "evaluation), 1 wherever L >= 512")
     ap.add_argument("--tune-file", default="", help="evaluation launch shapes to load (psl_tune_load)")
     ap.add_argument("--eval-items", type=int, default=0,
                     help="minimum work items per evaluation launch (0 = the library default)")
@@ -654,7 +654,9 @@ def main():
     split_work = sum(count * min(L_, args.n_lmt or L_) * (L_ - 1) for L_, count in groups if L_ >= SPLIT_MIN_L)
     if wl == "paper":
         split_work = sum(count * min(L_, 6912) * (L_ - 1) for L_, count in groups if L_ >= SPLIT_MIN_L)
-    split_on = split_work > 0 and (args.split == 1 or (args.split in (-1, 2) and split_work >= SPLIT_MIN_WORK))
+    shifts = sum(count * (L_ - 1) for L_, count in groups if L_ >= SPLIT_MIN_L)
+    split_on = split_work > 0 and (args.split == 1 or
+                                   (args.split in (-1, 2) and split_work >= SPLIT_MIN_CAND * shifts))
     tag = f"{wl}_L{'-'.join(str(g[0]) for g in groups)}_w{nw}" + ("" if split_on else "_table")
     valu = measured_valu(tag)
     if valu is not None:

@@ -395,14 +395,15 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
 /* PSL_OPT_SPLIT: the matrix path of the evaluation (Eq. (5) over the
  * neighbours as 0/1 matrices, the XOR and AND of the two neighbours of
  * Section 3's one-element flip, times fixed-point coefficients, summed exactly
- * on the matrix cores) for walks of L >= 2048, in the steps that allow it (the
+ * on the matrix cores) for walks of L >= 512, in the steps that allow it (the
  * near-peak list holds the PSL and the quantization bound of the coefficients
  * is below 1e-14 of every neighbour's F). 2 (default; -1 restores it): in
- * batches and evaluations whose walks of L >= 2048 hold at least 2^34
- * nominal updates (N_lmt x (L-1) summed), below which its fixed cost exceeds
- * what it saves; 1: in every batch and evaluation; 0: never (every step takes
- * the table evaluation). Moves and PSL are the same either way (F agrees to
- * about 1e-14 relative); errors: PSL_E_INVAL outside -1..2. */
+ * batches and evaluations whose walks of L >= 512 evaluate at least 512
+ * candidates on average (N_lmt weighted by L-1), below which its preparation
+ * of every shift costs more than it saves; 1: in every batch and evaluation;
+ * 0: never (every step takes the table evaluation). Moves and PSL are the same
+ * either way (F agrees to about 1e-14 relative); errors: PSL_E_INVAL outside
+ * -1..2. */
 #define PSL_OPT_SPLIT 4
 /* PSL_OPT_TEST_FAIL_ADMIT: a test hook of the request loop. With n >= 1, the
  * n-th admission (counted per psl_serve_start, admissions that take at least

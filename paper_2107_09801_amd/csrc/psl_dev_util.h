@@ -121,4 +121,22 @@ __device__ __forceinline__ void seg_of(const SegMap &m, uint32_t i, uint32_t &b,
     seg = i - m.off[lo];
 }
 
+// The fields of an evaluation call into its plan's entry, by one thread of the
+// call's first kernel.
+__device__ __forceinline__ void eval_call(BatchEntry *batch, const EvalCall &call)
+{
+    if (!call.on) return;
+    batch[0].start = call.start;
+    batch[0].F = call.F;
+    batch[0].P = call.P;
+}
+
+// Prefix sum x (0 .. 3, BatchEntry::pre) of a matrix walk over the shifts
+// 1 .. k: the one within the segment plus the segment's offset.
+__device__ __forceinline__ double split_prefix(const BatchEntry &be, uint32_t L, int x, uint32_t k)
+{
+    const uint32_t seg = min(k >> be.seg_shift, seg_count(L, be.seg_shift) - 1u);
+    return be.pre[(size_t)x * L + k] + be.segoff[4 * (size_t)seg + x];
+}
+
 }  // namespace psl

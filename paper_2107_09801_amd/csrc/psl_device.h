@@ -105,23 +105,27 @@ struct BatchEntry {
     // matrix path (psl_split.hip): this step's coefficients of the walk
     uint8_t *dig_both;      // [split_both_chunks(L)][2] digit records of the XOR and AND coefficients
     uint8_t *dig_one;       // [split_chunks(L)] digit records of the one-neighbour coefficient
-    double *pre;            // [4][L]: prefix sums over 1..k of T(|C_k-4|) (both-neighbour shifts), T(|C_k-2|),
-                            // T(|C_k+2|), T(|C_k|); entry 0 is 0
+    double *pre;            // [4][L]: prefix sums over the segment's shifts up to k of T(|C_k-4|) (both-neighbour
+                            // shifts), T(|C_k-2|), T(|C_k+2|), T(|C_k|)
+    double *segoff;         // [segments][4]: their segments' totals, then offsets (SegMap segments)
+    uint32_t seg_shift;     // log2 of a segment's shifts
+    uint32_t pad;
     struct SplitState *ss;  // scale and path choice of this step
-    double *lpart;          // [lsplit][L]: partial sums (in units of the scale), by element
+    double *lpart;          // [lsplit + 1][L]: partial sums (in units of the scale), by element; the last the edges'
 };
 
 // Matrix path (psl_split.hip): items of kMxTile elements (a padding item has
 // walk kMxNoWalk); digit records of kRecBytes, one per coefficient and 32-shift
 // chunk (shifts 32c .. 32c+31, the shifts 0 and past L-1 with digits 0), for
-// the chunks of all shifts and those of the both-neighbour shifts; kRecPad
-// records after the last are read ahead and not used.
+// the chunks of all shifts and those of the both-neighbour shifts, and a
+// record of zeros after the last.
 constexpr int kMxTile = 256;
 constexpr int kRecBytes = 384;
-constexpr uint32_t kRecPad = 4;
+constexpr uint32_t kRecPad = 1;
 __host__ __device__ constexpr uint32_t split_chunks(uint32_t L) { return (L - 1) / 32 + 1; }
 __host__ __device__ constexpr uint32_t split_both_chunks(uint32_t L) { return (L - 1) / 2 / 32 + 1; }
 constexpr uint32_t kMxNoWalk = 0xFFFFFFFFu;
+constexpr uint32_t kMxOffsets = 0xFFFFFFFFu;   // tile of the item that makes a walk's offsets
 struct SplitState {
     double U;               // the quantum, a power of two
     uint32_t use;           // 1: this step evaluates the walk on the split path
@@ -136,6 +140,15 @@ struct SelPart {
     uint32_t i;
 };
 constexpr uint32_t kCombMaxBlocks = 256;   // combine blocks per walk, at most
+
+// What one evaluation call adds to its plan's entry (the first kernel writes
+// it, before any kernel reads it): the start and the F and PSL arrays.
+struct EvalCall {
+    double *F;
+    int32_t *P;
+    uint32_t start;
+    uint32_t on;            // 0: a step, nothing to write
+};
 
 // Blocks of an O(L) pass over a batch: a walk's shifts k = 1..L-1 are cut
 // into segments of 2^shift (256 .. 4096, chosen per batch so that the pass
@@ -167,6 +180,8 @@ struct EvalItem {
     uint32_t ks;
     uint32_t pad;
 };
+// Matrix item: ks below lsplit: a main item; lsplit + part: an edge item (pad:
+// all four parts); tile kMxOffsets: the offsets of the walk's prefix sums, array ks.
 
 // XCDs of the MI355X (32 CUs and one L2 each); workgroup i of a launch runs
 // on XCD i mod kXcds.

@@ -62,7 +62,7 @@ struct EvalLds {
 
 // The sweep of one item. kMax: keep the PSL maximum in the main loop (dense
 // form); otherwise the near-peak pass supplies it.
-template <int WAVES, bool kMax>
+template <int WAVES, bool kMax, bool kMatrix>
 __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w, const BatchEntry &be,
                                            const EvalItem &it, const double *__restrict__ T,
                                            uint32_t n_lmt, int j, uint32_t SJ, int k_lo, int k_hi,
@@ -296,6 +296,17 @@ __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w,
     // and take the chunks' largest |C_k|.
     const int kn = max(k_lo, k_wend);
     if (kn < k_hi) {
+        if (kMatrix && be.lsplit) {
+            // a matrix walk left to this evaluation has prefix sums instead of
+            // chunk arrays; the largest |C_k| comes from C itself
+            nsum_add(sum, comp, split_prefix(be, L, 3, k_hi - 1) - split_prefix(be, L, 3, kn - 1));
+            if (kMax) {
+                int cm = 0;
+                for (int k = kn + lane; k < k_hi; k += 64) cm = max(cm, C[k] < 0 ? -C[k] : C[k]);
+                mx = max(mx, hi32(T[wave_max(cm, lane)]));
+            }
+            return;
+        }
         const int nchunks = (L - 1 + 31) / 32;
         const int xa = (kn - 1) >> 5;
         const int xb = k_hi >= L ? nchunks : (k_hi - 1) >> 5;
@@ -335,13 +346,15 @@ __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w,
 // max(j, L-1-j) come from the suffix sums. The PSL comes from the near-peak
 // shifts (spread over the k-splits), or, for pivots with many near-peak shifts, from
 // 32-bit maxima kept in the main loop.
-template <int WAVES>
+// kMatrix: the batch has matrix walks (a walk on the matrix path in this step
+// is left out; one that is not has prefix sums in place of chunk arrays).
+template <int WAVES, bool kMatrix>
 __device__ __forceinline__ void eval_item(EvalLds<WAVES> &sh, const WalkDev *__restrict__ walks,
                                           const BatchEntry *__restrict__ batch, const EvalItem it,
                                           const Tables &tabs, int tid)
 {
     const BatchEntry be = batch[it.walk];
-    if (be.lsplit != 0 && be.ss->use != 0) return;    // on the matrix path (psl_split.hip) in this step
+    if (kMatrix && be.lsplit != 0 && be.ss->use != 0) return;
     const WalkDev &w = walks[be.slot];
     const int L = (int)w.L;
     const uint32_t n_lmt = be.fixed ? be.n_lmt : w.n_lmt;
@@ -369,9 +382,9 @@ __device__ __forceinline__ void eval_item(EvalLds<WAVES> &sh, const WalkDev *__r
     uint32_t mx = 0;
     const uint32_t n_near = be.near[0];
     if (n_near > be.near_lim) {
-        eval_sweep<WAVES, true>(sh, w, be, it, T, n_lmt, j, SJ, k_lo, k_hi, tid, sum, comp, mx);
+        eval_sweep<WAVES, true, kMatrix>(sh, w, be, it, T, n_lmt, j, SJ, k_lo, k_hi, tid, sum, comp, mx);
     } else {
-        eval_sweep<WAVES, false>(sh, w, be, it, T, n_lmt, j, SJ, k_lo, k_hi, tid, sum, comp, mx);
+        eval_sweep<WAVES, false, kMatrix>(sh, w, be, it, T, n_lmt, j, SJ, k_lo, k_hi, tid, sum, comp, mx);
         {
             // PSL over the near-peak shifts, every candidate, all bounds
             // cases; split s takes entries s, s + ksplit, ... (the combine
@@ -422,20 +435,20 @@ void k_eval(const WalkDev *__restrict__ walks,
     __shared__ EvalLds<WAVES> sh;
     const EvalItem it = items[xcd_remap(blockIdx.x, gridDim.x)];
     if (it.walk == kNoItem) return;     // padding of an XCD's range
-    eval_item<WAVES>(sh, walks, batch, it, tabs, (int)threadIdx.x);
+    eval_item<WAVES, false>(sh, walks, batch, it, tabs, (int)threadIdx.x);
 }
 
 // Persistent form: a fixed grid (blocks per CU x CUs) takes items from 8
 // per-XCD queues, its own XCD's first (longest items first), then the
 // others'. Every block leaves once all 8 queues are drained.
-template <int WAVES>
+template <int WAVES, bool kMatrix>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kEvalWavesPerEU<WAVES>)))
 void k_eval_persistent(const WalkDev *__restrict__ walks,
                                                                 const BatchEntry *__restrict__ batch,
                                                                 const EvalItem *__restrict__ items,
                                                                 Tables tabs, EvalQueues *queues, const uint32_t *tab)
 {
-    if (tab && *tab == 0) return;       // every walk is on the matrix path
+    if (kMatrix && *tab == 0) return;   // every walk is on the matrix path
     __shared__ EvalLds<WAVES> sh;
     __shared__ uint32_t s_item;
     uint32_t q = blockIdx.x % 8, dry = 0;
@@ -458,7 +471,7 @@ void k_eval_persistent(const WalkDev *__restrict__ walks,
         int tid = (int)threadIdx.x;
         asm volatile("" : "+v"(tid));
         __builtin_assume(tid >= 0 && tid < 64 * WAVES);
-        eval_item<WAVES>(sh, walks, batch, items[item], tabs, tid);
+        eval_item<WAVES, kMatrix>(sh, walks, batch, items[item], tabs, tid);
     }
 }
 
@@ -479,7 +492,7 @@ void k_eval_strided(const WalkDev *__restrict__ walks, const BatchEntry *__restr
         int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
         asm volatile("" : "+v"(tid));
         __builtin_assume(tid >= 0 && tid < 64 * WAVES);
-        eval_item<WAVES>(sh, walks, batch, it, tabs, tid);
+        eval_item<WAVES, true>(sh, walks, batch, it, tabs, tid);
     }
 }
 
@@ -495,10 +508,12 @@ static void launch_eval_waves(const WalkDev *walks, const BatchEntry *batch, con
                               const Tables &tabs, const EvalShape &shape, EvalQueues *queues, const uint32_t *tab,
                               uint32_t n_cu, hipStream_t s)
 {
-    if (shape.persistent)
-        k_eval_persistent<WAVES><<<shape.grid, 64 * WAVES, 0, s>>>(walks, batch, items, tabs, queues, tab);
+    if (shape.persistent && tab)
+        k_eval_persistent<WAVES, true><<<shape.grid, 64 * WAVES, 0, s>>>(walks, batch, items, tabs, queues, tab);
+    else if (shape.persistent)
+        k_eval_persistent<WAVES, false><<<shape.grid, 64 * WAVES, 0, s>>>(walks, batch, items, tabs, queues, tab);
     else if (tab)
-        k_eval_strided<WAVES><<<std::min(n_items, 8u * n_cu), 64 * WAVES, 0, s>>>(walks, batch, items, n_items, tabs, tab);
+        k_eval_strided<WAVES><<<std::min(n_items, (WAVES == 4 ? 6u : WAVES == 8 ? 3u : 2u) * n_cu), 64 * WAVES, 0, s>>>(walks, batch, items, n_items, tabs, tab);
     else
         k_eval<WAVES><<<n_items, 64 * WAVES, 0, s>>>(walks, batch, items, tabs);
 }

@@ -7,6 +7,7 @@
 #include "psl_launch.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -109,7 +110,6 @@ struct BatchPlan {
     uint32_t *d_pend = nullptr;       // pending list: count, then batch positions
     uint32_t *d_done = nullptr;       // per batch position: combine blocks finished (0 between launches)
     uint32_t fixed_n = 0;             // plans of a fixed neighbourhood: its N_lmt (0: not fixed)
-    uint32_t fixed_start = 0;         // ... and the start its batch entry holds
     uint32_t *d_seg = nullptr;        // segment map of the O(L) passes
     double *d_segtot = nullptr;       // per segment: chunk-sum total (suffix pass)
     uint32_t *d_segmax = nullptr;     // per segment: maximum |C_k|
@@ -122,6 +122,8 @@ struct BatchPlan {
     EvalItem *d_mitems = nullptr;     // matrix items
     uint32_t n_mitems = 0;
     uint32_t *d_tab = nullptr;        // walks left to the table evaluation in this step
+    double *d_segoff = nullptr;       // per segment: totals, then offsets, of the prefix sums
+    bool all_split = false;           // every walk of the plan can take the matrix path
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -130,10 +132,19 @@ constexpr size_t kPlanCache = 8;   // step batches whose layout (and graph) is k
 constexpr uint32_t kEvalItemsDefault = 4096;    // PSL_OPT_EVAL_ITEMS default
 constexpr uint32_t kEvalItemsMax = 1u << 18;    // and its largest value
 constexpr int64_t kAmbigMarginMax = 1000000000000000ll;  // PSL_OPT_AMBIG_MARGIN: 1.0 in units of 1e-15
-constexpr uint32_t kSplitMinL = 2048;          // shortest walk the split evaluation takes
-constexpr uint64_t kSplitMinWork = 1ull << 34; // fewest nominal updates of a launch that takes it
-constexpr uint32_t kMxItemsTarget = 4096;      // matrix items per launch the k-splits aim for
-constexpr uint32_t kMxMinChunks = 32;           // fewest shift chunks per k-split of a matrix item
+// The matrix path takes walks of at least kSplitMinL elements (its windows stay
+// within the guards from 400 elements on) in launches that evaluate on average
+// at least kSplitMinCand candidates per shift: its preparation costs every
+// shift the same however few candidates there are. Table against matrix, us
+// per step of one walk: L = 600 full 53 / 38, 16383 N_lmt = 2048 41 / 41,
+// 262143 N_lmt = 256 / 512 / 1024 49 / 60, 56 / 62, 75 / 62; of 64 walks at
+// L = 16383 N_lmt = 256 / 512 / 1024 88 / 90, 106 / 95, 141 / 107.
+constexpr uint32_t kSplitMinL = 512;
+constexpr uint64_t kSplitMinCand = 512;
+constexpr uint32_t kMxMinChunks = 8;            // fewest shift chunks per k-split of a matrix item
+constexpr uint64_t kCombLanes = 32768;          // lanes a combine of few candidates spreads over
+constexpr uint64_t kCombBlocks = 4096;          // and blocks, at one pass of candidates each
+constexpr uint32_t kMxEdgeWhole = 8192;         // main items of a launch from which a tile's edge is one item
 
 
 struct Server;   // serving loop (psl_serve.hip)
@@ -158,7 +169,7 @@ struct psl_ctx {
     std::vector<BatchPlan> plans;     // recent step batches, most recent last
     BatchPlan pure;                   // single-walk plan of psl_eval_neighbourhood (kept for the next call)
     psl::BatchEntry *d_one = nullptr; // psl_apply_flip's batch entry (allocated on first use)
-    void *d_choice = nullptr;
+    void *d_choice = nullptr;         // choice record of psl_eval_neighbourhood (pinned host memory)
     std::string err;
     int64_t near_limit = -1;          // PSL_OPT_NEAR_LIMIT
     uint32_t eval_items = psl_rt::kEvalItemsDefault;  // PSL_OPT_EVAL_ITEMS

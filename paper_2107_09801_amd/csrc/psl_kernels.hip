@@ -3,6 +3,7 @@
 // correlations of Eq. (2), the phase-switch rebuild, the per-step chunk sums
 // and near-peak list the evaluation reads, the selection of Algorithm 1's
 // scan, the O(L) flip of Section 3 and the step's bookkeeping.
+#include "psl_chunks.h"
 #include "psl_dev_util.h"
 #include "psl_device.h"
 #include "psl_launch.h"
@@ -115,12 +116,11 @@ __device__ __forceinline__ int32_t switch_flip_delta(const uint64_t *lb, uint32_
     return -2 * sp * d;
 }
 
-// C_k of the switched pivot for a shift k in D: each flip reads the elements
-// as the earlier flips left them.
-__device__ __forceinline__ int32_t switch_corr_seq(const uint64_t *lb, const int32_t *C_lb, uint32_t L,
-                                                   uint32_t k, const uint32_t *fl, uint32_t nf)
+// C_k of the switched pivot for a shift k in D, from c = C_k of local_best: each
+// flip reads the elements as the earlier flips left them.
+__device__ __forceinline__ int32_t switch_corr_seq(const uint64_t *lb, int32_t c, uint32_t L, uint32_t k,
+                                                   const uint32_t *fl, uint32_t nf)
 {
-    int32_t c = C_lb[k];
     for (uint32_t h = 0; h < nf; ++h) {
         // element x after flips 0..h-1
         auto bit = [&](uint32_t x) {
@@ -138,113 +138,91 @@ __device__ __forceinline__ int32_t switch_corr_seq(const uint64_t *lb, const int
     return c;
 }
 
-// After the step's bookkeeping, in two launches: C of every pending walk's
-// new pivot from C of its local best (a switch of more than kFlipIncremental
-// flips has C rebuilt by k_corr before), then F (Eq. (5)) and the PSL (Eq.
-// (3)) of that pivot, which become F_pivot, psl_pivot and v_local.
-// k_pending: work units of kPendUnit shifts are dealt round-robin over the
-// grid, walk after walk. A unit marks the shifts of D in its range in an LDS
-// bitmap, computes and stores its C values, and leaves the sum of T(|C_k|)
-// (lanes, then wavefronts, in a fixed order) and the maximum |C_k| in the
-// walk's chunk arrays. k_pending_fin adds each walk's unit sums in unit order.
+// The sum of T(|C_k|) (sum + comp) and the maximum |C_k| over a block's
+// threads (lanes by a butterfly, then wavefronts in order) into pair u of the
+// walk's chunk arrays.
 constexpr int kPendThreads = 256;
+struct PendLds {
+    double s[kPendThreads / 64], c[kPendThreads / 64];
+    uint32_t m[kPendThreads / 64];
+};
+__device__ __forceinline__ void pend_store(PendLds &sh, double ts, double tc, uint32_t tm, const BatchEntry &be, uint32_t u)
+{
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    // every lane of the butterfly ends with the same sums
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ps = __shfl_xor(ts, o), pc = __shfl_xor(tc, o);
+        const uint32_t pm = (uint32_t)__shfl_xor((int)tm, o);
+        nsum_add(ts, tc, ps);
+        tc += pc;
+        tm = max(tm, pm);
+    }
+    if (lane == 0) {
+        sh.s[wave] = ts;
+        sh.c[wave] = tc;
+        sh.m[wave] = tm;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double us = 0.0, uc = 0.0;
+        uint32_t um = 0;
+        for (int x = 0; x < kPendThreads / 64; ++x) {
+            nsum_add(us, uc, sh.s[x]);
+            uc += sh.c[x];
+            um = max(um, sh.m[x]);
+        }
+        be.S0[2 * u] = us;
+        be.S0[2 * u + 1] = uc;
+        be.M0[u] = um;
+    }
+}
 
+// Pending walks whose Rand_flip is too large for the one-flip rebuild, after
+// k_corr: the sums of T(|C_k|) of their new pivot, in work units of kPendUnit
+// shifts dealt round-robin over the grid, walk after walk.
 __global__ __launch_bounds__(kPendThreads) void k_pending(WalkDev *walks, const BatchEntry *batch, Tables tabs,
                                                           const uint32_t *pend)
 {
-    __shared__ uint32_t s_fl[kFlipIncremental];
-    __shared__ uint32_t s_in[kPendUnit / 32];
-    __shared__ double s_s[kPendThreads / 64], s_c[kPendThreads / 64];
-    __shared__ uint32_t s_m[kPendThreads / 64];
+    __shared__ PendLds sh;
     const uint32_t np = pend[0];
     const uint32_t G = gridDim.x;
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
     uint32_t base = 0;                  // units of the earlier pending walks
     for (uint32_t q = 0; q < np; ++q) {
         const BatchEntry be = batch[pend[1 + q]];
         WalkDev &w = walks[be.slot];
+        if (w.n_flips <= kFlipIncremental) continue;
         const uint32_t L = w.L;
         const uint32_t nu = (L - 1 + kPendUnit - 1) / kPendUnit;
-        const uint32_t nf = w.n_flips;
-        const bool incr = nf <= kFlipIncremental;
         const double *T = tabs.T[w.alpha];
         for (uint32_t u = (blockIdx.x + G - base % G) % G; u < nu; u += G) {
             const uint32_t k_lo = 1 + u * kPendUnit, k_hi = min(L, k_lo + kPendUnit);
-            __syncthreads();            // the previous unit is done with the LDS
-            if (incr) {
-                if (threadIdx.x < nf) s_fl[threadIdx.x] = w.flips[threadIdx.x];
-                if (threadIdx.x < kPendUnit / 32) s_in[threadIdx.x] = 0;
-            }
-            __syncthreads();
-            if (incr) {
-                for (uint32_t pr = threadIdx.x; pr < nf * nf; pr += kPendThreads) {
-                    const uint32_t f = pr / nf, g = pr - f * nf;
-                    if (g >= f) continue;
-                    const uint32_t k = s_fl[f] > s_fl[g] ? s_fl[f] - s_fl[g] : s_fl[g] - s_fl[f];
-                    if (k >= k_lo && k < k_hi) atomicOr(&s_in[(k - k_lo) >> 5], 1u << ((k - k_lo) & 31u));
-                }
-            }
-            __syncthreads();
             double ts = 0.0, tc = 0.0;
             uint32_t tm = 0;
             for (uint32_t k = k_lo + threadIdx.x; k < k_hi; k += kPendThreads) {
-                int32_t c;
-                if (incr) {
-                    const uint32_t o = k - k_lo;
-                    if ((s_in[o >> 5] >> (o & 31u)) & 1u) {
-                        c = switch_corr_seq(w.local_best, w.C_lb, L, k, s_fl, nf);
-                    } else {
-                        c = w.C_lb[k];
-                        for (uint32_t f = 0; f < nf; ++f) c += switch_flip_delta(w.local_best, L, k, s_fl[f]);
-                    }
-                    w.C[k] = c;
-                } else {
-                    c = w.C[k];
-                }
+                const int32_t c = w.C[k];
                 const uint32_t a = (uint32_t)(c < 0 ? -c : c);
                 nsum_add(ts, tc, T[a]);
                 tm = max(tm, a);
             }
-            // every lane of the butterfly ends with the same sums
-            for (int o = 32; o > 0; o >>= 1) {
-                const double ps = __shfl_xor(ts, o), pc = __shfl_xor(tc, o);
-                const uint32_t pm = (uint32_t)__shfl_xor((int)tm, o);
-                nsum_add(ts, tc, ps);
-                tc += pc;
-                tm = max(tm, pm);
-            }
-            if (lane == 0) {
-                s_s[wave] = ts;
-                s_c[wave] = tc;
-                s_m[wave] = tm;
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                double us = 0.0, uc = 0.0;
-                uint32_t um = 0;
-                for (int x = 0; x < kPendThreads / 64; ++x) {
-                    nsum_add(us, uc, s_s[x]);
-                    uc += s_c[x];
-                    um = max(um, s_m[x]);
-                }
-                be.S0[2 * u] = us;
-                be.S0[2 * u + 1] = uc;
-                be.M0[u] = um;
-            }
+            __syncthreads();            // the previous unit is done with the LDS
+            pend_store(sh, ts, tc, tm, be, u);
         }
         base += nu;
     }
 }
 
-// One wavefront per pending walk: the units' sums in unit order.
-__global__ __launch_bounds__(64) void k_pending_fin(WalkDev *walks, const BatchEntry *batch, const uint32_t *pend)
+// One wavefront per pending walk: the sums of its segments (k_apply) or units
+// (k_pending) in order become F_pivot = v_local and psl_pivot.
+__global__ __launch_bounds__(64) void k_pending_fin(WalkDev *walks, const BatchEntry *batch, const uint32_t *pend,
+                                                    uint32_t seg_shift)
 {
     const uint32_t np = pend[0];
     const int lane = (int)threadIdx.x;
     for (uint32_t q = blockIdx.x; q < np; q += gridDim.x) {
         const BatchEntry be = batch[pend[1 + q]];
         WalkDev &w = walks[be.slot];
-        const uint32_t nu = (w.L - 1 + kPendUnit - 1) / kPendUnit;
+        const uint32_t nu = w.n_flips <= kFlipIncremental ? seg_count(w.L, seg_shift)
+                                                          : (w.L - 1 + kPendUnit - 1) / kPendUnit;
         // lane l adds units l, l + 64, ... in order, then the lanes in a
         // fixed butterfly (every lane ends with the same sums)
         double s = 0.0, c = 0.0;
@@ -321,157 +299,24 @@ __global__ __launch_bounds__(kFitThreads) void k_fitness(WalkDev *walks, const B
 
 // --------------------------------------------- neighbourhood evaluation
 
-// Per walk and step, from the pivot's C:
-//  * chunk suffix sums S0[x] = sum_{1+32x <= k' < L} T(|C_k'|) and
-//    M0[x] = max |C_k'| over the same range, x = 0..nchunks (the last entry
-//    0). A candidate j leaves every C_k with k > max(j, L-1-j) unchanged
-//    (both neighbours of the flipped element are out of bounds), so that
-//    part of its F (and PSL) is read from them; the evaluation only needs
-//    them at 32-shift chunk starts;
-//  * the near-peak shift list: with P the pivot's PSL, every neighbour has
-//    PSL >= P - 4 (one flip moves each C_k by at most 4), and a shift with
-//    |C_k| <= P - 9 reaches at most P - 5, so a neighbour's PSL is the maximum
-//    of |C'_k| over the shifts with |C_k| >= P - 8 alone. near[0] = count,
-//    near[1..] = those shifts (any order), while the count fits kNearCap.
-// Two kernels: k_chunks (several blocks per walk) writes per-chunk sums and
-// maxima and appends to the near list; k_seg_scan (step) or k_scan (init)
-// turns the chunk values into suffix values in a fixed order. The same pair
-// is also the fitness of a pivot: S0[0] = F and M0[0] = PSL (mode 2, init).
-constexpr int kChunkThreads = 256;
 constexpr uint32_t kMaxGridY = 65535;      // walks per launch of the 2-D grids
-// Octets o0, o0 + step, ... below o1 of one walk (an octet is 256 consecutive
-// shifts, eight chunks), for the calling wavefront: four coalesced passes of
-// 64 shifts put T(|C_k|) and |C_k| in the wavefront's LDS rows (sv, sa); then
-// lane l adds the four consecutive values 4(l mod 8) .. +3 of chunk l / 8
-// (left to right) and a three-level butterfly over the chunk's eight lanes
-// finishes its sum and maximum, the same in all eight. The octet's total (a
-// fixed tree over its chunks) goes into the wavefront's running total.
-__device__ __forceinline__ void chunk_octs(const BatchEntry &be, const WalkDev &w, const double *T, int cut,
-                                           bool near, int o0, int o1, int step, double *sv, int *sa,
-                                           double &ws, double &wc, uint32_t &wm)
-{
-    const int L = (int)w.L;
-    const int nchunks = (L - 1 + 31) / 32;
-    const int lane = threadIdx.x & 63;
-    for (int o = o0; o < o1; o += step) {
-        // the four passes' C values, then their T values, are all loaded
-        // before any is used (two waits per octet, not eight)
-        int av[4];
-        double tv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 1 + 256 * o + 64 * i + lane;
-            const int32_t x = k < L ? w.C[k] : 0;
-            av[i] = x < 0 ? -x : x;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 1 + 256 * o + 64 * i + lane;
-            tv[i] = k < L ? T[av[i]] : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = 64 * i + lane;
-            const int k = 1 + 256 * o + e;
-            const int a = av[i];
-            sv[e] = tv[i];
-            sa[e] = a;
-            if (near) {
-                const bool take = k < L && a >= cut;
-                const uint64_t bal = __ballot(take);
-                if (bal) {
-                    uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&be.near[0], (uint32_t)__popcll(bal));
-                    base = (uint32_t)__shfl((int)base, 0);
-                    const uint32_t q = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-                    if (take && q < (uint32_t)kNearCap) be.near[1 + q] = (uint32_t)k;
-                }
-            }
-        }
-        // the wavefront's rows are written before any lane reads them
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int r = 32 * (lane >> 3) + 4 * (lane & 7);
-        double v = sv[r];
-        v += sv[r + 1];
-        v += sv[r + 2];
-        v += sv[r + 3];
-        int m = max(max(sa[r], sa[r + 1]), max(sa[r + 2], sa[r + 3]));
-        for (int d = 1; d < 8; d <<= 1) {
-            v += __shfl_xor(v, d);
-            m = max(m, __shfl_xor(m, d));
-        }
-        const int c = 8 * o + (lane >> 3);
-        if ((lane & 7) == 0 && c < nchunks) {
-            be.S0[c] = v;
-            be.M0[c] = (uint32_t)m;
-        }
-        // the octet's total over its chunk leaders (every lane ends with it)
-        double ts = v, tc = 0.0;
-        for (int d = 8; d < 64; d <<= 1) {
-            const double ps = __shfl_xor(ts, d), pc = __shfl_xor(tc, d);
-            nsum_add(ts, tc, ps);
-            tc += pc;
-            m = max(m, __shfl_xor(m, d));
-        }
-        nsum_add(ws, wc, ts);
-        wc += tc;
-        wm = max(wm, (uint32_t)m);
-        // every lane has read the rows before the next octet overwrites them
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
-}
 
 // Mode 0 (step, with the near list) and 2 (init): one block per segment of
 // the map.
-__global__ __launch_bounds__(kChunkThreads) void k_chunks(const WalkDev *walks, const BatchEntry *batch,
+__global__ __launch_bounds__(kChunkThreads) void k_chunks(const WalkDev *walks, BatchEntry *batch,
                                                           Tables tabs, int mode, SegMap map, uint32_t *pend,
-                                                          uint32_t *tab)
+                                                          EvalCall call)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) eval_call(batch, call);
     // the previous step's pending list has been consumed; this step's
     // bookkeeping (in the selection) refills it
     if (pend && blockIdx.x == 0 && threadIdx.x == 0) pend[0] = 0;
-    if (tab && blockIdx.x == 0 && threadIdx.x == 0) tab[0] = 0;
-    const int wave = (int)threadIdx.x >> 6;
-    constexpr int kWaves = kChunkThreads / 64;
+    __shared__ ChunkLds sh;
     uint32_t b, seg;
     seg_of(map, blockIdx.x, b, seg);
     const BatchEntry be = batch[b];
     const WalkDev &w = walks[be.slot];
-    const int nocts = ((int)w.L - 1 + 255) / 256;
-    const int octs_per_seg = 1 << (map.shift - 8);
-    const int o0 = (int)seg * octs_per_seg;
-    const int o1 = min(nocts, o0 + octs_per_seg);
-    __shared__ double s_v[kWaves][256];
-    __shared__ int s_a[kWaves][256];
-    // the near-peak cut (the pivot's PSL is kept current by every step)
-    double ws = 0.0, wc = 0.0;
-    uint32_t wm = 0;
-    chunk_octs(be, w, tabs.T[w.alpha], w.psl_pivot - 8, mode == 0, o0 + wave, o1, kWaves, s_v[wave], s_a[wave],
-               ws, wc, wm);
-    if (map.tot) {
-        // the segment's total (waves in order) for the segment-parallel scan
-        __shared__ double s_s[kWaves], s_c[kWaves];
-        __shared__ uint32_t s_m[kWaves];
-        if ((threadIdx.x & 63) == 0) {
-            s_s[wave] = ws;
-            s_c[wave] = wc;
-            s_m[wave] = wm;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double ts = 0.0, tc = 0.0;
-            uint32_t tm = 0;
-            for (int x = 0; x < kWaves; ++x) {
-                nsum_add(ts, tc, s_s[x]);
-                tc += s_c[x];
-                tm = max(tm, s_m[x]);
-            }
-            map.tot[blockIdx.x] = ts + tc;
-            map.tmax[blockIdx.x] = tm;
-        }
-    }
+    chunk_segment(sh, be, w, tabs.T[w.alpha], mode, map, seg);
 }
 
 // Suffix values of the step's chunk arrays, one wavefront per segment of the
@@ -489,6 +334,7 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(const WalkDev *wal
     uint32_t b, seg;
     seg_of(map, i, b, seg);
     const BatchEntry be = batch[b];
+    if (be.lsplit) return;                   // a matrix walk has no chunk arrays
     const WalkDev &w = walks[be.slot];
     const int nchunks = ((int)w.L - 1 + 31) / 32;
     const int cps = 1 << (map.shift - 5);    // chunks per segment
@@ -655,7 +501,8 @@ struct ChoiceDev {
     uint32_t j_psl;
     int32_t psl_min;
     int32_t psl_k;
-    uint32_t flags;         // CHOICE_AMBIG_ARGMIN (set with the selection)
+    uint32_t flags;         // CHOICE_AMBIG_ARGMIN
+    uint32_t table;         // 1: no choice yet, the walk is left to the table evaluation
 };
 
 constexpr int kCombThreads = 256;
@@ -684,102 +531,201 @@ __device__ __forceinline__ void sel_merge(double &f, int32_t &p, uint32_t &i, do
     }
 }
 
-// The scan of Algorithm 1 over the combined F and PSL: the move is the first
-// candidate in scan order within F_min*(1+tau); the best-PSL neighbour is the
-// first with the minimum PSL.
-// pure != 0: write the choice to out[b] and leave the walk unchanged.
-// Otherwise record the choice in the walk and, on a strict PSL improvement,
-// update psl_best and solution_best = pivot with j_psl flipped.
-// The selection of walk w (batch position bi) by a block of NT threads.
-template <int NT>
-__device__ __forceinline__ void select_walk(WalkDev &w, const BatchEntry &be, uint32_t bi, uint32_t comb_blocks,
-                                            uint32_t comb_group, int pure, ChoiceDev *out)
-{
-    const uint32_t n = be.fixed ? be.n_lmt : w.n_lmt;
-    const uint32_t start = be.fixed ? be.start : step_start(w);
-    const uint32_t L = w.L;
+// The scan of Algorithm 1 over the combined F and PSL of one walk (batch
+// position bi), its ambiguity flags and, pure == 0, the rest of the iteration
+// but for the C update, by a block of NT threads.
+//
+// Selection: the move is the first candidate in scan order within
+// F_min*(1+tau); the best-PSL neighbour is the first with the minimum PSL. On a
+// strict PSL improvement psl_best and solution_best = pivot with j_psl flipped.
+// Ambiguity:
+//   ARGMIN: some scanned neighbour's F lies within amb = margin*F_min of the
+//     band edge thr = F_min*(1+tau) (|F - thr| <= amb): a different rounding
+//     of Eq. (5) could move it across the edge and change the move;
+//   COMPARE (steps only): the move's F lies strictly within margin*v_local of
+//     v_local*(1-tau) or of v_local*(1+tau), the edges of the three-way
+//     comparison with the local best.
+// Every F of a combine block is at least that block's minimum and the blocks
+// cover the scan order in runs, so the first band member is in the first block
+// whose minimum is in the band, and only the blocks whose minimum is at most
+// thr + amb are read (usually the one that holds F_min): one pass over them
+// gives both.
+// Bookkeeping: the move's bit, the three-way comparison with v_local, the
+// unimproved counter, the local best, and the phase switch (Rand_flip of the
+// local best and the exponent swap; the walk joins the batch's pending list,
+// whose C, F and PSL k_pending then rebuilds). The C update runs after it
+// (k_apply), from bits that equal the pre-move pivot's at every position but j:
+// the pivot's, or on a switch the local best's (which are then the move's
+// pivot, if the move improved; if it did not, C is rebuilt from C of the local
+// best anyway).
+// pure != 0: the choice record goes to out[bi] and the walk stays unchanged.
+//
+// Everything is latency here: the walk's fields are read at the start, and what
+// the parts hand on stays in LDS (through global memory, one after the other,
+// the same work took 5 us more of a single walk's step).
+struct FinishLds {
+    SelPart w[16];
+    uint64_t near[16];
+    uint32_t first[16];
+    double Fb;
+    int32_t Pb;
+    int hit[16];
+    int improve, improved, sw;
+    uint32_t kb, jp;
+    uint32_t pos[1024];
+};
 
+template <int NT>
+__device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const BatchEntry &be, uint32_t bi,
+                                            uint32_t comb_blocks, uint32_t comb_group, int pure, ChoiceDev *out,
+                                            uint32_t *pend, double margin)
+{
+    constexpr int kWaves = NT / 64;
+    static_assert(kCombMaxBlocks <= NT && kWaves <= 16, "one combine block per thread");
+    const uint32_t t = threadIdx.x;
+    if (pure == 1 && be.lsplit && !be.ss->use) {
+        if (t == 0) out[bi].table = 1;
+        return;
+    }
+    const int lane = (int)t & 63, wave = (int)t >> 6;
     double fmin = INFINITY;
     int32_t pmin = INT_MAX;
     uint32_t ipmin = UINT_MAX;
-    if (threadIdx.x < comb_blocks) {
-        const SelPart r = be.red[threadIdx.x];
+    if (t < comb_blocks) {
+        const SelPart r = be.red[t];
         fmin = r.f;
         pmin = r.p;
         ipmin = r.i;
     }
+    const uint32_t n = be.fixed ? be.n_lmt : w.n_lmt;
+    const uint32_t start = be.fixed ? be.start : step_start(w);
+    const uint32_t L = w.L;
+    const double vl = w.value_local;
+    const int32_t psl_best = w.psl_best;
     const double my_f = fmin;           // this thread's combine block minimum
     // block minima: within each wavefront, then across the wavefronts (the
     // minimum F and the first minimum (PSL, index) do not depend on the order)
-    constexpr int kSelWaves = NT / 64;
-    __shared__ SelPart s_w[kSelWaves];
-    __shared__ uint32_t s_first[kSelWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int o = 32; o > 0; o >>= 1) {
         const double of = __shfl_xor(fmin, o);
         const int32_t op = __shfl_xor(pmin, o);
         const uint32_t oi = (uint32_t)__shfl_xor((int)ipmin, o);
         sel_merge(fmin, pmin, ipmin, of, op, oi);
     }
-    if (lane == 0) s_w[wave] = SelPart{fmin, pmin, ipmin};
+    if (lane == 0) sh.w[wave] = SelPart{fmin, pmin, ipmin};
     __syncthreads();
-    SelPart r = s_w[0];
-    for (int x = 1; x < kSelWaves; ++x) sel_merge(r.f, r.p, r.i, s_w[x].f, s_w[x].p, s_w[x].i);
+    SelPart r = sh.w[0];
+    for (int x = 1; x < kWaves; ++x) sel_merge(r.f, r.p, r.i, sh.w[x].f, sh.w[x].p, sh.w[x].i);
     const double Fmin = r.f;
     const int32_t Pmin = r.p;
     const uint32_t iPmin = r.i;
-    const double thr = Fmin * (1.0 + kTau);
+    const double thr = Fmin * (1.0 + kTau), amb = margin * Fmin;
 
-    // the first band member lies in the first combine block (they cover
-    // contiguous runs of scan indices in order) whose minimum is in the band
-    uint32_t bfirst = my_f <= thr ? (uint32_t)threadIdx.x : UINT_MAX;
-    for (int o = 32; o > 0; o >>= 1) bfirst = min(bfirst, (uint32_t)__shfl_xor((int)bfirst, o));
-    if (lane == 0) s_first[wave] = bfirst;
+    // the combine blocks to read, one 64-bit mask per wavefront
+    const uint64_t m = __ballot(t < comb_blocks && (my_f <= thr || my_f - thr <= amb));
+    if (lane == 0) sh.near[wave] = m;
     __syncthreads();
-    for (int x = 0; x < kSelWaves; ++x) bfirst = min(bfirst, s_first[x]);
-    uint32_t lo, hi;
-    comb_range(n, comb_blocks, comb_group, bfirst, lo, hi);
-    __syncthreads();                    // s_first is reused below
-
-    // first scan index inside the band within [lo, hi): rounds of
-    // 8 * NT indices, each thread's eight loads issued together;
-    // the first round with a hit holds the answer
-    uint32_t ifirst = UINT_MAX;
-    for (uint32_t i0 = lo; i0 < hi; i0 += 8 * NT) {
-        double v[8];
+    uint32_t ifirst = UINT_MAX;         // this thread's first candidate in the band, its F and PSL
+    double Fi = 0.0;
+    int32_t Pi = 0;
+    int hit = 0;
+    for (int q = 0; q < kWaves; ++q) {
+        for (uint64_t bits = sh.near[q]; bits; bits &= bits - 1) {      // the same for every thread of the block
+            const uint32_t b = 64u * (uint32_t)q + (uint32_t)__builtin_ctzll(bits);
+            uint32_t lo, hi;
+            comb_range(n, comb_blocks, comb_group, b, lo, hi);
+            for (uint32_t i0 = lo; i0 < hi; i0 += 4 * NT) {
+                double v[4];
+                int32_t pv[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t i = i0 + u * NT + threadIdx.x;
-            v[u] = i < hi ? be.F[i] : INFINITY;
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t i = i0 + (uint32_t)u * NT + t;
+                    v[u] = i < hi ? be.F[i] : INFINITY;
+                    pv[u] = i < hi ? be.P[i] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double g = v[u] - thr;
+                    hit |= (g < 0.0 ? -g : g) <= amb;
+                    const uint32_t i = i0 + (uint32_t)u * NT + t;
+                    if (v[u] <= thr && i < ifirst) {
+                        ifirst = i;
+                        Fi = v[u];
+                        Pi = pv[u];
+                    }
+                }
+            }
         }
-#pragma unroll
-        for (int u = 7; u >= 0; --u)
-            if (v[u] <= thr) ifirst = i0 + u * NT + threadIdx.x;
-        if (__syncthreads_or(ifirst != UINT_MAX)) break;
     }
-    for (int o = 32; o > 0; o >>= 1) ifirst = min(ifirst, (uint32_t)__shfl_xor((int)ifirst, o));
-    if (lane == 0) s_first[wave] = ifirst;
+    uint32_t ib = ifirst;
+    for (int o = 32; o > 0; o >>= 1) ib = min(ib, (uint32_t)__shfl_xor((int)ib, o));
+    hit = __any(hit);
+    if (lane == 0) {
+        sh.first[wave] = ib;
+        sh.hit[wave] = hit;
+    }
     __syncthreads();
-    uint32_t ib = s_first[0];
-    for (int x = 1; x < kSelWaves; ++x) ib = min(ib, s_first[x]);
+    ib = sh.first[0];
+    hit = sh.hit[0];
+    for (int x = 1; x < kWaves; ++x) {
+        ib = min(ib, sh.first[x]);
+        hit |= sh.hit[x];
+    }
     // with finite F the block holding F_min is in the band, so a member was
-    // found; the clamp only keeps the reads below in bounds otherwise
-    ib = ib < n ? ib : iPmin < n ? iPmin : 0u;
-    const uint32_t kb = (uint32_t)(((uint64_t)start + 1u + ib) % L);
-    const uint32_t jp = (uint32_t)(((uint64_t)start + 1u + iPmin) % L);
-
-    __shared__ int s_improve;
-    if (threadIdx.x == 0) {
-        be.near[0] = 0;           // the evaluation has read it; k_chunks appends to it
-        const double Fb = be.F[ib];
-        const int32_t Pb = be.P[ib];
+    // found; otherwise only the reads stay in bounds
+    if (ib < n) {
+        if (ifirst == ib) {
+            sh.Fb = Fi;
+            sh.Pb = Pi;
+        }
+    } else {
+        ib = iPmin < n ? iPmin : 0u;
+        if (t == 0) {
+            sh.Fb = be.F[ib];
+            sh.Pb = be.P[ib];
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        const uint32_t kb = (uint32_t)(((uint64_t)start + 1u + ib) % L);
+        const uint32_t jp = (uint32_t)(((uint64_t)start + 1u + iPmin) % L);
+        const double Fb = sh.Fb;
+        const int32_t Pb = sh.Pb;
+        be.near[0] = 0;           // the evaluation has read it; the next step appends to it
+        sh.improve = sh.improved = sh.sw = 0;
         if (pure) {
             ChoiceDev c;
             c.i_best = ib; c.j_best = kb; c.F_best = Fb; c.F_min = Fmin;
-            c.j_psl = jp; c.psl_min = Pmin; c.psl_k = Pb; c.flags = 0;
+            c.j_psl = jp; c.psl_min = Pmin; c.psl_k = Pb; c.flags = hit ? CHOICE_AMBIG_ARGMIN : 0u;
+            c.table = 0;
             out[bi] = c;
-            s_improve = 0;
         } else {
+            // three-way comparison of the move with v_local (Algorithm 1)
+            uint32_t fl = 0;
+            const double elo = vl * (1.0 - kTau), ehi = vl * (1.0 + kTau), band = margin * vl;
+            if (Fb < elo) fl = STEP_IMPROVED;
+            else if (Fb > ehi) fl = STEP_WORSE;
+            int32_t best = psl_best;
+            if (Pmin < psl_best) {
+                best = Pmin;
+                w.psl_best = Pmin;
+                fl |= STEP_PSL_IMPROVED;
+                sh.improve = 1;
+            }
+            if (hit) fl |= STEP_AMBIG_ARGMIN;
+            if ((Fb - elo < band && elo - Fb < band) || (Fb - ehi < band && ehi - Fb < band)) fl |= STEP_AMBIG_COMPARE;
+            uint32_t unimproved = w.unimproved;
+            int sw = 0;
+            if (fl & STEP_IMPROVED) {
+                sh.improved = 1;
+                unimproved = 0;
+                w.value_local = Fb;
+            } else if (fl & STEP_WORSE) {
+                unimproved += 1;
+                if (w.switch_period == 0 && unimproved > w.ls_lmt) sw = 1;
+            }
+            if (w.switch_period > 0 && ((w.t + 1u) % w.switch_period) == 0) sw = 1;
+            if (sw) fl |= STEP_SWITCHED;
+            w.unimproved = unimproved;
             w.start = start;
             w.k = kb;
             w.i_best = ib;
@@ -788,155 +734,62 @@ __device__ __forceinline__ void select_walk(WalkDev &w, const BatchEntry &be, ui
             w.psl_k = Pb;
             w.j_psl = jp;
             w.psl_min = Pmin;
-            // three-way comparison of the move with v_local (Algorithm 1)
-            uint32_t fl = 0;
-            if (Fb < w.value_local * (1.0 - kTau)) fl = STEP_IMPROVED;
-            else if (Fb > w.value_local * (1.0 + kTau)) fl = STEP_WORSE;
+            w.F_pivot = Fb;
+            w.psl_pivot = Pb;
             w.flags = fl;
-            s_improve = Pmin < w.psl_best;
-            if (s_improve) {
-                w.psl_best = Pmin;
-                w.flags |= STEP_PSL_IMPROVED;
+            if (w.trace_cap) {
+                TraceEntry e;
+                e.t = w.t;
+                e.start = start;
+                e.k = kb;
+                e.value_step = Fb;
+                e.psl_k = Pb;
+                e.psl_best = best;
+                e.alpha = sw ? (w.alpha == w.alpha1 ? w.alpha2 : w.alpha1) : w.alpha;
+                e.flags = fl;
+                w.trace[w.t % w.trace_cap] = e;
             }
+            w.t += 1;
+            sh.sw = sw;
+            sh.kb = kb;
+            sh.jp = jp;
         }
     }
+    if (pure) return;
     __syncthreads();
-    if (s_improve) copy_words(w.best, w.pivot, w.nw, threadIdx.x, NT, jp >> 6, 1ull << (jp & 63u));
-}
-
-// ------------------------------------------------------- ambiguity flags
-
-// The ambiguity flags of a step's scan, from the selection's results (by the
-// block that made the selection, after it and before the flip and the
-// bookkeeping):
-//   ARGMIN: some scanned neighbour's F lies within amb = margin*F_min of the
-//     band edge thr = F_min*(1+tau) (|F - thr| <= amb): a different rounding
-//     of Eq. (5) could move it across the edge and change the move;
-//   COMPARE (steps only): the move's F lies strictly within margin*v_local of
-//     v_local*(1-tau) or of v_local*(1+tau), the edges of the three-way
-//     comparison with the local best.
-// Every F of a combine block is at least that block's minimum, so only the
-// blocks whose minimum is at most thr + amb are read. pure != 0: the flag
-// goes into the choice record out[b]; otherwise into the walk's step flags.
-// Made by a block of NT threads.
-template <int NT>
-__device__ __forceinline__ void ambig_walk(WalkDev &w, const BatchEntry &be, uint32_t bi, uint32_t comb_blocks,
-                                           uint32_t comb_group, int pure, ChoiceDev *out, double margin)
-{
-    const uint32_t n = be.fixed ? be.n_lmt : w.n_lmt;
-    const double Fmin = pure ? out[bi].F_min : w.F_min;
-    const double thr = Fmin * (1.0 + kTau), amb = margin * Fmin;
-    // the combine blocks whose minimum lies at or below thr + amb, one per
-    // thread (comb_blocks <= NT), as one 64-bit mask per wavefront
-    static_assert(kCombMaxBlocks <= NT, "one combine block per thread");
-    __shared__ uint64_t s_near[NT / 64];
-    const uint32_t t = threadIdx.x;
-    const bool near = t < comb_blocks && be.red[t].f - thr <= amb;
-    const uint64_t m = __ballot(near);
-    if ((t & 63) == 0) s_near[t >> 6] = m;
-    __syncthreads();
-    int hit = 0;
-    for (uint32_t q = 0; q < NT / 64; ++q) {
-        for (uint64_t bits = s_near[q]; bits; bits &= bits - 1) {   // the same for every thread of the block
-            const uint32_t b = 64 * q + (uint32_t)__builtin_ctzll(bits);
-            uint32_t lo, hi;
-            comb_range(n, comb_blocks, comb_group, b, lo, hi);
-            for (uint32_t i = lo + t; i < hi; i += NT) {
-                const double g = be.F[i] - thr;
-                hit |= (g < 0.0 ? -g : g) <= amb;
-            }
-        }
+    const uint32_t kb = sh.kb;
+    // solution_best from the pre-move pivot, then the move, then local_best
+    // from the new pivot
+    if (sh.improve) {
+        copy_words(w.best, w.pivot, w.nw, t, NT, sh.jp >> 6, 1ull << (sh.jp & 63u));
+        __syncthreads();                // before the bit flips
     }
-    hit = __syncthreads_or(hit);
-    if (threadIdx.x == 0) {
-        if (pure) {
-            out[bi].flags = hit ? CHOICE_AMBIG_ARGMIN : 0u;
-        } else {
-            uint32_t fl = w.flags;
-            if (hit) fl |= STEP_AMBIG_ARGMIN;
-            const double vl = w.value_local, v = w.value_step;
-            const double elo = vl * (1.0 - kTau), ehi = vl * (1.0 + kTau), band = margin * vl;
-            if ((v - elo < band && elo - v < band) || (v - ehi < band && ehi - v < band)) fl |= STEP_AMBIG_COMPARE;
-            w.flags = fl;
-        }
-    }
-}
-
-// The rest of one loop iteration of Algorithm 1 after the selection, by the
-// block of NT threads that made it (batch position bi): the move's bit, the
-// three-way comparison with v_local, the unimproved counter, the local best,
-// and the phase switch (Rand_flip of the local best and the exponent swap;
-// the walk joins the batch's pending list, whose C, F and PSL k_pending then
-// rebuilds). The C update runs after it (k_apply), from bits that equal the
-// pre-move pivot's at every position but j: the pivot's, or on a switch the
-// local best's (which are then the move's pivot, if the move improved; if it
-// did not, C is rebuilt from C of the local best anyway).
-template <int NT>
-__device__ __forceinline__ void bookkeep_walk(WalkDev &w, uint32_t bi, uint32_t *pend)
-{
-    __shared__ int s_improved, s_switch;
-    __shared__ uint32_t s_pos[1024];
-    if (threadIdx.x == 0) {
-        const uint32_t k = w.k;
-        w.pivot[k >> 6] ^= 1ull << (k & 63u);
-        w.F_pivot = w.value_step;
-        w.psl_pivot = w.psl_k;
-        // the comparison with v_local was taken by the selection
-        int improved = 0, sw = 0;
-        uint32_t flags = w.flags;
-        if (flags & STEP_IMPROVED) {
-            improved = 1;
-            w.unimproved = 0;
-            w.value_local = w.value_step;
-        } else if (flags & STEP_WORSE) {
-            w.unimproved += 1;
-            if (w.switch_period == 0 && w.unimproved > w.ls_lmt) sw = 1;
-        }
-        if (w.switch_period > 0 && ((w.t + 1u) % w.switch_period) == 0) sw = 1;
-        if (sw) flags |= STEP_SWITCHED;
-        w.flags = flags;
-        if (w.trace_cap) {
-            TraceEntry e;
-            e.t = w.t;
-            e.start = w.start;
-            e.k = w.k;
-            e.value_step = w.value_step;
-            e.psl_k = w.psl_k;
-            e.psl_best = w.psl_best;
-            e.alpha = sw ? (w.alpha == w.alpha1 ? w.alpha2 : w.alpha1) : w.alpha;
-            e.flags = flags;
-            w.trace[w.t % w.trace_cap] = e;
-        }
-        w.t += 1;
-        s_improved = improved;
-        s_switch = sw;
-    }
+    if (t == 0) w.pivot[kb >> 6] ^= 1ull << (kb & 63u);
+    if (!sh.improved && !sh.sw) return;
     __syncthreads();
-    if (s_improved) copy_words(w.local_best, w.pivot, w.nw, threadIdx.x, NT, UINT32_MAX, 0);
+    if (sh.improved) copy_words(w.local_best, w.pivot, w.nw, t, NT, UINT32_MAX, 0);
+    if (!sh.sw) return;
     __syncthreads();
-    if (s_switch) {
-        copy_words(w.pivot, w.local_best, w.nw, threadIdx.x, NT, UINT32_MAX, 0);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t L = w.L;
-            uint32_t cnt = 0;
-            for (uint64_t r = 0; cnt < w.flip_lmt && r < (1ull << 24); ++r) {
-                const uint64_t ctr = (2ull << 60) | (w.q << 24) | r;
-                const uint32_t pos = (uint32_t)(draw(w.seed, ctr) % (uint64_t)L);
-                bool dup = false;
-                for (uint32_t x = 0; x < cnt; ++x) dup |= (s_pos[x] == pos);
-                if (dup) continue;
-                s_pos[cnt] = pos;
-                w.flips[cnt] = pos;
-                ++cnt;
-                w.pivot[pos >> 6] ^= 1ull << (pos & 63u);
-            }
-            w.n_flips = cnt;
-            w.alpha = (w.alpha == w.alpha1) ? w.alpha2 : w.alpha1;
-            w.q += 1;
-            w.pending = 1;
-            pend[1 + atomicAdd(&pend[0], 1u)] = bi;
+    copy_words(w.pivot, w.local_best, w.nw, t, NT, UINT32_MAX, 0);
+    __syncthreads();
+    if (t == 0) {
+        uint32_t cnt = 0;
+        for (uint64_t a = 0; cnt < w.flip_lmt && a < (1ull << 24); ++a) {
+            const uint64_t ctr = (2ull << 60) | (w.q << 24) | a;
+            const uint32_t pos = (uint32_t)(draw(w.seed, ctr) % (uint64_t)L);
+            bool dup = false;
+            for (uint32_t x = 0; x < cnt; ++x) dup |= (sh.pos[x] == pos);
+            if (dup) continue;
+            sh.pos[cnt] = pos;
+            w.flips[cnt] = pos;
+            ++cnt;
+            w.pivot[pos >> 6] ^= 1ull << (pos & 63u);
         }
+        w.n_flips = cnt;
+        w.alpha = (w.alpha == w.alpha1) ? w.alpha2 : w.alpha1;
+        w.q += 1;
+        w.pending = 1;
+        pend[1 + atomicAdd(&pend[0], 1u)] = bi;
     }
 }
 
@@ -973,7 +826,7 @@ __device__ __forceinline__ uint32_t near_peak(const uint32_t *__restrict__ list,
 // butterfly over the wavefront's split lanes, then the four wavefronts' sums
 // are added in wavefront order.
 // With tail != 0 the walk's last block to finish then makes its selection
-// (select_walk) and its ambiguity flags; b0 = the batch position of
+// (finish_walk); b0 = the batch position of
 // blockIdx.y = 0; done holds one zeroed counter per batch position.
 __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const BatchEntry *batch, Tables tabs,
                                                           int G, int tail, int pure, ChoiceDev *out, uint32_t *pend,
@@ -1012,7 +865,7 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
         if (split) {
             if (i < hi) {
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
-                for (uint32_t x = g; x < be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
+                for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
                 m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
                               (uint32_t)G);
             }
@@ -1074,8 +927,9 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
                 //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
                 const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
-                const double *p1 = be.pre + (size_t)L * (get_bit(w.pivot, j) ? 2 : 1), *pt = be.pre + 3 * (size_t)L;
-                f = be.pre[mj] + (p1[Mj] - p1[mj]) + (pt[L - 1] - pt[Mj]) + U * f;
+                const int p1 = get_bit(w.pivot, j) ? 2 : 1;
+                f = split_prefix(be, L, 0, mj) + (split_prefix(be, L, p1, Mj) - split_prefix(be, L, p1, mj)) +
+                    (split_prefix(be, L, 3, L - 1) - split_prefix(be, L, 3, Mj)) + U * f;
             }
             be.F[i] = f;
             be.P[i] = p;
@@ -1118,13 +972,8 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
     __syncthreads();
     if (!s_last) return;
     if (gridDim.x > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    select_walk<kCombThreads>(w, be, bi, gridDim.x, (uint32_t)G, pure, out);
-    __syncthreads();
-    ambig_walk<kCombThreads>(w, be, bi, gridDim.x, (uint32_t)G, pure, out, margin);
-    if (!pure) {
-        __syncthreads();
-        bookkeep_walk<kCombThreads>(w, bi, pend);
-    }
+    __shared__ FinishLds fin;
+    finish_walk<kCombThreads>(fin, w, be, bi, gridDim.x, (uint32_t)G, pure, out, pend, margin);
 }
 
 // The selection of a walk, its ambiguity flags and (pure == 0) its
@@ -1137,13 +986,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select(WalkDev *walks, const Ba
 {
     const BatchEntry be = batch[blockIdx.x];
     WalkDev &w = walks[be.slot];
-    select_walk<kSelThreads>(w, be, blockIdx.x, comb_blocks, comb_group, pure, out);
-    __syncthreads();
-    ambig_walk<kSelThreads>(w, be, blockIdx.x, comb_blocks, comb_group, pure, out, margin);
-    if (!pure) {
-        __syncthreads();
-        bookkeep_walk<kSelThreads>(w, blockIdx.x, pend);
-    }
+    __shared__ FinishLds fin;
+    finish_walk<kSelThreads>(fin, w, be, blockIdx.x, comb_blocks, comb_group, pure, out, pend, margin);
 }
 
 
@@ -1192,26 +1036,85 @@ __device__ __forceinline__ void apply_range(int32_t *__restrict__ C, int32_t *__
 }
 
 
-__global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const BatchEntry *batch,
+// The shifts k0 .. k1-1 (at most 2^kSegShiftMax) of a walk that switched phase
+// after this move: C of the new pivot, by the FLIP_lmt one-flip updates from C of
+// local_best (which the move makes of C if it improved), the sum of T(|C_k|) in
+// the new exponent and the maximum |C_k|. The shifts of D in the range are
+// marked in an LDS bitmap first. In one pass with the move's update (a pass and
+// a launch of its own before: 5 us of a single walk's step, switching or not).
+struct SwitchLds {
+    uint32_t fl[kFlipIncremental];
+    uint32_t in[(1u << kSegShiftMax) / 32];
+    PendLds pend;
+};
+__device__ __forceinline__ void switch_range(SwitchLds &sh, WalkDev &w, const BatchEntry &be, const double *T, uint32_t j,
+                                             int sj, bool improved, uint32_t k0, uint32_t k1, uint32_t seg)
+{
+    const uint32_t L = w.L, nf = w.n_flips;
+    const uint64_t *lb = w.local_best;
+    if (threadIdx.x < nf) sh.fl[threadIdx.x] = w.flips[threadIdx.x];
+    if (threadIdx.x < (1u << kSegShiftMax) / 32) sh.in[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t pr = threadIdx.x; pr < nf * nf; pr += kApplyThreads) {
+        const uint32_t f = pr / nf, g = pr - f * nf;
+        if (g >= f) continue;
+        const uint32_t k = sh.fl[f] > sh.fl[g] ? sh.fl[f] - sh.fl[g] : sh.fl[g] - sh.fl[f];
+        if (k >= k0 && k < k1) atomicOr(&sh.in[(k - k0) >> 5], 1u << ((k - k0) & 31u));
+    }
+    __syncthreads();
+    double ts = 0.0, tc = 0.0;
+    uint32_t tm = 0;
+    for (uint32_t k = k0 + threadIdx.x; k < k1; k += kApplyThreads) {
+        int32_t c;
+        if (improved) {
+            int d = 0;
+            if (j + k < L) d += get_bit(lb, j + k) ? -1 : 1;
+            if (k <= j) d += get_bit(lb, j - k) ? -1 : 1;
+            c = w.C[k] - 2 * sj * d;
+            w.C_lb[k] = c;
+        } else {
+            c = w.C_lb[k];
+        }
+        const uint32_t o = k - k0;
+        if ((sh.in[o >> 5] >> (o & 31u)) & 1u)
+            c = switch_corr_seq(lb, c, L, k, sh.fl, nf);
+        else
+            for (uint32_t f = 0; f < nf; ++f) c += switch_flip_delta(lb, L, k, sh.fl[f]);
+        w.C[k] = c;
+        const uint32_t a = (uint32_t)(c < 0 ? -c : c);
+        nsum_add(ts, tc, T[a]);
+        tm = max(tm, a);
+    }
+    pend_store(sh.pend, ts, tc, tm, be, seg);
+}
+
+__global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const BatchEntry *batch, Tables tabs,
                                                          int64_t j_fixed, SegMap map)
 {
+    __shared__ SwitchLds sh;
     uint32_t bi, seg;
     seg_of(map, blockIdx.x, bi, seg);
-    WalkDev &w = walks[batch[bi].slot];
+    const BatchEntry be = batch[bi];
+    WalkDev &w = walks[be.slot];
     const uint32_t L = w.L;
     const uint32_t j = j_fixed >= 0 ? (uint32_t)j_fixed : w.k;
     // a forced flip reads the pivot before its bit changes; the step's move
     // comes after the bookkeeping, which flipped bit j, and on a phase switch
     // replaced the pivot: then the local best holds the pre-move bits at
-    // every position but j (an improving move), or C is rebuilt afterwards
+    // every position but j (an improving move), or C is rebuilt from C of the
+    // local best
     const bool moved = j_fixed < 0;
-    const uint64_t *b = moved && (w.flags & STEP_SWITCHED) ? w.local_best : w.pivot;
+    const bool switched = moved && (w.flags & STEP_SWITCHED);
+    const uint64_t *b = switched ? w.local_best : w.pivot;
     const int sj = (get_bit(b, j) != 0) != moved ? -1 : 1;      // s_j before the flip
     // the move improves on v_local: the new pivot becomes local_best
     const bool lb = moved && (w.flags & STEP_IMPROVED);
     const uint32_t k0 = 1u + (seg << map.shift);
     const uint32_t k1 = min(L, k0 + (1u << map.shift));
-    apply_range(w.C, w.C_lb, b, L, j, sj, lb, k0, k1);
+    if (switched && w.n_flips <= kFlipIncremental)
+        switch_range(sh, w, be, tabs.T[w.alpha], j, sj, lb, k0, k1, seg);
+    else
+        apply_range(w.C, w.C_lb, b, L, j, sj, lb, k0, k1);
 }
 
 // Flip(pivot, j), part 2, for a forced flip: the bit itself.
@@ -1254,15 +1157,17 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uin
 }
 
 hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint64_t units,
-                          const Tables &tabs, const uint32_t *pend, hipStream_t s)
+                          const Tables &tabs, const uint32_t *pend, const SegMap &map, int big, hipStream_t s)
 {
     if (!pend) return hipErrorInvalidValue;
-    // every unit of the batch's walks gets a block when all of them switch
-    const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(4096, units));
-    k_pending<<<grid, kPendThreads, 0, s>>>(walks, batch, tabs, pend);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_pending_fin<<<std::max<uint32_t>(1, std::min<uint32_t>(nb, 1024)), 64, 0, s>>>(walks, batch, pend);
+    if (big) {
+        // every unit of the batch's walks gets a block when all of them switch
+        const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(4096, units));
+        k_pending<<<grid, kPendThreads, 0, s>>>(walks, batch, tabs, pend);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    k_pending_fin<<<std::max<uint32_t>(1, std::min<uint32_t>(nb, 1024)), 64, 0, s>>>(walks, batch, pend, map.shift);
     return hipGetLastError();
 }
 
@@ -1273,8 +1178,15 @@ hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, 
     return hipGetLastError();
 }
 
-hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan, uint32_t *tab,
+hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const SegMap &map, hipStream_t s)
+{
+    constexpr uint32_t per = kSegScanThreads / 64;
+    k_seg_scan<<<(map.total + per - 1) / per, kSegScanThreads, 0, s>>>(walks, batch, map);
+    return hipGetLastError();
+}
+
+hipError_t launch_suffix(WalkDev *walks, BatchEntry *batch, uint32_t nb, uint32_t max_L,
+                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan, const EvalCall &call,
                          hipStream_t s)
 {
     if (mode != 0 && mode != 2) return hipErrorInvalidValue;
@@ -1284,13 +1196,12 @@ hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, u
     if (scan && (!map->tot || !map->tmax)) return hipErrorInvalidValue;
     SegMap m = *map;
     if (!scan) m.tot = nullptr, m.tmax = nullptr;
-    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, mode, m, mode == 0 ? pend : nullptr, tab);
+    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, mode, m, mode == 0 ? pend : nullptr, call);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (scan) {
         // suffix values segment by segment (evaluations in 16-wavefront blocks)
-        constexpr uint32_t per = kSegScanThreads / 64;
-        k_seg_scan<<<(m.total + per - 1) / per, kSegScanThreads, 0, s>>>(walks, batch, m);
+        return launch_seg_scan(walks, batch, m, s);
     } else if (mode == 2) {
         // the initial fitness: totals per walk
         k_scan<<<nb, kScanThreads, 0, s>>>(walks, batch);
@@ -1338,6 +1249,8 @@ hipError_t launch_select(WalkDev *walks, const BatchEntry *batch, uint32_t nb, u
 
 size_t choice_dev_size() { return sizeof(ChoiceDev); }
 
+bool choice_dev_table(const void *p) { return ((const ChoiceDev *)p)->table != 0; }
+
 void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double *F_best,
                        double *F_min, uint32_t *j_psl, int32_t *psl_min, int32_t *psl_k, uint32_t *flags)
 {
@@ -1346,12 +1259,12 @@ void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double
     *j_psl = c->j_psl; *psl_min = c->psl_min; *psl_k = c->psl_k; *flags = c->flags;
 }
 
-hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, int64_t j_fixed,
-                        hipStream_t s)
+hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, const Tables &tabs,
+                        int64_t j_fixed, hipStream_t s)
 {
     if (map.shift < kSegShiftMin || map.shift > kSegShiftMax) return hipErrorInvalidValue;
     if (map.total == 0) return hipSuccess;       // L = 1 has no shift to update
-    k_apply<<<map.total, kApplyThreads, 0, s>>>(walks, batch, j_fixed, map);
+    k_apply<<<map.total, kApplyThreads, 0, s>>>(walks, batch, tabs, j_fixed, map);
     return hipGetLastError();
 }
 

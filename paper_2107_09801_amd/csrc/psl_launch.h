@@ -12,12 +12,13 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uin
                        int only_pending, hipStream_t s);
 constexpr uint32_t kPendUnit = 1024;   // shifts per work unit of the pending-walk rebuild
 
-// After the step's C update and bookkeeping: C, F and PSL of the walks on the
-// pending list (pend: count, then batch positions) that switched phase, in
-// work units of kPendUnit shifts (units: how many the batch's nb walks hold in
-// all).
+// C, F and PSL of the walks on the pending list (pend: count, then batch
+// positions) whose switch flipped more than kFlipIncremental elements, after
+// k_corr rebuilt C (big: some walk of the batch has that many; units: work
+// units of kPendUnit shifts the batch's nb walks hold in all), and the sums
+// that launch_update left for the others.
 hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint64_t units,
-                          const Tables &tabs, const uint32_t *pend, hipStream_t s);
+                          const Tables &tabs, const uint32_t *pend, const SegMap &map, int big, hipStream_t s);
 hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
                           int mode, hipStream_t s);
 // tab (batches with a matrix path): the number of the batch's walks left to
@@ -26,13 +27,14 @@ hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const Eval
                        uint32_t n_items, const Tables &tabs, const EvalShape &shape,
                        EvalQueues *queues, const uint32_t *tab, uint32_t n_cu, hipStream_t s);
 // mode 0: the step's chunk arrays and near-peak list (and, with pend, the
-// step's pending list emptied; with tab, *tab zeroed), turned into suffix values when scan != 0 (the
+// step's pending list emptied), turned into suffix values when scan != 0 (the
 // evaluation in 16-wavefront blocks reads those; smaller blocks add the chunk
 // values themselves); mode 2: the initial fitness (value_local, F_pivot,
 // psl_pivot, psl_best) of every walk.
-hipError_t launch_suffix(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
+hipError_t launch_suffix(WalkDev *walks, BatchEntry *batch, uint32_t nb, uint32_t max_L,
                          const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan,
-                         uint32_t *tab, hipStream_t s);
+                         const EvalCall &call, hipStream_t s);
+hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const SegMap &map, hipStream_t s);
 // Zero the near-peak counts of a batch, its pending count and its combine
 // counters (done, nb entries; may be null) after its scratch is allocated.
 hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done, hipStream_t s);
@@ -42,28 +44,37 @@ hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pen
 // each walk's last combine block in launches of at most 256 combine blocks
 // (done: one zeroed counter per batch position, left zero; without it the
 // selection takes a launch of its own): pure != 0 writes the choice record
-// `out` (one walk), else the walks' step records.
+// `out` (one walk), else the walks' step records. pure == 1: the table
+// evaluation has not run, and the record of a walk it is left to says so
+// (choice_dev_table) instead.
 hipError_t launch_select(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
                          uint32_t comb_group, const Tables &tabs, int pure, void *out, uint32_t *pend,
                          uint32_t *done, double margin, hipStream_t s);
 size_t choice_dev_size();
+bool choice_dev_table(const void *p);
 void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double *F_best,
                        double *F_min, uint32_t *j_psl, int32_t *psl_min, int32_t *psl_k, uint32_t *flags);
 // The C update of each walk's recorded move (j_fixed < 0, after the
-// bookkeeping) or of a forced flip of element j_fixed (before its bit flips).
-hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, int64_t j_fixed,
-                        hipStream_t s);
+// bookkeeping; for a walk that switched phase, C of its new pivot) or of a
+// forced flip of element j_fixed (before its bit flips).
+hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, const Tables &tabs,
+                        int64_t j_fixed, hipStream_t s);
 hipError_t launch_flip_bit(WalkDev *walks, const BatchEntry *batch, uint32_t j, hipStream_t s);
 // Units of launch_pending for walks of length L.
 inline uint64_t pending_units(uint32_t L) { return (L - 1 + kPendUnit - 1) / kPendUnit; }
 
-// Matrix path (psl_split.hip): the step's coefficients, digits, prefix sums,
-// scale and path choice of the batch's split walks (after the suffix pass,
-// before the evaluation; *tab counts the walks left to the table evaluation),
-// and the matrix products (items: walk, kMxTile-element tile, k-split).
-hipError_t launch_split_prep(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                             const SegMap &map, uint32_t *tab, hipStream_t s);
+// Matrix path (psl_split.hip), in a step of a batch with matrix walks: the
+// first pass over C in place of launch_suffix (the matrix walks' near-peak
+// lists, digits and prefix sums, the other walks' chunk arrays, with scan
+// their suffix values; *pend and *tab zeroed), then the matrix products
+// (items: walk, kMxTile-element tile, k-split), whose first items choose each
+// walk's path; *tab counts the walks left to the table evaluation, launched
+// after them. launch_rec_pad: once per batch layout, the zero records.
+hipError_t launch_prep(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs,
+                       const SegMap &map, int scan, uint32_t *pend, uint32_t *tab, const EvalCall &call,
+                       hipStream_t s);
+hipError_t launch_rec_pad(const BatchEntry *batch, const WalkDev *walks, uint32_t nb, hipStream_t s);
 hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
-                     hipStream_t s);
+                     const Tables &tabs, uint32_t *tab, hipStream_t s);
 
 }  // namespace psl

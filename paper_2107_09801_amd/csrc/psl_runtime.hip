@@ -86,8 +86,9 @@ void timing_drop(psl_ctx *ctx)
 // Folds recorded events into the totals (the stream must be idle).
 psl_status timing_collect(psl_ctx *ctx)
 {
-    // five events per step: evaluation start, after the split preparation,
-    // after the evaluation kernel, after the linear sums, step end
+    // five events per step: its start (batches without matrix walks: after
+    // the chunk sums), after the matrix path's preparation, after the matrix
+    // products, after the table evaluation, step end
     for (size_t i = 0; i + 4 < ctx->ev.size(); i += 5) {
         float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
         HIP_TRY(ctx, hipEventElapsedTime(&a, ctx->ev[i], ctx->ev[i + 1]));
@@ -95,8 +96,8 @@ psl_status timing_collect(psl_ctx *ctx)
         HIP_TRY(ctx, hipEventElapsedTime(&c, ctx->ev[i + 2], ctx->ev[i + 3]));
         HIP_TRY(ctx, hipEventElapsedTime(&d, ctx->ev[i + 3], ctx->ev[i + 4]));
         ctx->prep_ms += a;
-        ctx->eval_ms += b;
-        ctx->lin_ms += c;
+        ctx->lin_ms += b;
+        ctx->eval_ms += c;
         ctx->rest_ms += d;
         ctx->eval_launches += 1;
         ctx->steps_timed += 1;
@@ -144,6 +145,7 @@ void plan_free(psl_ctx *ctx, BatchPlan &pl)
     dev_free(ctx, pl.d_ss, false);
     dev_free(ctx, pl.d_mitems, false);
     dev_free(ctx, pl.d_tab, false);
+    dev_free(ctx, pl.d_segoff, false);
     pl = BatchPlan();
 }
 
@@ -361,45 +363,61 @@ static size_t dig_bytes(uint32_t L)
     return (size_t)kRecBytes * (split_chunks(L) + kRecPad + 2 * (split_both_chunks(L) + kRecPad));
 }
 
+// K-splits of a walk's matrix items in a launch of `tiles` tiles. Main items of
+// equal cost: with c chunks of shifts per walk an item takes a fixed time (its
+// windows' loads, the sums' way out) plus c / splits chunks; the GPU holds 2048
+// of them. The launch's time is its items' fixed times plus about half an item
+// at its end, which is least at sqrt(const c / tiles) splits. Measured at
+// const 8 / 16 / 32, us per step: one walk L = 40009 63 / 66 / 70, L = 131071
+// 167 / 178 / 176, L = 1048575 5866 / 5881 / 5965, N_lmt = 6912 L = 65535
+// 53 / 51 / 51, 64 of L = 131071 693 / 678 / 676.
+static uint32_t mx_splits(uint32_t chunks, uint64_t tiles)
+{
+    const double s = std::sqrt(12.0 * (double)chunks / (double)tiles);
+    return (uint32_t)std::max(1l, std::min(std::lround(s), (long)(chunks / kMxMinChunks)));
+}
+
 // The matrix path's k-splits per walk (0: none) and items in launch order.
 static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl, uint32_t n, std::vector<uint32_t> &lsp,
                       std::vector<EvalItem> &items)
 {
-    uint64_t work = 0, tiles = 0;
+    uint64_t work = 0, shifts = 0, tiles = 0;
     std::vector<uint32_t> nq(n, 0);
     for (uint32_t b = 0; b < n; ++b) {
         if (Ls[b] < kSplitMinL) continue;
         work += (uint64_t)nl[b] * (Ls[b] - 1);
+        shifts += Ls[b] - 1;
         // tiles that nl[b] consecutive elements can touch, the last tile of
         // the sequence possibly short
         nq[b] = std::min<uint32_t>((Ls[b] + kMxTile - 1) / kMxTile, (nl[b] + kMxTile - 1) / kMxTile + 2);
         tiles += nq[b];
     }
-    if (!tiles || !(ctx->split_mode == 1 || (ctx->split_mode == 2 && work >= kSplitMinWork))) return;
+    if (!tiles || !(ctx->split_mode == 1 || (ctx->split_mode == 2 && work >= kSplitMinCand * shifts))) return;
     struct Piece {
-        uint32_t b, first, count;   // items first .. first+count-1 of walk b (tile-major, k-split minor)
+        uint32_t b, first, count;   // tiles first .. first+count-1 of walk b
         uint64_t cost;
     };
     std::vector<Piece> pieces;
-    std::vector<uint64_t> item_cost(n, 0);
-    uint64_t total = 0;
+    std::vector<uint64_t> tile_cost(n, 0);
+    uint64_t total = 0, items_all = 0;
     for (uint32_t b = 0; b < n; ++b) {
         if (!nq[b]) continue;
         const uint32_t nco = split_chunks(Ls[b]);
-        const uint64_t want = (kMxItemsTarget + tiles - 1) / tiles;
-        lsp[b] = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, nco / kMxMinChunks));
-        item_cost[b] = (nco + lsp[b] - 1) / lsp[b];
-        total += item_cost[b] * nq[b] * lsp[b];
+        lsp[b] = mx_splits(nco, tiles);
+        tile_cost[b] = nco;
+        total += tile_cost[b] * nq[b];
+        items_all += (uint64_t)nq[b] * lsp[b];
     }
+    // a tile's edge as four items while the launch does not fill the GPU
+    const uint32_t parts = items_all < kMxEdgeWhole ? 4u : 1u;
     const uint64_t cap = std::max<uint64_t>(1, total / 16);
     for (uint32_t b = 0; b < n; ++b) {
         if (!nq[b]) continue;
-        const uint32_t cnt = nq[b] * lsp[b];
-        const uint64_t cost = item_cost[b] * cnt;
-        const uint32_t np = (uint32_t)std::min<uint64_t>(cnt, (cost + cap - 1) / cap);
+        const uint64_t cost = tile_cost[b] * nq[b];
+        const uint32_t np = (uint32_t)std::min<uint64_t>(nq[b], (cost + cap - 1) / cap);
         for (uint32_t p = 0; p < np; ++p) {
-            const uint32_t lo = (uint32_t)((uint64_t)cnt * p / np), hi = (uint32_t)((uint64_t)cnt * (p + 1) / np);
-            pieces.push_back(Piece{b, lo, hi - lo, item_cost[b] * (hi - lo)});
+            const uint32_t lo = (uint32_t)((uint64_t)nq[b] * p / np), hi = (uint32_t)((uint64_t)nq[b] * (p + 1) / np);
+            pieces.push_back(Piece{b, lo, hi - lo, tile_cost[b] * (hi - lo)});
         }
     }
     std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &c) { return a.cost > c.cost; });
@@ -407,13 +425,21 @@ static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl
     uint64_t load[kXcds] = {};
     for (const Piece &pc : pieces) {
         const int x = (int)(std::min_element(load, load + kXcds) - load);
-        for (uint32_t i = pc.first; i < pc.first + pc.count; ++i)
-            xq[x].push_back(EvalItem{pc.b, i / lsp[pc.b], i % lsp[pc.b], 0});
+        // k-split by k-split, so that the tiles in flight sweep the same digits
+        for (uint32_t ks = 0; ks < lsp[pc.b]; ++ks)
+            for (uint32_t t = pc.first; t < pc.first + pc.count; ++t) xq[x].push_back(EvalItem{pc.b, t, ks, 0});
+        for (uint32_t t = pc.first; t < pc.first + pc.count; ++t)
+            for (uint32_t e = 0; e < parts; ++e)
+                xq[x].push_back(EvalItem{pc.b, t, lsp[pc.b] + e, parts == 1 ? 1u : 0u});
         load[x] += pc.cost;
     }
     size_t rounds = 0;
     for (int x = 0; x < kXcds; ++x) rounds = std::max(rounds, xq[x].size());
-    items.reserve(rounds * kXcds);
+    items.reserve(align_up(4 * (size_t)n, kXcds) + rounds * kXcds);
+    // first the walks' offsets, padded to whole rounds
+    for (uint32_t b = 0; b < n; ++b)
+        for (uint32_t x = 0; x < 4; ++x) items.push_back(EvalItem{b, kMxOffsets, x, 0});
+    while (items.size() % kXcds) items.push_back(EvalItem{kMxNoWalk, 0, 0, 0});
     for (size_t r = 0; r < rounds; ++r)
         for (int x = 0; x < kXcds; ++x)
             items.push_back(r < xq[x].size() ? xq[x][r] : EvalItem{kMxNoWalk, 0, 0, 0});
@@ -498,7 +524,6 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     plan_free(ctx, pl);
     pl.ids.assign(ids, ids + n);
     pl.fixed_n = fixed ? n_fixed : 0;
-    pl.fixed_start = fixed ? start_fixed : 0;
     std::vector<uint32_t> n_l(n), Ls(n);
     for (uint32_t b = 0; b < n; ++b) {
         const WalkHost &h = ctx->walks[ids[b]];
@@ -522,8 +547,18 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         // the combine adds a matrix walk's own partials
         std::vector<uint32_t> cs(ks);
         for (uint32_t b = 0; b < n; ++b)
-            if (lsp[b]) cs[b] = lsp[b];
+            if (lsp[b]) cs[b] = lsp[b] + 1;
         comb_shape(cs.data(), n_l.data(), n, &lay.comb_blocks, &lay.comb_group);
+        // few candidates: more lanes for each (the near-peak list and the
+        // partials are their serial chains), a quarter of the GPU's lanes in all
+        uint64_t nmax = 0;
+        for (uint32_t b = 0; b < n; ++b) nmax = std::max<uint64_t>(nmax, n_l[b]);
+        uint32_t G = lay.comb_group;
+        while (G < 64 && 2ull * G * nmax * n <= kCombLanes) G <<= 1;
+        lay.comb_group = G;
+        lay.comb_blocks = std::max<uint32_t>(
+            lay.comb_blocks, (uint32_t)std::min<uint64_t>({(nmax * G + 255) / 256, (uint64_t)kCombMaxBlocks,
+                                                           std::max<uint64_t>(1, kCombBlocks / n)}));
     }
     pl.shape = lay.shape;
     pl.comb_blocks = lay.comb_blocks;
@@ -579,8 +614,8 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     pl.d_pend = (uint32_t *)p;
     if ((st = get(&p, sizeof(uint32_t) * n))) return st;
     pl.d_done = (uint32_t *)p;
+    std::vector<uint32_t> off(n + 1);
     {
-        std::vector<uint32_t> off(n + 1);
         pl.seg = seg_prefix(Ls.data(), n, off.data());
         if ((st = get(&p, sizeof(uint32_t) * (n + 1)))) return st;
         pl.d_seg = (uint32_t *)p;
@@ -595,7 +630,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     }
     // matrix path: per walk of at least kSplitMinL elements (not for plans
     // carved from fixed scratch, nor for launches with less work than
-    // kSplitMinWork nominal updates): its digit records, prefix and partial
+    // kSplitMinCand candidates per shift): its digit records, prefix and partial
     // sums and matrix items (walk, tile, k-split). Workgroup i runs on XCD
     // i mod 8: each walk's items (cost: the chunks of its k-split) form one
     // piece, or several of consecutive items when the walk holds more than
@@ -609,7 +644,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         if (!lsp[b]) continue;
         n_dig += dig_bytes(Ls[b]);
         n_pre += 4 * (size_t)Ls[b];
-        n_lp += (size_t)lsp[b] * Ls[b];
+        n_lp += (size_t)(lsp[b] + 1) * Ls[b];
     }
     pl.split = !mitems.empty();
     if (pl.split) {
@@ -625,6 +660,9 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         pl.d_mitems = (EvalItem *)p;
         if ((st = get(&p, sizeof(uint32_t)))) return st;
         pl.d_tab = (uint32_t *)p;
+        if ((st = get(&p, 4 * sizeof(double) * pl.seg.total))) return st;
+        pl.d_segoff = (double *)p;
+        pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
         pl.n_mitems = (uint32_t)mitems.size();
         HIP_TRY(ctx, hipMemcpy(pl.d_mitems, mitems.data(), sizeof(EvalItem) * mitems.size(),
                                hipMemcpyHostToDevice));
@@ -649,18 +687,22 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         e.tiles = tiles[b];
         e.n_lmt = n_l[b];
         e.start = fixed ? start_fixed : 0;
-        e.near_lim = near_limit_for(ctx, ctx->walks[ids[b]].L);
+        // a matrix walk's PSL costs its combine a pass over the list, not a share of
+        // the table evaluation's loop: the list may be as long as it holds
+        e.near_lim = lsp[b] && ctx->near_limit < 0 ? (uint32_t)kNearCap : near_limit_for(ctx, ctx->walks[ids[b]].L);
         e.fixed = fixed ? 1 : 0;
         if (lsp[b]) {
             e.lsplit = lsp[b];
             e.dig_one = pl.d_dig + o_dig;
             e.dig_both = e.dig_one + (size_t)kRecBytes * (split_chunks(Ls[b]) + kRecPad);
             e.pre = pl.d_pre + o_pre;
+            e.segoff = pl.d_segoff + 4 * (size_t)off[b];
+            e.seg_shift = pl.seg.shift;
             e.lpart = pl.d_lpart + o_lp;
             e.ss = pl.d_ss + b;
             o_dig += dig_bytes(Ls[b]);
             o_pre += 4 * (size_t)Ls[b];
-            o_lp += (size_t)lsp[b] * Ls[b];
+            o_lp += (size_t)(lsp[b] + 1) * Ls[b];
         }
         op += (size_t)ks[b] * n_l[b];
         oc += n_l[b];
@@ -676,6 +718,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     HIP_TRY(ctx, hipMemcpy(pl.d_items, items.data(), sizeof(EvalItem) * items.size(),
                            hipMemcpyHostToDevice));
     HIP_TRY(ctx, launch_near_reset(pl.d_batch, n, pl.d_pend, pl.d_done, ctx->stream));
+    if (pl.split) HIP_TRY(ctx, launch_rec_pad(pl.d_batch, ctx->d_walks, n, ctx->stream));
     pl.n_items = (uint32_t)items.size();
     return PSL_OK;
 }
@@ -733,25 +776,46 @@ psl_status check_cfg(psl_ctx *ctx, const psl_walk_cfg *c)
     return PSL_OK;
 }
 
+// The launches of a plan's evaluation up to the partial sums; timed: the
+// events between its parts.
+// call: an evaluation call's fields, or none for a step; table: the table
+// evaluation follows the matrix products (a batch without matrix walks always
+// has it).
+psl_status launch_partials(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, uint32_t n, uint32_t *pend, bool timed,
+                           const EvalCall &call, bool table)
+{
+    psl_status st;
+    const int scan = pl.shape.waves >= kEvalWavesMax;
+    if (timed && pl.split && (st = timing_mark(ctx))) return st;
+    if (pl.split)
+        HIP_TRY(ctx, launch_prep(ctx->d_walks, pl.d_batch, n, tabs, pl.seg, scan && !pl.all_split, pend, pl.d_tab, call,
+                                 ctx->stream));
+    else
+        HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, n, pl.max_L, tabs, 0, &pl.seg, pend, scan, call,
+                                   ctx->stream));
+    if (timed && !pl.split && (st = timing_mark(ctx))) return st;
+    if (timed && (st = timing_mark(ctx))) return st;
+    if (pl.split)
+        HIP_TRY(ctx, launch_mx(ctx->d_walks, pl.d_batch, pl.d_mitems, pl.n_mitems, tabs, pl.d_tab, ctx->stream));
+    if (timed && (st = timing_mark(ctx))) return st;
+    if (table || !pl.split)
+        HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues,
+                                 pl.d_tab, ctx->n_cu, ctx->stream));
+    if (timed && (st = timing_mark(ctx))) return st;
+    return PSL_OK;
+}
+
 // The launches of one iteration of Algorithm 1 for every walk of a plan.
 psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, uint32_t n, bool timed)
 {
     psl_status st;
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, n, pl.max_L, tabs, 0, &pl.seg, pl.d_pend,
-                               pl.shape.waves >= kEvalWavesMax, pl.d_tab, ctx->stream));
-    if (timed && (st = timing_mark(ctx))) return st;
-    if (pl.split) HIP_TRY(ctx, launch_split_prep(ctx->d_walks, pl.d_batch, n, tabs, pl.seg, pl.d_tab, ctx->stream));
-    if (timed && (st = timing_mark(ctx))) return st;
-    HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues,
-                             pl.d_tab, ctx->n_cu, ctx->stream));
-    if (timed && (st = timing_mark(ctx))) return st;
-    if (pl.split) HIP_TRY(ctx, launch_mx(ctx->d_walks, pl.d_batch, pl.d_mitems, pl.n_mitems, ctx->stream));
-    if (timed && (st = timing_mark(ctx))) return st;
+    if ((st = launch_partials(ctx, pl, tabs, n, pl.d_pend, timed, EvalCall{}, true))) return st;
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
                                pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
-    HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, -1, ctx->stream));
+    HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, tabs, -1, ctx->stream));
     if (pl.big_flips) HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.max_L, 1, ctx->stream));
-    HIP_TRY(ctx, launch_pending(ctx->d_walks, pl.d_batch, n, pl.pend_units, tabs, pl.d_pend, ctx->stream));
+    HIP_TRY(ctx, launch_pending(ctx->d_walks, pl.d_batch, n, pl.pend_units, tabs, pl.d_pend, pl.seg, pl.big_flips,
+                                ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
     return PSL_OK;
 }
@@ -840,7 +904,7 @@ psl_status psl_ctx_create(int device, void *hip_stream, void *arena, size_t aren
             ctx->noalloc_err = std::string("hipGetSymbolAddress: ") + hipGetErrorString(e);
         }
     }
-    if (hipMalloc(&ctx->d_choice, 256) != hipSuccess) {
+    if (hipHostMalloc(&ctx->d_choice, 256, hipHostMallocMapped) != hipSuccess) {
         if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
         delete ctx;
         return PSL_E_HIP;
@@ -862,7 +926,7 @@ void psl_ctx_destroy(psl_ctx *ctx)
     plans_clear(ctx);
     for (uint32_t a = 1; a <= PSL_ALPHA_MAX; ++a) dev_free(ctx, ctx->d_T[a], false);
     dev_free(ctx, ctx->d_walks, false);
-    dev_free(ctx, ctx->d_choice, false);
+    if (ctx->d_choice) (void)hipHostFree(ctx->d_choice);
     dev_free(ctx, ctx->d_one, false);
     timing_drop(ctx);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
@@ -989,7 +1053,7 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         hipError_t e = launch_init_bits(ctx->d_walks, tmp.d_batch, (const uint32_t *)dw, n, nw, ctx->stream);
         if (e == hipSuccess) e = launch_corr(ctx->d_walks, tmp.d_batch, n, L, 0, ctx->stream);
         const SegMap sm = seg_uniform(n, L);
-        if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, nullptr, ctx->stream);
+        if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, EvalCall{}, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         dev_free(ctx, dw, false);
         plan_free(ctx, tmp);
@@ -1034,45 +1098,44 @@ psl_status psl_eval_neighbourhood(psl_ctx *ctx, uint32_t walk, uint32_t start, u
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     // The plan of the previous call serves again when it was made for the
     // same walk and N_lmt (freeing walks or changing options drops it): its
-    // layout does not depend on the start, which the batch entry holds.
+    // layout does not depend on the start or the output arrays, which the
+    // call's first kernel writes into the batch entry.
     BatchPlan &pp = ctx->pure;
-    if (pp.d_batch && pp.ids.size() == 1 && pp.ids[0] == walk && pp.fixed_n == n_lmt) {
-        if (pp.fixed_start != start) {
-            pp.fixed_start = start;      // the copy's source outlives the call
-            HIP_TRY(ctx, hipMemcpyAsync(reinterpret_cast<char *>(pp.d_batch) + offsetof(BatchEntry, start),
-                                        &pp.fixed_start, sizeof(uint32_t), hipMemcpyHostToDevice, ctx->stream));
-        }
-    } else {
+    if (!(pp.d_batch && pp.ids.size() == 1 && pp.ids[0] == walk && pp.fixed_n == n_lmt)) {
         const psl_status st = make_plan(ctx, pp, &walk, 1, n_lmt, start);
         if (st) return st;
     }
+    // the kernels write aligned output arrays themselves
+    const bool own_f = !F_dev || (uintptr_t)F_dev % sizeof(double), own_p = !psl_dev || (uintptr_t)psl_dev % sizeof(int32_t);
+    const EvalCall call{own_f ? pp.d_f : F_dev, own_p ? pp.d_p : psl_dev, start, 1};
     const Tables tabs = tables_of(ctx);
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, ctx->pure.d_batch, 1, h.L, tabs, 0, &ctx->pure.seg, nullptr,
-                               ctx->pure.shape.waves >= kEvalWavesMax, ctx->pure.d_tab, ctx->stream));
-    if (ctx->pure.split)
-        HIP_TRY(ctx, launch_split_prep(ctx->d_walks, ctx->pure.d_batch, 1, tabs, ctx->pure.seg, ctx->pure.d_tab,
-                                       ctx->stream));
-    HIP_TRY(ctx, launch_eval(ctx->d_walks, ctx->pure.d_batch, ctx->pure.d_items, ctx->pure.n_items,
-                             tabs, ctx->pure.shape, ctx->pure.d_queues, ctx->pure.d_tab, ctx->n_cu, ctx->stream));
-    if (ctx->pure.split)
-        HIP_TRY(ctx, launch_mx(ctx->d_walks, ctx->pure.d_batch, ctx->pure.d_mitems, ctx->pure.n_mitems,
-                               ctx->stream));
-    HIP_TRY(ctx, launch_select(ctx->d_walks, ctx->pure.d_batch, 1, ctx->pure.comb_blocks, ctx->pure.comb_group, tabs, 1,
-                               ctx->d_choice, nullptr, ctx->pure.d_done, ctx->amb_margin, ctx->stream));
-    if (F_dev)
-        HIP_TRY(ctx, hipMemcpyAsync(F_dev, ctx->pure.d_f, sizeof(double) * n_lmt,
-                                    hipMemcpyDeviceToDevice, ctx->stream));
-    if (psl_dev)
-        HIP_TRY(ctx, hipMemcpyAsync(psl_dev, ctx->pure.d_p, sizeof(int32_t) * n_lmt,
-                                    hipMemcpyDeviceToDevice, ctx->stream));
-    std::vector<char> host(choice_dev_size());
-    HIP_TRY(ctx, hipMemcpyAsync(host.data(), ctx->d_choice, host.size(), hipMemcpyDeviceToHost,
-                                ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    // the choice record lies in pinned host memory: the kernel that selects
+    // writes it there
+    auto select = [&](int pure) -> psl_status {
+        HIP_TRY(ctx, launch_select(ctx->d_walks, pp.d_batch, 1, pp.comb_blocks, pp.comb_group, tabs, pure, ctx->d_choice,
+                                   nullptr, pp.d_done, ctx->amb_margin, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        return PSL_OK;
+    };
+    if (const psl_status st = launch_partials(ctx, pp, tabs, 1, nullptr, false, call, false)) return st;
+    if (const psl_status st = select(1)) return st;
+    if (choice_dev_table(ctx->d_choice)) {
+        // the matrix path does not take the walk as it is now
+        HIP_TRY(ctx, launch_eval(ctx->d_walks, pp.d_batch, pp.d_items, pp.n_items, tabs, pp.shape, pp.d_queues,
+                                 pp.d_tab, ctx->n_cu, ctx->stream));
+        if (const psl_status st = select(2)) return st;
+    }
+    if ((own_f && F_dev) || (own_p && psl_dev)) {
+        if (own_f && F_dev)
+            HIP_TRY(ctx, hipMemcpyAsync(F_dev, pp.d_f, sizeof(double) * n_lmt, hipMemcpyDeviceToDevice, ctx->stream));
+        if (own_p && psl_dev)
+            HIP_TRY(ctx, hipMemcpyAsync(psl_dev, pp.d_p, sizeof(int32_t) * n_lmt, hipMemcpyDeviceToDevice, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    }
     if (out) {
         memset(out, 0, sizeof *out);
-        choice_dev_unpack(host.data(), &out->i_best, &out->j_best, &out->F_best, &out->F_min,
-                          &out->j_psl, &out->psl_min, &out->psl_k, &out->flags);
+        choice_dev_unpack(ctx->d_choice, &out->i_best, &out->j_best, &out->F_best, &out->F_min, &out->j_psl,
+                          &out->psl_min, &out->psl_k, &out->flags);
     }
     return PSL_OK;
 }
@@ -1105,10 +1168,10 @@ psl_status psl_eval_neighbourhood_noalloc(psl_ctx *ctx, uint32_t walk, uint32_t 
         return st;
     }
     const Tables tabs = tables_of(ctx);
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, 1, h.L, tabs, 0, &pl.seg, nullptr,
-                               pl.shape.waves >= kEvalWavesMax, nullptr, ctx->stream));
-    HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues,
-                             nullptr, ctx->n_cu, ctx->stream));
+    if ((st = launch_partials(ctx, pl, tabs, 1, nullptr, false, EvalCall{}, true))) {
+        plan_free(ctx, pl);
+        return st;
+    }
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, 1, pl.comb_blocks, pl.comb_group, tabs, 1, d_choice,
                                nullptr, pl.d_done, ctx->amb_margin, ctx->stream));
     alignas(16) unsigned char host[256];
@@ -1138,7 +1201,7 @@ psl_status psl_apply_flip(psl_ctx *ctx, uint32_t walk, uint32_t j)
     e.slot = walk;
     hipError_t r = hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice);
     const Tables tabs = tables_of(ctx);
-    if (r == hipSuccess) r = launch_apply(ctx->d_walks, ctx->d_one, seg_uniform(1, h.L), (int64_t)j, ctx->stream);
+    if (r == hipSuccess) r = launch_apply(ctx->d_walks, ctx->d_one, seg_uniform(1, h.L), tabs, (int64_t)j, ctx->stream);
     if (r == hipSuccess) r = launch_flip_bit(ctx->d_walks, ctx->d_one, j, ctx->stream);
     if (r == hipSuccess) r = launch_fitness(ctx->d_walks, ctx->d_one, 1, tabs, 2, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
@@ -1303,20 +1366,29 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
         BatchPlan tmp;
         psl_status s2 = make_plan(ctx, tmp, walk_ids, n, UINT32_MAX, 0, &c, items);
         if (s2) return s2;
-        hipError_t e = launch_suffix(ctx->d_walks, tmp.d_batch, n, tmp.max_L, tabs, 0, &tmp.seg, nullptr,
-                                     tmp.shape.waves >= kEvalWavesMax, tmp.d_tab, ctx->stream);
-        if (e == hipSuccess && tmp.split)
-            e = launch_split_prep(ctx->d_walks, tmp.d_batch, n, tabs, tmp.seg, tmp.d_tab, ctx->stream);
-        auto launch = [&]() {
-            const hipError_t r = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape,
-                                             tmp.d_queues, tmp.d_tab, ctx->n_cu, ctx->stream);
-            if (r != hipSuccess || !tmp.split) return r;
-            return launch_mx(ctx->d_walks, tmp.d_batch, tmp.d_mitems, tmp.n_mitems, ctx->stream);
-        };
-        if (e == hipSuccess) e = launch();     // warm-up
+        s2 = launch_partials(ctx, tmp, tabs, n, nullptr, false, EvalCall{}, true);      // warm-up
+        if (s2) {
+            plan_free(ctx, tmp);
+            return s2;
+        }
+        hipError_t e = tmp.split ? launch_near_reset(tmp.d_batch, n, nullptr, nullptr, ctx->stream) : hipSuccess;
         const int reps = 2;
+        // a batch with matrix walks is timed with its preparation (the offsets
+        // are made from its totals); the near-peak lists start empty each time
         if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-        for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch();
+        for (int r = 0; r < reps && e == hipSuccess; ++r) {
+            if (tmp.split) {
+                s2 = launch_partials(ctx, tmp, tabs, n, nullptr, false, EvalCall{}, true);
+                if (!s2) e = launch_near_reset(tmp.d_batch, n, nullptr, nullptr, ctx->stream);
+            } else {
+                e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape, tmp.d_queues,
+                                nullptr, ctx->n_cu, ctx->stream);
+            }
+            if (s2) {
+                plan_free(ctx, tmp);
+                return s2;
+            }
+        }
         if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;

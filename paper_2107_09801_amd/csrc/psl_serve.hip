@@ -517,7 +517,7 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
     HIP_TRY(ctx, launch_corr(ctx->d_walks, d_admit.p, n, maxL, 0, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_adm_seg.p, adm_off, sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice,
                                 ctx->stream));
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_admit.p, n, maxL, tabs, 2, &adm_map, nullptr, 0, nullptr, ctx->stream));
+    HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_admit.p, n, maxL, tabs, 2, &adm_map, nullptr, 0, EvalCall{}, ctx->stream));
     return PSL_OK;
 }
 
@@ -664,12 +664,12 @@ psl_status Server::iterate()
     const uint32_t n = (uint32_t)active.size();
     const Tables tabs = tables_of(ctx);
     HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_batch.p, n, max_L, tabs, 0, &seg, d_pend.p, shape.waves >= kEvalWavesMax,
-                               nullptr, ctx->stream));
+                               EvalCall{}, ctx->stream));
     HIP_TRY(ctx, launch_eval(ctx->d_walks, d_batch.p, d_items.p, n_items, tabs, shape, d_queues.p, nullptr, ctx->n_cu,
                              ctx->stream));
     HIP_TRY(ctx, launch_select(ctx->d_walks, d_batch.p, n, comb_blocks, comb_group, tabs, 0, nullptr, d_pend.p,
                                d_done.p, ctx->amb_margin, ctx->stream));
-    HIP_TRY(ctx, launch_apply(ctx->d_walks, d_batch.p, seg, -1, ctx->stream));
+    HIP_TRY(ctx, launch_apply(ctx->d_walks, d_batch.p, seg, tabs, -1, ctx->stream));
     bool big = false;
     uint64_t units = 0;
     for (auto &j : active) {
@@ -677,7 +677,7 @@ psl_status Server::iterate()
         units += pending_units(j.cfg.L);
     }
     if (big) HIP_TRY(ctx, launch_corr(ctx->d_walks, d_batch.p, n, max_L, 1, ctx->stream));
-    HIP_TRY(ctx, launch_pending(ctx->d_walks, d_batch.p, n, units, tabs, d_pend.p, ctx->stream));
+    HIP_TRY(ctx, launch_pending(ctx->d_walks, d_batch.p, n, units, tabs, d_pend.p, seg, big, ctx->stream));
     uint64_t evals = 0, upd = 0;
     for (auto &j : active) {
         const uint64_t nl = j.cfg.n_lmt ? j.cfg.n_lmt : j.cfg.L;

@@ -17,6 +17,7 @@
 // exact integers, and only the rounding of a coefficient to the quantum U
 // enters. This file holds the per-step preparation (coefficients, digits,
 // prefix sums, scale and path choice) and the matrix kernel.
+#include "psl_chunks.h"
 #include "psl_dev_util.h"
 #include "psl_device.h"
 #include "psl_launch.h"
@@ -73,209 +74,235 @@ __device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out
     for (int q = 0; q < 4; ++q) out[q] = digit_codes(out[q], even);
 }
 
-// Per shift k of every split walk (one block per segment of the walk's shifts,
-// in tiles of 256): the values T(|C_k - 4|), T(|C_k - 2|), T(|C_k + 2|),
-// T(|C_k|) that k_split_scan turns into prefix sums, and the digit records.
+// The step's preparation of a matrix walk, one block per segment of its shifts
+// (2^shift of them, in tiles of 256), in one pass over C: the near-peak list
+// (chunk_octs builds the same one), the digit records, and the prefix sums of
+// T(|C_k-4|), T(|C_k-2|), T(|C_k+2|), T(|C_k|) within the segment, whose
+// totals k_mx's first items turn into offsets (split_offsets). Blocks of the
+// batch's other walks make the chunk sums of the table evaluation (k_chunks).
+//
 // A record holds one 32-shift chunk (shifts 32c .. 32c+31) of one coefficient:
-// 16 columns (digits) of 32 FP6 codes, the first 16 bytes of each column, then
-// the last 8 of each (kRecBytes); slot 8 r + q of a column is shift 32c + 4q + r,
+// 16 columns (digits) of 32 FP6 codes, the first 12 bytes of each column, then
+// the last 12 of each (kRecBytes); slot 8 r + q of a column is shift 32c + 4q + r,
 // the order in which the matrix kernel's masks leave the bits of a word. The
 // threads leave the codes of a tile in LDS (one word per shift and four
-// columns); then one thread per (coefficient, chunk, four columns) packs them.
+// columns); then one thread per (coefficient, chunk, four columns, half the
+// slots) packs them. All values of a prefix are non-negative and go through
+// about 16 roundings within a segment.
+//
+// One pass instead of three (chunk sums, coefficients, a serial scan per walk
+// that took 0.94 ms of a step at L = 1048575 and 0.21 ms for 64 walks at
+// L = 131071).
 constexpr int kPrepThreads = 256;
 constexpr int kPrepStride = 36;         // words per chunk and four columns in LDS (32 and padding)
-__global__ __launch_bounds__(kPrepThreads) void k_split_prep(const WalkDev *walks, const BatchEntry *batch,
-                                                             Tables tabs, SegMap map)
+
+struct PrepLds {
+    __align__(16) uint32_t codes[3][4][8 * kPrepStride];
+    double tot[4][kPrepThreads / 64];   // the wavefronts' totals of a tile
+};
+
+// Inclusive scan of v over the wavefront.
+__device__ __forceinline__ double wave_scan(double v, int lane)
 {
-    __shared__ __align__(16) uint32_t s_c[3][4][8 * kPrepStride];
-    uint32_t b, seg;
-    seg_of(map, blockIdx.x, b, seg);
-    const BatchEntry be = batch[b];
-    if (!be.lsplit) return;
-    const WalkDev &w = walks[be.slot];
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double o = __shfl_up(v, d);
+        if (lane >= d) v += o;
+    }
+    return v;
+}
+
+__device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, const BatchEntry &be,
+                                             const double *__restrict__ T, int seg, int shift, double *segtot)
+{
     const int L = (int)w.L;
-    const double *__restrict__ T = tabs.T[w.alpha];
     const double inv = 1.0 / split_scale(T, w.psl_pivot);      // exact: U is a power of two
+    const int cut = w.psl_pivot - 8;                           // the near-peak cut
     const int half = (L - 1) / 2;                              // the largest m_j
     const int nbo = (int)split_both_chunks((uint32_t)L), nco = (int)split_chunks((uint32_t)L);
-    const int k_end = (int)seg + 1 == (int)seg_count((uint32_t)L, map.shift) ? 32 * nco : (int)((seg + 1) << map.shift);
-    const int t = (int)threadIdx.x;
+    const int k_end = seg + 1 == (int)seg_count((uint32_t)L, (uint32_t)shift) ? 32 * nco : (seg + 1) << shift;
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
     const int slot = (t >> 5) * kPrepStride + 8 * (t & 3) + ((t & 31) >> 2);
     double *__restrict__ pre = be.pre;
-    for (int k0 = (int)(seg << map.shift); k0 < k_end; k0 += kPrepThreads) {
+    double carry[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = seg << shift; k0 < k_end; k0 += kPrepThreads) {
         const int k = k0 + t;
         const bool in = k >= 1 && k < L;
         const bool both = (k0 >> 5) < nbo;                     // some chunk of the tile has both-neighbour shifts
         const int c = in ? w.C[k] : 0;
+        const int a0 = c < 0 ? -c : c;
         const int a4 = c + 4 < 0 ? -(c + 4) : c + 4, m4 = c - 4 < 0 ? 4 - c : c - 4;
         const int a2 = c + 2 < 0 ? -(c + 2) : c + 2, m2 = c - 2 < 0 ? 2 - c : c - 2;
-        const double t0 = T[c < 0 ? -c : c], tp2 = T[a2], tm2 = T[m2];
-        if (in) {
-            pre[(size_t)L + k] = tm2;
-            pre[2 * (size_t)L + k] = tp2;
-            pre[3 * (size_t)L + k] = t0;
+        const double t0 = T[a0], tp2 = T[a2], tm2 = T[m2], tp4 = T[a4], tm4 = T[m4];
+        {
+            const bool take = in && a0 >= cut;
+            const uint64_t bal = __ballot(take);
+            if (bal) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&be.near[0], (uint32_t)__popcll(bal));
+                base = (uint32_t)__shfl((int)base, 0);
+                const uint32_t q = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+                if (take && q < (uint32_t)kNearCap) be.near[1 + q] = (uint32_t)k;
+            }
         }
         uint32_t d[4];
         split_digits(in ? (tp2 - tm2) * inv : 0.0, !(t & 1), d);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s_c[2][q][slot] = d[q];
+        for (int q = 0; q < 4; ++q) sh.codes[2][q][slot] = d[q];
         if (both) {
-            const double tp4 = T[a4], tm4 = T[m4];
-            if (in && k <= half) pre[k] = tm4;
             split_digits(in ? (t0 - tm4) * inv : 0.0, !(t & 1), d);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) s_c[0][q][slot] = d[q];
+            for (int q = 0; q < 4; ++q) sh.codes[0][q][slot] = d[q];
             split_digits(in ? (tp4 - tm4) * inv : 0.0, !(t & 1), d);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) s_c[1][q][slot] = d[q];
+            for (int q = 0; q < 4; ++q) sh.codes[1][q][slot] = d[q];
+        }
+        double v[4] = {in && k <= half ? tm4 : 0.0, in ? tm2 : 0.0, in ? tp2 : 0.0, in ? t0 : 0.0};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            v[x] = wave_scan(v[x], lane);
+            if (lane == 63) sh.tot[x][wave] = v[x];
         }
         __syncthreads();
-        // task e: coefficient e / 32, chunk (e / 4) % 8, columns 4 (e % 4) .. +3
-        const int set = t >> 5, cc = (t >> 2) & 7, q = t & 3;
-        const int ch = (k0 >> 5) + cc;
-        if (t < 96 && ch < (set == 2 ? nco : nbo)) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(&s_c[set][q][cc * kPrepStride]);
-            uint32_t o[4][6];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t x[4][4];                              // [column][4 codes in 24 bits]
-#pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    const uint4 v = src[4 * h + y];
-                    // 16-bit lanes: columns 0 and 2, columns 1 and 3
-                    const uint32_t e01 = (v.x & 0x00FF00FFu) | ((v.y & 0x00FF00FFu) << 6);
-                    const uint32_t e23 = (v.z & 0x00FF00FFu) | ((v.w & 0x00FF00FFu) << 6);
-                    const uint32_t f01 = ((v.x >> 8) & 0x00FF00FFu) | (((v.y >> 8) & 0x00FF00FFu) << 6);
-                    const uint32_t f23 = ((v.z >> 8) & 0x00FF00FFu) | (((v.w >> 8) & 0x00FF00FFu) << 6);
-                    x[0][y] = (e01 & 0xFFFFu) | ((e23 & 0xFFFFu) << 12);
-                    x[1][y] = (f01 & 0xFFFFu) | ((f23 & 0xFFFFu) << 12);
-                    x[2][y] = (e01 >> 16) | ((e23 >> 16) << 12);
-                    x[3][y] = (f01 >> 16) | ((f23 >> 16) << 12);
-                }
-#pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    o[y][3 * h] = x[y][0] | (x[y][1] << 24);
-                    o[y][3 * h + 1] = (x[y][1] >> 8) | (x[y][2] << 16);
-                    o[y][3 * h + 2] = (x[y][2] >> 16) | (x[y][3] << 8);
-                }
+        for (int x = 0; x < 4; ++x) {
+            double off = carry[x];
+            for (int q = 0; q < kPrepThreads / 64; ++q) {
+                if (q < wave) off += sh.tot[x][q];
+                carry[x] += sh.tot[x][q];
             }
-            uint8_t *rec = set == 2 ? be.dig_one + (size_t)ch * kRecBytes
-                                    : be.dig_both + ((size_t)ch * 2 + (size_t)set) * kRecBytes;
+            if (k < L && (x > 0 || both)) pre[(size_t)x * L + k] = off + v[x];
+        }
+        // task e: half e / 96 of the slots, coefficient (e / 32) % 3, chunk (e / 4) % 8, columns 4 (e % 4) .. +3
+        const int h = t >= 96 ? 1 : 0, e = t - 96 * h;
+        const int set = e >> 5, cc = (e >> 2) & 7, q = e & 3;
+        const int ch = (k0 >> 5) + cc;
+        if (t < 192 && ch < (set == 2 ? nco : nbo)) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(&sh.codes[set][q][cc * kPrepStride]) + 4 * h;
+            uint32_t x[4][4];                              // [column][4 codes in 24 bits]
 #pragma unroll
             for (int y = 0; y < 4; ++y) {
-                *reinterpret_cast<uint4 *>(rec + 16 * (4 * q + y)) = make_uint4(o[y][0], o[y][1], o[y][2], o[y][3]);
-                *reinterpret_cast<uint2 *>(rec + 256 + 8 * (4 * q + y)) = make_uint2(o[y][4], o[y][5]);
+                const uint4 u = src[y];
+                // 16-bit lanes: columns 0 and 2, columns 1 and 3
+                const uint32_t e01 = (u.x & 0x00FF00FFu) | ((u.y & 0x00FF00FFu) << 6);
+                const uint32_t e23 = (u.z & 0x00FF00FFu) | ((u.w & 0x00FF00FFu) << 6);
+                const uint32_t f01 = ((u.x >> 8) & 0x00FF00FFu) | (((u.y >> 8) & 0x00FF00FFu) << 6);
+                const uint32_t f23 = ((u.z >> 8) & 0x00FF00FFu) | (((u.w >> 8) & 0x00FF00FFu) << 6);
+                x[0][y] = (e01 & 0xFFFFu) | ((e23 & 0xFFFFu) << 12);
+                x[1][y] = (f01 & 0xFFFFu) | ((f23 & 0xFFFFu) << 12);
+                x[2][y] = (e01 >> 16) | ((e23 >> 16) << 12);
+                x[3][y] = (f01 >> 16) | ((f23 >> 16) << 12);
+            }
+            uint8_t *rec = (set == 2 ? be.dig_one + (size_t)ch * kRecBytes
+                                     : be.dig_both + ((size_t)ch * 2 + (size_t)set) * kRecBytes) +
+                           kRecBytes / 2 * h;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                uint32_t *o = reinterpret_cast<uint32_t *>(rec + 12 * (4 * q + y));
+                o[0] = x[y][0] | (x[y][1] << 24);
+                o[1] = (x[y][1] >> 8) | (x[y][2] << 16);
+                o[2] = (x[y][2] >> 16) | (x[y][3] << 8);
             }
         }
-        __syncthreads();
+        __syncthreads();                                   // the tile's codes and totals have been read
     }
+    if (t < 4) segtot[t] = t == 0 ? carry[0] : t == 1 ? carry[1] : t == 2 ? carry[2] : carry[3];
 }
 
-// One block per (split walk, value array): the array becomes its inclusive
-// prefix sums over k = 1..k (entry 0 = 0). Chunks of kScanChunk consecutive
-// entries go through the block in order: each thread sums its kScanPer
-// entries, the wavefronts scan their threads' totals and the block adds the
-// wavefronts' totals before them, and the chunks' totals are carried with
-// Neumaier's compensation. Every summand is non-negative, so each prefix is
-// within a few dozen roundings of its exact value. Block (walk, 0) also
-// stores the step's scale and path choice: the matrix path is taken when the
-// near-peak list holds the PSL (sparse form) and the quantization error,
-// at most (L-1) U, is below 1e-14 of a lower bound of every neighbour's F
-// (T(P-4) for the pivot's PSL P, and at least 1); a walk that does not take
-// it is counted in *tab, which the table evaluation looks at first.
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 4;
-constexpr int kScanChunk = kScanThreads * kScanPer;
-__global__ __launch_bounds__(kScanThreads) void k_split_scan(const WalkDev *walks, const BatchEntry *batch,
-                                                             Tables tabs, uint32_t *tab)
+__global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, BatchEntry *batch, Tables tabs,
+                                                       SegMap map, uint32_t *pend, uint32_t *tab, EvalCall call)
 {
-    const uint32_t wb = blockIdx.x / 4, x = blockIdx.x % 4;
-    const BatchEntry be = batch[wb];
-    if (!be.lsplit) {
-        if (x == 0 && threadIdx.x == 0) atomicAdd(tab, 1u);
-        return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        eval_call(batch, call);
+        if (pend) pend[0] = 0;          // the previous step's pending list has been consumed
+        tab[0] = 0;
     }
+    __shared__ union Lds {
+        PrepLds prep;
+        ChunkLds chunk;
+        __device__ Lds() {}
+    } sh;
+    uint32_t b, seg;
+    seg_of(map, blockIdx.x, b, seg);
+    const BatchEntry be = batch[b];
     const WalkDev &w = walks[be.slot];
+    if (be.lsplit)
+        prep_segment(sh.prep, w, be, tabs.T[w.alpha], (int)seg, (int)map.shift, be.segoff + 4 * (size_t)seg);
+    else
+        chunk_segment(sh.chunk, be, w, tabs.T[w.alpha], 0, map, seg);
+}
+
+// The segment totals of value array x of a matrix walk as the offsets of
+// its segments (the sum of the segments before; in place), by one wavefront:
+// each lane the totals of a run of segments, carried with Neumaier's
+// compensation. With x = 0 also the step's scale and path choice: the matrix path is
+// taken when the near-peak list holds the PSL (sparse form) and the
+// quantization error, at most (L-1) U, is below 1e-14 of a lower bound of
+// every neighbour's F (T(P-4) for the pivot's PSL P, and at least 1); a walk
+// that does not take it is counted in *tab, which the table evaluation looks
+// at first.
+__device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry &be, const Tables &tabs, uint32_t *tab,
+                                              int x, int lane)
+{
     const int L = (int)w.L;
-    const int K = x == 0 ? (L - 1) / 2 + 1 : L;     // T(|C_k - 4|) is summed over both-neighbour shifts only
-    double *__restrict__ v = be.pre + (size_t)x * L;
-    __shared__ double s_tot[kScanThreads / 64];
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
-    auto load = [&](int base, double (&e)[kScanPer]) {
-        const int k0 = base + (int)threadIdx.x * kScanPer;
-#pragma unroll
-        for (int i = 0; i < kScanPer; ++i) e[i] = k0 + i < K ? v[k0 + i] : 0.0;
-    };
-    double carry = 0.0, ccomp = 0.0;
-    double cur[kScanPer], nxt[kScanPer];
-    load(1, cur);
-    for (int base = 1; base < K; base += kScanChunk) {
-        if (base + kScanChunk < K) load(base + kScanChunk, nxt);
-#pragma unroll
-        for (int i = 1; i < kScanPer; ++i) cur[i] += cur[i - 1];
-        // inclusive scan of the thread totals over the wavefront
-        double t = cur[kScanPer - 1];
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const double o = __shfl_up(t, d);
-            if (lane >= d) t += o;
-        }
-        double excl = __shfl_up(t, 1);
-        if (lane == 0) excl = 0.0;
-        if (lane == 63) s_tot[wave] = t;
-        __syncthreads();
-        double off = carry + ccomp, tot = 0.0;
-#pragma unroll
-        for (int q = 0; q < kScanThreads / 64; ++q) {
-            if (q < wave) off += s_tot[q];
-            tot += s_tot[q];
-        }
-        off += excl;
-        const int k0 = base + (int)threadIdx.x * kScanPer;
-#pragma unroll
-        for (int i = 0; i < kScanPer; ++i)
-            if (k0 + i < K) v[k0 + i] = off + cur[i];
-        nsum_add(carry, ccomp, tot);
-        __syncthreads();                           // s_tot is rewritten by the next chunk
-#pragma unroll
-        for (int i = 0; i < kScanPer; ++i) cur[i] = nxt[i];
+    if (lane == 0 && x == 0) {
+        const double *__restrict__ T = tabs.T[w.alpha];
+        const int P = w.psl_pivot;
+        const double U = split_scale(T, P);
+        const double flow = P > 4 ? T[P - 4] : 0.0;
+        const bool exact_enough = (double)(L - 1) * U <= 1e-14 * (flow > 1.0 ? flow : 1.0);
+        const bool sparse_psl = be.near[0] <= be.near_lim;
+        SplitState st;
+        st.U = U;
+        st.use = exact_enough && sparse_psl ? 1u : 0u;
+        st.pad = 0;
+        *be.ss = st;
+        if (!st.use) atomicAdd(tab, 1u);
     }
-    if (threadIdx.x == 0) {
-        v[0] = 0.0;
-        if (x == 0) {
-            const double *__restrict__ T = tabs.T[w.alpha];
-            const int P = w.psl_pivot;
-            const double U = split_scale(T, P);
-            const double flow = P > 4 ? T[P - 4] : 0.0;
-            const bool exact_enough = (double)(L - 1) * U <= 1e-14 * (flow > 1.0 ? flow : 1.0);
-            const bool sparse_psl = be.near[0] <= be.near_lim;
-            SplitState st;
-            st.U = U;
-            st.use = exact_enough && sparse_psl ? 1u : 0u;
-            st.pad = 0;
-            *be.ss = st;
-            if (!st.use) atomicAdd(tab, 1u);
+    const int n = (int)seg_count((uint32_t)L, be.seg_shift);
+    const int per = (n + 63) / 64, lo = lane * per, hi = min(n, lo + per);
+    double *__restrict__ v = be.segoff + x;
+    double s = 0.0, c = 0.0;
+#pragma unroll 4
+    for (int i = lo; i < hi; ++i) nsum_add(s, c, v[4 * i]);
+    // exclusive scan of the lanes' sums
+    for (int d = 1; d < 64; d <<= 1) {
+        const double os = __shfl_up(s, d), oc = __shfl_up(c, d);
+        if (lane >= d) {
+            nsum_add(s, c, os);
+            c += oc;
         }
+    }
+    double es = __shfl_up(s, 1), ec = __shfl_up(c, 1);
+    if (lane == 0) es = ec = 0.0;
+#pragma unroll 4
+    for (int i = lo; i < hi; ++i) {
+        const double a = v[4 * i];
+        v[4 * i] = es + ec;
+        nsum_add(es, ec, a);
     }
 }
 
-hipError_t launch_split_prep(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                             const SegMap &map, uint32_t *tab, hipStream_t s)
+hipError_t launch_prep(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs,
+                       const SegMap &map, int scan, uint32_t *pend, uint32_t *tab, const EvalCall &call,
+                       hipStream_t s)
 {
     if (map.shift < kSegShiftMin || map.shift > kSegShiftMax || map.nb != nb || !tab) return hipErrorInvalidValue;
+    if (scan && (!map.tot || !map.tmax)) return hipErrorInvalidValue;
     if (nb == 0 || map.total == 0) return hipSuccess;
-    k_split_prep<<<map.total, kPrepThreads, 0, s>>>(walks, batch, tabs, map);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_split_scan<<<4 * nb, kScanThreads, 0, s>>>(walks, batch, tabs, tab);
-    return hipGetLastError();
+    SegMap m = map;
+    if (!scan) m.tot = nullptr, m.tmax = nullptr;
+    k_prep<<<map.total, kPrepThreads, 0, s>>>(walks, batch, tabs, m, pend, tab, call);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !scan) return e;
+    return launch_seg_scan(walks, batch, m, s);
 }
 
 // ------------------------------------------------------- matrix kernel
 
-// One wavefront per work item (walk, tile of kMxTile = 256 consecutive
-// elements, k-split). The tile's elements J0 + 32 b + 16 p + r (b = 0..7,
-// p = 0..1, r = 0..15) are the rows of 16 products per step of
+// Items of one wavefront. A main item is (walk, tile of kMxTile = 256
+// consecutive elements, k-split). The tile's elements J0 + 32 b + 16 p + r
+// (b = 0..7, p = 0..1, r = 0..15) are the rows of 16 products per step of
 // v_mfma_f32_16x16x128_f8f6f4: lane l has row r = l % 16 (FP4 matrix) or
 // column l % 16 (FP6 digits) and the 32 shifts of one chunk, lane group
 // g = l / 16 having a chunk of its own. Element j and chunk c read the right
@@ -287,22 +314,25 @@ hipError_t launch_split_prep(const WalkDev *walks, const BatchEntry *batch, uint
 // of a 16 x 128 matrix. Per product the wavefront makes four words of eight
 // nibbles: (bits & 0x11111111) holds shifts 4q as 0.5, (bits & 0x22222222)
 // shifts 4q + 1 as 1.0, and the same of (bits >> 2) shifts 4q + 2 and 4q + 3;
-// the record's slot order and digit scales match.
+// the record's slot order and digit scales match. Chunks past the range's end
+// (N is rounded up) read a record of zeros.
 //
-// One-neighbour shifts come first, with the sequence's bits as they are (the
+// One-neighbour chunks come first, with the sequence's bits as they are (the
 // matrix of a window is the same for all b + c, so it is masked once); then
 // the rows with s_j = -1 change sign (their x is 1 minus the bit, and the
-// combine takes T(c+2) as their constant part), and the both-neighbour shifts
+// combine takes T(c+2) as their constant part), and the both-neighbour chunks
 // add XOR (which s_j does not change) and AND of the bits times s_j. Both go
 // into the same accumulators: |digit| <= 16 over at most L-1 shifts, one
 // coefficient each, stays within 2^24 units of 1/8, exact in FP32.
 //
-// Chunks in which some row of the tile has a bound (m_j) inside, and the up to
-// three that do not fill a step, are taken by mx_edge: four consecutive
-// chunks per step, every row's shifts outside its bounds masked.
+// Main items hold the chunks all of whose shifts have both neighbours, or one,
+// for every row of the tile. The chunks between (those with some row's m_j,
+// and in the tile across the middle all one-neighbour ones) are an edge item's,
+// every row's shifts masked on either side of its m_j: the edge items of a
+// tile, of 64 rows each (or one that takes them in turn, in launches that fill
+// the GPU anyway), write partial sums of their own.
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v3i __attribute__((ext_vector_type(3), aligned(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kM0 = 0x11111111u, kM1 = 0x22222222u;
@@ -326,11 +356,11 @@ __device__ __forceinline__ uint32_t and_signed(uint32_t a, uint32_t b, uint32_t 
 }
 
 // This lane's column of a digit record.
-__device__ __forceinline__ v8i mx_rec(const uint8_t *__restrict__ base, uint32_t off16, uint32_t off8)
+__device__ __forceinline__ v8i mx_rec(const uint8_t *__restrict__ base, uint32_t off)
 {
-    const v4i a = *(const __attribute__((address_space(1))) v4i *)(base + off16);
-    const v2i b = *(const __attribute__((address_space(1))) v2i *)(base + off8);
-    return v8i{a.x, a.y, a.z, a.w, b.x, b.y, 0, 0};
+    const v3i a = *(const __attribute__((address_space(1))) v3i *)(base + off);
+    const v3i b = *(const __attribute__((address_space(1))) v3i *)(base + off + kRecBytes / 2);
+    return v8i{a.x, a.y, a.z, b.x, b.y, b.z, 0, 0};
 }
 
 struct MxLane {
@@ -344,20 +374,22 @@ struct MxLane {
     }
 };
 
-// The both-neighbour products of chunks c0 + g N + s, s < N, all of whose
-// shifts are at most every row's m_j.
+// The both-neighbour products of chunks c0 .. c1-1, all of whose shifts are at
+// most every row's m_j; record `zero` holds zeros.
 __device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int c0,
-                                        int N)
+                                        int c1, int zero)
 {
+    const int N = (c1 - c0 + 3) >> 2;
     const int cb = c0 + ln.g * N;
+    const int ng = min(N, c1 - cb);                       // this lane's chunks
+    const uint32_t offz = (uint32_t)zero * (2 * kRecBytes) + 12u * (uint32_t)ln.col;
     const uint32_t shr = (uint32_t)ln.r, shl = (uint32_t)(31 - ln.r);
     uint32_t R[8][2], R2[8][2], W[8][2], W2[8][2];        // right and left windows, and shifted by 2
     uint32_t rprev, lprev, rq[4], lq[4];
     v8i bx[2], ba[2];
-    uint32_t o16 = (uint32_t)cb * (2 * kRecBytes) + 16u * (uint32_t)ln.col;
-    uint32_t o8 = (uint32_t)cb * (2 * kRecBytes) + 256u + 8u * (uint32_t)ln.col;
-    bx[0] = mx_rec(dig, o16, o8);
-    ba[0] = mx_rec(dig + kRecBytes, o16, o8);
+    uint32_t off = (uint32_t)cb * (2 * kRecBytes) + 12u * (uint32_t)ln.col;
+    bx[0] = mx_rec(dig, ng > 0 ? off : offz);
+    ba[0] = mx_rec(dig + kRecBytes, ng > 0 ? off : offz);
     {
         uint32_t x[9], y[9];
 #pragma unroll
@@ -384,14 +416,14 @@ __device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, 
         rprev = x[8];
         lprev = y[0];
     }
-    for (int s = 0;;) {
+    for (int s = 0; s < N;) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
-            if (s >= N) return;
-            o16 += 2 * kRecBytes;
-            o8 += 2 * kRecBytes;
-            bx[(v + 1) & 1] = mx_rec(dig, o16, o8);
-            ba[(v + 1) & 1] = mx_rec(dig + kRecBytes, o16, o8);
+            if (s >= N) break;
+            off += 2 * kRecBytes;
+            const uint32_t on = s + 1 < ng ? off : offz;
+            bx[(v + 1) & 1] = mx_rec(dig, on);
+            ba[(v + 1) & 1] = mx_rec(dig + kRecBytes, on);
             const uint32_t rn = rq[v & 3], lw = lq[v & 3];
             rq[v & 3] = ln.word(ln.J32 + cb + s + 13);
             lq[v & 3] = ln.word(ln.J32 - cb - s - 6);
@@ -423,24 +455,25 @@ __device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, 
     }
 }
 
-// The one-neighbour products (right or left side) of chunks c0 + g N + s,
-// s < N, all of whose shifts are past every row's m_j.
+// The one-neighbour products (right or left side) of chunks c0 .. c1-1, all of
+// whose shifts are past every row's m_j.
 template <bool RIGHT>
 __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int c0,
-                                       int N)
+                                       int c1, int zero)
 {
+    const int N = (c1 - c0 + 3) >> 2;
     const int cb = c0 + ln.g * N;
+    const int ng = min(N, c1 - cb);
+    const uint32_t offz = (uint32_t)zero * kRecBytes + 12u * (uint32_t)ln.col;
     const uint32_t sh = RIGHT ? (uint32_t)ln.r : (uint32_t)(31 - ln.r);
     uint32_t A[8][2][4];                    // the matrices of eight windows
     uint32_t prev, wq[4];
     v8i bq[4];
-    uint32_t o16 = (uint32_t)cb * kRecBytes + 16u * (uint32_t)ln.col;
-    uint32_t o8 = (uint32_t)cb * kRecBytes + 256u + 8u * (uint32_t)ln.col;
+    uint32_t off = (uint32_t)cb * kRecBytes + 12u * (uint32_t)ln.col;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        bq[k] = mx_rec(dig, o16, o8);
-        o16 += kRecBytes;
-        o8 += kRecBytes;
+        bq[k] = mx_rec(dig, k < ng ? off : offz);
+        off += kRecBytes;
     }
     auto make = [&](uint32_t hi, uint32_t lo, uint32_t(&a)[2][4]) {
 #pragma unroll
@@ -466,13 +499,12 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
         for (int u = 0; u < 8; ++u) make(RIGHT ? x[u + 1] : x[u], RIGHT ? x[u] : x[u + 1], A[u]);
         prev = RIGHT ? x[8] : x[0];
     }
-    for (int s = 0;;) {
+    for (int s = 0; s < N;) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
-            if (s >= N) return;
-            bq[(v + 2) & 3] = mx_rec(dig, o16, o8);
-            o16 += kRecBytes;
-            o8 += kRecBytes;
+            if (s >= N) break;
+            bq[(v + 2) & 3] = mx_rec(dig, s + 2 < ng ? off : offz);
+            off += kRecBytes;
             uint32_t wn = wq[v & 3];
             wq[v & 3] = ln.word(RIGHT ? ln.J32 + cb + s + 13 : ln.J32 - cb - s - 6);
 #pragma unroll
@@ -492,68 +524,88 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
     }
 }
 
-// Chunks ca .. ce-1, four consecutive ones per step, with every row's shifts
-// outside its bounds masked: BOTH: shifts up to m_j; otherwise the shifts past
-// m_j, on the row's one-neighbour side (right for j <= half). Only a side that
-// some row uses is read: the other side's words can lie outside the guards.
-template <bool BOTH>
-__device__ __forceinline__ void mx_edge(v4f (&acc)[2 * kBlk], const MxLane &ln, const uint8_t *__restrict__ dig, int L,
-                                        int ca, int ce, int nrec)
+// The edge of 64 rows (64 qd .. +63 of the tile): chunks ca .. ce-1, four
+// consecutive ones per step; shifts up to a row's m_j go into the
+// both-neighbour sums, the others into the one-neighbour sums of its side
+// (right for j <= half; the sign of a row with s_j = -1 as FP4's sign bit).
+__device__ __forceinline__ void mx_edge(const MxLane &ln, const BatchEntry &be, int L, int qd, int ca, int ce, int nco,
+                                        int nbo, double *__restrict__ out)
 {
     const int half = (L - 1) / 2;
     const uint32_t shr = (uint32_t)ln.r, shl = (uint32_t)(31 - ln.r);
-    constexpr uint32_t kStep = BOTH ? 2 * kRecBytes : kRecBytes;
-    const bool need_r = BOTH || 32 * ln.J32 <= half, need_l = BOTH || min(32 * ln.J32 + kMxTile, L) - 1 > half;
+    const int w0 = ln.J32 + 2 * qd;                       // the rows' first word
+    v4f acc[4];
+    uint32_t S[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+        S[i] = (uint32_t)-(int)((ln.word(w0 + (i >> 1)) >> (16 * (i & 1) + ln.r)) & 1u);
+    }
 #pragma unroll 1
     for (int c4 = ca; c4 < ce; c4 += 4) {
         const int c = c4 + ln.g;
-        const uint32_t cl = (uint32_t)min(c, nrec - 1);
-        const uint32_t o16 = cl * kStep + 16u * (uint32_t)ln.col, o8 = cl * kStep + 256u + 8u * (uint32_t)ln.col;
-        const v8i bx = mx_rec(dig, o16, o8);
-        v8i ba = bx;
-        if (BOTH) ba = mx_rec(dig + kRecBytes, o16, o8);
-        uint32_t x[kBlk + 1], y[kBlk + 1];
+        const bool both = c4 <= (half >> 5);              // some chunk of the step has both-neighbour shifts
+        const uint32_t oo = (uint32_t)min(c, nco) * kRecBytes + 12u * (uint32_t)ln.col;
+        const uint32_t ob = (uint32_t)min(c, nbo) * (2 * kRecBytes) + 12u * (uint32_t)ln.col;
+        const v8i bo = mx_rec(be.dig_one, oo), bx = mx_rec(be.dig_both, ob), ba = mx_rec(be.dig_both + kRecBytes, ob);
+        uint32_t x[3], y[3];
 #pragma unroll
-        for (int i = 0; i < kBlk + 1; ++i) {
-            x[i] = need_r ? ln.word(ln.J32 + c + i) : 0u;
-            y[i] = need_l ? __builtin_bitreverse32(ln.word(ln.J32 - c - 1 + i)) : 0u;
+        for (int i = 0; i < 3; ++i) {
+            x[i] = ln.word(w0 + c + i);
+            y[i] = __builtin_bitreverse32(ln.word(w0 - c - 1 + i));
         }
 #pragma unroll
-        for (int b = 0; b < kBlk; ++b) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int i = 2 * b + p;
-                const int j = 32 * (ln.J32 + b) + 16 * p + ln.r;
-                const int m = min(j, L - 1 - j);
-                // the shifts 32c + t of this row: t < n (BOTH) or t >= n
-                const int n = min(32, max(0, m + 1 - 32 * c));
-                const uint32_t lowm = n > 0 ? 0xFFFFFFFFu >> (32 - n) : 0u;
-                const uint32_t V = c >= ce ? 0u : BOTH ? lowm : ~lowm;
-                if (!__any(V != 0u)) continue;
-                const uint32_t R = __builtin_amdgcn_alignbit(x[b + 1], x[b], shr + 16u * p);
-                const uint32_t W = __builtin_amdgcn_alignbit(y[b], y[b + 1], shl - 16u * p);
-                if (BOTH) {
-                    const uint32_t q = xor_and(R, W, V), q2 = q >> 2;
-                    acc[i] = mx_mfma(q & kM0, q & kM1, q2 & kM0, q2 & kM1, bx, acc[i]);
-                    const uint32_t t = and_signed(R, W, ln.S[i]) & V, t2 = t >> 2;
-                    acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba, acc[i]);
-                } else {
-                    const uint32_t q = (j <= half ? R : W) & V, q2 = q >> 2;
-                    acc[i] = mx_mfma(q & kM0, q & kM1, q2 & kM0, q2 & kM1, bx, acc[i]);
-                }
+        for (int i = 0; i < 4; ++i) {
+            const int j = 32 * (w0 + (i >> 1)) + 16 * (i & 1) + ln.r;
+            const int n = min(32, max(0, min(j, L - 1 - j) + 1 - 32 * c));     // shifts 32c + t, t < n: both
+            const uint32_t low = n > 0 ? 0xFFFFFFFFu >> (32 - n) : 0u;
+            const uint32_t VB = c < ce ? low : 0u, VO = c < ce ? ~low : 0u;
+            const uint32_t R = __builtin_amdgcn_alignbit(x[(i >> 1) + 1], x[i >> 1], shr + 16u * (i & 1));
+            const uint32_t W = __builtin_amdgcn_alignbit(y[i >> 1], y[(i >> 1) + 1], shl - 16u * (i & 1));
+            const uint32_t q = (j <= half ? R : W) & VO, q2 = q >> 2, sg = S[i] & 0x88888888u;
+            acc[i] = mx_mfma((q & kM0) | sg, (q & kM1) | sg, (q2 & kM0) | sg, (q2 & kM1) | sg, bo, acc[i]);
+            if (both) {
+                const uint32_t e = xor_and(R, W, VB), e2 = e >> 2;
+                acc[i] = mx_mfma(e & kM0, e & kM1, e2 & kM0, e2 & kM1, bx, acc[i]);
+                const uint32_t t = and_signed(R, W, S[i]) & VB, t2 = t >> 2;
+                acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba, acc[i]);
             }
         }
     }
+    // as in k_mx, down to one value per lane: register col % 4 of block col / 4
+    const double wcol = ldexp(8.0, 5 * ln.col);
+    double v[8];
+    {
+        const bool up = ln.col & 8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const double lo = (double)acc[i >> 2][i & 3] * wcol, hi = (double)acc[2 + (i >> 2)][i & 3] * wcol;
+            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, 8);
+        }
+    }
+#pragma unroll
+    for (int n = 4, d = 4; n >= 1; n >>= 1, d >>= 1) {
+        const bool up = ln.col & d;
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + __shfl_xor(up ? v[i] : v[i + n], d);
+    }
+    const int j = 32 * w0 + 16 * (ln.col >> 2) + 4 * ln.g + (ln.col & 3);
+    if (j < L) out[j] = v[0];
 }
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx(
-    const WalkDev *__restrict__ walks, const BatchEntry *__restrict__ batch, const EvalItem *__restrict__ items)
+    const WalkDev *__restrict__ walks, const BatchEntry *__restrict__ batch, const EvalItem *__restrict__ items,
+    Tables tabs, uint32_t *tab)
 {
     const EvalItem it = items[blockIdx.x];
     if (it.walk == kMxNoWalk) return;
     const BatchEntry be = batch[it.walk];
-    if (!be.lsplit || !be.ss->use) return;
     const WalkDev &w = walks[be.slot];
+    if (it.tile == kMxOffsets) {        // the walk's offsets and path choice, beside the products
+        if (be.lsplit) split_offsets(w, be, tabs, tab, (int)it.ks, (int)threadIdx.x);
+        else if (threadIdx.x == 0 && it.ks == 0) atomicAdd(tab, 1u);
+        return;
+    }
     const int L = (int)w.L;
     const uint32_t n_lmt = be.fixed ? be.n_lmt : w.n_lmt;
     const uint32_t start = be.fixed ? be.start : step_start(w);
@@ -566,11 +618,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (!(j_first >= J0 && j_first <= jt) && (J0 - j_first + (J0 < j_first ? L : 0)) >= (int)n_lmt) return;
     const int half = (L - 1) / 2;
     const int nco = (int)split_chunks((uint32_t)L), nbo = (int)split_both_chunks((uint32_t)L);
-    const int per = (nco + (int)be.lsplit - 1) / (int)be.lsplit;
-    const int c_lo = (int)it.ks * per, c_hi = min(nco, c_lo + per);
     const int m0 = min(J0, L - 1 - J0), m1 = min(jt, L - 1 - jt);
     const int m_min = min(m0, m1), m_max = J0 <= half && half <= jt ? half : max(m0, m1);
     const int M_max = max(L - 1 - J0, jt);
+    // chunks: both neighbours [0, fb), one [f0, oe), between them the edge
+    const bool one_side = jt <= half || J0 > half;
+    const int fb = (m_min + 1) >> 5, oe = (M_max >> 5) + 1, f0 = one_side ? min(oe, (m_max + 32) >> 5) : oe;
 
     const int lane = (int)threadIdx.x;
     MxLane ln;
@@ -579,25 +632,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     ln.r = lane & 15;
     ln.g = lane >> 4;
     ln.col = lane & 15;
+    if (it.ks >= be.lsplit) {           // edge item: its part of the tile's rows
+        const int part = (int)(it.ks - be.lsplit);
+        double *out = be.lpart + (size_t)be.lsplit * L;
+        for (int qd = it.pad ? 0 : part; qd < (it.pad ? 4 : part + 1); ++qd)
+            if (J0 + 64 * qd < L) mx_edge(ln, be, L, qd, fb, f0, nco, nbo, out);
+        return;
+    }
+    // the k-split: an equal part of the tile's work, a both-neighbour chunk
+    // (two products of 26 cycles each on the vector units) counting as three
+    // one-neighbour chunks
+    const int total = 3 * fb + (oe - f0);
+    const int per = (total + (int)be.lsplit - 1) / (int)be.lsplit;
+    const int p0 = (int)it.ks * per, p1 = p0 + per;
+    const int b0 = min(fb, (p0 + 2) / 3), b1 = min(fb, (p1 + 2) / 3);
+    const int o0 = min(oe, f0 + max(0, p0 - 3 * fb)), o1 = min(oe, f0 + max(0, p1 - 3 * fb));
     v4f acc[2 * kBlk];
 #pragma unroll
     for (int i = 0; i < 2 * kBlk; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    {
-        // one neighbour: chunks o0 .. o1-1, those from f0 on past every m_j;
-        // a tile across the middle has both sides and is all edge
-        const int o0 = max(c_lo, (m_min + 1) >> 5), o1 = min(c_hi, (M_max >> 5) + 1);
-        int f0 = o1, N = 0;
-        if (jt <= half || J0 > half) {
-            f0 = max(o0, (m_max + 32) >> 5);
-            N = f0 < o1 ? (o1 - f0) / 4 : 0;
-        }
-        if (N > 0) {
-            if (jt <= half) mx_one<true>(acc, ln, be.dig_one, f0, N);
-            else            mx_one<false>(acc, ln, be.dig_one, f0, N);
-            mx_edge<false>(acc, ln, be.dig_one, L, f0 + 4 * N, o1, nco);
-        }
-        mx_edge<false>(acc, ln, be.dig_one, L, o0, N > 0 ? f0 : o1, nco);
+    if (o0 < o1) {
+        if (jt <= half) mx_one<true>(acc, ln, be.dig_one, o0, o1, nco);
+        else            mx_one<false>(acc, ln, be.dig_one, o0, o1, nco);
     }
     {
         uint32_t sw[kBlk];
@@ -613,13 +668,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             ln.S[i] = (uint32_t)-(int)((sw[i >> 1] >> (16 * (i & 1) + ln.r)) & 1u);
         }
     }
-    const int b1 = min(c_hi, (m_max >> 5) + 1);
-    if (c_lo < b1) {
-        const int fb = min(b1, (m_min + 1) >> 5);
-        const int N = fb > c_lo ? (fb - c_lo) / 4 : 0;
-        if (N > 0) mx_both(acc, ln, be.dig_both, c_lo, N);
-        mx_edge<true>(acc, ln, be.dig_both, L, c_lo + 4 * N, b1, nbo);
-    }
+    if (b0 < b1) mx_both(acc, ln, be.dig_both, b0, b1, nbo);
 
     // digit column x weighs 32^x (in units of 8: the products are eighths);
     // the 16 columns of a row sit in 16 lanes: each stage adds a partner's half
@@ -647,11 +696,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         if (j + q < L) out[j + q] = v[q];
 }
 
+// The records after each coefficient's last: zeros.
+__global__ void k_rec_pad(const BatchEntry *batch, const WalkDev *walks)
+{
+    const BatchEntry be = batch[blockIdx.x];
+    if (!be.lsplit) return;
+    const uint32_t L = walks[be.slot].L;
+    uint32_t *one = reinterpret_cast<uint32_t *>(be.dig_one + (size_t)split_chunks(L) * kRecBytes);
+    uint32_t *both = reinterpret_cast<uint32_t *>(be.dig_both + (size_t)split_both_chunks(L) * 2 * kRecBytes);
+    for (uint32_t i = threadIdx.x; i < kRecPad * kRecBytes / 4; i += blockDim.x) one[i] = 0;
+    for (uint32_t i = threadIdx.x; i < kRecPad * 2 * kRecBytes / 4; i += blockDim.x) both[i] = 0;
+}
+
+hipError_t launch_rec_pad(const BatchEntry *batch, const WalkDev *walks, uint32_t nb, hipStream_t s)
+{
+    k_rec_pad<<<nb, 256, 0, s>>>(batch, walks);
+    return hipGetLastError();
+}
+
 hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
-                     hipStream_t s)
+                     const Tables &tabs, uint32_t *tab, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    k_mx<<<n_items, 64, 0, s>>>(walks, batch, items);
+    k_mx<<<n_items, 64, 0, s>>>(walks, batch, items, tabs, tab);
     return hipGetLastError();
 }
 
