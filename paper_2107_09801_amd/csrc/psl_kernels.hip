@@ -1,6 +1,6 @@
 // psl_kernels.hip -- gfx950 kernels of libpsl around the neighbourhood
-// evaluation (which lives in psl_eval.hip): power tables, init and the
-// correlations of Eq. (2), the phase-switch rebuild, the per-step chunk sums
+// evaluation (which lives in psl_eval.hip): power tables, init (the
+// correlations of Eq. (2) are psl_corr.hip's), the phase-switch rebuild, the per-step chunk sums
 // and near-peak list the evaluation reads, the selection of Algorithm 1's
 // scan, the O(L) flip of Section 3 and the step's bookkeeping.
 #include "psl_chunks.h"
@@ -41,60 +41,6 @@ __global__ void k_init_bits(WalkDev *walks, const BatchEntry *batch, const uint3
     }
     w.local_best[i] = v;
     w.best[i] = v;
-}
-
-// Eq. (2) from the packed pivot: C_k = (L-k) - 2 * #(s_i != s_{i+k}).
-// A block owns 256 consecutive shifts k0..k0+255 and sweeps the sequence in
-// LDS-staged segments of 32-bit words: word x of the sequence and the word at
-// bit offset 32x + k (one funnel shift of two staged words) give 32 products
-// per XOR and popcount.
-// only_pending == 0: every walk (init; C of local_best = C as well);
-// only_pending == 1: walks left pending by a switch whose Rand_flip is too
-// large for the one-flip rebuild (k_switch_corr);
-// only_pending == 2: every walk, C only (checkpoint restore).
-constexpr int kCorrThreads = 256;
-constexpr int kCorrSeg = 1024;        // staged 32-bit words per segment
-__global__ __launch_bounds__(kCorrThreads) void k_corr(WalkDev *walks, const BatchEntry *batch,
-                                                       int only_pending)
-{
-    WalkDev &w = walks[batch[blockIdx.y].slot];
-    if (only_pending == 1 && !(w.pending && w.n_flips > kFlipIncremental)) return;
-    const uint32_t L = w.L;
-    const uint32_t k0 = blockIdx.x * kCorrThreads;
-    if (k0 >= L) return;
-    __shared__ uint32_t A[kCorrSeg];
-    __shared__ uint32_t B[kCorrSeg + 16];
-    const uint32_t *s32 = reinterpret_cast<const uint32_t *>(w.pivot);
-    const uint32_t n32 = (L + 31) / 32;
-    const uint32_t k = k0 + threadIdx.x;
-    const uint32_t d = threadIdx.x, dq = d >> 5, dr = d & 31u;
-    const uint32_t nprod = k < L ? L - k : 0;          // products of this shift
-    const uint32_t nwb = (L - k0 + 31) / 32;           // words the block needs
-    const uint32_t kq = k0 / 32;
-    uint32_t diff = 0;
-    for (uint32_t w0 = 0; w0 < nwb; w0 += kCorrSeg) {
-        __syncthreads();
-        for (uint32_t t = threadIdx.x; t < kCorrSeg; t += kCorrThreads)
-            A[t] = (w0 + t < n32) ? s32[w0 + t] : 0u;
-        for (uint32_t t = threadIdx.x; t < kCorrSeg + 16; t += kCorrThreads)
-            B[t] = (w0 + kq + t < n32) ? s32[w0 + kq + t] : 0u;
-        __syncthreads();
-        // this shift's products in the segment: bits 32*w0 .. nprod
-        const uint32_t have = nprod > 32 * w0 ? nprod - 32 * w0 : 0;
-        const uint32_t full = min((uint32_t)kCorrSeg, have / 32);
-        for (uint32_t x = 0; x < full; ++x)
-            diff += __popc(A[x] ^ __builtin_amdgcn_alignbit(B[x + dq + 1], B[x + dq], dr));
-        if (full < (uint32_t)kCorrSeg && (have & 31u)) {
-            const uint32_t x = full;
-            const uint32_t v = A[x] ^ __builtin_amdgcn_alignbit(B[x + dq + 1], B[x + dq], dr);
-            diff += __popc(v & ((1u << (have & 31u)) - 1u));
-        }
-    }
-    if (k < L) {
-        const int32_t c = (int32_t)nprod - 2 * (int32_t)diff;
-        w.C[k] = c;
-        if (only_pending == 0) w.C_lb[k] = c;
-    }
 }
 
 // The pending list of a batch: pend[0] = count, pend[1..] = batch positions
@@ -1138,18 +1084,6 @@ hipError_t launch_init_bits(WalkDev *walks, const BatchEntry *batch, const uint3
     for (uint32_t b0 = 0; b0 < nb; b0 += kMaxGridY) {
         k_init_bits<<<dim3((max_nw + 255) / 256, std::min(kMaxGridY, nb - b0)), 256, 0, s>>>(walks, batch + b0,
                                                                                              want + b0);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                       int only_pending, hipStream_t s)
-{
-    for (uint32_t b0 = 0; b0 < nb; b0 += kMaxGridY) {
-        k_corr<<<dim3((max_L + kCorrThreads - 1) / kCorrThreads, std::min(kMaxGridY, nb - b0)), kCorrThreads, 0,
-                 s>>>(walks, batch + b0, only_pending);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -8,8 +8,23 @@ namespace psl {
 hipError_t launch_power_table(double *T, uint32_t n, uint32_t alpha, hipStream_t s);
 hipError_t launch_init_bits(WalkDev *walks, const BatchEntry *batch, const uint32_t *want,
                             uint32_t nb, uint32_t max_nw, hipStream_t s);
-hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                       int only_pending, hipStream_t s);
+// Lengths of the walks a correlation covers: the shortest, the longest, and the
+// work, in 32-position chunks per 4096 shifts (add each walk once).
+struct CorrDims {
+    uint32_t min_L = UINT32_MAX, max_L = 0;
+    uint64_t chunks = 0;
+    void add(uint32_t L, uint64_t count = 1)
+    {
+        if (L < min_L) min_L = L;
+        if (L > max_L) max_L = L;
+        chunks += count * ((uint64_t)L * L / (2ull * 4096 * 32) + 1);
+    }
+};
+// C (Eq. (2)) from the pivot's bits (psl_corr.hip). mode 0: every walk (init; C
+// of local_best = C as well); 1: walks left pending by a switch whose Rand_flip
+// is too large for the one-flip rebuild; 2: every walk, C only (restore).
+hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const CorrDims &dims, int mode,
+                       hipStream_t s);
 constexpr uint32_t kPendUnit = 1024;   // shifts per work unit of the pending-walk rebuild
 
 // C, F and PSL of the walks on the pending list (pend: count, then batch

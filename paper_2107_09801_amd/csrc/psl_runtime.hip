@@ -530,6 +530,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         n_l[b] = fixed ? n_fixed : h.n_lmt;
         Ls[b] = h.L;
         pl.big_flips |= h.flip_lmt > kFlipIncremental;
+        pl.corr.add(h.L);
         pl.pend_units += pending_units(h.L);
         pl.max_L = std::max(pl.max_L, h.L);
         pl.max_nw = std::max(pl.max_nw, h.nw);
@@ -813,7 +814,7 @@ psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, ui
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
                                pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
     HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, tabs, -1, ctx->stream));
-    if (pl.big_flips) HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.max_L, 1, ctx->stream));
+    if (pl.big_flips) HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.corr, 1, ctx->stream));
     HIP_TRY(ctx, launch_pending(ctx->d_walks, pl.d_batch, n, pl.pend_units, tabs, pl.d_pend, pl.seg, pl.big_flips,
                                 ctx->stream));
     if (timed && (st = timing_mark(ctx))) return st;
@@ -1051,7 +1052,9 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         HIP_TRY(ctx, hipMemcpy(dw, want.data(), sizeof(uint32_t) * n, hipMemcpyHostToDevice));
         const Tables tabs = tables_of(ctx);
         hipError_t e = launch_init_bits(ctx->d_walks, tmp.d_batch, (const uint32_t *)dw, n, nw, ctx->stream);
-        if (e == hipSuccess) e = launch_corr(ctx->d_walks, tmp.d_batch, n, L, 0, ctx->stream);
+        CorrDims cd;
+        cd.add(L, n);
+        if (e == hipSuccess) e = launch_corr(ctx->d_walks, tmp.d_batch, n, cd, 0, ctx->stream);
         const SegMap sm = seg_uniform(n, L);
         if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, EvalCall{}, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -1634,12 +1637,14 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     hipError_t r = hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice);
     const Tables tabs = tables_of(ctx);
     if (r == hipSuccess) r = hipMemcpy(w.pivot, local_best, 8ull * nw, hipMemcpyHostToDevice);
-    if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, L, 0, ctx->stream);
+    CorrDims cd;
+    cd.add(L);
+    if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 0, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r == hipSuccess) r = hipMemcpy(w.pivot, pivot, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = hipMemcpy(w.local_best, local_best, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = hipMemcpy(w.best, best, 8ull * nw, hipMemcpyHostToDevice);
-    if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, L, 2, ctx->stream);
+    if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 2, ctx->stream);
     if (r == hipSuccess) r = launch_fitness(ctx->d_walks, ctx->d_one, 1, tabs, 2, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r != hipSuccess) return fail(ctx, PSL_E_HIP, "restore: %s", hipGetErrorString(r));

@@ -455,6 +455,7 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
                          buf(d_adm_m0, n_suf), buf(d_adm_seg, adm.size() + 1)})))
         return st;
     size_t os = 0;
+    CorrDims cd;
     uint32_t maxL = 0, maxnw = 0;
     BatchEntry *be = (BatchEntry *)sp;
     sp += sizeof(BatchEntry) * adm.size();
@@ -506,6 +507,7 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
         os += suffix_len(j.cfg.L);
         want[b] = 1;
         maxL = std::max(maxL, j.cfg.L);
+        cd.add(j.cfg.L);
         maxnw = std::max(maxnw, h.nw);
         j.t_admit = t;
     }
@@ -514,7 +516,7 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
     HIP_TRY(ctx, hipMemcpyAsync(d_want.p, want, sizeof(uint32_t) * n, hipMemcpyHostToDevice, ctx->stream));
     const Tables tabs = tables_of(ctx);
     HIP_TRY(ctx, launch_init_bits(ctx->d_walks, d_admit.p, d_want.p, n, maxnw, ctx->stream));
-    HIP_TRY(ctx, launch_corr(ctx->d_walks, d_admit.p, n, maxL, 0, ctx->stream));
+    HIP_TRY(ctx, launch_corr(ctx->d_walks, d_admit.p, n, cd, 0, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_adm_seg.p, adm_off, sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice,
                                 ctx->stream));
     HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_admit.p, n, maxL, tabs, 2, &adm_map, nullptr, 0, EvalCall{}, ctx->stream));
@@ -672,11 +674,13 @@ psl_status Server::iterate()
     HIP_TRY(ctx, launch_apply(ctx->d_walks, d_batch.p, seg, tabs, -1, ctx->stream));
     bool big = false;
     uint64_t units = 0;
+    CorrDims cd;
     for (auto &j : active) {
         big |= j.cfg.flip_lmt > kFlipIncremental;
+        cd.add(j.cfg.L);
         units += pending_units(j.cfg.L);
     }
-    if (big) HIP_TRY(ctx, launch_corr(ctx->d_walks, d_batch.p, n, max_L, 1, ctx->stream));
+    if (big) HIP_TRY(ctx, launch_corr(ctx->d_walks, d_batch.p, n, cd, 1, ctx->stream));
     HIP_TRY(ctx, launch_pending(ctx->d_walks, d_batch.p, n, units, tabs, d_pend.p, seg, big, ctx->stream));
     uint64_t evals = 0, upd = 0;
     for (auto &j : active) {
