@@ -20,9 +20,8 @@ namespace psl {
 //    of |C'_k| over the shifts with |C_k| >= P - 8 alone. near[0] = count,
 //    near[1..] = those shifts (any order), while the count fits kNearCap.
 // Two kernels: k_chunks (several blocks per walk) writes per-chunk sums and
-// maxima and appends to the near list; k_seg_scan (step) or k_scan (init)
-// turns the chunk values into suffix values in a fixed order. The same pair
-// is also the fitness of a pivot: S0[0] = F and M0[0] = PSL (mode 2, init).
+// maxima and appends to the near list; k_seg_scan turns the chunk values into
+// suffix values in a fixed order, for the evaluation shapes that read those.
 constexpr int kChunkThreads = 256;
 // Octets o0, o0 + step, ... below o1 of one walk (an octet is 256 consecutive
 // shifts, eight chunks), for the calling wavefront: four coalesced passes of
@@ -32,7 +31,7 @@ constexpr int kChunkThreads = 256;
 // finishes its sum and maximum, the same in all eight. The octet's total (a
 // fixed tree over its chunks) goes into the wavefront's running total.
 __device__ __forceinline__ void chunk_octs(const BatchEntry &be, const WalkDev &w, const double *T, int cut,
-                                           bool near, int o0, int o1, int step, double *sv, int *sa,
+                                           int o0, int o1, int step, double *sv, int *sa,
                                            double &ws, double &wc, uint32_t &wm)
 {
     const int L = (int)w.L;
@@ -61,16 +60,14 @@ __device__ __forceinline__ void chunk_octs(const BatchEntry &be, const WalkDev &
             const int a = av[i];
             sv[e] = tv[i];
             sa[e] = a;
-            if (near) {
-                const bool take = k < L && a >= cut;
-                const uint64_t bal = __ballot(take);
-                if (bal) {
-                    uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&be.near[0], (uint32_t)__popcll(bal));
-                    base = (uint32_t)__shfl((int)base, 0);
-                    const uint32_t q = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-                    if (take && q < (uint32_t)kNearCap) be.near[1 + q] = (uint32_t)k;
-                }
+            const bool take = k < L && a >= cut;
+            const uint64_t bal = __ballot(take);
+            if (bal) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&be.near[0], (uint32_t)__popcll(bal));
+                base = (uint32_t)__shfl((int)base, 0);
+                const uint32_t q = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+                if (take && q < (uint32_t)kNearCap) be.near[1 + q] = (uint32_t)k;
             }
         }
         // the wavefront's rows are written before any lane reads them
@@ -115,10 +112,9 @@ struct ChunkLds {
     uint32_t m[kChunkThreads / 64];
 };
 
-// Segment `seg` (block blockIdx.x of the map) of one walk: mode 0 (step, with
-// the near list) or 2 (init).
+// Segment `seg` (block blockIdx.x of the map) of one walk.
 __device__ __forceinline__ void chunk_segment(ChunkLds &sh, const BatchEntry &be, const WalkDev &w, const double *T,
-                                              int mode, const SegMap &map, uint32_t seg)
+                                              const SegMap &map, uint32_t seg)
 {
     const int wave = (int)threadIdx.x >> 6;
     constexpr int kWaves = kChunkThreads / 64;
@@ -129,7 +125,7 @@ __device__ __forceinline__ void chunk_segment(ChunkLds &sh, const BatchEntry &be
     // the near-peak cut (the pivot's PSL is kept current by every step)
     double ws = 0.0, wc = 0.0;
     uint32_t wm = 0;
-    chunk_octs(be, w, T, w.psl_pivot - 8, mode == 0, o0 + wave, o1, kWaves, sh.v[wave], sh.a[wave], ws, wc, wm);
+    chunk_octs(be, w, T, w.psl_pivot - 8, o0 + wave, o1, kWaves, sh.v[wave], sh.a[wave], ws, wc, wm);
     if (map.tot) {
         // the segment's total (waves in order) for the segment-parallel scan
         if ((threadIdx.x & 63) == 0) {

@@ -141,6 +141,19 @@ struct SelPart {
 };
 constexpr uint32_t kCombMaxBlocks = 256;   // combine blocks per walk, at most
 
+// A walk's start (k_init_slabs, k_init_bits): its record, slab and, when its
+// pivot is given, the place of its bits among the staged words.
+constexpr uint64_t kNoBits = ~0ull;
+struct InitRec {
+    WalkDev dev;
+    uint64_t *slab;
+    uint64_t bytes;         // a multiple of 16
+    uint64_t given;         // kNoBits: random
+    uint32_t slot;
+    uint32_t pad;
+};
+enum { kFitInit, kFitPivot, kFitFlip };   // launch_fit's modes
+
 // What one evaluation call adds to its plan's entry (the first kernel writes
 // it, before any kernel reads it): the start and the F and PSL arrays.
 struct EvalCall {

@@ -129,6 +129,7 @@ struct BatchPlan {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+constexpr size_t kInitKeep = (size_t)16 << 20;   // largest start buffer a context keeps
 constexpr size_t kPlanCache = 8;   // step batches whose layout (and graph) is kept
 constexpr uint32_t kEvalItemsDefault = 4096;    // PSL_OPT_EVAL_ITEMS default
 constexpr uint32_t kEvalItemsMax = 1u << 18;    // and its largest value
@@ -169,7 +170,10 @@ struct psl_ctx {
     uint32_t T_n = 0;                 // entries per power table
     std::vector<BatchPlan> plans;     // recent step batches, most recent last
     BatchPlan pure;                   // single-walk plan of psl_eval_neighbourhood (kept for the next call)
-    psl::BatchEntry *d_one = nullptr; // psl_apply_flip's batch entry (allocated on first use)
+    psl::BatchEntry *d_one = nullptr; // psl_apply_flip's batch entry and its sums (allocated on first use)
+    uint32_t one_slot = UINT32_MAX;   // the walk slot it holds
+    char *d_init = nullptr;           // psl_init_walks' records, entries and staged bits (kept while small)
+    size_t init_cap = 0;
     void *d_choice = nullptr;         // choice record of psl_eval_neighbourhood (pinned host memory)
     std::string err;
     int64_t near_limit = -1;          // PSL_OPT_NEAR_LIMIT

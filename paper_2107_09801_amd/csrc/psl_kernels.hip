@@ -26,19 +26,43 @@ __global__ void k_power_table(double *T, uint32_t n, uint32_t alpha)
 
 // ------------------------------------------------------------- init
 
-// Random initial pivots (Rand(L, SEED)) for batch entries with want[b] != 0,
-// then local_best = best = pivot for every entry.
-__global__ void k_init_bits(WalkDev *walks, const BatchEntry *batch, const uint32_t *want)
+// A walk's start: block (x, b) zeroes its part of walk b's slab (the pivot sits
+// between zeroed guard words, see guard_words) and block (0, b) writes the
+// walk's record. One launch for a batch; a memset and a copy per walk took 15 us
+// of host time each.
+constexpr uint32_t kInitSpan = 16384;      // bytes of a slab per block
+__global__ __launch_bounds__(256) void k_init_slabs(WalkDev *walks, const InitRec *recs)
 {
-    WalkDev &w = walks[batch[blockIdx.y].slot];
+    const InitRec &rec = recs[blockIdx.y];
+    if (blockIdx.x == 0) {
+        constexpr uint32_t kWords = sizeof(WalkDev) / 4;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(&rec.dev);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(&walks[rec.slot]);
+        for (uint32_t i = threadIdx.x; i < kWords; i += 256) dst[i] = src[i];
+    }
+    const uint64_t lo = (uint64_t)blockIdx.x * kInitSpan;
+    if (lo >= rec.bytes) return;
+    uint4 *p = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(rec.slab) + lo);
+    const uint32_t n = (uint32_t)((rec.bytes - lo < kInitSpan ? rec.bytes - lo : kInitSpan) / 16);
+    for (uint32_t i = threadIdx.x; i < n; i += 256) p[i] = make_uint4(0, 0, 0, 0);
+}
+
+// The initial pivots: the given bits (rec.given, in words of the staged bits) or
+// Rand(L, SEED); then local_best = best = pivot.
+__global__ void k_init_bits(WalkDev *walks, const InitRec *recs, const uint64_t *bits)
+{
+    const InitRec &rec = recs[blockIdx.y];
+    const WalkDev &w = walks[rec.slot];
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= w.nw) return;
-    uint64_t v = w.pivot[i];
-    if (want[blockIdx.y]) {
+    uint64_t v;
+    if (rec.given != kNoBits) {
+        v = bits[rec.given + i];
+    } else {
         v = draw(w.seed, i);
         if (i == w.nw - 1 && (w.L & 63u)) v &= (1ull << (w.L & 63u)) - 1ull;
-        w.pivot[i] = v;
     }
+    w.pivot[i] = v;
     w.local_best[i] = v;
     w.best[i] = v;
 }
@@ -196,50 +220,73 @@ __global__ __launch_bounds__(64) void k_pending_fin(WalkDev *walks, const BatchE
     }
 }
 
-// F of the pivot (Eq. (5)) and its PSL (Eq. (3)) from C, one block per walk,
-// fixed blocking so a given C always gives the same F bits.
-// mode 0: initial (value_local, F_pivot, psl_pivot, psl_best);
-// mode 2: after a forced flip or a restore (F_pivot, psl_pivot).
-constexpr int kFitThreads = 256;
-__global__ __launch_bounds__(kFitThreads) void k_fitness(WalkDev *walks, const BatchEntry *batch,
-                                                         Tables tabs, int mode)
+// F of the pivot (Eq. (5)) and its PSL (Eq. (3)) from C in two launches: the
+// sums of the walk's segments, then (k_fit_fin) the segments' in order. The same
+// C always gives the same F bits. One block per walk took 55 us of a forced flip
+// at L = 40009.
+constexpr int kFitBatch = 4;
+__global__ __launch_bounds__(kPendThreads) void k_fit(const WalkDev *walks, const BatchEntry *batch, Tables tabs, SegMap map)
 {
-    WalkDev &w = walks[batch[blockIdx.x].slot];
+    __shared__ PendLds sh;
+    uint32_t bi, seg;
+    seg_of(map, blockIdx.x, bi, seg);
+    const BatchEntry be = batch[bi];
+    const WalkDev &w = walks[be.slot];
     const double *T = tabs.T[w.alpha];
-    double sum = 0.0, comp = 0.0;
-    int32_t peak = 0;
-    for (uint32_t k = 1 + threadIdx.x; k < w.L; k += kFitThreads) {
-        int32_t c = w.C[k];
-        int32_t a = c < 0 ? -c : c;
-        nsum_add(sum, comp, T[a]);
-        peak = a > peak ? a : peak;
-    }
-    __shared__ double s_sum[kFitThreads], s_comp[kFitThreads];
-    __shared__ int32_t s_peak[kFitThreads];
-    s_sum[threadIdx.x] = sum;
-    s_comp[threadIdx.x] = comp;
-    s_peak[threadIdx.x] = peak;
-    __syncthreads();
-    for (int h = kFitThreads / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            double a = s_sum[threadIdx.x], ca = s_comp[threadIdx.x];
-            nsum_add(a, ca, s_sum[threadIdx.x + h]);
-            s_sum[threadIdx.x] = a;
-            s_comp[threadIdx.x] = ca + s_comp[threadIdx.x + h];
-            int32_t p2 = s_peak[threadIdx.x + h];
-            if (p2 > s_peak[threadIdx.x]) s_peak[threadIdx.x] = p2;
+    const uint32_t k0 = 1u + (seg << map.shift), k1 = min(w.L, k0 + (1u << map.shift));
+    double ts = 0.0, tc = 0.0;
+    uint32_t tm = 0;
+    for (uint32_t k = k0 + threadIdx.x; k < k1; k += kFitBatch * kPendThreads) {
+        uint32_t a[kFitBatch];
+#pragma unroll
+        for (int u = 0; u < kFitBatch; ++u) {
+            const uint32_t kk = k + (uint32_t)u * kPendThreads;
+            const int32_t c = kk < k1 ? w.C[kk] : 0;       // T[0] = 0
+            a[u] = (uint32_t)(c < 0 ? -c : c);
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kFitBatch; ++u) {
+            nsum_add(ts, tc, T[a[u]]);
+            tm = max(tm, a[u]);
+        }
     }
-    if (threadIdx.x == 0) {
-        double F = s_sum[0] + s_comp[0];
-        int32_t p = s_peak[0];
+    pend_store(sh, ts, tc, tm, be, seg);
+}
+
+// mode kFitInit: value_local, F_pivot, psl_pivot and psl_best; kFitPivot (a
+// restore): F_pivot and psl_pivot; kFitFlip (after a forced flip's C update):
+// the same, and element j changes sign.
+__global__ __launch_bounds__(64) void k_fit_fin(WalkDev *walks, const BatchEntry *batch, uint32_t seg_shift, int mode,
+                                                uint32_t j)
+{
+    const BatchEntry be = batch[blockIdx.x];
+    WalkDev &w = walks[be.slot];
+    const int lane = (int)threadIdx.x;
+    const uint32_t n = seg_count(w.L, seg_shift);
+    double s = 0.0, c = 0.0;
+    uint32_t m = 0;
+#pragma unroll 4
+    for (uint32_t x = (uint32_t)lane; x < n; x += 64) {
+        nsum_add(s, c, be.S0[2 * x]);
+        c += be.S0[2 * x + 1];
+        m = max(m, be.M0[x]);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ps = __shfl_xor(s, o), pc = __shfl_xor(c, o);
+        const uint32_t pm = (uint32_t)__shfl_xor((int)m, o);
+        nsum_add(s, c, ps);
+        c += pc;
+        m = max(m, pm);
+    }
+    if (lane == 0) {
+        const double F = s + c;
         w.F_pivot = F;
-        w.psl_pivot = p;
-        if (mode == 0) {
+        w.psl_pivot = (int32_t)m;
+        if (mode == kFitInit) {
             w.value_local = F;
-            w.psl_best = p;
+            w.psl_best = (int32_t)m;
         }
+        if (mode == kFitFlip) w.pivot[j >> 6] ^= 1ull << (j & 63u);
     }
 }
 
@@ -247,11 +294,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fitness(WalkDev *walks, const B
 
 constexpr uint32_t kMaxGridY = 65535;      // walks per launch of the 2-D grids
 
-// Mode 0 (step, with the near list) and 2 (init): one block per segment of
-// the map.
+// The chunk sums and near list of a step: one block per segment of the map.
 __global__ __launch_bounds__(kChunkThreads) void k_chunks(const WalkDev *walks, BatchEntry *batch,
-                                                          Tables tabs, int mode, SegMap map, uint32_t *pend,
-                                                          EvalCall call)
+                                                          Tables tabs, SegMap map, uint32_t *pend, EvalCall call)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) eval_call(batch, call);
     // the previous step's pending list has been consumed; this step's
@@ -262,7 +307,7 @@ __global__ __launch_bounds__(kChunkThreads) void k_chunks(const WalkDev *walks, 
     seg_of(map, blockIdx.x, b, seg);
     const BatchEntry be = batch[b];
     const WalkDev &w = walks[be.slot];
-    chunk_segment(sh, be, w, tabs.T[w.alpha], mode, map, seg);
+    chunk_segment(sh, be, w, tabs.T[w.alpha], map, seg);
 }
 
 // Suffix values of the step's chunk arrays, one wavefront per segment of the
@@ -345,97 +390,6 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(const WalkDev *wal
     if (c1 == nchunks && lane == 0) {
         be.S0[nchunks] = 0.0;
         be.M0[nchunks] = 0;
-    }
-}
-
-constexpr int kScanThreads = 1024;
-// The initial fitness: block b scans walk b's chunk sums into suffix values
-// and sets value_local, F_pivot, psl_pivot and psl_best.
-__global__ __launch_bounds__(kScanThreads) void k_scan(WalkDev *walks, const BatchEntry *batch)
-{
-    const BatchEntry be = batch[blockIdx.x];
-    WalkDev &w = walks[be.slot];
-    const int L = (int)w.L;
-    const int nchunks = (L - 1 + 31) / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __shared__ double s_ts[kScanThreads], s_tc[kScanThreads];
-    __shared__ uint32_t s_tm[kScanThreads];
-
-    // each thread a contiguous segment (right to left, Neumaier), then an
-    // exclusive suffix scan of the segment totals (one wave, 16 per lane),
-    // then the offsets
-    const int seg = (nchunks + kScanThreads - 1) / kScanThreads;
-    const int lo = (int)threadIdx.x * seg, hi = min(nchunks, lo + seg);
-    double ts = 0.0, tc = 0.0;
-    uint32_t tm = 0;
-#pragma unroll 4
-    for (int c = hi - 1; c >= lo; --c) {
-        nsum_add(ts, tc, be.S0[c]);
-        tm = max(tm, be.M0[c]);
-    }
-    s_ts[threadIdx.x] = ts;
-    s_tc[threadIdx.x] = tc;
-    s_tm[threadIdx.x] = tm;
-    __syncthreads();
-    if (wave == 0) {
-        // lane l owns segment totals 16l .. 16l+15
-        double ls = 0.0, lc = 0.0;
-        uint32_t lm = 0;
-        for (int x = 15; x >= 0; --x) {
-            const int t = 16 * lane + x;
-            nsum_add(ls, lc, s_ts[t]);
-            lc += s_tc[t];
-            lm = max(lm, s_tm[t]);
-        }
-        // inclusive suffix over lanes in six doubling steps, then shifted
-        // down one lane: the totals of the lanes above l
-        for (int d = 1; d < 64; d <<= 1) {
-            const double os = __shfl_down(ls, d), oc = __shfl_down(lc, d);
-            const uint32_t om = (uint32_t)__shfl_down((int)lm, d);
-            if (lane + d < 64) {
-                nsum_add(ls, lc, os);
-                lc += oc;
-                lm = max(lm, om);
-            }
-        }
-        double es = __shfl_down(ls, 1), ec = __shfl_down(lc, 1);
-        uint32_t em = (uint32_t)__shfl_down((int)lm, 1);
-        if (lane == 63) {
-            es = 0.0;
-            ec = 0.0;
-            em = 0;
-        }
-        for (int x = 15; x >= 0; --x) {
-            const int t = 16 * lane + x;
-            const double ns = s_ts[t], nc = s_tc[t];
-            const uint32_t nm = s_tm[t];
-            s_ts[t] = es;
-            s_tc[t] = ec;
-            s_tm[t] = em;
-            nsum_add(es, ec, ns);
-            ec += nc;
-            em = max(em, nm);
-        }
-    }
-    __syncthreads();
-    ts = s_ts[threadIdx.x];
-    tc = s_tc[threadIdx.x];
-    tm = s_tm[threadIdx.x];
-    for (int c = hi - 1; c >= lo; --c) {
-        nsum_add(ts, tc, be.S0[c]);
-        tm = max(tm, be.M0[c]);
-        be.S0[c] = ts + tc;
-        be.M0[c] = tm;
-    }
-    if (threadIdx.x == 0) {
-        be.S0[nchunks] = 0.0;
-        be.M0[nchunks] = 0;
-        // thread 0's segment starts at chunk 0: the totals over k >= 1
-        const double F = ts + tc;
-        w.F_pivot = F;
-        w.psl_pivot = (int32_t)tm;
-        w.value_local = F;
-        w.psl_best = (int32_t)tm;
     }
 }
 
@@ -950,9 +904,12 @@ constexpr int kApplyThreads = 256;
 // read whether or not those elements exist: the pivot's zero guard words
 // (nw + 2 on each side) hold every index from -(L-1) to 2L-2.
 constexpr int kApplyBatch = 4;
+// With SUM (a forced flip) also the sum of T(|C_k|) and the maximum |C_k|.
+template <bool SUM>
 __device__ __forceinline__ void apply_range(int32_t *__restrict__ C, int32_t *__restrict__ C_lb,
                                             const uint64_t *__restrict__ b, uint32_t L, uint32_t j, int sj,
-                                            bool lb, uint32_t k0, uint32_t k1)
+                                            bool lb, uint32_t k0, uint32_t k1, const double *__restrict__ T, double &ts,
+                                            double &tc, uint32_t &tm)
 {
     for (uint32_t k = k0 + threadIdx.x; k < k1; k += kApplyBatch * kApplyThreads) {
         int32_t cv[kApplyBatch];
@@ -976,6 +933,11 @@ __device__ __forceinline__ void apply_range(int32_t *__restrict__ C, int32_t *__
                 const int32_t c = cv[u] - 2 * sj * d;
                 C[kk] = c;
                 if (lb) C_lb[kk] = c;
+                if (SUM) {
+                    const uint32_t a = (uint32_t)(c < 0 ? -c : c);
+                    nsum_add(ts, tc, T[a]);
+                    tm = max(tm, a);
+                }
             }
         }
     }
@@ -1057,17 +1019,16 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const B
     const bool lb = moved && (w.flags & STEP_IMPROVED);
     const uint32_t k0 = 1u + (seg << map.shift);
     const uint32_t k1 = min(L, k0 + (1u << map.shift));
-    if (switched && w.n_flips <= kFlipIncremental)
+    double ts = 0.0, tc = 0.0;
+    uint32_t tm = 0;
+    if (!moved) {
+        apply_range<true>(w.C, w.C_lb, b, L, j, sj, lb, k0, k1, tabs.T[w.alpha], ts, tc, tm);
+        pend_store(sh.pend, ts, tc, tm, be, seg);
+    } else if (switched && w.n_flips <= kFlipIncremental) {
         switch_range(sh, w, be, tabs.T[w.alpha], j, sj, lb, k0, k1, seg);
-    else
-        apply_range(w.C, w.C_lb, b, L, j, sj, lb, k0, k1);
-}
-
-// Flip(pivot, j), part 2, for a forced flip: the bit itself.
-__global__ void k_flip_bit(WalkDev *walks, const BatchEntry *batch, uint32_t j)
-{
-    WalkDev &w = walks[batch[0].slot];
-    if (threadIdx.x == 0) w.pivot[j >> 6] ^= 1ull << (j & 63u);
+    } else {
+        apply_range<false>(w.C, w.C_lb, b, L, j, sj, lb, k0, k1, nullptr, ts, tc, tm);
+    }
 }
 
 // ------------------------------------------------------------ launches
@@ -1078,12 +1039,13 @@ hipError_t launch_power_table(double *T, uint32_t n, uint32_t alpha, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_init_bits(WalkDev *walks, const BatchEntry *batch, const uint32_t *want,
-                            uint32_t nb, uint32_t max_nw, hipStream_t s)
+hipError_t launch_init(WalkDev *walks, const InitRec *recs, const uint64_t *bits, uint32_t nb, uint64_t max_bytes,
+                       uint32_t max_nw, hipStream_t s)
 {
     for (uint32_t b0 = 0; b0 < nb; b0 += kMaxGridY) {
-        k_init_bits<<<dim3((max_nw + 255) / 256, std::min(kMaxGridY, nb - b0)), 256, 0, s>>>(walks, batch + b0,
-                                                                                             want + b0);
+        const uint32_t ny = std::min(kMaxGridY, nb - b0);
+        k_init_slabs<<<dim3((uint32_t)((max_bytes + kInitSpan - 1) / kInitSpan), ny), 256, 0, s>>>(walks, recs + b0);
+        k_init_bits<<<dim3((max_nw + 255) / 256, ny), 256, 0, s>>>(walks, recs + b0, bits);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1105,10 +1067,14 @@ hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, 
     return hipGetLastError();
 }
 
-hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                          int mode, hipStream_t s)
+hipError_t launch_fit(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap &map,
+                      int mode, uint32_t j, hipStream_t s)
 {
-    k_fitness<<<nb, kFitThreads, 0, s>>>(walks, batch, tabs, mode);
+    if (map.total == 0 || map.nb != nb || map.shift < kSegShiftMin || map.shift > kSegShiftMax)
+        return hipErrorInvalidValue;
+    // a forced flip's C update has left the segments' sums
+    if (mode != kFitFlip) k_fit<<<map.total, kPendThreads, 0, s>>>(walks, batch, tabs, map);
+    k_fit_fin<<<nb, 64, 0, s>>>(walks, batch, map.shift, mode, j);
     return hipGetLastError();
 }
 
@@ -1119,28 +1085,19 @@ hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const 
     return hipGetLastError();
 }
 
-hipError_t launch_suffix(WalkDev *walks, BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan, const EvalCall &call,
-                         hipStream_t s)
+hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap *map,
+                         uint32_t *pend, int scan, const EvalCall &call, hipStream_t s)
 {
-    if (mode != 0 && mode != 2) return hipErrorInvalidValue;
     if (!map || map->total == 0 || map->nb != nb || map->shift < kSegShiftMin || map->shift > kSegShiftMax)
         return hipErrorInvalidValue;
-    scan = mode == 0 && scan;
     if (scan && (!map->tot || !map->tmax)) return hipErrorInvalidValue;
     SegMap m = *map;
     if (!scan) m.tot = nullptr, m.tmax = nullptr;
-    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, mode, m, mode == 0 ? pend : nullptr, call);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (scan) {
-        // suffix values segment by segment (evaluations in 16-wavefront blocks)
-        return launch_seg_scan(walks, batch, m, s);
-    } else if (mode == 2) {
-        // the initial fitness: totals per walk
-        k_scan<<<nb, kScanThreads, 0, s>>>(walks, batch);
-    }
-    return hipGetLastError();
+    k_chunks<<<m.total, kChunkThreads, 0, s>>>(walks, batch, tabs, m, pend, call);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !scan) return e;
+    // suffix values segment by segment (evaluations in 16-wavefront blocks)
+    return launch_seg_scan(walks, batch, m, s);
 }
 
 __global__ void k_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done)
@@ -1201,12 +1158,5 @@ hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &m
     k_apply<<<map.total, kApplyThreads, 0, s>>>(walks, batch, tabs, j_fixed, map);
     return hipGetLastError();
 }
-
-hipError_t launch_flip_bit(WalkDev *walks, const BatchEntry *batch, uint32_t j, hipStream_t s)
-{
-    k_flip_bit<<<1, 64, 0, s>>>(walks, batch, j);
-    return hipGetLastError();
-}
-
 
 }  // namespace psl

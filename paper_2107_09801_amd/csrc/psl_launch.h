@@ -6,8 +6,10 @@
 namespace psl {
 
 hipError_t launch_power_table(double *T, uint32_t n, uint32_t alpha, hipStream_t s);
-hipError_t launch_init_bits(WalkDev *walks, const BatchEntry *batch, const uint32_t *want,
-                            uint32_t nb, uint32_t max_nw, hipStream_t s);
+// Slabs zeroed, records written and pivots set (bits: the staged words of given
+// pivots) of nb walks of at most max_bytes of slab and max_nw words.
+hipError_t launch_init(WalkDev *walks, const InitRec *recs, const uint64_t *bits, uint32_t nb, uint64_t max_bytes,
+                       uint32_t max_nw, hipStream_t s);
 // Lengths of the walks a correlation covers: the shortest, the longest, and the
 // work, in 32-position chunks per 4096 shifts (add each walk once).
 struct CorrDims {
@@ -34,21 +36,22 @@ constexpr uint32_t kPendUnit = 1024;   // shifts per work unit of the pending-wa
 // that launch_update left for the others.
 hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint64_t units,
                           const Tables &tabs, const uint32_t *pend, const SegMap &map, int big, hipStream_t s);
-hipError_t launch_fitness(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs,
-                          int mode, hipStream_t s);
+// F and PSL of the pivots from C (kFitFlip: from the sums launch_apply's forced
+// flip of element j left; the element then changes sign). The segments' sums go
+// through the entries' chunk arrays (2 and 1 entries per segment).
+hipError_t launch_fit(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap &map,
+                      int mode, uint32_t j, hipStream_t s);
 // tab (batches with a matrix path): the number of the batch's walks left to
 // this evaluation in this step; with none, its blocks return at once.
 hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items,
                        uint32_t n_items, const Tables &tabs, const EvalShape &shape,
                        EvalQueues *queues, const uint32_t *tab, uint32_t n_cu, hipStream_t s);
-// mode 0: the step's chunk arrays and near-peak list (and, with pend, the
-// step's pending list emptied), turned into suffix values when scan != 0 (the
-// evaluation in 16-wavefront blocks reads those; smaller blocks add the chunk
-// values themselves); mode 2: the initial fitness (value_local, F_pivot,
-// psl_pivot, psl_best) of every walk.
-hipError_t launch_suffix(WalkDev *walks, BatchEntry *batch, uint32_t nb, uint32_t max_L,
-                         const Tables &tabs, int mode, const SegMap *map, uint32_t *pend, int scan,
-                         const EvalCall &call, hipStream_t s);
+// The step's chunk arrays and near-peak list (and, with pend, the step's pending
+// list emptied), turned into suffix values when scan != 0 (the evaluation in
+// 16-wavefront blocks reads those; smaller blocks add the chunk values
+// themselves).
+hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap *map,
+                         uint32_t *pend, int scan, const EvalCall &call, hipStream_t s);
 hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const SegMap &map, hipStream_t s);
 // Zero the near-peak counts of a batch, its pending count and its combine
 // counters (done, nb entries; may be null) after its scratch is allocated.
@@ -74,7 +77,6 @@ void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double
 // forced flip of element j_fixed (before its bit flips).
 hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, const Tables &tabs,
                         int64_t j_fixed, hipStream_t s);
-hipError_t launch_flip_bit(WalkDev *walks, const BatchEntry *batch, uint32_t j, hipStream_t s);
 // Units of launch_pending for walks of length L.
 inline uint64_t pending_units(uint32_t L) { return (L - 1 + kPendUnit - 1) / kPendUnit; }
 

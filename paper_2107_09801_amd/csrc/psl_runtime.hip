@@ -792,8 +792,7 @@ psl_status launch_partials(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs
         HIP_TRY(ctx, launch_prep(ctx->d_walks, pl.d_batch, n, tabs, pl.seg, scan && !pl.all_split, pend, pl.d_tab, call,
                                  ctx->stream));
     else
-        HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, n, pl.max_L, tabs, 0, &pl.seg, pend, scan, call,
-                                   ctx->stream));
+        HIP_TRY(ctx, launch_suffix(ctx->d_walks, pl.d_batch, n, tabs, &pl.seg, pend, scan, call, ctx->stream));
     if (timed && !pl.split && (st = timing_mark(ctx))) return st;
     if (timed && (st = timing_mark(ctx))) return st;
     if (pl.split)
@@ -844,15 +843,31 @@ psl_status capture_step(psl_ctx *ctx, BatchPlan &pl, const Tables &tabs, uint32_
     return PSL_OK;
 }
 
-// The context's one-walk batch entry (psl_apply_flip, psl_restore_walk),
-// allocated on first use and kept until the context is destroyed.
-psl_status one_entry(psl_ctx *ctx)
+// The context's one-walk batch entry (psl_apply_flip, psl_restore_walk) for
+// walk `slot`, with the arrays of its fitness sums, allocated on first use and
+// kept until the context is destroyed.
+psl_status one_entry(psl_ctx *ctx, uint32_t slot)
 {
-    if (ctx->d_one) return PSL_OK;
-    void *p;
-    const psl_status st = dev_alloc(ctx, &p, sizeof(BatchEntry), false);
-    if (st) return st;
-    ctx->d_one = (BatchEntry *)p;
+    constexpr uint32_t kSegs = 4096;         // a walk's segments, at most
+    constexpr size_t kHead = 512;
+    static_assert(sizeof(BatchEntry) <= kHead, "the entry comes first");
+    if (!ctx->d_one) {
+        void *p;
+        const psl_status st = dev_alloc(ctx, &p, kHead + kSegs * (2 * sizeof(double) + sizeof(uint32_t)), false);
+        if (st) return st;
+        ctx->d_one = (BatchEntry *)p;
+        ctx->one_slot = UINT32_MAX;
+    }
+    if (ctx->one_slot == slot) return PSL_OK;
+    BatchEntry e;
+    memset(&e, 0, sizeof e);
+    e.slot = slot;
+    e.S0 = (double *)((char *)ctx->d_one + kHead);
+    e.M0 = (uint32_t *)(e.S0 + 2 * kSegs);
+    ctx->one_slot = UINT32_MAX;
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    HIP_TRY(ctx, hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice));
+    ctx->one_slot = slot;
     return PSL_OK;
 }
 
@@ -929,6 +944,7 @@ void psl_ctx_destroy(psl_ctx *ctx)
     dev_free(ctx, ctx->d_walks, false);
     if (ctx->d_choice) (void)hipHostFree(ctx->d_choice);
     dev_free(ctx, ctx->d_one, false);
+    dev_free(ctx, ctx->d_init, false);
     timing_drop(ctx);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -983,8 +999,32 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         rollback(0);
         return st;
     }
-    std::vector<WalkDev> wd(n);
-    std::vector<uint32_t> want(n);
+    // one buffer, staged on the host and copied once: the walks' records, their
+    // batch entries and the given bits; then the segment sums of the fitness
+    const SegMap sm = seg_uniform(n, L);
+    size_t n_given = 0;
+    for (uint32_t b = 0; b < n; ++b) n_given += init_bits && init_bits[b];
+    const size_t o_be = align_up(sizeof(InitRec) * n, 256), o_bits = align_up(o_be + sizeof(BatchEntry) * n, 256),
+                 o_s0 = align_up(o_bits + sizeof(uint64_t) * nw * n_given, 256),
+                 o_m0 = align_up(o_s0 + 2 * sizeof(double) * sm.total, 256),
+                 need = o_m0 + sizeof(uint32_t) * sm.total;
+    if (need > ctx->init_cap) {
+        dev_free(ctx, ctx->d_init, false);
+        ctx->d_init = nullptr;
+        ctx->init_cap = 0;
+        void *p;
+        if ((st = dev_alloc(ctx, &p, need, false))) {
+            rollback(0);
+            return st;
+        }
+        ctx->d_init = (char *)p;
+        ctx->init_cap = need;
+    }
+    std::vector<char> stage(o_s0);
+    InitRec *recs = (InitRec *)stage.data();
+    BatchEntry *be = (BatchEntry *)(stage.data() + o_be);
+    uint64_t *bits = (uint64_t *)(stage.data() + o_bits);
+    size_t given_at = 0;
     for (uint32_t b = 0; b < n; ++b) {
         void *slab;
         if ((st = dev_alloc(ctx, &slab, slab_bytes, true))) {
@@ -999,67 +1039,44 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         h.flip_lmt = cfg->flip_lmt;
         h.slab = slab;
         h.slab_bytes = slab_bytes;
-        WalkDev &w = wd[b];
-        // the pivot sits between zeroed guard words (see guard_words)
-        HIP_TRY(ctx, hipMemsetAsync(slab, 0, slab_bytes, ctx->stream));
-        fill_walk(w, *cfg, cfg->seed + b, slab, lay);
-        const uint64_t *given = init_bits ? init_bits[b] : nullptr;
-        want[b] = given ? 0u : 1u;
-        if (given) {
-            uint64_t last = given[nw - 1];
-            if ((L & 63u) && (last >> (L & 63u))) {
+        InitRec &rec = recs[b];
+        fill_walk(rec.dev, *cfg, cfg->seed + b, slab, lay);
+        rec.slab = (uint64_t *)slab;
+        rec.bytes = slab_bytes;
+        rec.slot = ids[b];
+        rec.given = kNoBits;
+        if (init_bits && init_bits[b]) {
+            const uint64_t *given = init_bits[b];
+            if ((L & 63u) && (given[nw - 1] >> (L & 63u))) {
                 rollback(b + 1);
                 return fail(ctx, PSL_E_INVAL, "init_bits[%u] has bits set at or beyond L", b);
             }
-            HIP_TRY(ctx, hipMemcpyAsync(w.pivot, given, sizeof(uint64_t) * nw,
-                                        hipMemcpyHostToDevice, ctx->stream));
+            memcpy(bits + given_at, given, sizeof(uint64_t) * nw);
+            rec.given = given_at;
+            given_at += nw;
         }
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->d_walks + ids[b], &w, sizeof(WalkDev),
-                                    hipMemcpyHostToDevice, ctx->stream));
+        memset(&be[b], 0, sizeof(BatchEntry));
+        be[b].slot = ids[b];
+        be[b].S0 = (double *)(ctx->d_init + o_s0) + 2 * (size_t)sm.spw * b;
+        be[b].M0 = (uint32_t *)(ctx->d_init + o_m0) + (size_t)sm.spw * b;
     }
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    // init plan: entries and the chunk arrays of the fitness pass, on a
-    // temporary plan
-    BatchPlan tmp;
     {
-        void *p;
-        if ((st = dev_alloc(ctx, &p, sizeof(BatchEntry) * n, false))) return st;
-        tmp.d_batch = (BatchEntry *)p;
-        const size_t ns = suffix_len(L);
-        if ((st = dev_alloc(ctx, &p, sizeof(double) * ns * n, false))) {
-            plan_free(ctx, tmp);
-            return st;
-        }
-        tmp.d_s0 = (double *)p;
-        if ((st = dev_alloc(ctx, &p, sizeof(uint32_t) * ns * n, false))) {
-            plan_free(ctx, tmp);
-            return st;
-        }
-        tmp.d_m0 = (uint32_t *)p;
-        std::vector<BatchEntry> be(n);
-        for (uint32_t b = 0; b < n; ++b) {
-            memset(&be[b], 0, sizeof(BatchEntry));
-            be[b].slot = ids[b];
-            be[b].S0 = tmp.d_s0 + ns * b;
-            be[b].M0 = tmp.d_m0 + ns * b;
-        }
-        void *dw;
-        if ((st = dev_alloc(ctx, &dw, sizeof(uint32_t) * n, false))) {
-            plan_free(ctx, tmp);
-            return st;
-        }
-        HIP_TRY(ctx, hipMemcpy(tmp.d_batch, be.data(), sizeof(BatchEntry) * n, hipMemcpyHostToDevice));
-        HIP_TRY(ctx, hipMemcpy(dw, want.data(), sizeof(uint32_t) * n, hipMemcpyHostToDevice));
         const Tables tabs = tables_of(ctx);
-        hipError_t e = launch_init_bits(ctx->d_walks, tmp.d_batch, (const uint32_t *)dw, n, nw, ctx->stream);
+        const BatchEntry *d_be = (const BatchEntry *)(ctx->d_init + o_be);
         CorrDims cd;
         cd.add(L, n);
-        if (e == hipSuccess) e = launch_corr(ctx->d_walks, tmp.d_batch, n, cd, 0, ctx->stream);
-        const SegMap sm = seg_uniform(n, L);
-        if (e == hipSuccess) e = launch_suffix(ctx->d_walks, tmp.d_batch, n, L, tabs, 2, &sm, nullptr, 0, EvalCall{}, ctx->stream);
+        hipError_t e = hipMemcpyAsync(ctx->d_init, stage.data(), stage.size(), hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess)
+            e = launch_init(ctx->d_walks, (const InitRec *)ctx->d_init, (const uint64_t *)(ctx->d_init + o_bits), n,
+                            slab_bytes, nw, ctx->stream);
+        if (e == hipSuccess) e = launch_corr(ctx->d_walks, d_be, n, cd, 0, ctx->stream);
+        if (e == hipSuccess) e = launch_fit(ctx->d_walks, d_be, n, tabs, sm, kFitInit, 0, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        dev_free(ctx, dw, false);
-        plan_free(ctx, tmp);
+        if (ctx->init_cap > kInitKeep) {
+            dev_free(ctx, ctx->d_init, false);
+            ctx->d_init = nullptr;
+            ctx->init_cap = 0;
+        }
         if (e != hipSuccess) return fail(ctx, PSL_E_HIP, "walk init: %s", hipGetErrorString(e));
     }
     memcpy(walk_ids_out, ids.data(), sizeof(uint32_t) * n);
@@ -1198,15 +1215,11 @@ psl_status psl_apply_flip(psl_ctx *ctx, uint32_t walk, uint32_t j)
     const WalkHost &h = ctx->walks[walk];
     if (j >= h.L) return fail(ctx, PSL_E_INVAL, "j=%u >= L=%u", j, h.L);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    if (const psl_status st = one_entry(ctx)) return st;
-    BatchEntry e;
-    memset(&e, 0, sizeof e);
-    e.slot = walk;
-    hipError_t r = hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice);
+    if (const psl_status st = one_entry(ctx, walk)) return st;
     const Tables tabs = tables_of(ctx);
-    if (r == hipSuccess) r = launch_apply(ctx->d_walks, ctx->d_one, seg_uniform(1, h.L), tabs, (int64_t)j, ctx->stream);
-    if (r == hipSuccess) r = launch_flip_bit(ctx->d_walks, ctx->d_one, j, ctx->stream);
-    if (r == hipSuccess) r = launch_fitness(ctx->d_walks, ctx->d_one, 1, tabs, 2, ctx->stream);
+    const SegMap sm = seg_uniform(1, h.L);
+    hipError_t r = launch_apply(ctx->d_walks, ctx->d_one, sm, tabs, (int64_t)j, ctx->stream);
+    if (r == hipSuccess) r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, sm, kFitFlip, j, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r != hipSuccess) return fail(ctx, PSL_E_HIP, "apply_flip: %s", hipGetErrorString(r));
     return PSL_OK;
@@ -1630,13 +1643,9 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     h.flip_lmt = w.flip_lmt;
     plans_clear(ctx);            // N_lmt may differ
     // C of local_best (and C) from local_best's bits, then C from the pivot's
-    if (const psl_status rs = one_entry(ctx)) return rs;
-    BatchEntry e;
-    memset(&e, 0, sizeof e);
-    e.slot = walk;
-    hipError_t r = hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice);
+    if (const psl_status rs = one_entry(ctx, walk)) return rs;
     const Tables tabs = tables_of(ctx);
-    if (r == hipSuccess) r = hipMemcpy(w.pivot, local_best, 8ull * nw, hipMemcpyHostToDevice);
+    hipError_t r = hipMemcpy(w.pivot, local_best, 8ull * nw, hipMemcpyHostToDevice);
     CorrDims cd;
     cd.add(L);
     if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 0, ctx->stream);
@@ -1645,7 +1654,8 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     if (r == hipSuccess) r = hipMemcpy(w.local_best, local_best, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = hipMemcpy(w.best, best, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 2, ctx->stream);
-    if (r == hipSuccess) r = launch_fitness(ctx->d_walks, ctx->d_one, 1, tabs, 2, ctx->stream);
+    if (r == hipSuccess)
+        r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, seg_uniform(1, L), kFitPivot, 0, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r != hipSuccess) return fail(ctx, PSL_E_HIP, "restore: %s", hipGetErrorString(r));
     return PSL_OK;

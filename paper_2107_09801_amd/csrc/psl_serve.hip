@@ -74,7 +74,7 @@ size_t scratch_bound(uint32_t L, uint32_t n_lmt, uint32_t items_cap)
                     + 24ull * suffix_len(L)                // chunk suffix arrays: step, admission
                     + 4ull * (kNearCap + 1)                // near-peak list
                     + sizeof(SelPart) * kCombMaxBlocks     // combine-block minima
-                    + 2 * sizeof(BatchEntry) + 32          // batch and admission entries, list slots
+                    + 2 * sizeof(BatchEntry) + sizeof(InitRec) + 32   // batch and admission entries, start, list slots
                     + sizeof(EvalItem) * 8 * ks_tiles      // work items, with the flat form's padding
                     + 12ull * segs);                       // per-segment totals of the O(L) passes
 }
@@ -153,7 +153,8 @@ struct Server {
     DevBuf<BatchEntry> d_batch, d_admit;
     DevBuf<EvalItem> d_items;
     DevBuf<double> d_fpart, d_f, d_s0;
-    DevBuf<uint32_t> d_mpart, d_m0, d_near, d_want;
+    DevBuf<uint32_t> d_mpart, d_m0, d_near;
+    DevBuf<InitRec> d_rec;        // the admitted walks' starts
     DevBuf<SelPart> d_red;
     DevBuf<uint32_t> d_pend;      // pending list of the iteration's batch
     DevBuf<uint32_t> d_done;      // per batch position: combine blocks finished (0 between launches)
@@ -302,7 +303,7 @@ psl_status Server::flush_free()
 std::vector<Server::BufNeed> Server::all_bufs()
 {
     return {buf(d_batch, 0),  buf(d_admit, 0),  buf(d_items, 0),   buf(d_fpart, 0),  buf(d_f, 0),
-            buf(d_s0, 0),     buf(d_mpart, 0),  buf(d_m0, 0),      buf(d_near, 0),   buf(d_want, 0),
+            buf(d_s0, 0),     buf(d_mpart, 0),  buf(d_m0, 0),      buf(d_near, 0),   buf(d_rec, 0),
             buf(d_red, 0),    buf(d_pend, 0),   buf(d_done, 0),    buf(d_seg, 0),    buf(d_adm_seg, 0),
             buf(d_segtot, 0), buf(d_segmax, 0), buf(d_adm_s0, 0),  buf(d_adm_m0, 0), buf(d_p, 0),
             buf(d_queues, 0)};
@@ -413,7 +414,7 @@ psl_status Server::admit(char *&sp, char *stage_end)
         pending.pop_front();
     }
     if (adm.empty()) return PSL_OK;
-    const size_t need = adm.size() * (sizeof(WalkDev) + sizeof(BatchEntry) + 2 * sizeof(uint32_t)) + 192;
+    const size_t need = adm.size() * (sizeof(InitRec) + sizeof(BatchEntry) + sizeof(uint32_t)) + 192;
     if ((size_t)(stage_end - sp) < need) {
         // put them back in order; admitted next iteration
         for (auto it = adm.rbegin(); it != adm.rend(); ++it) {
@@ -451,16 +452,17 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
     psl_status st;
     size_t n_suf = 0;
     for (const Job &j : adm) n_suf += suffix_len(j.cfg.L);
-    if ((st = size_bufs({buf(d_admit, adm.size()), buf(d_want, adm.size()), buf(d_adm_s0, n_suf),
+    if ((st = size_bufs({buf(d_admit, adm.size()), buf(d_rec, adm.size()), buf(d_adm_s0, n_suf),
                          buf(d_adm_m0, n_suf), buf(d_adm_seg, adm.size() + 1)})))
         return st;
     size_t os = 0;
     CorrDims cd;
-    uint32_t maxL = 0, maxnw = 0;
+    uint32_t maxnw = 0;
+    uint64_t max_bytes = 0;
     BatchEntry *be = (BatchEntry *)sp;
     sp += sizeof(BatchEntry) * adm.size();
-    uint32_t *want = (uint32_t *)sp;
-    sp += sizeof(uint32_t) * adm.size();
+    InitRec *recs = (InitRec *)sp;
+    sp += sizeof(InitRec) * adm.size();
     uint32_t *adm_off = (uint32_t *)sp;
     sp += sizeof(uint32_t) * (adm.size() + 1);
     sp = (char *)(((uintptr_t)sp + 63) & ~(uintptr_t)63);
@@ -493,33 +495,33 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
         h.n_lmt = j.cfg.n_lmt ? j.cfg.n_lmt : j.cfg.L;
         h.slab = j.slab;
         h.slab_bytes = lay.slab_bytes;
-        WalkDev *wd = (WalkDev *)sp;
-        sp += sizeof(WalkDev);
-        fill_walk(*wd, j.cfg, j.cfg.seed, j.slab, lay);
-        j.dev = *wd;
-        HIP_TRY(ctx, hipMemsetAsync(j.slab, 0, lay.slab_bytes, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->d_walks + slot, wd, sizeof(WalkDev), hipMemcpyHostToDevice,
-                                    ctx->stream));
+        InitRec &rec = recs[b];
+        fill_walk(rec.dev, j.cfg, j.cfg.seed, j.slab, lay);
+        rec.slab = (uint64_t *)j.slab;
+        rec.bytes = lay.slab_bytes;
+        rec.given = kNoBits;
+        rec.slot = slot;
+        rec.pad = 0;
+        j.dev = rec.dev;
         memset(&be[b], 0, sizeof(BatchEntry));
         be[b].slot = slot;
         be[b].S0 = d_adm_s0.p + os;
         be[b].M0 = d_adm_m0.p + os;
         os += suffix_len(j.cfg.L);
-        want[b] = 1;
-        maxL = std::max(maxL, j.cfg.L);
+        max_bytes = std::max<uint64_t>(max_bytes, lay.slab_bytes);
         cd.add(j.cfg.L);
         maxnw = std::max(maxnw, h.nw);
         j.t_admit = t;
     }
     const uint32_t n = (uint32_t)adm.size();
     HIP_TRY(ctx, hipMemcpyAsync(d_admit.p, be, sizeof(BatchEntry) * n, hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(d_want.p, want, sizeof(uint32_t) * n, hipMemcpyHostToDevice, ctx->stream));
+    HIP_TRY(ctx, hipMemcpyAsync(d_rec.p, recs, sizeof(InitRec) * n, hipMemcpyHostToDevice, ctx->stream));
     const Tables tabs = tables_of(ctx);
-    HIP_TRY(ctx, launch_init_bits(ctx->d_walks, d_admit.p, d_want.p, n, maxnw, ctx->stream));
+    HIP_TRY(ctx, launch_init(ctx->d_walks, d_rec.p, nullptr, n, max_bytes, maxnw, ctx->stream));
     HIP_TRY(ctx, launch_corr(ctx->d_walks, d_admit.p, n, cd, 0, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_adm_seg.p, adm_off, sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice,
                                 ctx->stream));
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_admit.p, n, maxL, tabs, 2, &adm_map, nullptr, 0, EvalCall{}, ctx->stream));
+    HIP_TRY(ctx, launch_fit(ctx->d_walks, d_admit.p, n, tabs, adm_map, kFitInit, 0, ctx->stream));
     return PSL_OK;
 }
 
@@ -560,7 +562,7 @@ psl_status Server::upload_layout(char *&sp, char *stage_end)
                          buf(d_near, (size_t)(kNearCap + 1) * n), buf(d_queues, 1),
                          buf(d_red, (size_t)comb_blocks * n), buf(d_pend, (size_t)n + 1), buf(d_done, n),
                          buf(d_seg, (size_t)n + 1), buf(d_segtot, seg_host.total),
-                         buf(d_segmax, seg_host.total), buf(d_admit, 0), buf(d_want, 0), buf(d_adm_s0, 0),
+                         buf(d_segmax, seg_host.total), buf(d_admit, 0), buf(d_rec, 0), buf(d_adm_s0, 0),
                          buf(d_adm_m0, 0), buf(d_adm_seg, 0)})))
         return st;
     BatchEntry *be = (BatchEntry *)sp;
@@ -654,7 +656,7 @@ psl_status Server::iterate()
             const Job &j = pending[x];
             tiles += ((j.cfg.n_lmt ? j.cfg.n_lmt : j.cfg.L) + tl - 1) / tl;
         }
-        const size_t need = (n_adm + active.size()) * (sizeof(WalkDev) + 2 * sizeof(BatchEntry) + 16) +
+        const size_t need = (n_adm + active.size()) * (sizeof(InitRec) + 2 * sizeof(BatchEntry) + 16) +
                             sizeof(EvalItem) * 8 * ((uint64_t)items_max(ctx) + tiles) + 8192;
         if ((st = ensure_stage(need))) return st;
     }
@@ -665,8 +667,8 @@ psl_status Server::iterate()
     if (dirty && (st = upload_layout(sp, se))) return st;
     const uint32_t n = (uint32_t)active.size();
     const Tables tabs = tables_of(ctx);
-    HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_batch.p, n, max_L, tabs, 0, &seg, d_pend.p, shape.waves >= kEvalWavesMax,
-                               EvalCall{}, ctx->stream));
+    HIP_TRY(ctx, launch_suffix(ctx->d_walks, d_batch.p, n, tabs, &seg, d_pend.p, shape.waves >= kEvalWavesMax, EvalCall{},
+                               ctx->stream));
     HIP_TRY(ctx, launch_eval(ctx->d_walks, d_batch.p, d_items.p, n_items, tabs, shape, d_queues.p, nullptr, ctx->n_cu,
                              ctx->stream));
     HIP_TRY(ctx, launch_select(ctx->d_walks, d_batch.p, n, comb_blocks, comb_group, tabs, 0, nullptr, d_pend.p,
@@ -825,7 +827,7 @@ void serve_shutdown(psl_ctx *ctx)
     release(ctx, s->d_segmax);
     release(ctx, s->d_adm_s0);
     release(ctx, s->d_adm_m0);
-    release(ctx, s->d_want);
+    release(ctx, s->d_rec);
     release(ctx, s->d_p);
     release(ctx, s->d_queues);
     for (int h = 0; h < 2; ++h) {

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, Bat
     if (be.lsplit)
         prep_segment(sh.prep, w, be, tabs.T[w.alpha], (int)seg, (int)map.shift, be.segoff + 4 * (size_t)seg);
     else
-        chunk_segment(sh.chunk, be, w, tabs.T[w.alpha], 0, map, seg);
+        chunk_segment(sh.chunk, be, w, tabs.T[w.alpha], map, seg);
 }
 
 // The segment totals of value array x of a matrix walk as the offsets of
