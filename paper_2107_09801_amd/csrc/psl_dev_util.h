@@ -131,12 +131,12 @@ __device__ __forceinline__ void eval_call(BatchEntry *batch, const EvalCall &cal
     batch[0].P = call.P;
 }
 
-// Prefix sum x (0 .. 3, BatchEntry::pre) of a matrix walk over the shifts
+// Prefix sum x (0 .. 2, BatchEntry::pre) of a matrix walk over the shifts
 // 1 .. k: the one within the segment plus the segment's offset.
 __device__ __forceinline__ double split_prefix(const BatchEntry &be, uint32_t L, int x, uint32_t k)
 {
     const uint32_t seg = min(k >> be.seg_shift, seg_count(L, be.seg_shift) - 1u);
-    return be.pre[(size_t)x * L + k] + be.segoff[4 * (size_t)seg + x];
+    return be.pre[(size_t)x * L + k] + be.segoff[3 * (size_t)seg + x];
 }
 
 }  // namespace psl

@@ -103,11 +103,10 @@ struct BatchEntry {
     uint32_t near_lim;      // largest near-peak list handled sparsely
     uint32_t lsplit;        // matrix path: k-splits of its items (0: no matrix path)
     // matrix path (psl_split.hip): this step's coefficients of the walk
-    uint8_t *dig_both;      // [split_both_chunks(L)][2] digit records of the XOR and AND coefficients
+    uint8_t *dig_both;      // [split_both_chunks(L)][2] digit records of the XNOR and AND coefficients
     uint8_t *dig_one;       // [split_chunks(L)] digit records of the one-neighbour coefficient
-    double *pre;            // [4][L]: prefix sums over the segment's shifts up to k of T(|C_k-4|) (both-neighbour
-                            // shifts), T(|C_k-2|), T(|C_k+2|), T(|C_k|)
-    double *segoff;         // [segments][4]: their segments' totals, then offsets (SegMap segments)
+    double *pre;            // [3][L]: prefix sums over the segment's shifts up to k of T(|C_k-2|), T(|C_k+2|), T(|C_k|)
+    double *segoff;         // [segments][3]: their segments' totals, then offsets (SegMap segments)
     uint32_t seg_shift;     // log2 of a segment's shifts
     uint32_t pad;
     struct SplitState *ss;  // scale and path choice of this step

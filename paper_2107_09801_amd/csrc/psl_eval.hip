@@ -299,7 +299,7 @@ __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w,
         if (kMatrix && be.lsplit) {
             // a matrix walk left to this evaluation has prefix sums instead of
             // chunk arrays; the largest |C_k| comes from C itself
-            nsum_add(sum, comp, split_prefix(be, L, 3, k_hi - 1) - split_prefix(be, L, 3, kn - 1));
+            nsum_add(sum, comp, split_prefix(be, L, 2, k_hi - 1) - split_prefix(be, L, 2, kn - 1));
             if (kMax) {
                 int cm = 0;
                 for (int k = kn + lane; k < k_hi; k += 64) cm = max(cm, C[k] < 0 ? -C[k] : C[k]);

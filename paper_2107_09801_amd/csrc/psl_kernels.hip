@@ -823,13 +823,13 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
             // because |C'_{L-1}| = 1 for every sequence
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
             if (split) {
-                // F_j = sum_{k<=m} T(|C_k-4|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
+                // F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
                 //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
                 const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
-                const int p1 = get_bit(w.pivot, j) ? 2 : 1;
-                f = split_prefix(be, L, 0, mj) + (split_prefix(be, L, p1, Mj) - split_prefix(be, L, p1, mj)) +
-                    (split_prefix(be, L, 3, L - 1) - split_prefix(be, L, 3, Mj)) + U * f;
+                const int p1 = get_bit(w.pivot, j) ? 1 : 0;
+                f = split_prefix(be, L, 2, mj) + (split_prefix(be, L, p1, Mj) - split_prefix(be, L, p1, mj)) +
+                    (split_prefix(be, L, 2, L - 1) - split_prefix(be, L, 2, Mj)) + U * f;
             }
             be.F[i] = f;
             be.P[i] = p;

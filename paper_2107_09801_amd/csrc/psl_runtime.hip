@@ -435,10 +435,10 @@ static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl
     }
     size_t rounds = 0;
     for (int x = 0; x < kXcds; ++x) rounds = std::max(rounds, xq[x].size());
-    items.reserve(align_up(4 * (size_t)n, kXcds) + rounds * kXcds);
+    items.reserve(align_up(3 * (size_t)n, kXcds) + rounds * kXcds);
     // first the walks' offsets, padded to whole rounds
     for (uint32_t b = 0; b < n; ++b)
-        for (uint32_t x = 0; x < 4; ++x) items.push_back(EvalItem{b, kMxOffsets, x, 0});
+        for (uint32_t x = 0; x < 3; ++x) items.push_back(EvalItem{b, kMxOffsets, x, 0});
     while (items.size() % kXcds) items.push_back(EvalItem{kMxNoWalk, 0, 0, 0});
     for (size_t r = 0; r < rounds; ++r)
         for (int x = 0; x < kXcds; ++x)
@@ -644,7 +644,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     for (uint32_t b = 0; b < n; ++b) {
         if (!lsp[b]) continue;
         n_dig += dig_bytes(Ls[b]);
-        n_pre += 4 * (size_t)Ls[b];
+        n_pre += 3 * (size_t)Ls[b];
         n_lp += (size_t)(lsp[b] + 1) * Ls[b];
     }
     pl.split = !mitems.empty();
@@ -661,7 +661,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         pl.d_mitems = (EvalItem *)p;
         if ((st = get(&p, sizeof(uint32_t)))) return st;
         pl.d_tab = (uint32_t *)p;
-        if ((st = get(&p, 4 * sizeof(double) * pl.seg.total))) return st;
+        if ((st = get(&p, 3 * sizeof(double) * pl.seg.total))) return st;
         pl.d_segoff = (double *)p;
         pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
         pl.n_mitems = (uint32_t)mitems.size();
@@ -697,12 +697,12 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
             e.dig_one = pl.d_dig + o_dig;
             e.dig_both = e.dig_one + (size_t)kRecBytes * (split_chunks(Ls[b]) + kRecPad);
             e.pre = pl.d_pre + o_pre;
-            e.segoff = pl.d_segoff + 4 * (size_t)off[b];
+            e.segoff = pl.d_segoff + 3 * (size_t)off[b];
             e.seg_shift = pl.seg.shift;
             e.lpart = pl.d_lpart + o_lp;
             e.ss = pl.d_ss + b;
             o_dig += dig_bytes(Ls[b]);
-            o_pre += 4 * (size_t)Ls[b];
+            o_pre += 3 * (size_t)Ls[b];
             o_lp += (size_t)(lsp[b] + 1) * Ls[b];
         }
         op += (size_t)ks[b] * n_l[b];

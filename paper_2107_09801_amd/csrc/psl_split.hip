@@ -7,7 +7,7 @@
 // (k <= m_j = min(j, L-1-j)) and c + 2(2x - 1) where one does
 // (m_j < k <= M_j = max(j, L-1-j)); x_R = 1 where s_j s_{j+k} = -1, x_L = 1
 // where s_j s_{j-k} = -1. So
-//   both: T(c-4) + XOR(x_R, x_L) (T(c) - T(c-4)) + AND(x_R, x_L) (T(c+4) - T(c-4)),
+//   both: T(c) + XNOR(x_R, x_L) (T(c-4) - T(c)) + AND(x_R, x_L) (T(c+4) - T(c-4)),
 //   one:  T(c-2) + x (T(c+2) - T(c-2)),
 // and F_j is a sum of prefix sums of the constant parts plus three 0/1
 // matrices times coefficient vectors. The matrix cores take the matrices as
@@ -77,9 +77,9 @@ __device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out
 // The step's preparation of a matrix walk, one block per segment of its shifts
 // (2^shift of them, in tiles of 256), in one pass over C: the near-peak list
 // (chunk_octs builds the same one), the digit records, and the prefix sums of
-// T(|C_k-4|), T(|C_k-2|), T(|C_k+2|), T(|C_k|) within the segment, whose
-// totals k_mx's first items turn into offsets (split_offsets). Blocks of the
-// batch's other walks make the chunk sums of the table evaluation (k_chunks).
+// T(|C_k-2|), T(|C_k+2|), T(|C_k|) within the segment, whose totals k_mx's first
+// items turn into offsets (split_offsets). Blocks of the batch's other walks make
+// the chunk sums of the table evaluation (k_chunks).
 //
 // A record holds one 32-shift chunk (shifts 32c .. 32c+31) of one coefficient:
 // 16 columns (digits) of 32 FP6 codes, the first 12 bytes of each column, then
@@ -98,7 +98,7 @@ constexpr int kPrepStride = 36;         // words per chunk and four columns in L
 
 struct PrepLds {
     __align__(16) uint32_t codes[3][4][8 * kPrepStride];
-    double tot[4][kPrepThreads / 64];   // the wavefronts' totals of a tile
+    double tot[3][kPrepThreads / 64];   // the wavefronts' totals of a tile
 };
 
 // Inclusive scan of v over the wavefront.
@@ -118,13 +118,12 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
     const int L = (int)w.L;
     const double inv = 1.0 / split_scale(T, w.psl_pivot);      // exact: U is a power of two
     const int cut = w.psl_pivot - 8;                           // the near-peak cut
-    const int half = (L - 1) / 2;                              // the largest m_j
     const int nbo = (int)split_both_chunks((uint32_t)L), nco = (int)split_chunks((uint32_t)L);
     const int k_end = seg + 1 == (int)seg_count((uint32_t)L, (uint32_t)shift) ? 32 * nco : (seg + 1) << shift;
     const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
     const int slot = (t >> 5) * kPrepStride + 8 * (t & 3) + ((t & 31) >> 2);
     double *__restrict__ pre = be.pre;
-    double carry[4] = {0.0, 0.0, 0.0, 0.0};
+    double carry[3] = {0.0, 0.0, 0.0};
     for (int k0 = seg << shift; k0 < k_end; k0 += kPrepThreads) {
         const int k = k0 + t;
         const bool in = k >= 1 && k < L;
@@ -150,28 +149,28 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
 #pragma unroll
         for (int q = 0; q < 4; ++q) sh.codes[2][q][slot] = d[q];
         if (both) {
-            split_digits(in ? (t0 - tm4) * inv : 0.0, !(t & 1), d);
+            split_digits(in ? (tm4 - t0) * inv : 0.0, !(t & 1), d);
 #pragma unroll
             for (int q = 0; q < 4; ++q) sh.codes[0][q][slot] = d[q];
             split_digits(in ? (tp4 - tm4) * inv : 0.0, !(t & 1), d);
 #pragma unroll
             for (int q = 0; q < 4; ++q) sh.codes[1][q][slot] = d[q];
         }
-        double v[4] = {in && k <= half ? tm4 : 0.0, in ? tm2 : 0.0, in ? tp2 : 0.0, in ? t0 : 0.0};
+        double v[3] = {in ? tm2 : 0.0, in ? tp2 : 0.0, in ? t0 : 0.0};
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < 3; ++x) {
             v[x] = wave_scan(v[x], lane);
             if (lane == 63) sh.tot[x][wave] = v[x];
         }
         __syncthreads();
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
+        for (int x = 0; x < 3; ++x) {
             double off = carry[x];
             for (int q = 0; q < kPrepThreads / 64; ++q) {
                 if (q < wave) off += sh.tot[x][q];
                 carry[x] += sh.tot[x][q];
             }
-            if (k < L && (x > 0 || both)) pre[(size_t)x * L + k] = off + v[x];
+            if (k < L) pre[(size_t)x * L + k] = off + v[x];
         }
         // task e: half e / 96 of the slots, coefficient (e / 32) % 3, chunk (e / 4) % 8, columns 4 (e % 4) .. +3
         const int h = t >= 96 ? 1 : 0, e = t - 96 * h;
@@ -206,7 +205,7 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
         }
         __syncthreads();                                   // the tile's codes and totals have been read
     }
-    if (t < 4) segtot[t] = t == 0 ? carry[0] : t == 1 ? carry[1] : t == 2 ? carry[2] : carry[3];
+    if (t < 3) segtot[t] = t == 0 ? carry[0] : t == 1 ? carry[1] : carry[2];
 }
 
 __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, BatchEntry *batch, Tables tabs,
@@ -227,7 +226,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, Bat
     const BatchEntry be = batch[b];
     const WalkDev &w = walks[be.slot];
     if (be.lsplit)
-        prep_segment(sh.prep, w, be, tabs.T[w.alpha], (int)seg, (int)map.shift, be.segoff + 4 * (size_t)seg);
+        prep_segment(sh.prep, w, be, tabs.T[w.alpha], (int)seg, (int)map.shift, be.segoff + 3 * (size_t)seg);
     else
         chunk_segment(sh.chunk, be, w, tabs.T[w.alpha], map, seg);
 }
@@ -264,7 +263,7 @@ __device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry
     double *__restrict__ v = be.segoff + x;
     double s = 0.0, c = 0.0;
 #pragma unroll 4
-    for (int i = lo; i < hi; ++i) nsum_add(s, c, v[4 * i]);
+    for (int i = lo; i < hi; ++i) nsum_add(s, c, v[3 * i]);
     // exclusive scan of the lanes' sums
     for (int d = 1; d < 64; d <<= 1) {
         const double os = __shfl_up(s, d), oc = __shfl_up(c, d);
@@ -277,8 +276,8 @@ __device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry
     if (lane == 0) es = ec = 0.0;
 #pragma unroll 4
     for (int i = lo; i < hi; ++i) {
-        const double a = v[4 * i];
-        v[4 * i] = es + ec;
+        const double a = v[3 * i];
+        v[3 * i] = es + ec;
         nsum_add(es, ec, a);
     }
 }
@@ -321,9 +320,20 @@ hipError_t launch_prep(const WalkDev *walks, BatchEntry *batch, uint32_t nb, con
 // matrix of a window is the same for all b + c, so it is masked once); then
 // the rows with s_j = -1 change sign (their x is 1 minus the bit, and the
 // combine takes T(c+2) as their constant part), and the both-neighbour chunks
-// add XOR (which s_j does not change) and AND of the bits times s_j. Both go
-// into the same accumulators: |digit| <= 16 over at most L-1 shifts, one
-// coefficient each, stays within 2^24 units of 1/8, exact in FP32.
+// add XNOR (which s_j does not change) and AND of the bits times s_j: with the
+// XNOR word masked, the AND word is one more operation. Both go into the same
+// accumulators: |digit| <= 16 over at most L-1 shifts, one coefficient each,
+// stays within 2^24 units of 1/8, exact in FP32. The digits and the sequence's
+// words are loaded steps ahead, into rings: two wavefronts per SIMD (what the
+// 64 accumulators and the windows leave) do not hide a load's latency.
+//
+// What bounds it: at 1024 walks of L = 131071 the matrix cores are busy 66 % of
+// the time and vector issue 71 %; the 8.6e9 products alone take 76 ms (9.1 ns each
+// per SIMD, measured with nothing beside them).
+// 86.7 ms per step of that batch; with XOR and AND words masked one by one and
+// digits loaded one step ahead 99.4 ms, as int8 digit products for the linear
+// part and table lookups for the rest 228 ms. One walk at L = 1048575 6.19 ms
+// per step (7.2 before), 64 walks at L = 131071 with N_lmt = 6912 419 us (464).
 //
 // Main items hold the chunks all of whose shifts have both neighbours, or one,
 // for every row of the tile. The chunks between (those with some row's m_j,
@@ -345,14 +355,15 @@ __device__ __forceinline__ v4f mx_mfma(uint32_t x0, uint32_t x1, uint32_t x2, ui
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, acc, 4, 2, 0, 0, 0, 0);
 }
 
-// (a ^ b) & m and (a ^ s) & (b ^ s), one operation each
-__device__ __forceinline__ uint32_t xor_and(uint32_t a, uint32_t b, uint32_t m)
+// ~(a ^ b) & m, and (a ^ s) & y, one operation each: with y the former of two
+// windows a and b, the latter is (a ^ s) & (b ^ s) & m
+__device__ __forceinline__ uint32_t xnor_and(uint32_t a, uint32_t b, uint32_t m)
 {
-    return __builtin_amdgcn_bitop3_b32(a, b, m, 0x28);
+    return __builtin_amdgcn_bitop3_b32(a, b, m, 0x82);
 }
-__device__ __forceinline__ uint32_t and_signed(uint32_t a, uint32_t b, uint32_t s)
+__device__ __forceinline__ uint32_t signed_and(uint32_t a, uint32_t s, uint32_t y)
 {
-    return __builtin_amdgcn_bitop3_b32(a, b, s, 0x42);
+    return __builtin_amdgcn_bitop3_b32(a, s, y, 0x28);
 }
 
 // This lane's column of a digit record.
@@ -386,10 +397,14 @@ __device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, 
     const uint32_t shr = (uint32_t)ln.r, shl = (uint32_t)(31 - ln.r);
     uint32_t R[8][2], R2[8][2], W[8][2], W2[8][2];        // right and left windows, and shifted by 2
     uint32_t rprev, lprev, rq[4], lq[4];
-    v8i bx[2], ba[2];
+    v8i bx[4], ba[4];
     uint32_t off = (uint32_t)cb * (2 * kRecBytes) + 12u * (uint32_t)ln.col;
-    bx[0] = mx_rec(dig, ng > 0 ? off : offz);
-    ba[0] = mx_rec(dig + kRecBytes, ng > 0 ? off : offz);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        bx[k] = mx_rec(dig, k < ng ? off : offz);
+        ba[k] = mx_rec(dig + kRecBytes, k < ng ? off : offz);
+        off += 2 * kRecBytes;
+    }
     {
         uint32_t x[9], y[9];
 #pragma unroll
@@ -420,24 +435,32 @@ __device__ __forceinline__ void mx_both(v4f (&acc)[2 * kBlk], const MxLane &ln, 
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
             if (s >= N) break;
+            const uint32_t on = s + 2 < ng ? off : offz;
+            bx[(v + 2) & 3] = mx_rec(dig, on);
+            ba[(v + 2) & 3] = mx_rec(dig + kRecBytes, on);
             off += 2 * kRecBytes;
-            const uint32_t on = s + 1 < ng ? off : offz;
-            bx[(v + 1) & 1] = mx_rec(dig, on);
-            ba[(v + 1) & 1] = mx_rec(dig + kRecBytes, on);
             const uint32_t rn = rq[v & 3], lw = lq[v & 3];
             rq[v & 3] = ln.word(ln.J32 + cb + s + 13);
             lq[v & 3] = ln.word(ln.J32 - cb - s - 6);
 #pragma unroll
             for (int b = 0; b < kBlk; ++b) {
+                const int u = (v + b) & 7, x = (b - v) & 7;
+                uint32_t y[2][4];
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    const int i = 2 * b + p, u = (v + b) & 7, x = (b - v) & 7;
-                    acc[i] = mx_mfma(xor_and(R[u][p], W[x][p], kM0), xor_and(R[u][p], W[x][p], kM1),
-                                     xor_and(R2[u][p], W2[x][p], kM0), xor_and(R2[u][p], W2[x][p], kM1), bx[v & 1],
-                                     acc[i]);
-                    const uint32_t t = and_signed(R[u][p], W[x][p], ln.S[i]);
-                    const uint32_t t2 = and_signed(R2[u][p], W2[x][p], ln.S[i]);
-                    acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba[v & 1], acc[i]);
+                    y[p][0] = xnor_and(R[u][p], W[x][p], kM0);
+                    y[p][1] = xnor_and(R[u][p], W[x][p], kM1);
+                    y[p][2] = xnor_and(R2[u][p], W2[x][p], kM0);
+                    y[p][3] = xnor_and(R2[u][p], W2[x][p], kM1);
+                    acc[2 * b + p] = mx_mfma(y[p][0], y[p][1], y[p][2], y[p][3], bx[v & 3], acc[2 * b + p]);
+                }
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const uint32_t S = ln.S[2 * b + p];
+                    acc[2 * b + p] =
+                        mx_mfma(signed_and(R[u][p], S, y[p][0]), signed_and(R[u][p], S, y[p][1]),
+                                signed_and(R2[u][p], S, y[p][2]), signed_and(R2[u][p], S, y[p][3]), ba[v & 3],
+                                acc[2 * b + p]);
                 }
             }
             const uint32_t ly = __builtin_bitreverse32(lw);
@@ -468,10 +491,11 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
     const uint32_t sh = RIGHT ? (uint32_t)ln.r : (uint32_t)(31 - ln.r);
     uint32_t A[8][2][4];                    // the matrices of eight windows
     uint32_t prev, wq[4];
-    v8i bq[4];
+    v8i bq[8];                              // digits, loaded kAhead steps ahead
+    constexpr int kAhead = 6;
     uint32_t off = (uint32_t)cb * kRecBytes + 12u * (uint32_t)ln.col;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < kAhead; ++k) {
         bq[k] = mx_rec(dig, k < ng ? off : offz);
         off += kRecBytes;
     }
@@ -503,7 +527,7 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
 #pragma unroll
         for (int v = 0; v < 8; ++v) {
             if (s >= N) break;
-            bq[(v + 2) & 3] = mx_rec(dig, s + 2 < ng ? off : offz);
+            bq[(v + kAhead) & 7] = mx_rec(dig, s + kAhead < ng ? off : offz);
             off += kRecBytes;
             uint32_t wn = wq[v & 3];
             wq[v & 3] = ln.word(RIGHT ? ln.J32 + cb + s + 13 : ln.J32 - cb - s - 6);
@@ -513,7 +537,7 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
                 for (int p = 0; p < 2; ++p) {
                     const int i = 2 * b + p;
                     const uint32_t(&a)[4] = A[RIGHT ? (v + b) & 7 : (b - v) & 7][p];
-                    acc[i] = mx_mfma(a[0], a[1], a[2], a[3], bq[v & 3], acc[i]);
+                    acc[i] = mx_mfma(a[0], a[1], a[2], a[3], bq[v], acc[i]);
                 }
             }
             if (!RIGHT) wn = __builtin_bitreverse32(wn);
@@ -565,9 +589,9 @@ __device__ __forceinline__ void mx_edge(const MxLane &ln, const BatchEntry &be, 
             const uint32_t q = (j <= half ? R : W) & VO, q2 = q >> 2, sg = S[i] & 0x88888888u;
             acc[i] = mx_mfma((q & kM0) | sg, (q & kM1) | sg, (q2 & kM0) | sg, (q2 & kM1) | sg, bo, acc[i]);
             if (both) {
-                const uint32_t e = xor_and(R, W, VB), e2 = e >> 2;
+                const uint32_t e = xnor_and(R, W, VB), e2 = e >> 2;
                 acc[i] = mx_mfma(e & kM0, e & kM1, e2 & kM0, e2 & kM1, bx, acc[i]);
-                const uint32_t t = and_signed(R, W, S[i]) & VB, t2 = t >> 2;
+                const uint32_t t = signed_and(R, S[i], e), t2 = t >> 2;
                 acc[i] = mx_mfma(t & kM0, t & kM1, t2 & kM0, t2 & kM1, ba, acc[i]);
             }
         }
