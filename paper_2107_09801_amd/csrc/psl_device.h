@@ -151,7 +151,7 @@ struct InitRec {
     uint32_t slot;
     uint32_t pad;
 };
-enum { kFitInit, kFitPivot, kFitFlip };   // launch_fit's modes
+enum { kFitInit, kFitPivot };   // launch_fit's modes
 
 // What one evaluation call adds to its plan's entry (the first kernel writes
 // it, before any kernel reads it): the start and the F and PSL arrays.

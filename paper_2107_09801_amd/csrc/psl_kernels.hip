@@ -181,42 +181,51 @@ __global__ __launch_bounds__(kPendThreads) void k_pending(WalkDev *walks, const 
     }
 }
 
-// One wavefront per pending walk: the sums of its segments (k_apply) or units
-// (k_pending) in order become F_pivot = v_local and psl_pivot.
-__global__ __launch_bounds__(64) void k_pending_fin(WalkDev *walks, const BatchEntry *batch, const uint32_t *pend,
-                                                    uint32_t seg_shift)
+// The sums of a walk's n segments or units (pend_store) in order, by one
+// wavefront: lane l adds l, l + 64, ..., then the lanes in a fixed butterfly.
+// Every lane ends with the walk's F and PSL.
+__device__ __forceinline__ void pend_sum(const BatchEntry &be, uint32_t n, int lane, double &F, uint32_t &m)
+{
+    double s = 0.0, c = 0.0;
+    m = 0;
+#pragma unroll 4
+    for (uint32_t x = (uint32_t)lane; x < n; x += 64) {
+        nsum_add(s, c, be.S0[2 * x]);
+        c += be.S0[2 * x + 1];
+        m = max(m, be.M0[x]);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ps = __shfl_xor(s, o), pc = __shfl_xor(c, o);
+        const uint32_t pm = (uint32_t)__shfl_xor((int)m, o);
+        nsum_add(s, c, ps);
+        c += pc;
+        m = max(m, pm);
+    }
+    F = s + c;
+}
+
+// A walk that switched phase starts over from its new pivot's F and PSL.
+__device__ __forceinline__ void pend_done(WalkDev &w, double F, uint32_t m)
+{
+    w.F_pivot = F;
+    w.psl_pivot = (int32_t)m;
+    w.value_local = F;
+    w.unimproved = 0;
+    w.pending = 0;
+}
+
+// One wavefront per pending walk that k_pending took (k_apply finishes the others).
+__global__ __launch_bounds__(64) void k_pending_fin(WalkDev *walks, const BatchEntry *batch, const uint32_t *pend)
 {
     const uint32_t np = pend[0];
-    const int lane = (int)threadIdx.x;
     for (uint32_t q = blockIdx.x; q < np; q += gridDim.x) {
         const BatchEntry be = batch[pend[1 + q]];
         WalkDev &w = walks[be.slot];
-        const uint32_t nu = w.n_flips <= kFlipIncremental ? seg_count(w.L, seg_shift)
-                                                          : (w.L - 1 + kPendUnit - 1) / kPendUnit;
-        // lane l adds units l, l + 64, ... in order, then the lanes in a
-        // fixed butterfly (every lane ends with the same sums)
-        double s = 0.0, c = 0.0;
-        uint32_t m = 0;
-        for (uint32_t x = (uint32_t)lane; x < nu; x += 64) {
-            nsum_add(s, c, be.S0[2 * x]);
-            c += be.S0[2 * x + 1];
-            m = max(m, be.M0[x]);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double ps = __shfl_xor(s, o), pc = __shfl_xor(c, o);
-            const uint32_t pm = (uint32_t)__shfl_xor((int)m, o);
-            nsum_add(s, c, ps);
-            c += pc;
-            m = max(m, pm);
-        }
-        if (lane == 0) {
-            const double F = s + c;
-            w.F_pivot = F;
-            w.psl_pivot = (int32_t)m;
-            w.value_local = F;
-            w.unimproved = 0;
-            w.pending = 0;
-        }
+        if (w.n_flips <= kFlipIncremental) continue;
+        double F;
+        uint32_t m;
+        pend_sum(be, (w.L - 1 + kPendUnit - 1) / kPendUnit, (int)threadIdx.x, F, m);
+        if (threadIdx.x == 0) pend_done(w, F, m);
     }
 }
 
@@ -254,39 +263,21 @@ __global__ __launch_bounds__(kPendThreads) void k_fit(const WalkDev *walks, cons
 }
 
 // mode kFitInit: value_local, F_pivot, psl_pivot and psl_best; kFitPivot (a
-// restore): F_pivot and psl_pivot; kFitFlip (after a forced flip's C update):
-// the same, and element j changes sign.
-__global__ __launch_bounds__(64) void k_fit_fin(WalkDev *walks, const BatchEntry *batch, uint32_t seg_shift, int mode,
-                                                uint32_t j)
+// restore): F_pivot and psl_pivot.
+__global__ __launch_bounds__(64) void k_fit_fin(WalkDev *walks, const BatchEntry *batch, uint32_t seg_shift, int mode)
 {
     const BatchEntry be = batch[blockIdx.x];
     WalkDev &w = walks[be.slot];
-    const int lane = (int)threadIdx.x;
-    const uint32_t n = seg_count(w.L, seg_shift);
-    double s = 0.0, c = 0.0;
-    uint32_t m = 0;
-#pragma unroll 4
-    for (uint32_t x = (uint32_t)lane; x < n; x += 64) {
-        nsum_add(s, c, be.S0[2 * x]);
-        c += be.S0[2 * x + 1];
-        m = max(m, be.M0[x]);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const double ps = __shfl_xor(s, o), pc = __shfl_xor(c, o);
-        const uint32_t pm = (uint32_t)__shfl_xor((int)m, o);
-        nsum_add(s, c, ps);
-        c += pc;
-        m = max(m, pm);
-    }
-    if (lane == 0) {
-        const double F = s + c;
+    double F;
+    uint32_t m;
+    pend_sum(be, seg_count(w.L, seg_shift), (int)threadIdx.x, F, m);
+    if (threadIdx.x == 0) {
         w.F_pivot = F;
         w.psl_pivot = (int32_t)m;
         if (mode == kFitInit) {
             w.value_local = F;
             w.psl_best = (int32_t)m;
         }
-        if (mode == kFitFlip) w.pivot[j >> 6] ^= 1ull << (j & 63u);
     }
 }
 
@@ -996,10 +987,15 @@ __device__ __forceinline__ void switch_range(SwitchLds &sh, WalkDev &w, const Ba
     pend_store(sh.pend, ts, tc, tm, be, seg);
 }
 
+// Of a walk whose F and PSL are new with this update (a switched phase, a forced
+// flip) the last block to finish, counted in done[bi] (zero between launches),
+// adds up the segments' sums. (A launch of its own for that took 3.6 us of a
+// single walk's step, switching or not, and 4.5 us of a forced flip.)
 __global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const BatchEntry *batch, Tables tabs,
-                                                         int64_t j_fixed, SegMap map)
+                                                         int64_t j_fixed, SegMap map, uint32_t *done)
 {
     __shared__ SwitchLds sh;
+    __shared__ uint32_t s_last;
     uint32_t bi, seg;
     seg_of(map, blockIdx.x, bi, seg);
     const BatchEntry be = batch[bi];
@@ -1028,6 +1024,29 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const B
         switch_range(sh, w, be, tabs.T[w.alpha], j, sj, lb, k0, k1, seg);
     } else {
         apply_range<false>(w.C, w.C_lb, b, L, j, sj, lb, k0, k1, nullptr, ts, tc, tm);
+        return;
+    }
+    const uint32_t n = seg_count(L, map.shift);
+    if (threadIdx.x == 0) {             // it stored the segment's sums
+        s_last = 1;
+        if (n > 1) {
+            s_last = __hip_atomic_fetch_add(&done[bi], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+            if (s_last) done[bi] = 0;
+        }
+    }
+    __syncthreads();
+    if (!s_last || threadIdx.x >= 64) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    double F;
+    uint32_t m;
+    pend_sum(be, n, (int)threadIdx.x, F, m);
+    if (threadIdx.x) return;
+    if (moved) {
+        pend_done(w, F, m);
+    } else {
+        w.F_pivot = F;
+        w.psl_pivot = (int32_t)m;
+        w.pivot[j >> 6] ^= 1ull << (j & 63u);
     }
 }
 
@@ -1053,28 +1072,25 @@ hipError_t launch_init(WalkDev *walks, const InitRec *recs, const uint64_t *bits
 }
 
 hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint64_t units,
-                          const Tables &tabs, const uint32_t *pend, const SegMap &map, int big, hipStream_t s)
+                          const Tables &tabs, const uint32_t *pend, hipStream_t s)
 {
     if (!pend) return hipErrorInvalidValue;
-    if (big) {
-        // every unit of the batch's walks gets a block when all of them switch
-        const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(4096, units));
-        k_pending<<<grid, kPendThreads, 0, s>>>(walks, batch, tabs, pend);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    k_pending_fin<<<std::max<uint32_t>(1, std::min<uint32_t>(nb, 1024)), 64, 0, s>>>(walks, batch, pend, map.shift);
+    // every unit of the batch's walks gets a block when all of them switch
+    const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(4096, units));
+    k_pending<<<grid, kPendThreads, 0, s>>>(walks, batch, tabs, pend);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_pending_fin<<<std::max<uint32_t>(1, std::min<uint32_t>(nb, 1024)), 64, 0, s>>>(walks, batch, pend);
     return hipGetLastError();
 }
 
 hipError_t launch_fit(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap &map,
-                      int mode, uint32_t j, hipStream_t s)
+                      int mode, hipStream_t s)
 {
     if (map.total == 0 || map.nb != nb || map.shift < kSegShiftMin || map.shift > kSegShiftMax)
         return hipErrorInvalidValue;
-    // a forced flip's C update has left the segments' sums
-    if (mode != kFitFlip) k_fit<<<map.total, kPendThreads, 0, s>>>(walks, batch, tabs, map);
-    k_fit_fin<<<nb, 64, 0, s>>>(walks, batch, map.shift, mode, j);
+    k_fit<<<map.total, kPendThreads, 0, s>>>(walks, batch, tabs, map);
+    k_fit_fin<<<nb, 64, 0, s>>>(walks, batch, map.shift, mode);
     return hipGetLastError();
 }
 
@@ -1151,11 +1167,12 @@ void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double
 }
 
 hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, const Tables &tabs,
-                        int64_t j_fixed, hipStream_t s)
+                        int64_t j_fixed, uint32_t *done, hipStream_t s)
 {
+    if (!done) return hipErrorInvalidValue;
     if (map.shift < kSegShiftMin || map.shift > kSegShiftMax) return hipErrorInvalidValue;
     if (map.total == 0) return hipSuccess;       // L = 1 has no shift to update
-    k_apply<<<map.total, kApplyThreads, 0, s>>>(walks, batch, tabs, j_fixed, map);
+    k_apply<<<map.total, kApplyThreads, 0, s>>>(walks, batch, tabs, j_fixed, map, done);
     return hipGetLastError();
 }
 

@@ -29,18 +29,16 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, con
                        hipStream_t s);
 constexpr uint32_t kPendUnit = 1024;   // shifts per work unit of the pending-walk rebuild
 
-// C, F and PSL of the walks on the pending list (pend: count, then batch
-// positions) whose switch flipped more than kFlipIncremental elements, after
-// k_corr rebuilt C (big: some walk of the batch has that many; units: work
-// units of kPendUnit shifts the batch's nb walks hold in all), and the sums
-// that launch_update left for the others.
+// F and PSL of the walks on the pending list (pend: count, then batch positions)
+// whose switch flipped more than kFlipIncremental elements, after launch_corr
+// rebuilt C (units: work units of kPendUnit shifts the batch's nb walks hold in
+// all).
 hipError_t launch_pending(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint64_t units,
-                          const Tables &tabs, const uint32_t *pend, const SegMap &map, int big, hipStream_t s);
-// F and PSL of the pivots from C (kFitFlip: from the sums launch_apply's forced
-// flip of element j left; the element then changes sign). The segments' sums go
-// through the entries' chunk arrays (2 and 1 entries per segment).
+                          const Tables &tabs, const uint32_t *pend, hipStream_t s);
+// F and PSL of the pivots from C. The segments' sums go through the entries'
+// chunk arrays (2 and 1 entries per segment).
 hipError_t launch_fit(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap &map,
-                      int mode, uint32_t j, hipStream_t s);
+                      int mode, hipStream_t s);
 // tab (batches with a matrix path): the number of the batch's walks left to
 // this evaluation in this step; with none, its blocks return at once.
 hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items,
@@ -73,10 +71,11 @@ bool choice_dev_table(const void *p);
 void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double *F_best,
                        double *F_min, uint32_t *j_psl, int32_t *psl_min, int32_t *psl_k, uint32_t *flags);
 // The C update of each walk's recorded move (j_fixed < 0, after the
-// bookkeeping; for a walk that switched phase, C of its new pivot) or of a
-// forced flip of element j_fixed (before its bit flips).
+// bookkeeping; for a walk that switched phase, C, F and PSL of its new pivot) or
+// of a forced flip of element j_fixed, with F, PSL and the element's bit. done:
+// one zeroed counter per batch position, left zero.
 hipError_t launch_apply(WalkDev *walks, const BatchEntry *batch, const SegMap &map, const Tables &tabs,
-                        int64_t j_fixed, hipStream_t s);
+                        int64_t j_fixed, uint32_t *done, hipStream_t s);
 // Units of launch_pending for walks of length L.
 inline uint64_t pending_units(uint32_t L) { return (L - 1 + kPendUnit - 1) / kPendUnit; }
 

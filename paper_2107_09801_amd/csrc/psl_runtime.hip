@@ -812,10 +812,11 @@ psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, ui
     if ((st = launch_partials(ctx, pl, tabs, n, pl.d_pend, timed, EvalCall{}, true))) return st;
     HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
                                pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
-    HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, tabs, -1, ctx->stream));
-    if (pl.big_flips) HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.corr, 1, ctx->stream));
-    HIP_TRY(ctx, launch_pending(ctx->d_walks, pl.d_batch, n, pl.pend_units, tabs, pl.d_pend, pl.seg, pl.big_flips,
-                                ctx->stream));
+    HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, tabs, -1, pl.d_done, ctx->stream));
+    if (pl.big_flips) {
+        HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.corr, 1, ctx->stream));
+        HIP_TRY(ctx, launch_pending(ctx->d_walks, pl.d_batch, n, pl.pend_units, tabs, pl.d_pend, ctx->stream));
+    }
     if (timed && (st = timing_mark(ctx))) return st;
     return PSL_OK;
 }
@@ -844,13 +845,15 @@ psl_status capture_step(psl_ctx *ctx, BatchPlan &pl, const Tables &tabs, uint32_
 }
 
 // The context's one-walk batch entry (psl_apply_flip, psl_restore_walk) for
-// walk `slot`, with the arrays of its fitness sums, allocated on first use and
-// kept until the context is destroyed.
+// walk `slot`, with the arrays of its fitness sums and its block counter,
+// allocated on first use and kept until the context is destroyed.
+constexpr size_t kOneDone = 512;
+uint32_t *one_done(psl_ctx *ctx) { return (uint32_t *)((char *)ctx->d_one + kOneDone); }
 psl_status one_entry(psl_ctx *ctx, uint32_t slot)
 {
     constexpr uint32_t kSegs = 4096;         // a walk's segments, at most
-    constexpr size_t kHead = 512;
-    static_assert(sizeof(BatchEntry) <= kHead, "the entry comes first");
+    constexpr size_t kHead = kOneDone + 64;
+    static_assert(sizeof(BatchEntry) <= kOneDone, "the entry comes first");
     if (!ctx->d_one) {
         void *p;
         const psl_status st = dev_alloc(ctx, &p, kHead + kSegs * (2 * sizeof(double) + sizeof(uint32_t)), false);
@@ -859,6 +862,8 @@ psl_status one_entry(psl_ctx *ctx, uint32_t slot)
         ctx->one_slot = UINT32_MAX;
     }
     if (ctx->one_slot == slot) return PSL_OK;
+    char head[kHead];                        // the entry and a zero counter
+    memset(head, 0, sizeof head);
     BatchEntry e;
     memset(&e, 0, sizeof e);
     e.slot = slot;
@@ -866,7 +871,8 @@ psl_status one_entry(psl_ctx *ctx, uint32_t slot)
     e.M0 = (uint32_t *)(e.S0 + 2 * kSegs);
     ctx->one_slot = UINT32_MAX;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    HIP_TRY(ctx, hipMemcpy(ctx->d_one, &e, sizeof e, hipMemcpyHostToDevice));
+    memcpy(head, &e, sizeof e);
+    HIP_TRY(ctx, hipMemcpy(ctx->d_one, head, sizeof head, hipMemcpyHostToDevice));
     ctx->one_slot = slot;
     return PSL_OK;
 }
@@ -1070,7 +1076,7 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
             e = launch_init(ctx->d_walks, (const InitRec *)ctx->d_init, (const uint64_t *)(ctx->d_init + o_bits), n,
                             slab_bytes, nw, ctx->stream);
         if (e == hipSuccess) e = launch_corr(ctx->d_walks, d_be, n, cd, 0, ctx->stream);
-        if (e == hipSuccess) e = launch_fit(ctx->d_walks, d_be, n, tabs, sm, kFitInit, 0, ctx->stream);
+        if (e == hipSuccess) e = launch_fit(ctx->d_walks, d_be, n, tabs, sm, kFitInit, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (ctx->init_cap > kInitKeep) {
             dev_free(ctx, ctx->d_init, false);
@@ -1218,8 +1224,7 @@ psl_status psl_apply_flip(psl_ctx *ctx, uint32_t walk, uint32_t j)
     if (const psl_status st = one_entry(ctx, walk)) return st;
     const Tables tabs = tables_of(ctx);
     const SegMap sm = seg_uniform(1, h.L);
-    hipError_t r = launch_apply(ctx->d_walks, ctx->d_one, sm, tabs, (int64_t)j, ctx->stream);
-    if (r == hipSuccess) r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, sm, kFitFlip, j, ctx->stream);
+    hipError_t r = launch_apply(ctx->d_walks, ctx->d_one, sm, tabs, (int64_t)j, one_done(ctx), ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r != hipSuccess) return fail(ctx, PSL_E_HIP, "apply_flip: %s", hipGetErrorString(r));
     return PSL_OK;
@@ -1655,7 +1660,7 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     if (r == hipSuccess) r = hipMemcpy(w.best, best, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 2, ctx->stream);
     if (r == hipSuccess)
-        r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, seg_uniform(1, L), kFitPivot, 0, ctx->stream);
+        r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, seg_uniform(1, L), kFitPivot, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
     if (r != hipSuccess) return fail(ctx, PSL_E_HIP, "restore: %s", hipGetErrorString(r));
     return PSL_OK;

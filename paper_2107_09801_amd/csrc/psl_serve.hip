@@ -521,7 +521,7 @@ psl_status Server::admit_start(std::vector<Job> &adm, char *&sp, char *stage_end
     HIP_TRY(ctx, launch_corr(ctx->d_walks, d_admit.p, n, cd, 0, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(d_adm_seg.p, adm_off, sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice,
                                 ctx->stream));
-    HIP_TRY(ctx, launch_fit(ctx->d_walks, d_admit.p, n, tabs, adm_map, kFitInit, 0, ctx->stream));
+    HIP_TRY(ctx, launch_fit(ctx->d_walks, d_admit.p, n, tabs, adm_map, kFitInit, ctx->stream));
     return PSL_OK;
 }
 
@@ -673,7 +673,7 @@ psl_status Server::iterate()
                              ctx->stream));
     HIP_TRY(ctx, launch_select(ctx->d_walks, d_batch.p, n, comb_blocks, comb_group, tabs, 0, nullptr, d_pend.p,
                                d_done.p, ctx->amb_margin, ctx->stream));
-    HIP_TRY(ctx, launch_apply(ctx->d_walks, d_batch.p, seg, tabs, -1, ctx->stream));
+    HIP_TRY(ctx, launch_apply(ctx->d_walks, d_batch.p, seg, tabs, -1, d_done.p, ctx->stream));
     bool big = false;
     uint64_t units = 0;
     CorrDims cd;
@@ -682,8 +682,10 @@ psl_status Server::iterate()
         cd.add(j.cfg.L);
         units += pending_units(j.cfg.L);
     }
-    if (big) HIP_TRY(ctx, launch_corr(ctx->d_walks, d_batch.p, n, cd, 1, ctx->stream));
-    HIP_TRY(ctx, launch_pending(ctx->d_walks, d_batch.p, n, units, tabs, d_pend.p, seg, big, ctx->stream));
+    if (big) {
+        HIP_TRY(ctx, launch_corr(ctx->d_walks, d_batch.p, n, cd, 1, ctx->stream));
+        HIP_TRY(ctx, launch_pending(ctx->d_walks, d_batch.p, n, units, tabs, d_pend.p, ctx->stream));
+    }
     uint64_t evals = 0, upd = 0;
     for (auto &j : active) {
         const uint64_t nl = j.cfg.n_lmt ? j.cfg.n_lmt : j.cfg.L;
