@@ -297,14 +297,22 @@ __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w,
     const int kn = max(k_lo, k_wend);
     if (kn < k_hi) {
         if (kMatrix && be.lsplit) {
-            // a matrix walk left to this evaluation has prefix sums instead of
-            // chunk arrays; the largest |C_k| comes from C itself
-            nsum_add(sum, comp, split_prefix(be, L, 2, k_hi - 1) - split_prefix(be, L, 2, kn - 1));
-            if (kMax) {
-                int cm = 0;
-                for (int k = kn + lane; k < k_hi; k += 64) cm = max(cm, C[k] < 0 ? -C[k] : C[k]);
-                mx = max(mx, hi32(T[wave_max(cm, lane)]));
+            // a matrix walk left to this evaluation has no chunk arrays: from C
+            double s = 0.0, c = 0.0;
+            int cm = 0;
+            for (int k = kn + lane; k < k_hi; k += 64) {
+                const int a = C[k] < 0 ? -C[k] : C[k];
+                nsum_add(s, c, T[a]);
+                cm = max(cm, a);
             }
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ps = __shfl_xor(s, o), pc = __shfl_xor(c, o);
+                nsum_add(s, c, ps);
+                c += pc;
+            }
+            nsum_add(sum, comp, s);
+            comp += c;
+            if (kMax) mx = max(mx, hi32(T[wave_max(cm, lane)]));
             return;
         }
         const int nchunks = (L - 1 + 31) / 32;

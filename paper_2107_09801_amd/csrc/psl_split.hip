@@ -92,30 +92,57 @@ __device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out
 //
 // One pass instead of three (chunk sums, coefficients, a serial scan per walk
 // that took 0.94 ms of a step at L = 1048575 and 0.21 ms for 64 walks at
-// L = 131071).
+// L = 131071). Prefixes, 24 of the 52 bytes written per shift, are scanned and
+// stored only in tiles that hold some candidate's m_j or M_j; the others' values
+// stay in their threads until the next such tile. The next tile's C is loaded
+// while a tile's digits are made, and the scans go through lane permutations of
+// the vector units instead of LDS. Bound by vector issue, mostly the digits
+// (about 100 operations per coefficient), and by the writes: 64 walks at
+// L = 131071, N_lmt = 6912, 184 -> 129 us (their 220 MB take 45 us), full
+// neighbourhoods at 1024 walks 3.10 -> 2.86 ms (7 GB), one walk at L = 16383
+// 7.2 -> 6.2 us.
 constexpr int kPrepThreads = 256;
 constexpr int kPrepStride = 36;         // words per chunk and four columns in LDS (32 and padding)
 
 struct PrepLds {
     __align__(16) uint32_t codes[3][4][8 * kPrepStride];
     double tot[3][kPrepThreads / 64];   // the wavefronts' totals of a tile
+    double acc[3][kPrepThreads / 64];   // and of the tiles before it without stored prefixes
 };
 
-// Inclusive scan of v over the wavefront.
-__device__ __forceinline__ double wave_scan(double v, int lane)
+// v plus the value that lane-permuting control CTRL brings from another lane (0
+// where it brings none, or outside the rows of ROWS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double o = __shfl_up(v, d);
-        if (lane >= d) v += o;
-    }
-    return v;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return v + __hiloint2double(hi, lo);
+}
+// Inclusive scan of v over the wavefront: within rows of 16 lanes by row shifts,
+// then the rows before (row_bcast:15 into rows 1 and 3, row_bcast:31 into 2 and 3).
+__device__ __forceinline__ double wave_scan(double v)
+{
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    return dpp_add<0x143, 0xC>(v);
+}
+
+// Whether some element of a circular range of n elements from j0 lies in a .. b.
+__device__ __forceinline__ bool range_hits(int L, int j0, int n, int a, int b)
+{
+    return (j0 >= a && j0 <= b) || a - j0 + (a < j0 ? L : 0) < n;
 }
 
 __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, const BatchEntry &be,
-                                             const double *__restrict__ T, int seg, int shift, double *segtot)
+                                             const double *__restrict__ T, uint32_t start, int n_lmt, int seg,
+                                             int shift, double *segtot)
 {
     const int L = (int)w.L;
+    const int j0 = (int)((start + 1u) % (uint32_t)L);
     const double inv = 1.0 / split_scale(T, w.psl_pivot);      // exact: U is a power of two
     const int cut = w.psl_pivot - 8;                           // the near-peak cut
     const int nbo = (int)split_both_chunks((uint32_t)L), nco = (int)split_chunks((uint32_t)L);
@@ -123,12 +150,21 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
     const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
     const int slot = (t >> 5) * kPrepStride + 8 * (t & 3) + ((t & 31) >> 2);
     double *__restrict__ pre = be.pre;
-    double carry[3] = {0.0, 0.0, 0.0};
+    const int32_t *__restrict__ C = w.C;
+    double carry[3] = {0.0, 0.0, 0.0}, acc[3] = {0.0, 0.0, 0.0};
+    bool kept = false;                                         // acc holds tiles without stored prefixes
+    int next = C[min((seg << shift) + t, L - 1)];
     for (int k0 = seg << shift; k0 < k_end; k0 += kPrepThreads) {
         const int k = k0 + t;
         const bool in = k >= 1 && k < L;
         const bool both = (k0 >> 5) < nbo;                     // some chunk of the tile has both-neighbour shifts
-        const int c = in ? w.C[k] : 0;
+        const int kz = min(k0 + kPrepThreads, L) - 1;
+        // the tiles that the combine reads prefixes of: shifts m_j and M_j of a
+        // candidate, and L - 1
+        const bool want = kz == L - 1 || range_hits(L, j0, n_lmt, k0, kz) ||
+                          range_hits(L, j0, n_lmt, L - 1 - kz, L - 1 - k0);
+        const int c = in ? next : 0;
+        next = C[min(k + kPrepThreads, L - 1)];
         const int a0 = c < 0 ? -c : c;
         const int a4 = c + 4 < 0 ? -(c + 4) : c + 4, m4 = c - 4 < 0 ? 4 - c : c - 4;
         const int a2 = c + 2 < 0 ? -(c + 2) : c + 2, m2 = c - 2 < 0 ? 2 - c : c - 2;
@@ -157,20 +193,40 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
             for (int q = 0; q < 4; ++q) sh.codes[1][q][slot] = d[q];
         }
         double v[3] = {in ? tm2 : 0.0, in ? tp2 : 0.0, in ? t0 : 0.0};
+        if (!want) {
 #pragma unroll
-        for (int x = 0; x < 3; ++x) {
-            v[x] = wave_scan(v[x], lane);
-            if (lane == 63) sh.tot[x][wave] = v[x];
+            for (int x = 0; x < 3; ++x) acc[x] += v[x];
+            kept = true;
+        } else {
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                v[x] = wave_scan(v[x]);
+                if (lane == 63) sh.tot[x][wave] = v[x];
+            }
+            if (kept) {
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    const double a = wave_scan(acc[x]);
+                    if (lane == 63) sh.acc[x][wave] = a;
+                }
+            }
         }
         __syncthreads();
+        if (want) {
 #pragma unroll
-        for (int x = 0; x < 3; ++x) {
-            double off = carry[x];
-            for (int q = 0; q < kPrepThreads / 64; ++q) {
-                if (q < wave) off += sh.tot[x][q];
-                carry[x] += sh.tot[x][q];
+            for (int x = 0; x < 3; ++x) {
+                if (kept) {
+                    for (int q = 0; q < kPrepThreads / 64; ++q) carry[x] += sh.acc[x][q];
+                    acc[x] = 0.0;
+                }
+                double off = carry[x];
+                for (int q = 0; q < kPrepThreads / 64; ++q) {
+                    if (q < wave) off += sh.tot[x][q];
+                    carry[x] += sh.tot[x][q];
+                }
+                if (k < L) pre[(size_t)x * L + k] = off + v[x];
             }
-            if (k < L) pre[(size_t)x * L + k] = off + v[x];
+            kept = false;
         }
         // task e: half e / 96 of the slots, coefficient (e / 32) % 3, chunk (e / 4) % 8, columns 4 (e % 4) .. +3
         const int h = t >= 96 ? 1 : 0, e = t - 96 * h;
@@ -205,6 +261,17 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
         }
         __syncthreads();                                   // the tile's codes and totals have been read
     }
+    if (kept) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const double a = wave_scan(acc[x]);
+            if (lane == 63) sh.acc[x][wave] = a;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+            for (int q = 0; q < kPrepThreads / 64; ++q) carry[x] += sh.acc[x][q];
+    }
     if (t < 3) segtot[t] = t == 0 ? carry[0] : t == 1 ? carry[1] : carry[2];
 }
 
@@ -226,7 +293,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, Bat
     const BatchEntry be = batch[b];
     const WalkDev &w = walks[be.slot];
     if (be.lsplit)
-        prep_segment(sh.prep, w, be, tabs.T[w.alpha], (int)seg, (int)map.shift, be.segoff + 3 * (size_t)seg);
+        prep_segment(sh.prep, w, be, tabs.T[w.alpha], call.on ? call.start : be.fixed ? be.start : step_start(w),
+                     (int)(be.fixed ? be.n_lmt : w.n_lmt), (int)seg, (int)map.shift, be.segoff + 3 * (size_t)seg);
     else
         chunk_segment(sh.chunk, be, w, tabs.T[w.alpha], map, seg);
 }

@@ -67,3 +67,27 @@ def test_matrix_biased_sequences(ctx, p_minus):
     _, Ft, Pt = _eval(ctx, w, 77, L, 0)
     assert np.array_equal(P, Pt) and np.max(np.abs(F - Ft) / Ft) <= 1e-13
     ctx.free_walks([w])
+
+
+@pytest.mark.parametrize("L", [4097, 8193, 40009])
+def test_limited_neighbourhoods_one_after_another(ctx, L):
+    """The preparation stores prefix sums only where a candidate reads them: small
+    and large neighbourhoods at ends, middle and tile edges, each after others
+    whose prefixes lie elsewhere; once more with the near-peak list cut off, so
+    that the table evaluation takes the walk after the preparation."""
+    from paper_2107_09801_amd import libpsl
+    bits = si.random_bits(L, L + 3)
+    (w,) = ctx.init_walks(L, 1, 1, alpha1=4, alpha2=13, init_bits=[bits])
+    half = L // 2
+    for start, n in ((0, 1), (half - 3, 7), (L - 1, L), (L - 2, 3), (254, 2), (255, 1), (256, 257), (half, 1),
+                     (L - 258, 5), (half + 255, 600), (L - 300, 900)):
+        _, F, P = _eval(ctx, w, start, n, 1)
+        _, Ft, Pt = _eval(ctx, w, start, n, 0)
+        assert np.array_equal(P, Pt) and np.max(np.abs(F - Ft) / Ft) <= 1e-13, (start, n)
+        ctx.set_option(libpsl.OPT_NEAR_LIMIT, 1)
+        try:
+            _, F, P = _eval(ctx, w, start, n, 1)
+        finally:
+            ctx.set_option(libpsl.OPT_NEAR_LIMIT, -1)
+        assert np.array_equal(P, Pt) and np.max(np.abs(F - Ft) / Ft) <= 1e-13, (start, n)
+    ctx.free_walks([w])
