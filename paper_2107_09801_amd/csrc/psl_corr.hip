@@ -3,7 +3,7 @@
 // large for the one-flip rebuild.
 //
 // Long sequences: on the matrix cores, as products of two +-1 matrices made
-// from the sequence's bits in FP4. One wavefront takes kCorrTile = 4096
+// from the sequence's bits in FP4. One block takes kCorrTile = 4096
 // consecutive shifts and a range of the positions i, in 32-position chunks.
 // The 16 rows of v_mfma_f32_16x16x128_f8f6f4 hold s at i + K0 + 32 n + 16 p + r
 // (r the row; n = 0..7 and p = 0..1 one product each), the 16 columns s at
@@ -89,6 +89,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kCorrTile = 4096;     // shifts per wavefront
 constexpr int kWordPad = 256;            // words before the sequence that the word offsets start from
+constexpr int kMxThreads = 256;
 
 // 32 sequence bits as +-1 in FP4 (1.0 = 0x2, the sign 0x8), shifts 4q + r of
 // the chunk in nibble q of word r; v: the bits inside the sequence, others 0
@@ -114,9 +115,12 @@ __device__ __forceinline__ void pm1_nibbles(uint32_t x, uint32_t (&o)[4])
 // Block (x, y): walk x of the batch, tile y / splits, positions' part y % splits
 // (Q chunks each): the longest tiles of all walks start first. (With a walk's
 // tiles side by side, their falling lengths fell in step with the XCDs and SIMDs
-// that blocks are dealt to, and a third of the SIMDs ran dry.) One part: C (and C_lb in mode 0) is stored; several: added
-// into C, which is zero.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_corr_mx(
+// that blocks are dealt to, and a third of the SIMDs ran dry.) Four wavefronts
+// take a quarter of the chunks each and add their sums in LDS: with a part per
+// wavefront, added into C one by one, 64 walks at L = 65535 took 133 us (now 81)
+// and the 32 walks of a serving wave 4.0 ms (1.8). One part: C (and C_lb in mode
+// 0) is stored; several: added into C, which is zero.
+__global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_corr_mx(
     WalkDev *walks, const BatchEntry *batch, int mode, int splits, int Q)
 {
     WalkDev &w = walks[batch[blockIdx.x].slot];
@@ -124,10 +128,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     const int L = (int)w.L;
     const int K0 = (int)kCorrTile * ((int)blockIdx.y / splits);
     if (K0 >= L || L < (int)kCorrMxMinL) return;
-    // chunks with a position i below L - K0
-    const int c0 = Q * ((int)blockIdx.y % splits), c1 = min(c0 + Q, (L - K0 + 31) >> 5);
-    if (c0 >= c1) return;
-    const int lane = (int)threadIdx.x, r = lane & 15, g = lane >> 4;
+    // the block's chunks (those with a position i below L - K0), a quarter for each wavefront
+    const int p0 = Q * ((int)blockIdx.y % splits), p1 = min(p0 + Q, (L - K0 + 31) >> 5);
+    if (p0 >= p1) return;
+    __shared__ int sum[kCorrTile + 64];
+    for (int x = (int)threadIdx.x; x < (int)kCorrTile + 64; x += kMxThreads) sum[x] = 0;
+    __syncthreads();
+    const int wq4 = (p1 - p0 + 3) >> 2;
+    const int c0 = min(p1, p0 + wq4 * ((int)threadIdx.x >> 6)), c1 = min(p1, c0 + wq4);
+    const int lane = (int)threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int N = (c1 - c0 + 3) >> 2, cb = c0 + g * N;
     const uint32_t *base = reinterpret_cast<const uint32_t *>(w.pivot) - kWordPad;
     auto word = [&](int i) {
@@ -201,20 +210,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         }
     }
     // register j of product i, lane (g, q): shift 256 q + 16 i + 4 g + j of the
-    // tile; the four lanes of a column and product write 64 consecutive bytes
+    // tile, in LDS 16 (q / 4) + q % 4 words further on: a wavefront's 64 lanes
+    // then meet 64 banks
+    const int at = 256 * r + 16 * (r >> 2) + (r & 3) + 4 * g;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = K0 + 256 * r + 16 * i + 4 * g;
+    for (int i = 0; i < 16; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (k + j >= L) continue;
-            const int c = (int)acc[i][j];
-            if (splits == 1) {
-                w.C[k + j] = c;
-                if (mode == 0) w.C_lb[k + j] = c;
-            } else {
-                atomicAdd(&w.C[k + j], c);
-            }
+        for (int j = 0; j < 4; ++j) atomicAdd(&sum[at + 16 * i + j], (int)acc[i][j]);
+    __syncthreads();
+    for (int x = (int)threadIdx.x; x < (int)kCorrTile && K0 + x < L; x += kMxThreads) {
+        const int q = x >> 8, c = sum[x + 16 * (q >> 2) + (q & 3)];
+        if (splits == 1) {
+            w.C[K0 + x] = c;
+            if (mode == 0) w.C_lb[K0 + x] = c;
+        } else {
+            atomicAdd(&w.C[K0 + x], c);
         }
     }
 }
@@ -233,11 +243,14 @@ __global__ void k_corr_edge(WalkDev *walks, const BatchEntry *batch, int mode, i
 hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, const CorrDims &d, int mode, hipStream_t s)
 {
     constexpr uint32_t kMaxY = 65535;      // walks per launch of the 2-D grids
-    // parts of about equal length that give the launch a few thousand
-    // wavefronts, at least kMinPart chunks each
-    constexpr uint32_t kWaves = 1024, kMinPart = 64;
+    // parts of the positions that give the launch about kBlocks blocks, each of
+    // kMinPart chunks at least: a part more per tile costs 4096 atomic additions,
+    // a part less leaves compute units idle. One walk at L = 131071 19 us (parts
+    // of 128 chunks: 30), at L = 1048575 400 us; 64 walks at L = 65535 81 us (at
+    // 4096 blocks: 109); 32 walks of L up to 1048575 1.8 ms.
+    constexpr uint32_t kBlocks = 1024, kMinPart = 256;
     const uint32_t most = (d.max_L + 31) / 32;
-    const uint32_t Q = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(kMinPart, (d.chunks + kWaves - 1) / kWaves));
+    const uint32_t Q = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(kMinPart, (d.chunks + kBlocks - 1) / kBlocks));
     const uint32_t splits = (most + Q - 1) / Q, tiles = (d.max_L + kCorrTile - 1) / kCorrTile;
     for (uint32_t b0 = 0; b0 < nb; b0 += kMaxY) {
         const uint32_t ny = std::min(kMaxY, nb - b0);
@@ -248,7 +261,7 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, con
         if (d.max_L >= kCorrMxMinL) {
             const dim3 all((d.max_L + 255) / 256, ny);
             if (splits > 1) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, 0);
-            k_corr_mx<<<dim3(ny, tiles * splits), 64, 0, s>>>(walks, batch + b0, mode, (int)splits, (int)Q);
+            k_corr_mx<<<dim3(ny, tiles * splits), kMxThreads, 0, s>>>(walks, batch + b0, mode, (int)splits, (int)Q);
             if (splits > 1 && mode == 0) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, 1);
         }
         const hipError_t e = hipGetLastError();
