@@ -11,6 +11,7 @@
 #include "psl_dev_util.h"
 #include "psl_device.h"
 #include "psl_launch.h"
+#include "psl_select.h"
 
 #include <algorithm>
 #include <climits>
@@ -504,6 +505,38 @@ void k_eval_strided(const WalkDev *__restrict__ walks, const BatchEntry *__restr
     }
 }
 
+// The combine of a step of matrix walks, with the table evaluation of a walk that
+// the matrix path does not take in it: before the combine a block evaluates the
+// 256-candidate tiles that its candidates lie in (blocks that share a tile all
+// do, and store the same values). Steps where it has to are rare (a near-peak
+// list that overflows), and what they cost beyond k_eval_strided's is a walk's
+// blocks being at most 256; a launch that looks and returns costs every step
+// 3 to 4 us of about 40 (one walk at L = 16383).
+__global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, const BatchEntry *batch, Tables tabs, int G,
+                                                               uint32_t *pend, uint32_t *done, double margin)
+{
+    __shared__ union Lds {
+        EvalLds<4> eval;
+        CombLds comb;
+        __device__ Lds() {}
+    } sh;
+    const BatchEntry be = batch[blockIdx.y];
+    WalkDev &w = walks[be.slot];
+    if (!be.ss->use) {
+        uint32_t lo, hi;
+        comb_range(be.fixed ? be.n_lmt : w.n_lmt, gridDim.x, (uint32_t)G, blockIdx.x, lo, hi);
+        for (uint32_t t = lo / 256; t * 256 < hi; ++t)
+            for (uint32_t ks = 0; ks < be.ksplit; ++ks) {
+                int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
+                asm volatile("" : "+v"(tid));
+                __builtin_assume(tid >= 0 && tid < 256);
+                eval_item<4, true>(sh.eval, walks, batch, EvalItem{blockIdx.y, t, ks, 0}, tabs, tid);
+                __syncthreads();                // the next item, or the combine, takes the LDS
+            }
+    }
+    combine_block(sh.comb, w, be, tabs, G, 1, 0, nullptr, pend, done, margin, 0);
+}
+
 __global__ void k_queue_reset(EvalQueues *queues)
 {
     if (threadIdx.x < 8) queues->next[threadIdx.x] = 0;
@@ -524,6 +557,19 @@ static void launch_eval_waves(const WalkDev *walks, const BatchEntry *batch, con
         k_eval_strided<WAVES><<<std::min(n_items, (WAVES == 4 ? 6u : WAVES == 8 ? 3u : 2u) * n_cu), 64 * WAVES, 0, s>>>(walks, batch, items, n_items, tabs, tab);
     else
         k_eval<WAVES><<<n_items, 64 * WAVES, 0, s>>>(walks, batch, items, tabs);
+}
+
+bool select_takes_left(uint32_t nb, uint32_t comb_blocks) { return comb_small(nb, comb_blocks); }
+
+hipError_t launch_select_left(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
+                              uint32_t comb_group, const Tables &tabs, uint32_t *pend, uint32_t *done, double margin,
+                              hipStream_t s)
+{
+    if (comb_blocks < 1 || comb_blocks > kCombMaxBlocks || !comb_small(nb, comb_blocks) || !done) return hipErrorInvalidValue;
+    if (comb_group < 1 || comb_group > 64 || (comb_group & (comb_group - 1))) return hipErrorInvalidValue;
+    if (nb == 0) return hipSuccess;
+    k_combine_left<<<dim3(comb_blocks, nb), kCombThreads, 0, s>>>(walks, batch, tabs, (int)comb_group, pend, done, margin);
+    return hipGetLastError();
 }
 
 hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items,

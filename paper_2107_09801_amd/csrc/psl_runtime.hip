@@ -809,9 +809,14 @@ psl_status launch_partials(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs
 psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, uint32_t n, bool timed)
 {
     psl_status st;
-    if ((st = launch_partials(ctx, pl, tabs, n, pl.d_pend, timed, EvalCall{}, true))) return st;
-    HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
-                               pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
+    const bool left = pl.split && pl.all_split && select_takes_left(n, pl.comb_blocks);
+    if ((st = launch_partials(ctx, pl, tabs, n, pl.d_pend, timed, EvalCall{}, !left))) return st;
+    if (left)
+        HIP_TRY(ctx, launch_select_left(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, pl.d_pend,
+                                        pl.d_done, ctx->amb_margin, ctx->stream));
+    else
+        HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
+                                   pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
     HIP_TRY(ctx, launch_apply(ctx->d_walks, pl.d_batch, pl.seg, tabs, -1, pl.d_done, ctx->stream));
     if (pl.big_flips) {
         HIP_TRY(ctx, launch_corr(ctx->d_walks, pl.d_batch, n, pl.corr, 1, ctx->stream));

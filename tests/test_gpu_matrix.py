@@ -91,3 +91,25 @@ def test_limited_neighbourhoods_one_after_another(ctx, L):
             ctx.set_option(libpsl.OPT_NEAR_LIMIT, -1)
         assert np.array_equal(P, Pt) and np.max(np.abs(F - Ft) / Ft) <= 1e-13, (start, n)
     ctx.free_walks([w])
+
+
+@pytest.mark.parametrize("L,n_lmt", [(521, 521), (1021, 700), (4097, 4097), (16383, 6912), (40009, 513)])
+def test_steps_left_to_the_table_evaluation(ctx, L, n_lmt):
+    """Steps of one walk and of three whose near-peak lists are cut off: each is
+    evaluated by its combine blocks and makes the same moves."""
+    from paper_2107_09801_amd import libpsl
+    for n in (1, 3):
+        states = []
+        for limit in (-1, 1):
+            ids = ctx.init_walks(L, n, 11, alpha1=4, alpha2=10, n_lmt=n_lmt, switch_period=3)
+            ctx.set_option(libpsl.OPT_NEAR_LIMIT, limit)
+            try:
+                ctx.step_batch(ids, 7)
+                states.append([ctx.read_walk(w) for w in ids])
+            finally:
+                ctx.set_option(libpsl.OPT_NEAR_LIMIT, -1)
+            ctx.free_walks(ids)
+        for a, b in zip(*states):
+            assert all(np.array_equal(a[k], b[k]) for k in ("pivot", "best", "C", "t", "alpha", "psl_pivot", "psl_best",
+                                                            "last_k", "unimproved"))
+            assert abs(a["value_local"] - b["value_local"]) <= 1e-13 * b["value_local"]
