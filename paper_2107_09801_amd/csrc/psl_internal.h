@@ -102,8 +102,9 @@ struct BatchPlan {
     BatchEntry *d_batch = nullptr;
     EvalItem *d_items = nullptr;
     bool carved = false;              // arrays carved from caller memory: not freed here
-    hipGraph_t graph = nullptr;       // one captured step of this plan
+    hipGraph_t graph = nullptr;       // gsteps captured steps of this plan
     hipGraphExec_t gexec = nullptr;
+    uint32_t gsteps = 0;
     double *d_fpart = nullptr, *d_f = nullptr, *d_s0 = nullptr;
     uint32_t *d_mpart = nullptr, *d_m0 = nullptr, *d_near = nullptr;
     int32_t *d_p = nullptr;
