@@ -45,6 +45,15 @@ __device__ __forceinline__ void sel_merge(double &f, int32_t &p, uint32_t &i, do
     }
 }
 
+// The wavefront's smallest F, and its first smallest PSL (PSLs are not negative).
+__device__ __forceinline__ void sel_wave(double &f, int32_t &p, uint32_t &i)
+{
+    f = wave_least(f);
+    const uint64_t v = wave_least(((uint64_t)(uint32_t)p << 32) | i);
+    p = (int32_t)(v >> 32);
+    i = (uint32_t)v;
+}
+
 // The scan of Algorithm 1 over the combined F and PSL of one walk (batch
 // position bi), its ambiguity flags and, pure == 0, the rest of the iteration
 // but for the C update, by a block of NT threads.
@@ -76,7 +85,10 @@ __device__ __forceinline__ void sel_merge(double &f, int32_t &p, uint32_t &i, do
 //
 // Everything is latency here: the walk's fields are read at the start, and what
 // the parts hand on stays in LDS (through global memory, one after the other,
-// the same work took 5 us more of a single walk's step).
+// the same work took 5 us more of a single walk's step). Minima go through lane
+// permutations. Of the 13.7 us of a combine with its selection at L = 16383 (14.9
+// with butterflies through LDS and the prefix sums loaded after the lanes' sums)
+// the candidates take 4, the blocks' count with its release 2, the selection 4.
 struct FinishLds {
     SelPart w[16];
     uint64_t near[16];
@@ -116,15 +128,13 @@ __device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const Bat
     const uint32_t L = w.L;
     const double vl = w.value_local;
     const int32_t psl_best = w.psl_best;
+    const uint32_t unimproved0 = w.unimproved, ls_lmt = w.ls_lmt, period = w.switch_period;
+    const uint64_t step = w.t;
+    const uint32_t trace_cap = w.trace_cap, alpha = w.alpha;
     const double my_f = fmin;           // this thread's combine block minimum
     // block minima: within each wavefront, then across the wavefronts (the
     // minimum F and the first minimum (PSL, index) do not depend on the order)
-    for (int o = 32; o > 0; o >>= 1) {
-        const double of = __shfl_xor(fmin, o);
-        const int32_t op = __shfl_xor(pmin, o);
-        const uint32_t oi = (uint32_t)__shfl_xor((int)ipmin, o);
-        sel_merge(fmin, pmin, ipmin, of, op, oi);
-    }
+    sel_wave(fmin, pmin, ipmin);
     if (lane == 0) sh.w[wave] = SelPart{fmin, pmin, ipmin};
     __syncthreads();
     SelPart r = sh.w[0];
@@ -171,7 +181,7 @@ __device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const Bat
         }
     }
     uint32_t ib = ifirst;
-    for (int o = 32; o > 0; o >>= 1) ib = min(ib, (uint32_t)__shfl_xor((int)ib, o));
+    ib = (uint32_t)wave_least((uint64_t)ib);
     hit = __any(hit);
     if (lane == 0) {
         sh.first[wave] = ib;
@@ -227,7 +237,7 @@ __device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const Bat
             }
             if (hit) fl |= STEP_AMBIG_ARGMIN;
             if ((Fb - elo < band && elo - Fb < band) || (Fb - ehi < band && ehi - Fb < band)) fl |= STEP_AMBIG_COMPARE;
-            uint32_t unimproved = w.unimproved;
+            uint32_t unimproved = unimproved0;
             int sw = 0;
             if (fl & STEP_IMPROVED) {
                 sh.improved = 1;
@@ -235,9 +245,9 @@ __device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const Bat
                 w.value_local = Fb;
             } else if (fl & STEP_WORSE) {
                 unimproved += 1;
-                if (w.switch_period == 0 && unimproved > w.ls_lmt) sw = 1;
+                if (period == 0 && unimproved > ls_lmt) sw = 1;
             }
-            if (w.switch_period > 0 && ((w.t + 1u) % w.switch_period) == 0) sw = 1;
+            if (period > 0 && ((step + 1u) % period) == 0) sw = 1;
             if (sw) fl |= STEP_SWITCHED;
             w.unimproved = unimproved;
             w.start = start;
@@ -251,19 +261,19 @@ __device__ __forceinline__ void finish_walk(FinishLds &sh, WalkDev &w, const Bat
             w.F_pivot = Fb;
             w.psl_pivot = Pb;
             w.flags = fl;
-            if (w.trace_cap) {
+            if (trace_cap) {
                 TraceEntry e;
-                e.t = w.t;
+                e.t = step;
                 e.start = start;
                 e.k = kb;
                 e.value_step = Fb;
                 e.psl_k = Pb;
                 e.psl_best = best;
-                e.alpha = sw ? (w.alpha == w.alpha1 ? w.alpha2 : w.alpha1) : w.alpha;
+                e.alpha = sw ? (alpha == w.alpha1 ? w.alpha2 : w.alpha1) : alpha;
                 e.flags = fl;
-                w.trace[w.t % w.trace_cap] = e;
+                w.trace[step % trace_cap] = e;
             }
-            w.t += 1;
+            w.t = step + 1;
             sh.sw = sw;
             sh.kb = kb;
             sh.jp = jp;
@@ -379,9 +389,21 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
         const uint32_t i = i0 + ci;
         double f = 0.0;
         uint32_t m = 0;
+        double pv[5] = {}, po[5] = {};      // lane 0 of a group: the prefix sums of F_j
         if (split) {
             if (i < hi) {
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
+                if (g == 0) {
+                    // F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
+                    //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
+                    const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
+                    const int p1 = get_bit(w.pivot, j) ? 1 : 0;
+                    split_prefix(be, L, 2, mj, pv[0], po[0]);
+                    split_prefix(be, L, p1, Mj, pv[1], po[1]);
+                    split_prefix(be, L, p1, mj, pv[2], po[2]);
+                    split_prefix(be, L, 2, L - 1, pv[3], po[3]);
+                    split_prefix(be, L, 2, Mj, pv[4], po[4]);
+                }
                 for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
                 m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
                               (uint32_t)G);
@@ -439,27 +461,15 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
             // high word of T(PSL), which is at least hi32(T(1)) = 0x3FF00000
             // because |C'_{L-1}| = 1 for every sequence
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
-            if (split) {
-                // F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
-                //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
-                const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
-                const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
-                const int p1 = get_bit(w.pivot, j) ? 1 : 0;
-                f = split_prefix(be, L, 2, mj) + (split_prefix(be, L, p1, Mj) - split_prefix(be, L, p1, mj)) +
-                    (split_prefix(be, L, 2, L - 1) - split_prefix(be, L, 2, Mj)) + U * f;
-            }
+            if (split)
+                f = (pv[0] + po[0]) + ((pv[1] + po[1]) - (pv[2] + po[2])) + ((pv[3] + po[3]) - (pv[4] + po[4])) + U * f;
             be.F[i] = f;
             be.P[i] = p;
             fmin = f < fmin ? f : fmin;
             if (p < pmin) { pmin = p; ipmin = i; }
         }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        const double of = __shfl_xor(fmin, o);
-        const int32_t op = __shfl_xor(pmin, o);
-        const uint32_t oi = (uint32_t)__shfl_xor((int)ipmin, o);
-        sel_merge(fmin, pmin, ipmin, of, op, oi);
-    }
+    sel_wave(fmin, pmin, ipmin);
     if (lane == 0) sh.r[wave] = SelPart{fmin, pmin, ipmin};
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -115,9 +115,7 @@ struct PrepLds {
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_add(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
-    return v + __hiloint2double(hi, lo);
+    return v + __longlong_as_double((long long)dpp_mov<CTRL, ROWS>(0, (uint64_t)__double_as_longlong(v)));
 }
 // Inclusive scan of v over the wavefront: within rows of 16 lanes by row shifts,
 // then the rows before (row_bcast:15 into rows 1 and 3, row_bcast:31 into 2 and 3).
