@@ -534,7 +534,7 @@ __global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, c
                 __syncthreads();                // the next item, or the combine, takes the LDS
             }
     }
-    combine_block(sh.comb, w, be, tabs, G, 1, 0, nullptr, pend, done, margin, 0);
+    combine_block<true>(sh.comb, w, be, tabs, G, 0, nullptr, pend, done, margin, 0);
 }
 
 __global__ void k_queue_reset(EvalQueues *queues)

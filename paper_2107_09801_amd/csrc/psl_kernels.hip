@@ -387,13 +387,14 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(const WalkDev *wal
 
 // ------------------------------------------------------- selection
 
+template <bool TAIL>
 __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const BatchEntry *batch, Tables tabs,
-                                                          int G, int tail, int pure, ChoiceDev *out, uint32_t *pend,
+                                                          int G, int pure, ChoiceDev *out, uint32_t *pend,
                                                           uint32_t *done, double margin, uint32_t b0)
 {
     __shared__ CombLds sh;
     const BatchEntry be = batch[blockIdx.y];
-    combine_block(sh, walks[be.slot], be, tabs, G, tail, pure, out, pend, done, margin, b0);
+    combine_block<TAIL>(sh, walks[be.slot], be, tabs, G, pure, out, pend, done, margin, b0);
 }
 
 // The selection of a walk, its ambiguity flags and (pure == 0) its
@@ -672,8 +673,8 @@ hipError_t launch_select(WalkDev *walks, const BatchEntry *batch, uint32_t nb, u
     // device-scope release of the fused form costs more than the launches
     const int tail = comb_blocks == 1 || (comb_small(nb, comb_blocks) && done) ? 1 : 0;
     for (uint32_t b0 = 0; b0 < nb; b0 += kMaxGridY) {
-        k_combine<<<dim3(comb_blocks, std::min(kMaxGridY, nb - b0)), kCombThreads, 0, s>>>(
-            walks, batch + b0, tabs, (int)comb_group, tail, pure, (ChoiceDev *)out, pend, done, margin, b0);
+        (tail ? k_combine<true> : k_combine<false>)<<<dim3(comb_blocks, std::min(kMaxGridY, nb - b0)), kCombThreads, 0, s>>>(
+            walks, batch + b0, tabs, (int)comb_group, pure, (ChoiceDev *)out, pend, done, margin, b0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

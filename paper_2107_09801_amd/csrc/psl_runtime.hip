@@ -374,7 +374,10 @@ static size_t dig_bytes(uint32_t L)
 static uint32_t mx_splits(uint32_t chunks, uint64_t tiles)
 {
     const double s = std::sqrt(12.0 * (double)chunks / (double)tiles);
-    return (uint32_t)std::max(1l, std::min(std::lround(s), (long)(chunks / kMxMinChunks)));
+    // with two splits no item has more than 0.6 of a tile's coefficients (629000
+    // of the longest walk's; sums over 699050 are exact)
+    const long least = chunks > 16384 ? 2 : 1;
+    return (uint32_t)std::max(least, std::min(std::lround(s), (long)(chunks / kMxMinChunks)));
 }
 
 // The matrix path's k-splits per walk (0: none) and items in launch order.

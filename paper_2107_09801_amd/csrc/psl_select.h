@@ -349,7 +349,7 @@ __device__ __forceinline__ uint32_t near_peak(const uint32_t *__restrict__ list,
 // consecutive partials of each of 64 / cpb splits; the sums go through a
 // butterfly over the wavefront's split lanes, then the four wavefronts' sums
 // are added in wavefront order.
-// With tail != 0 the walk's last block to finish then makes its selection
+// With TAIL the walk's last block to finish then makes its selection
 // (finish_walk); b0 = the batch position of
 // blockIdx.y = 0; done holds one zeroed counter per batch position.
 struct CombLds {
@@ -359,8 +359,9 @@ struct CombLds {
     uint32_t last;
     FinishLds fin;
 };
+template <bool TAIL>
 __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const BatchEntry &be, const Tables &tabs, int G,
-                                              int tail, int pure, ChoiceDev *out, uint32_t *pend, uint32_t *done,
+                                              int pure, ChoiceDev *out, uint32_t *pend, uint32_t *done,
                                               double margin, uint32_t b0)
 {
     const uint32_t n = be.fixed ? be.n_lmt : w.n_lmt;
@@ -389,21 +390,27 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
         const uint32_t i = i0 + ci;
         double f = 0.0;
         uint32_t m = 0;
-        double pv[5] = {}, po[5] = {};      // lane 0 of a group: the prefix sums of F_j
+        // the prefix sums of F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|)
+        // + sum_{k>M} T(|C_k|) + U (matrix sums), m = min(j, L-1-j),
+        // M = max(j, L-1-j), -2 for s_j = +1; lane 0 of a group has them. In small
+        // launches they are loaded first, beside the other lanes' loads; in large
+        // ones last, for fewer registers (1024 walks at L = 131071: 2.6 ms per
+        // step, loaded first 2.9)
+        double pv[5] = {}, po[5] = {};
+        auto prefixes = [&]() {
+            const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
+            const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
+            const int p1 = get_bit(w.pivot, j) ? 1 : 0;
+            split_prefix(be, L, 2, mj, pv[0], po[0]);
+            split_prefix(be, L, p1, Mj, pv[1], po[1]);
+            split_prefix(be, L, p1, mj, pv[2], po[2]);
+            split_prefix(be, L, 2, L - 1, pv[3], po[3]);
+            split_prefix(be, L, 2, Mj, pv[4], po[4]);
+        };
         if (split) {
             if (i < hi) {
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
-                if (g == 0) {
-                    // F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|) + sum_{k>M} T(|C_k|)
-                    //       + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for s_j = +1
-                    const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
-                    const int p1 = get_bit(w.pivot, j) ? 1 : 0;
-                    split_prefix(be, L, 2, mj, pv[0], po[0]);
-                    split_prefix(be, L, p1, Mj, pv[1], po[1]);
-                    split_prefix(be, L, p1, mj, pv[2], po[2]);
-                    split_prefix(be, L, 2, L - 1, pv[3], po[3]);
-                    split_prefix(be, L, 2, Mj, pv[4], po[4]);
-                }
+                if (TAIL && g == 0) prefixes();
                 for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
                 m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
                               (uint32_t)G);
@@ -461,8 +468,10 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
             // high word of T(PSL), which is at least hi32(T(1)) = 0x3FF00000
             // because |C'_{L-1}| = 1 for every sequence
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
-            if (split)
+            if (split) {
+                if (!TAIL) prefixes();
                 f = (pv[0] + po[0]) + ((pv[1] + po[1]) - (pv[2] + po[2])) + ((pv[3] + po[3]) - (pv[4] + po[4])) + U * f;
+            }
             be.F[i] = f;
             be.P[i] = p;
             fmin = f < fmin ? f : fmin;
@@ -477,8 +486,8 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
         for (int x = 1; x < kCombThreads / 64; ++x) sel_merge(r.f, r.p, r.i, sh.r[x].f, sh.r[x].p, sh.r[x].i);
         be.red[blockIdx.x] = r;
     }
-    if (!tail) return;
-    // tail != 0: the walk's last block to finish (counted in done[bi], which
+    if (!TAIL) return;
+    // TAIL: the walk's last block to finish (counted in done[bi], which
     // it returns to 0 for the next launch) makes the selection and sets the
     // ambiguity flags. Each block's count is a device-scope release of its F,
     // P and minimum, and the last block acquires them all.

@@ -38,23 +38,23 @@ __device__ __forceinline__ double split_scale(const double *__restrict__ T, int 
 }
 
 // The digits of one coefficient as FP6 codes, four per word (digit 4q + i in
-// byte i of out[q]; digits 14 and 15 are 0). v = coefficient / U in three
-// 30-bit words of six digits; adding 16 to every 5-bit field (kBias) turns
-// the balanced digits d in -16..15 into plain fields d + 16. The FP6 (E2M3)
-// code of n/8, n = 0..16, is n; of n/4 it is n + min(n, 8); 0x20 is the sign.
-// Odd shifts meet 1.0 in the FP4 matrix and take d/8, even ones 0.5 and d/4.
+// byte i of out[q]; digits 14 and 15 are 0). v (below 2^68) in three 30-bit words
+// of six digits; adding 16 to every 5-bit field (kBias) turns the balanced digits
+// d in -16..15 into plain fields d + 16. The FP6 (E2M3) code of n/8, n = 0..16, is
+// n; 0x20 is the sign. Odd shifts meet 1.0 in the FP4 matrix and v is their
+// coefficient / U; even ones meet 0.5 and v is twice that. A shift's product is
+// then at most 2 or 1 in size and a multiple of 1/16: sums over 699050 successive
+// coefficients are exact in FP32, and no item has more (mx_splits).
 constexpr int kBias = 0x21084210;
 
-__device__ __forceinline__ uint32_t digit_codes(uint32_t v, bool even)
+__device__ __forceinline__ uint32_t digit_codes(uint32_t v)
 {
-    const uint32_t neg = ~(v >> 4) & 0x01010101u;                   // d < 0
+    const uint32_t neg = ~(v >> 4) & 0x01010101u;                          // d < 0
     const uint32_t mag = ((v ^ ((neg << 4) - neg)) & 0x0F0F0F0Fu) + neg;   // |d|
-    const uint32_t big = ((mag >> 3) | (mag >> 4)) & 0x01010101u;   // |d| >= 8
-    const uint32_t dbl = mag + ((mag & ~((big << 5) - big)) | (big << 3));
-    return (even ? dbl : mag) | (neg << 5);
+    return mag | (neg << 5);
 }
 
-__device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out)[4])
+__device__ __forceinline__ void split_digits(double v, uint32_t (&out)[4])
 {
     const double h2 = rint(v * 0x1p-60);
     const double r1 = fma(h2, -0x1p60, v);
@@ -71,7 +71,7 @@ __device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out
     out[2] = ((b >> 10) & 31u) | ((b >> 7) & 0x1F00u) | ((b >> 4) & 0x1F0000u) | ((b >> 1) & 0x1F000000u);
     out[3] = (c & 31u) | ((c << 3) & 0x1F00u) | 0x10100000u;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) out[q] = digit_codes(out[q], even);
+    for (int q = 0; q < 4; ++q) out[q] = digit_codes(out[q]);
 }
 
 // The step's preparation of a matrix walk, one block per segment of its shifts
@@ -97,10 +97,10 @@ __device__ __forceinline__ void split_digits(double v, bool even, uint32_t (&out
 // stay in their threads until the next such tile. The next tile's C is loaded
 // while a tile's digits are made, and the scans go through lane permutations of
 // the vector units instead of LDS. Bound by vector issue, mostly the digits
-// (about 100 operations per coefficient), and by the writes: 64 walks at
-// L = 131071, N_lmt = 6912, 184 -> 129 us (their 220 MB take 45 us), full
-// neighbourhoods at 1024 walks 3.10 -> 2.86 ms (7 GB), one walk at L = 16383
-// 7.2 -> 6.2 us.
+// (about 75 operations per coefficient; 100 with codes of n/4 for even shifts in
+// place of twice the coefficient), and by the writes: 64 walks at L = 131071,
+// N_lmt = 6912, 184 -> 115 us (their 220 MB take 45 us), full neighbourhoods at
+// 1024 walks 3.10 -> 2.77 ms (7 GB), one walk at L = 16383 7.2 -> 5.7 us.
 constexpr int kPrepThreads = 256;
 constexpr int kPrepStride = 36;         // words per chunk and four columns in LDS (32 and padding)
 
@@ -141,7 +141,8 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
 {
     const int L = (int)w.L;
     const int j0 = (int)((start + 1u) % (uint32_t)L);
-    const double inv = 1.0 / split_scale(T, w.psl_pivot);      // exact: U is a power of two
+    // exact: U is a power of two; twice the even shifts' coefficients (split_digits)
+    const double inv = (threadIdx.x & 1 ? 1.0 : 2.0) / split_scale(T, w.psl_pivot);
     const int cut = w.psl_pivot - 8;                           // the near-peak cut
     const int nbo = (int)split_both_chunks((uint32_t)L), nco = (int)split_chunks((uint32_t)L);
     const int k_end = seg + 1 == (int)seg_count((uint32_t)L, (uint32_t)shift) ? 32 * nco : (seg + 1) << shift;
@@ -179,14 +180,14 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
             }
         }
         uint32_t d[4];
-        split_digits(in ? (tp2 - tm2) * inv : 0.0, !(t & 1), d);
+        split_digits(in ? (tp2 - tm2) * inv : 0.0, d);
 #pragma unroll
         for (int q = 0; q < 4; ++q) sh.codes[2][q][slot] = d[q];
         if (both) {
-            split_digits(in ? (tm4 - t0) * inv : 0.0, !(t & 1), d);
+            split_digits(in ? (tm4 - t0) * inv : 0.0, d);
 #pragma unroll
             for (int q = 0; q < 4; ++q) sh.codes[0][q][slot] = d[q];
-            split_digits(in ? (tp4 - tm4) * inv : 0.0, !(t & 1), d);
+            split_digits(in ? (tp4 - tm4) * inv : 0.0, d);
 #pragma unroll
             for (int q = 0; q < 4; ++q) sh.codes[1][q][slot] = d[q];
         }
@@ -388,8 +389,7 @@ hipError_t launch_prep(const WalkDev *walks, BatchEntry *batch, uint32_t nb, con
 // combine takes T(c+2) as their constant part), and the both-neighbour chunks
 // add XNOR (which s_j does not change) and AND of the bits times s_j: with the
 // XNOR word masked, the AND word is one more operation. Both go into the same
-// accumulators: |digit| <= 16 over at most L-1 shifts, one coefficient each,
-// stays within 2^24 units of 1/8, exact in FP32. The digits and the sequence's
+// accumulators, which stay exact (split_digits). The digits and the sequence's
 // words are loaded steps ahead, into rings: two wavefronts per SIMD (what the
 // 64 accumulators and the windows leave) do not hide a load's latency.
 //
