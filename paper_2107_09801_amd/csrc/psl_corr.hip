@@ -15,8 +15,9 @@
 // matrices. Sums stay integers below 2^24, exact in FP32.
 //
 // What bounds it: a step is 16 products of 16 x 16 x 128 (16 cycles each) and
-// about 30 vector instructions (4 cycles each, products included): away from
-// the sequence's ends the matrices need no masks, which took 30 more. One XOR
+// about 40 vector instructions (4 cycles each): away from the sequence's ends the
+// matrices need no masks, which took 30 more. 1024 walks at L = 131071 take 3.7
+// ms, 14 ns per product and SIMD; alone, a product takes 7 to 10. One XOR
 // and popcount per 32 products, the form that short sequences keep, is bound by
 // vector issue.
 #include "psl_dev_util.h"
@@ -112,24 +113,26 @@ __device__ __forceinline__ void pm1_nibbles(uint32_t x, uint32_t (&o)[4])
     o[3] = (x & kS) | kV;
 }
 
-// Block (x, y): walk x of the batch, tile y / splits, positions' part y % splits
-// (Q chunks each): the longest tiles of all walks start first. (With a walk's
-// tiles side by side, their falling lengths fell in step with the XCDs and SIMDs
-// that blocks are dealt to, and a third of the SIMDs ran dry.) Four wavefronts
-// take a quarter of the chunks each and add their sums in LDS: with a part per
-// wavefront, added into C one by one, 64 walks at L = 65535 took 133 us (now 81)
-// and the 32 walks of a serving wave 4.0 ms (1.8). One part: C (and C_lb in mode
-// 0) is stored; several: added into C, which is zero.
+// Block (x, y): tile y % tiles, positions' part y / tiles (Q chunks each) of walk
+// (x + y) % walks: the longest parts of all walks start first, and the blocks of
+// a walk and of a tile are dealt to all XCDs. (In steps of 8 one XCD got the first
+// parts of every tile, the only ones that short tiles have, or all blocks of a
+// walk: one walk at L = 1048575 398 us, now 257; 32 walks of a serving wave 5.0
+// ms, now 1.5.) Four wavefronts take a quarter of the chunks each and add their
+// sums in LDS: with a part per wavefront, added into C one by one, 64 walks at
+// L = 65535 took 133 us (now 80). One part: C (and C_lb in mode 0) is stored;
+// several: added into C, which is zero.
 __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_corr_mx(
     WalkDev *walks, const BatchEntry *batch, int mode, int splits, int Q)
 {
-    WalkDev &w = walks[batch[blockIdx.x].slot];
+    WalkDev &w = walks[batch[(blockIdx.x + blockIdx.y) % gridDim.x].slot];
     if (!corr_takes(w, mode)) return;
     const int L = (int)w.L;
-    const int K0 = (int)kCorrTile * ((int)blockIdx.y / splits);
+    const int tiles = (int)(gridDim.y / (uint32_t)splits);
+    const int K0 = (int)kCorrTile * ((int)blockIdx.y % tiles);
     if (K0 >= L || L < (int)kCorrMxMinL) return;
     // the block's chunks (those with a position i below L - K0), a quarter for each wavefront
-    const int p0 = Q * ((int)blockIdx.y % splits), p1 = min(p0 + Q, (L - K0 + 31) >> 5);
+    const int p0 = Q * ((int)blockIdx.y / tiles), p1 = min(p0 + Q, (L - K0 + 31) >> 5);
     if (p0 >= p1) return;
     __shared__ int sum[kCorrTile + 64];
     for (int x = (int)threadIdx.x; x < (int)kCorrTile + 64; x += kMxThreads) sum[x] = 0;
@@ -245,9 +248,10 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, con
     constexpr uint32_t kMaxY = 65535;      // walks per launch of the 2-D grids
     // parts of the positions that give the launch about kBlocks blocks, each of
     // kMinPart chunks at least: a part more per tile costs 4096 atomic additions,
-    // a part less leaves compute units idle. One walk at L = 131071 19 us (parts
-    // of 128 chunks: 30), at L = 1048575 400 us; 64 walks at L = 65535 81 us (at
-    // 4096 blocks: 109); 32 walks of L up to 1048575 1.8 ms.
+    // a part less leaves compute units idle. At 1024 / 2048 / 4096 blocks, us: one
+    // walk at L = 1048575 257 / 240 / 252, 64 at L = 65535 80 / 86 / 112, 32 of L
+    // up to 1048575 1520 / 1530 / 1530; parts of at least 512 chunks: one walk at
+    // L = 131071 21 for 19, at L = 9001 18 for 15.
     constexpr uint32_t kBlocks = 1024, kMinPart = 256;
     const uint32_t most = (d.max_L + 31) / 32;
     const uint32_t Q = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(kMinPart, (d.chunks + kBlocks - 1) / kBlocks));
