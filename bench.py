@@ -91,7 +91,7 @@ def counter_record(kind: str, tag: str, kernel: str = ""):
 
 
 def measured_traffic(tag: str, kernel: str = ""):
-    """HBM bytes per launch of an evaluation kernel (k_eval or k_lin; any when
+    """HBM bytes per launch of an evaluation kernel (k_eval or k_mx; any when
     empty) for workload `tag`, from the `traffic-record:` line (FETCH_SIZE and
     WRITE_SIZE, each scaled by what the counter reads for a copy of known
     size)."""

@@ -174,7 +174,7 @@ __device__ __forceinline__ double wave_least(double v)
     return __longlong_as_double((long long)last_lane(bits(v)));
 }
 
-// Prefix sum x (0 .. 2, BatchEntry::pre) of a matrix walk over the shifts
+// Prefix sum x (0 or 1, BatchEntry::pre) of a matrix walk over the shifts
 // 1 .. k, in two parts to add: the one within the segment, and the segment's offset.
 __device__ __forceinline__ void split_prefix(const BatchEntry &be, uint32_t L, int x, uint32_t k, double &in, double &off)
 {

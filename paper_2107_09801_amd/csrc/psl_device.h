@@ -105,7 +105,7 @@ struct BatchEntry {
     // matrix path (psl_split.hip): this step's coefficients of the walk
     uint8_t *dig_both;      // [split_both_chunks(L)][2] digit records of the XNOR and AND coefficients
     uint8_t *dig_one;       // [split_chunks(L)] digit records of the one-neighbour coefficient
-    double *pre;            // [3][L]: prefix sums over the segment's shifts up to k of T(|C_k-2|), T(|C_k+2|), T(|C_k|)
+    double *pre;            // [2][L]: prefix sums over the segment's shifts up to k of T(|C_k-+2|) - T(|C_k|)
     double *segoff;         // [segments][3]: their segments' totals, then offsets (SegMap segments)
     uint32_t seg_shift;     // log2 of a segment's shifts
     uint32_t pad;
@@ -127,8 +127,9 @@ constexpr uint32_t kMxNoWalk = 0xFFFFFFFFu;
 constexpr uint32_t kMxOffsets = 0xFFFFFFFFu;   // tile of the item that makes a walk's offsets
 struct SplitState {
     double U;               // the quantum, a power of two
-    uint32_t use;           // 1: this step evaluates the walk on the split path
+    uint32_t use;           // 1: this step evaluates the walk on the matrix path
     uint32_t pad;
+    double total;           // the sum of T(|C_k|) over all shifts
 };
 
 // Per combine block: the smallest F, and the smallest PSL with its first scan

@@ -117,7 +117,7 @@ struct BatchPlan {
     uint32_t *d_segmax = nullptr;     // per segment: maximum |C_k|
     SegMap seg{};
     // split evaluation (walks with BatchEntry.lsplit > 0)
-    bool split = false;               // some walk of the plan can take the split path
+    bool split = false;               // some walk of the plan can take the matrix path
     uint8_t *d_dig = nullptr;
     double *d_pre = nullptr, *d_lpart = nullptr;
     SplitState *d_ss = nullptr;

@@ -647,7 +647,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     for (uint32_t b = 0; b < n; ++b) {
         if (!lsp[b]) continue;
         n_dig += dig_bytes(Ls[b]);
-        n_pre += 3 * (size_t)Ls[b];
+        n_pre += 2 * (size_t)Ls[b];
         n_lp += (size_t)(lsp[b] + 1) * Ls[b];
     }
     pl.split = !mitems.empty();
@@ -705,7 +705,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
             e.lpart = pl.d_lpart + o_lp;
             e.ss = pl.d_ss + b;
             o_dig += dig_bytes(Ls[b]);
-            o_pre += 3 * (size_t)Ls[b];
+            o_pre += 2 * (size_t)Ls[b];
             o_lp += (size_t)(lsp[b] + 1) * Ls[b];
         }
         op += (size_t)ks[b] * n_l[b];

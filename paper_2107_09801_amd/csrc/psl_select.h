@@ -76,7 +76,7 @@ __device__ __forceinline__ void sel_wave(double &f, int32_t &p, uint32_t &i)
 // Bookkeeping: the move's bit, the three-way comparison with v_local, the
 // unimproved counter, the local best, and the phase switch (Rand_flip of the
 // local best and the exponent swap; the walk joins the batch's pending list,
-// whose C, F and PSL k_pending then rebuilds). The C update runs after it
+// whose C, F and PSL the C update then rebuilds). The C update runs after it
 // (k_apply), from bits that equal the pre-move pivot's at every position but j:
 // the pivot's, or on a switch the local best's (which are then the move's
 // pivot, if the move improved; if it did not, C is rebuilt from C of the local
@@ -376,7 +376,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
     // matrix path: F_j from the prefix sums and the matrix sums (psl_split.hip),
     // PSL_j from the near-peak shifts here
     const bool split = be.lsplit != 0 && be.ss->use != 0;
-    const double U = split ? be.ss->U : 0.0;
+    const double U = split ? be.ss->U : 0.0, total = split ? be.ss->total : 0.0;
     const uint32_t start = be.fixed ? be.start : step_start(w);
     const uint32_t L = w.L;
     const uint32_t n_near = split ? be.near[0] : 0;
@@ -390,22 +390,19 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
         const uint32_t i = i0 + ci;
         double f = 0.0;
         uint32_t m = 0;
-        // the prefix sums of F_j = sum_{k<=m} T(|C_k|) + sum_{m<k<=M} T(|C_k-+2|)
-        // + sum_{k>M} T(|C_k|) + U (matrix sums), m = min(j, L-1-j),
-        // M = max(j, L-1-j), -2 for s_j = +1; lane 0 of a group has them. In small
-        // launches they are loaded first, beside the other lanes' loads; in large
-        // ones last, for fewer registers (1024 walks at L = 131071: 2.6 ms per
-        // step, loaded first 2.9)
-        double pv[5] = {}, po[5] = {};
+        // the prefix sums of F_j = sum_k T(|C_k|) + sum_{m<k<=M} (T(|C_k-+2|) - T(|C_k|))
+        // + U (matrix sums), m = min(j, L-1-j), M = max(j, L-1-j), -2 for
+        // s_j = +1; lane 0 of a group has them. In small launches they are loaded
+        // first, beside the other lanes' loads; in large ones last, for fewer
+        // registers (1024 walks at L = 131071 with five values: 2.6 ms per step, loaded
+        // first 2.9; with these two 2.3)
+        double pv[2] = {}, po[2] = {};
         auto prefixes = [&]() {
             const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
             const uint32_t mj = min(j, L - 1 - j), Mj = max(j, L - 1 - j);
             const int p1 = get_bit(w.pivot, j) ? 1 : 0;
-            split_prefix(be, L, 2, mj, pv[0], po[0]);
-            split_prefix(be, L, p1, Mj, pv[1], po[1]);
-            split_prefix(be, L, p1, mj, pv[2], po[2]);
-            split_prefix(be, L, 2, L - 1, pv[3], po[3]);
-            split_prefix(be, L, 2, Mj, pv[4], po[4]);
+            split_prefix(be, L, p1, Mj, pv[0], po[0]);
+            split_prefix(be, L, p1, mj, pv[1], po[1]);
         };
         if (split) {
             if (i < hi) {
@@ -470,7 +467,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
             if (split) {
                 if (!TAIL) prefixes();
-                f = (pv[0] + po[0]) + ((pv[1] + po[1]) - (pv[2] + po[2])) + ((pv[3] + po[3]) - (pv[4] + po[4])) + U * f;
+                f = total + ((pv[0] + po[0]) - (pv[1] + po[1])) + U * f;
             }
             be.F[i] = f;
             be.P[i] = p;

@@ -77,8 +77,8 @@ __device__ __forceinline__ void split_digits(double v, uint32_t (&out)[4])
 // The step's preparation of a matrix walk, one block per segment of its shifts
 // (2^shift of them, in tiles of 256), in one pass over C: the near-peak list
 // (chunk_octs builds the same one), the digit records, and the prefix sums of
-// T(|C_k-2|), T(|C_k+2|), T(|C_k|) within the segment, whose totals k_mx's first
-// items turn into offsets (split_offsets). Blocks of the batch's other walks make
+// T(|C_k-2|) - T(|C_k|) and T(|C_k+2|) - T(|C_k|) within the segment; their totals,
+// and those of T(|C_k|), k_mx's first items turn into offsets (split_offsets). Blocks of the batch's other walks make
 // the chunk sums of the table evaluation (k_chunks).
 //
 // A record holds one 32-shift chunk (shifts 32c .. 32c+31) of one coefficient:
@@ -92,21 +92,22 @@ __device__ __forceinline__ void split_digits(double v, uint32_t (&out)[4])
 //
 // One pass instead of three (chunk sums, coefficients, a serial scan per walk
 // that took 0.94 ms of a step at L = 1048575 and 0.21 ms for 64 walks at
-// L = 131071). Prefixes, 24 of the 52 bytes written per shift, are scanned and
+// L = 131071). Prefixes, 16 of the 44 bytes written per shift, are scanned and
 // stored only in tiles that hold some candidate's m_j or M_j; the others' values
 // stay in their threads until the next such tile. The next tile's C is loaded
 // while a tile's digits are made, and the scans go through lane permutations of
 // the vector units instead of LDS. Bound by vector issue, mostly the digits
 // (about 75 operations per coefficient; 100 with codes of n/4 for even shifts in
 // place of twice the coefficient), and by the writes: 64 walks at L = 131071,
-// N_lmt = 6912, 184 -> 115 us (their 220 MB take 45 us), full neighbourhoods at
-// 1024 walks 3.10 -> 2.77 ms (7 GB), one walk at L = 16383 7.2 -> 5.7 us.
+// N_lmt = 6912, 184 -> 113 us (their 220 MB take 45 us), full neighbourhoods at
+// 1024 walks 3.10 -> 2.46 ms (5.9 GB take 1.2 ms), one walk at L = 16383
+// 7.2 -> 5.8 us.
 constexpr int kPrepThreads = 256;
 constexpr int kPrepStride = 36;         // words per chunk and four columns in LDS (32 and padding)
 
 struct PrepLds {
     __align__(16) uint32_t codes[3][4][8 * kPrepStride];
-    double tot[3][kPrepThreads / 64];   // the wavefronts' totals of a tile
+    double tot[2][kPrepThreads / 64];   // the wavefronts' totals of a tile
     double acc[3][kPrepThreads / 64];   // and of the tiles before it without stored prefixes
 };
 
@@ -158,10 +159,8 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
         const bool in = k >= 1 && k < L;
         const bool both = (k0 >> 5) < nbo;                     // some chunk of the tile has both-neighbour shifts
         const int kz = min(k0 + kPrepThreads, L) - 1;
-        // the tiles that the combine reads prefixes of: shifts m_j and M_j of a
-        // candidate, and L - 1
-        const bool want = kz == L - 1 || range_hits(L, j0, n_lmt, k0, kz) ||
-                          range_hits(L, j0, n_lmt, L - 1 - kz, L - 1 - k0);
+        // the tiles that the combine reads prefixes of: shifts m_j and M_j of a candidate
+        const bool want = range_hits(L, j0, n_lmt, k0, kz) || range_hits(L, j0, n_lmt, L - 1 - kz, L - 1 - k0);
         const int c = in ? next : 0;
         next = C[min(k + kPrepThreads, L - 1)];
         const int a0 = c < 0 ? -c : c;
@@ -191,20 +190,21 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
 #pragma unroll
             for (int q = 0; q < 4; ++q) sh.codes[1][q][slot] = d[q];
         }
-        double v[3] = {in ? tm2 : 0.0, in ? tp2 : 0.0, in ? t0 : 0.0};
+        double v[2] = {in ? tm2 - t0 : 0.0, in ? tp2 - t0 : 0.0};
+        acc[2] += in ? t0 : 0.0;
         if (!want) {
 #pragma unroll
-            for (int x = 0; x < 3; ++x) acc[x] += v[x];
+            for (int x = 0; x < 2; ++x) acc[x] += v[x];
             kept = true;
         } else {
 #pragma unroll
-            for (int x = 0; x < 3; ++x) {
+            for (int x = 0; x < 2; ++x) {
                 v[x] = wave_scan(v[x]);
                 if (lane == 63) sh.tot[x][wave] = v[x];
             }
             if (kept) {
 #pragma unroll
-                for (int x = 0; x < 3; ++x) {
+                for (int x = 0; x < 2; ++x) {
                     const double a = wave_scan(acc[x]);
                     if (lane == 63) sh.acc[x][wave] = a;
                 }
@@ -213,7 +213,7 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
         __syncthreads();
         if (want) {
 #pragma unroll
-            for (int x = 0; x < 3; ++x) {
+            for (int x = 0; x < 2; ++x) {
                 if (kept) {
                     for (int q = 0; q < kPrepThreads / 64; ++q) carry[x] += sh.acc[x][q];
                     acc[x] = 0.0;
@@ -260,17 +260,15 @@ __device__ __forceinline__ void prep_segment(PrepLds &sh, const WalkDev &w, cons
         }
         __syncthreads();                                   // the tile's codes and totals have been read
     }
-    if (kept) {
 #pragma unroll
-        for (int x = 0; x < 3; ++x) {
-            const double a = wave_scan(acc[x]);
-            if (lane == 63) sh.acc[x][wave] = a;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-            for (int q = 0; q < kPrepThreads / 64; ++q) carry[x] += sh.acc[x][q];
+    for (int x = 0; x < 3; ++x) {                          // acc is 0 where the last tile took it
+        const double a = wave_scan(acc[x]);
+        if (lane == 63) sh.acc[x][wave] = a;
     }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+        for (int q = 0; q < kPrepThreads / 64; ++q) carry[x] += sh.acc[x][q];
     if (t < 3) segtot[t] = t == 0 ? carry[0] : t == 1 ? carry[1] : carry[2];
 }
 
@@ -299,7 +297,8 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, Bat
 }
 
 // The segment totals of value array x of a matrix walk as the offsets of
-// its segments (the sum of the segments before; in place), by one wavefront:
+// its segments (the sum of the segments before; in place; of x = 2 the walk's
+// total), by one wavefront:
 // each lane the totals of a run of segments, carried with Neumaier's
 // compensation. With x = 0 also the step's scale and path choice: the matrix path is
 // taken when the near-peak list holds the PSL (sparse form) and the
@@ -318,12 +317,10 @@ __device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry
         const double flow = P > 4 ? T[P - 4] : 0.0;
         const bool exact_enough = (double)(L - 1) * U <= 1e-14 * (flow > 1.0 ? flow : 1.0);
         const bool sparse_psl = be.near[0] <= be.near_lim;
-        SplitState st;
-        st.U = U;
-        st.use = exact_enough && sparse_psl ? 1u : 0u;
-        st.pad = 0;
-        *be.ss = st;
-        if (!st.use) atomicAdd(tab, 1u);
+        const uint32_t use = exact_enough && sparse_psl ? 1u : 0u;
+        be.ss->U = U;
+        be.ss->use = use;
+        if (!use) atomicAdd(tab, 1u);
     }
     const int n = (int)seg_count((uint32_t)L, be.seg_shift);
     const int per = (n + 63) / 64, lo = lane * per, hi = min(n, lo + per);
@@ -338,6 +335,10 @@ __device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry
             nsum_add(s, c, os);
             c += oc;
         }
+    }
+    if (x == 2) {                       // T(|C_k|): the sum over all shifts
+        if (lane == 63) be.ss->total = s + c;
+        return;
     }
     double es = __shfl_up(s, 1), ec = __shfl_up(c, 1);
     if (lane == 0) es = ec = 0.0;
