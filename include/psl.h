@@ -394,7 +394,7 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
  * the band rule's whatever the margin. Errors: PSL_E_INVAL outside the range. */
 #define PSL_OPT_AMBIG_MARGIN 3
 /* PSL_OPT_SPLIT: the matrix path of the evaluation (Eq. (5) over the
- * neighbours as 0/1 matrices, the XOR and AND of the two neighbours of
+ * neighbours as 0/1 matrices, the XNOR and AND of the two neighbours of
  * Section 3's one-element flip, times fixed-point coefficients, summed exactly
  * on the matrix cores) for walks of L >= 512, in the steps that allow it (the
  * near-peak list holds the PSL and the quantization bound of the coefficients
