@@ -441,6 +441,21 @@ __device__ __forceinline__ v8i mx_rec(const uint8_t *__restrict__ base, uint32_t
     return v8i{a.x, a.y, a.z, b.x, b.y, b.z, 0, 0};
 }
 
+// v of the lane that mirrors this one within 2 d lanes of a row of 16 (d = 8, 4, 2,
+// 1): a register move, where a butterfly's exchange goes through LDS (one walk at
+// L = 16383: 10.0 us per launch, 9.2 with these in the main items; 1024 walks at
+// L = 131071 no change. In the edge items as well the main items' loops came out
+// 1.7 % slower).
+__device__ __forceinline__ double mx_partner(double v, int d)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint64_t o = d == 8   ? dpp_mov<0x140, 0xF>(u, u)      // row_mirror
+                       : d == 4 ? dpp_mov<0x141, 0xF>(u, u)      // row_half_mirror
+                       : d == 2 ? dpp_mov<0x1B, 0xF>(u, u)       // quad_perm 3 2 1 0
+                                : dpp_mov<0xB1, 0xF>(u, u);      // quad_perm 1 0 3 2
+    return __longlong_as_double((long long)o);
+}
+
 struct MxLane {
     const uint32_t *w;      // kPad words before the sequence's first
     int J32;                // first word of the tile
@@ -771,14 +786,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
             const double lo = (double)acc[i >> 2][i & 3] * wcol, hi = (double)acc[8 + (i >> 2)][i & 3] * wcol;
-            v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, 8);
+            v[i] = (up ? hi : lo) + mx_partner(up ? lo : hi, 8);
         }
     }
 #pragma unroll
     for (int n = 16, d = 4; n >= 4; n >>= 1, d >>= 1) {
         const bool up = ln.col & d;
 #pragma unroll
-        for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + __shfl_xor(up ? v[i] : v[i + n], d);
+        for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + mx_partner(up ? v[i] : v[i + n], d);
     }
     double *__restrict__ out = be.lpart + (size_t)it.ks * L;
     const int j = J0 + 16 * ln.col + 4 * ln.g;
