@@ -2,6 +2,9 @@
 // batches and the C-ABI entry points declared in include/psl.h.
 #include "psl_internal.h"
 
+#include <memory>
+#include <new>
+
 using namespace psl;
 using namespace psl_rt;
 
@@ -1017,7 +1020,14 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
             ctx->walks.push_back(WalkHost());
         }
     }
+    auto trim = [&]() {                     // the staged buffer outlives the call up to kInitKeep
+        if (ctx->init_cap <= kInitKeep) return;
+        dev_free(ctx, ctx->d_init, false);
+        ctx->d_init = nullptr;
+        ctx->init_cap = 0;
+    };
     auto rollback = [&](uint32_t upto) {
+        trim();
         for (uint32_t b = 0; b < n; ++b) {
             WalkHost &h = ctx->walks[ids[b]];
             if (b < upto && h.slab) dev_free(ctx, h.slab, true);
@@ -1050,10 +1060,14 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         ctx->d_init = (char *)p;
         ctx->init_cap = need;
     }
-    std::vector<char> stage(o_s0);
-    InitRec *recs = (InitRec *)stage.data();
-    BatchEntry *be = (BatchEntry *)(stage.data() + o_be);
-    uint64_t *bits = (uint64_t *)(stage.data() + o_bits);
+    const std::unique_ptr<char[]> stage(new (std::nothrow) char[o_s0]());
+    if (!stage) {
+        rollback(0);
+        return fail(ctx, PSL_E_NOMEM, "out of host memory");
+    }
+    InitRec *recs = (InitRec *)stage.get();
+    BatchEntry *be = (BatchEntry *)(stage.get() + o_be);
+    uint64_t *bits = (uint64_t *)(stage.get() + o_bits);
     size_t given_at = 0;
     for (uint32_t b = 0; b < n; ++b) {
         void *slab;
@@ -1095,18 +1109,14 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         const BatchEntry *d_be = (const BatchEntry *)(ctx->d_init + o_be);
         CorrDims cd;
         cd.add(L, n);
-        hipError_t e = hipMemcpyAsync(ctx->d_init, stage.data(), stage.size(), hipMemcpyHostToDevice, ctx->stream);
+        hipError_t e = hipMemcpyAsync(ctx->d_init, stage.get(), o_s0, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess)
             e = launch_init(ctx->d_walks, (const InitRec *)ctx->d_init, (const uint64_t *)(ctx->d_init + o_bits), n,
                             slab_bytes, nw, ctx->stream);
         if (e == hipSuccess) e = launch_corr(ctx->d_walks, d_be, n, cd, 0, ctx->stream);
         if (e == hipSuccess) e = launch_fit(ctx->d_walks, d_be, n, tabs, sm, kFitInit, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        if (ctx->init_cap > kInitKeep) {
-            dev_free(ctx, ctx->d_init, false);
-            ctx->d_init = nullptr;
-            ctx->init_cap = 0;
-        }
+        trim();
         if (e != hipSuccess) return fail(ctx, PSL_E_HIP, "walk init: %s", hipGetErrorString(e));
     }
     memcpy(walk_ids_out, ids.data(), sizeof(uint32_t) * n);
