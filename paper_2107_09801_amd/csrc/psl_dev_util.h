@@ -174,6 +174,16 @@ __device__ __forceinline__ double wave_least(double v)
     return __longlong_as_double((long long)last_lane(bits(v)));
 }
 
+// Place of element j in a row of the matrix path's partial sums (BatchEntry::lpart):
+// tiles count from the one of the neighbourhood's first element, j_first. (Rows
+// of all L elements took 2.5 GB for one walk at L = 1048575 with N_lmt = 512,
+// whose few tiles split 313 ways; these 2.6 MB.)
+__device__ __forceinline__ uint32_t mx_place(uint32_t L, uint32_t j_first, uint32_t j)
+{
+    const uint32_t ntile = (L + kMxTile - 1) / kMxTile, t0 = j_first / kMxTile, t = j / kMxTile;
+    return kMxTile * (t < t0 ? t + ntile - t0 : t - t0) + j % kMxTile;
+}
+
 // Prefix sum x (0 or 1, BatchEntry::pre) of a matrix walk over the shifts
 // 1 .. k, in two parts to add: the one within the segment, and the segment's offset.
 __device__ __forceinline__ void split_prefix(const BatchEntry &be, uint32_t L, int x, uint32_t k, double &in, double &off)

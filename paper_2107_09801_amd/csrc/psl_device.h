@@ -108,9 +108,9 @@ struct BatchEntry {
     double *pre;            // [2][L]: prefix sums over the segment's shifts up to k of T(|C_k-+2|) - T(|C_k|)
     double *segoff;         // [segments][3]: their segments' totals, then offsets (SegMap segments)
     uint32_t seg_shift;     // log2 of a segment's shifts
-    uint32_t pad;
+    uint32_t lrow;          // kMxTile x the tiles the neighbourhood can touch
     struct SplitState *ss;  // scale and path choice of this step
-    double *lpart;          // [lsplit + 1][L]: partial sums (in units of the scale), by element; the last the edges'
+    double *lpart;          // [lsplit + 1][lrow]: partial sums (in units of the scale), see mx_place; the last the edges'
 };
 
 // Matrix path (psl_split.hip): items of kMxTile elements (a padding item has

@@ -383,12 +383,11 @@ static uint32_t mx_splits(uint32_t chunks, uint64_t tiles)
     return (uint32_t)std::max(least, std::min(std::lround(s), (long)(chunks / kMxMinChunks)));
 }
 
-// The matrix path's k-splits per walk (0: none) and items in launch order.
+// The matrix path's k-splits (0: none) and tiles per walk, and items in launch order.
 static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl, uint32_t n, std::vector<uint32_t> &lsp,
-                      std::vector<EvalItem> &items)
+                      std::vector<uint32_t> &nq, std::vector<EvalItem> &items)
 {
     uint64_t work = 0, shifts = 0, tiles = 0;
-    std::vector<uint32_t> nq(n, 0);
     for (uint32_t b = 0; b < n; ++b) {
         if (Ls[b] < kSplitMinL) continue;
         work += (uint64_t)nl[b] * (Ls[b] - 1);
@@ -547,9 +546,9 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
                 force_items ? force_items : items_for(ctx, Ls.data(), n_l.data(), n), lay);
     const std::vector<uint32_t> &tiles = lay.tiles, &ks = lay.ks;
     std::vector<EvalItem> &items = lay.items;
-    std::vector<uint32_t> lsp(n, 0);
+    std::vector<uint32_t> lsp(n, 0), nq(n, 0);
     std::vector<EvalItem> mitems;
-    if (!mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, mitems);
+    if (!mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, nq, mitems);
     if (!mitems.empty()) {
         // the combine adds a matrix walk's own partials
         std::vector<uint32_t> cs(ks);
@@ -651,7 +650,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         if (!lsp[b]) continue;
         n_dig += dig_bytes(Ls[b]);
         n_pre += 2 * (size_t)Ls[b];
-        n_lp += (size_t)(lsp[b] + 1) * Ls[b];
+        n_lp += (size_t)(lsp[b] + 1) * nq[b] * kMxTile;
     }
     pl.split = !mitems.empty();
     if (pl.split) {
@@ -705,11 +704,12 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
             e.pre = pl.d_pre + o_pre;
             e.segoff = pl.d_segoff + 3 * (size_t)off[b];
             e.seg_shift = pl.seg.shift;
+            e.lrow = nq[b] * kMxTile;
             e.lpart = pl.d_lpart + o_lp;
             e.ss = pl.d_ss + b;
             o_dig += dig_bytes(Ls[b]);
             o_pre += 2 * (size_t)Ls[b];
-            o_lp += (size_t)(lsp[b] + 1) * Ls[b];
+            o_lp += (size_t)(lsp[b] + 1) * e.lrow;
         }
         op += (size_t)ks[b] * n_l[b];
         oc += n_l[b];

@@ -379,6 +379,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
     const double U = split ? be.ss->U : 0.0, total = split ? be.ss->total : 0.0;
     const uint32_t start = be.fixed ? be.start : step_start(w);
     const uint32_t L = w.L;
+    const uint32_t j_first = (start + 1u) % L;
     const uint32_t n_near = split ? be.near[0] : 0;
 
     double fmin = INFINITY;
@@ -408,7 +409,8 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
             if (i < hi) {
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
                 if (TAIL && g == 0) prefixes();
-                for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += be.lpart[(size_t)x * L + j];
+                const double *part = be.lpart + mx_place(L, j_first, j);
+                for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += part[(size_t)x * be.lrow];
                 m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
                               (uint32_t)G);
             }

@@ -634,6 +634,7 @@ __device__ __forceinline__ void mx_one(v4f (&acc)[2 * kBlk], const MxLane &ln, c
 // consecutive ones per step; shifts up to a row's m_j go into the
 // both-neighbour sums, the others into the one-neighbour sums of its side
 // (right for j <= half; the sign of a row with s_j = -1 as FP4's sign bit).
+// out: the tile's places.
 __device__ __forceinline__ void mx_edge(const MxLane &ln, const BatchEntry &be, int L, int qd, int ca, int ce, int nco,
                                         int nbo, double *__restrict__ out)
 {
@@ -695,8 +696,7 @@ __device__ __forceinline__ void mx_edge(const MxLane &ln, const BatchEntry &be, 
 #pragma unroll
         for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + __shfl_xor(up ? v[i] : v[i + n], d);
     }
-    const int j = 32 * w0 + 16 * (ln.col >> 2) + 4 * ln.g + (ln.col & 3);
-    if (j < L) out[j] = v[0];
+    out[64 * qd + 16 * (ln.col >> 2) + 4 * ln.g + (ln.col & 3)] = v[0];      // rows past L - 1: not read
 }
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx(
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     ln.col = lane & 15;
     if (it.ks >= be.lsplit) {           // edge item: its part of the tile's rows
         const int part = (int)(it.ks - be.lsplit);
-        double *out = be.lpart + (size_t)be.lsplit * L;
+        double *out = be.lpart + (size_t)be.lsplit * be.lrow + (size_t)kMxTile * it.tile;
         for (int qd = it.pad ? 0 : part; qd < (it.pad ? 4 : part + 1); ++qd)
             if (J0 + 64 * qd < L) mx_edge(ln, be, L, qd, fb, f0, nco, nbo, out);
         return;
@@ -795,11 +795,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
         for (int i = 0; i < n; ++i) v[i] = (up ? v[i + n] : v[i]) + mx_partner(up ? v[i] : v[i + n], d);
     }
-    double *__restrict__ out = be.lpart + (size_t)it.ks * L;
-    const int j = J0 + 16 * ln.col + 4 * ln.g;
+    double *__restrict__ out = be.lpart + (size_t)it.ks * be.lrow + (size_t)kMxTile * it.tile + 16 * ln.col + 4 * ln.g;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (j + q < L) out[j + q] = v[q];
+    for (int q = 0; q < 4; ++q) out[q] = v[q];          // rows past L - 1: not read
 }
 
 // The records after each coefficient's last: zeros.
