@@ -116,8 +116,9 @@ struct BatchPlan {
     double *d_segtot = nullptr;       // per segment: chunk-sum total (suffix pass)
     uint32_t *d_segmax = nullptr;     // per segment: maximum |C_k|
     SegMap seg{};
-    // split evaluation (walks with BatchEntry.lsplit > 0)
+    // matrix path (walks with BatchEntry.lsplit > 0)
     bool split = false;               // some walk of the plan can take the matrix path
+    char *d_mx = nullptr;             // the allocation that holds the arrays below
     uint8_t *d_dig = nullptr;
     double *d_pre = nullptr, *d_lpart = nullptr;
     SplitState *d_ss = nullptr;
@@ -210,6 +211,8 @@ psl_status dev_alloc(psl_ctx *ctx, void **p, size_t bytes, bool from_arena);
 void dev_free(psl_ctx *ctx, void *p, bool from_arena);
 void plan_free(psl_ctx *ctx, BatchPlan &pl);
 void plans_clear(psl_ctx *ctx);
+// Frees what the kept layouts hold, but for one of them; true if there was any.
+bool plans_drop(psl_ctx *ctx, const BatchPlan *but);
 psl_status ensure_tables(psl_ctx *ctx, uint32_t L);
 Tables tables_of(const psl_ctx *ctx);
 psl_status ensure_walk_cap(psl_ctx *ctx, uint32_t cap);
@@ -253,6 +256,7 @@ struct PlanMem {
     double *F = nullptr;
     int32_t *P = nullptr;
 };
+// A plan for which the matrix path's memory cannot be had is made without it.
 psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t n, uint32_t n_fixed,
                      uint32_t start_fixed, const EvalShape *force = nullptr, uint32_t force_items = 0,
                      PlanMem *mem = nullptr);

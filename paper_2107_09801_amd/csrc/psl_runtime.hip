@@ -142,13 +142,7 @@ void plan_free(psl_ctx *ctx, BatchPlan &pl)
     dev_free(ctx, pl.d_segmax, false);
     dev_free(ctx, pl.d_near, false);
     dev_free(ctx, pl.d_queues, false);
-    dev_free(ctx, pl.d_dig, false);
-    dev_free(ctx, pl.d_pre, false);
-    dev_free(ctx, pl.d_lpart, false);
-    dev_free(ctx, pl.d_ss, false);
-    dev_free(ctx, pl.d_mitems, false);
-    dev_free(ctx, pl.d_tab, false);
-    dev_free(ctx, pl.d_segoff, false);
+    dev_free(ctx, pl.d_mx, false);
     pl = BatchPlan();
 }
 
@@ -157,6 +151,31 @@ void plans_clear(psl_ctx *ctx)
     for (auto &pl : ctx->plans) plan_free(ctx, pl);
     ctx->plans.clear();
     plan_free(ctx, ctx->pure);
+}
+
+bool plans_drop(psl_ctx *ctx, const BatchPlan *but)
+{
+    bool any = false;
+    (void)hipStreamSynchronize(ctx->stream);
+    auto drop = [&](BatchPlan &pl) {
+        if (&pl == but) return;
+        any |= pl.d_batch != nullptr;
+        plan_free(ctx, pl);              // its place in the list stays: it matches no batch
+    };
+    for (auto &pl : ctx->plans) drop(pl);
+    drop(ctx->pure);
+    return any;
+}
+
+// dev_alloc of what outlives a call, in memory that kept layouts hold if there is
+// no other.
+psl_status dev_alloc_kept(psl_ctx *ctx, void **p, size_t bytes, bool from_arena)
+{
+    const std::string err = ctx->err;
+    psl_status st = dev_alloc(ctx, p, bytes, from_arena);
+    if (st != PSL_E_NOMEM || (from_arena && ctx->arena.active()) || !plans_drop(ctx, nullptr)) return st;
+    if (!(st = dev_alloc(ctx, p, bytes, from_arena))) ctx->err = err;
+    return st;
 }
 
 // Power tables for every exponent, |c| up to L_max + 4.
@@ -198,7 +217,7 @@ psl_status ensure_walk_cap(psl_ctx *ctx, uint32_t cap)
     if (cap <= ctx->walk_cap) return PSL_OK;
     uint32_t ncap = std::max<uint32_t>(cap, std::max<uint32_t>(64, ctx->walk_cap * 2));
     void *p;
-    psl_status st = dev_alloc(ctx, &p, sizeof(WalkDev) * ncap, false);
+    psl_status st = dev_alloc_kept(ctx, &p, sizeof(WalkDev) * ncap, false);
     if (st) return st;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     plans_clear(ctx);            // captured launches name the old walk array
@@ -521,8 +540,9 @@ uint32_t items_max(const psl_ctx *ctx)
     return m;
 }
 
-psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t n, uint32_t n_fixed,
-                     uint32_t start_fixed, const EvalShape *force, uint32_t force_items, PlanMem *mem)
+// matrix: with the matrix path where it pays.
+static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t n, uint32_t n_fixed,
+                             uint32_t start_fixed, const EvalShape *force, uint32_t force_items, PlanMem *mem, bool matrix)
 {
     const bool fixed = n_fixed != UINT32_MAX;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
@@ -548,8 +568,9 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     std::vector<EvalItem> &items = lay.items;
     std::vector<uint32_t> lsp(n, 0), nq(n, 0);
     std::vector<EvalItem> mitems;
-    if (!mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, nq, mitems);
-    if (!mitems.empty()) {
+    if (matrix && !mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, nq, mitems);
+    pl.split = !mitems.empty();
+    if (pl.split) {
         // the combine adds a matrix walk's own partials
         std::vector<uint32_t> cs(ks);
         for (uint32_t b = 0; b < n; ++b)
@@ -652,22 +673,25 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         n_pre += 2 * (size_t)Ls[b];
         n_lp += (size_t)(lsp[b] + 1) * nq[b] * kMxTile;
     }
-    pl.split = !mitems.empty();
     if (pl.split) {
-        if ((st = get(&p, n_dig))) return st;
-        pl.d_dig = (uint8_t *)p;
-        if ((st = get(&p, sizeof(double) * n_pre))) return st;
-        pl.d_pre = (double *)p;
-        if ((st = get(&p, sizeof(double) * n_lp))) return st;
-        pl.d_lpart = (double *)p;
-        if ((st = get(&p, sizeof(SplitState) * n))) return st;
-        pl.d_ss = (SplitState *)p;
-        if ((st = get(&p, sizeof(EvalItem) * mitems.size()))) return st;
-        pl.d_mitems = (EvalItem *)p;
-        if ((st = get(&p, sizeof(uint32_t)))) return st;
-        pl.d_tab = (uint32_t *)p;
-        if ((st = get(&p, 3 * sizeof(double) * pl.seg.total))) return st;
-        pl.d_segoff = (double *)p;
+        size_t at = 0;                  // one allocation, in pieces
+        auto piece = [&](size_t bytes) {
+            const size_t o = at;
+            at += align_up(bytes, 256);
+            return o;
+        };
+        const size_t p_dig = piece(n_dig), p_pre = piece(sizeof(double) * n_pre), p_lp = piece(sizeof(double) * n_lp),
+                     p_ss = piece(sizeof(SplitState) * n), p_items = piece(sizeof(EvalItem) * mitems.size()),
+                     p_tab = piece(sizeof(uint32_t)), p_off = piece(3 * sizeof(double) * pl.seg.total);
+        if ((st = get(&p, at))) return st;
+        pl.d_mx = (char *)p;
+        pl.d_dig = (uint8_t *)(pl.d_mx + p_dig);
+        pl.d_pre = (double *)(pl.d_mx + p_pre);
+        pl.d_lpart = (double *)(pl.d_mx + p_lp);
+        pl.d_ss = (SplitState *)(pl.d_mx + p_ss);
+        pl.d_mitems = (EvalItem *)(pl.d_mx + p_items);
+        pl.d_tab = (uint32_t *)(pl.d_mx + p_tab);
+        pl.d_segoff = (double *)(pl.d_mx + p_off);
         pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
         pl.n_mitems = (uint32_t)mitems.size();
         HIP_TRY(ctx, hipMemcpy(pl.d_mitems, mitems.data(), sizeof(EvalItem) * mitems.size(),
@@ -728,6 +752,25 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     if (pl.split) HIP_TRY(ctx, launch_rec_pad(pl.d_batch, ctx->d_walks, n, ctx->stream));
     pl.n_items = (uint32_t)items.size();
     return PSL_OK;
+}
+
+psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t n, uint32_t n_fixed,
+                     uint32_t start_fixed, const EvalShape *force, uint32_t force_items, PlanMem *mem)
+{
+    const std::string err = ctx->err;
+    const size_t used = mem ? mem->used : 0;
+    auto build = [&](bool matrix) {
+        if (mem) mem->used = used;
+        return build_plan(ctx, pl, ids, n, n_fixed, start_fixed, force, force_items, mem, matrix);
+    };
+    psl_status st = build(true);
+    if (st != PSL_E_NOMEM) return st;
+    // without the matrix path, whose arrays come on top of the others; then in what
+    // the other kept layouts hold
+    if (pl.split) st = build(false);
+    if (st == PSL_E_NOMEM && !mem && plans_drop(ctx, &pl)) st = build(false);
+    if (!st) ctx->err = err;
+    return st;
 }
 
 SlabLayout slab_layout(uint32_t L)
@@ -883,7 +926,7 @@ psl_status one_entry(psl_ctx *ctx, uint32_t slot)
     static_assert(sizeof(BatchEntry) <= kOneDone, "the entry comes first");
     if (!ctx->d_one) {
         void *p;
-        const psl_status st = dev_alloc(ctx, &p, kHead + kSegs * (2 * sizeof(double) + sizeof(uint32_t)), false);
+        const psl_status st = dev_alloc_kept(ctx, &p, kHead + kSegs * (2 * sizeof(double) + sizeof(uint32_t)), false);
         if (st) return st;
         ctx->d_one = (BatchEntry *)p;
         ctx->one_slot = UINT32_MAX;
@@ -1053,7 +1096,7 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
         ctx->d_init = nullptr;
         ctx->init_cap = 0;
         void *p;
-        if ((st = dev_alloc(ctx, &p, need, false))) {
+        if ((st = dev_alloc_kept(ctx, &p, need, false))) {
             rollback(0);
             return st;
         }
@@ -1071,7 +1114,7 @@ psl_status psl_init_walks(psl_ctx *ctx, const psl_walk_cfg *cfg, uint32_t n,
     size_t given_at = 0;
     for (uint32_t b = 0; b < n; ++b) {
         void *slab;
-        if ((st = dev_alloc(ctx, &slab, slab_bytes, true))) {
+        if ((st = dev_alloc_kept(ctx, &slab, slab_bytes, true))) {
             rollback(b);
             return st;
         }
@@ -1588,7 +1631,7 @@ psl_status psl_trace_enable(psl_ctx *ctx, uint32_t walk, uint32_t capacity)
     WalkHost &h = ctx->walks[walk];
     void *ring = nullptr;
     if (capacity) {
-        psl_status st = dev_alloc(ctx, &ring, sizeof(TraceEntry) * capacity, false);
+        psl_status st = dev_alloc_kept(ctx, &ring, sizeof(TraceEntry) * capacity, false);
         if (st) return st;
     }
     WalkDev w;

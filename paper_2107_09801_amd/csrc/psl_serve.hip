@@ -873,7 +873,9 @@ psl_status psl_serve_start(psl_ctx *ctx, const psl_serve_cfg *cfg)
     {
         // the budget has to fit the device's free memory (taken as jobs come)
         size_t dfree = 0, dtotal = 0;
-        if (hipMemGetInfo(&dfree, &dtotal) != hipSuccess || dfree < cfg->hbm_budget) {
+        auto fits = [&] { return hipMemGetInfo(&dfree, &dtotal) == hipSuccess && dfree >= cfg->hbm_budget; };
+        // (layouts of step batches are of no use while the context serves)
+        if (!fits() && !(plans_drop(ctx, nullptr) && fits())) {
             (void)hipGetLastError();
             delete s;
             return fail(ctx, PSL_E_NOMEM, "hbm_budget of %llu bytes exceeds the free device memory (%zu)",
