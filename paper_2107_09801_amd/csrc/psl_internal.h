@@ -119,6 +119,7 @@ struct BatchPlan {
     // matrix path (walks with BatchEntry.lsplit > 0)
     bool split = false;               // some walk of the plan can take the matrix path
     char *d_mx = nullptr;             // the allocation that holds the arrays below
+    size_t mx_bytes = 0;
     uint8_t *d_dig = nullptr;
     double *d_pre = nullptr, *d_lpart = nullptr;
     SplitState *d_ss = nullptr;

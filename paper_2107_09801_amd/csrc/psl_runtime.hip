@@ -546,6 +546,16 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
 {
     const bool fixed = n_fixed != UINT32_MAX;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    // the matrix path's memory of the layout that this one replaces serves again if
+    // it is large enough: at L = 1048575 its 44 MB cost 270 us of every evaluation of
+    // another walk or N_lmt than the last (300 us in all without them)
+    struct Kept {
+        psl_ctx *ctx;
+        char *p;
+        size_t bytes;
+        ~Kept() { dev_free(ctx, p, false); }
+    } kept{ctx, pl.carved ? nullptr : pl.d_mx, pl.mx_bytes};
+    pl.d_mx = nullptr;
     plan_free(ctx, pl);
     pl.ids.assign(ids, ids + n);
     pl.fixed_n = fixed ? n_fixed : 0;
@@ -683,8 +693,15 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         const size_t p_dig = piece(n_dig), p_pre = piece(sizeof(double) * n_pre), p_lp = piece(sizeof(double) * n_lp),
                      p_ss = piece(sizeof(SplitState) * n), p_items = piece(sizeof(EvalItem) * mitems.size()),
                      p_tab = piece(sizeof(uint32_t)), p_off = piece(3 * sizeof(double) * pl.seg.total);
-        if ((st = get(&p, at))) return st;
-        pl.d_mx = (char *)p;
+        if (!mem && kept.p && at <= kept.bytes && at >= kept.bytes / 4) {
+            pl.d_mx = kept.p;
+            pl.mx_bytes = kept.bytes;
+            kept.p = nullptr;
+        } else {
+            if ((st = get(&p, at))) return st;
+            pl.d_mx = (char *)p;
+            pl.mx_bytes = at;
+        }
         pl.d_dig = (uint8_t *)(pl.d_mx + p_dig);
         pl.d_pre = (double *)(pl.d_mx + p_pre);
         pl.d_lpart = (double *)(pl.d_mx + p_lp);
