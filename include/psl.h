@@ -373,8 +373,10 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
  * within 8 of the pivot's PSL, the only ones that can set a neighbour's PSL)
  * for which the evaluation computes each neighbour's PSL from that list;
  * above it the PSL maximum is kept in the main loop. -1 (default): automatic,
- * min(4096, max(64, L/16)); 0 forces the in-loop maximum. Both give the same
- * results. Errors: PSL_E_INVAL for an unknown option or value. */
+ * min(4096, max(64, L/16)) for the table evaluation and 4096 for the matrix path
+ * (PSL_OPT_SPLIT), which leaves a walk with a longer list to the table
+ * evaluation in that step; 0 forces the in-loop maximum, so that no walk takes
+ * the matrix path. Both give the same results. Errors: PSL_E_INVAL for an unknown option or value. */
 #define PSL_OPT_NEAR_LIMIT 1
 /* PSL_OPT_EVAL_ITEMS: the number of work items (candidate tile x piece of
  * the shift range) an evaluation launch offers at least: a walk's shifts are

@@ -406,6 +406,9 @@ static uint32_t mx_splits(uint32_t chunks, uint64_t tiles)
 static void mx_layout(const psl_ctx *ctx, const uint32_t *Ls, const uint32_t *nl, uint32_t n, std::vector<uint32_t> &lsp,
                       std::vector<uint32_t> &nq, std::vector<EvalItem> &items)
 {
+    // no step takes the path with a near-peak list of no entries: the pivot's peak
+    // is always on it
+    if (ctx->near_limit == 0) return;
     uint64_t work = 0, shifts = 0, tiles = 0;
     for (uint32_t b = 0; b < n; ++b) {
         if (Ls[b] < kSplitMinL) continue;
