@@ -357,12 +357,14 @@ __device__ __forceinline__ void eval_sweep(EvalLds<WAVES> &sh, const WalkDev &w,
 // 32-bit maxima kept in the main loop.
 // kMatrix: the batch has matrix walks (a walk on the matrix path in this step
 // is left out; one that is not has prefix sums in place of chunk arrays).
+// splits: the k-splits, if not the layout's.
 template <int WAVES, bool kMatrix>
 __device__ __forceinline__ void eval_item(EvalLds<WAVES> &sh, const WalkDev *__restrict__ walks,
                                           const BatchEntry *__restrict__ batch, const EvalItem it,
-                                          const Tables &tabs, int tid)
+                                          const Tables &tabs, int tid, uint32_t splits = 0)
 {
     const BatchEntry be = batch[it.walk];
+    const uint32_t ksplit = splits ? splits : be.ksplit;
     if (kMatrix && be.lsplit != 0 && be.ss->use != 0) return;
     const WalkDev &w = walks[be.slot];
     const int L = (int)w.L;
@@ -373,7 +375,7 @@ __device__ __forceinline__ void eval_item(EvalLds<WAVES> &sh, const WalkDev *__r
 
     // shifts of this split, in whole 32-shift chunks from k = 1
     const int nchunks = (L - 1 + 31) / 32;
-    const int per = (nchunks + (int)be.ksplit - 1) / (int)be.ksplit;
+    const int per = (nchunks + (int)ksplit - 1) / (int)ksplit;
     const int c_lo = (int)it.ks * per;
     const int c_hi = min(nchunks, c_lo + per);
     const int k_lo = 1 + 32 * c_lo;
@@ -400,7 +402,7 @@ __device__ __forceinline__ void eval_item(EvalLds<WAVES> &sh, const WalkDev *__r
             // takes the maximum over the splits)
             const int jl = j, jr = L - 1 - j;
             int peak = 0;
-            for (uint32_t q = it.ks; q < n_near; q += be.ksplit) {
+            for (uint32_t q = it.ks; q < n_near; q += ksplit) {
                 const int k = (int)be.near[1 + q];
                 int c = w.C[k];
                 if (k <= jr) {
@@ -506,14 +508,20 @@ void k_eval_strided(const WalkDev *__restrict__ walks, const BatchEntry *__restr
 }
 
 // The combine of a step of matrix walks, with the table evaluation of a walk that
-// the matrix path does not take in it: before the combine a block evaluates the
-// 256-candidate tiles that its candidates lie in (blocks that share a tile all
-// do, and store the same values). Steps where it has to are rare (a near-peak
-// list that overflows), and what they cost beyond k_eval_strided's is a walk's
-// blocks being at most 256; a launch that looks and returns costs every step
-// 3 to 4 us of about 40 (one walk at L = 16383).
+// the matrix path does not take in it: the walk's blocks, with those past the
+// first `blocks` that have nothing else to do, share out its tiles of 256
+// candidates, in as many k-splits as give each block an item, and the last to
+// finish adds the partials and makes the selection. A launch that looks and
+// returns (k_eval_strided) costs every step 3 to 4 us of about 40 (one walk at
+// L = 16383), 1024 blocks here instead of 128 nothing; steps that need it are
+// rare, but those of a walk whose near-peak list overflows tend to follow each
+// other. Such a step, us, here and without the matrix path: L = 131071 N_lmt = 512
+// 97 / 33, L = 1048575 N_lmt = 512 221 / 115, L = 65535 N_lmt = 6912 244 / 77 (with
+// every block evaluating the tiles of its own candidates, one k-split after another,
+// 3140, 24900 and 1600), L = 16383 N_lmt = 16383 315 / 63.
 __global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, const BatchEntry *batch, Tables tabs, int G,
-                                                               uint32_t *pend, uint32_t *done, double margin)
+                                                               uint32_t *pend, uint32_t *done, double margin,
+                                                               uint32_t blocks)
 {
     __shared__ union Lds {
         EvalLds<4> eval;
@@ -523,18 +531,22 @@ __global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, c
     const BatchEntry be = batch[blockIdx.y];
     WalkDev &w = walks[be.slot];
     if (!be.ss->use) {
-        uint32_t lo, hi;
-        comb_range(be.fixed ? be.n_lmt : w.n_lmt, gridDim.x, (uint32_t)G, blockIdx.x, lo, hi);
-        for (uint32_t t = lo / 256; t * 256 < hi; ++t)
-            for (uint32_t ks = 0; ks < be.ksplit; ++ks) {
-                int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
-                asm volatile("" : "+v"(tid));
-                __builtin_assume(tid >= 0 && tid < 256);
-                eval_item<4, true>(sh.eval, walks, batch, EvalItem{blockIdx.y, t, ks, 0}, tabs, tid);
-                __syncthreads();                // the next item, or the combine, takes the LDS
-            }
+        const uint32_t tiles = ((be.fixed ? be.n_lmt : w.n_lmt) + 255) / 256;
+        const uint32_t ks = min(be.ksplit, max(1u, gridDim.x / tiles));
+        for (uint32_t x = blockIdx.x; x < tiles * ks; x += gridDim.x) {
+            int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
+            asm volatile("" : "+v"(tid));
+            __builtin_assume(tid >= 0 && tid < 256);
+            eval_item<4, true>(sh.eval, walks, batch, EvalItem{blockIdx.y, x % tiles, x / tiles, 0}, tabs, tid, ks);
+            __syncthreads();                // the next item, or the combine, takes the LDS
+        }
+        if (!last_block(sh.comb, done, blockIdx.y, gridDim.x)) return;
+        combine_part<true, Form::table>(sh.comb, w, be, tabs, 1, 1, 0, ks);
+        finish_walk<kCombThreads>(sh.comb.fin, w, be, blockIdx.y, 1, 1, 0, nullptr, pend, margin);
+        return;
     }
-    combine_block<true>(sh.comb, w, be, tabs, G, 0, nullptr, pend, done, margin, 0);
+    if (blockIdx.x < blocks)
+        combine_block<true, Form::matrix>(sh.comb, w, be, tabs, G, 0, nullptr, pend, done, margin, 0, blocks);
 }
 
 __global__ void k_queue_reset(EvalQueues *queues)
@@ -559,16 +571,26 @@ static void launch_eval_waves(const WalkDev *walks, const BatchEntry *batch, con
         k_eval<WAVES><<<n_items, 64 * WAVES, 0, s>>>(walks, batch, items, tabs);
 }
 
-bool select_takes_left(uint32_t nb, uint32_t comb_blocks) { return comb_small(nb, comb_blocks); }
+// Blocks for items of at least 2^17 updates (smaller ones cost more to add up than
+// they save: L = 131071 N_lmt = 512 97 us in 512 blocks, 132 in 1024), and at most
+// 1024 in all (1536: 2 us of every step). Past 2^31 updates the last block's adding
+// takes too long (L = 131071, all candidates: 6.3 ms, in launches of its own 0.95),
+// and the launch that looks is 2 % of a step.
+uint32_t select_left_blocks(uint32_t nb, uint32_t comb_blocks, uint64_t updates)
+{
+    if (!comb_small(nb, comb_blocks) || updates > 1ull << 31) return 0;
+    return std::max(comb_blocks, (uint32_t)std::min<uint64_t>(1024 / nb, updates >> 17));
+}
 
 hipError_t launch_select_left(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
-                              uint32_t comb_group, const Tables &tabs, uint32_t *pend, uint32_t *done, double margin,
-                              hipStream_t s)
+                              uint32_t comb_group, uint32_t grid, const Tables &tabs, uint32_t *pend, uint32_t *done,
+                              double margin, hipStream_t s)
 {
-    if (comb_blocks < 1 || comb_blocks > kCombMaxBlocks || !comb_small(nb, comb_blocks) || !done) return hipErrorInvalidValue;
+    if (grid < comb_blocks || comb_blocks < 1 || comb_blocks > kCombMaxBlocks || !comb_small(nb, comb_blocks) || !done) return hipErrorInvalidValue;
     if (comb_group < 1 || comb_group > 64 || (comb_group & (comb_group - 1))) return hipErrorInvalidValue;
     if (nb == 0) return hipSuccess;
-    k_combine_left<<<dim3(comb_blocks, nb), kCombThreads, 0, s>>>(walks, batch, tabs, (int)comb_group, pend, done, margin);
+    k_combine_left<<<dim3(grid, nb), kCombThreads, 0, s>>>(walks, batch, tabs, (int)comb_group, pend, done, margin,
+                                                           comb_blocks);
     return hipGetLastError();
 }
 

@@ -128,6 +128,7 @@ struct BatchPlan {
     uint32_t *d_tab = nullptr;        // walks left to the table evaluation in this step
     double *d_segoff = nullptr;       // per segment: totals, then offsets, of the prefix sums
     bool all_split = false;           // every walk of the plan can take the matrix path
+    uint32_t left_blocks = 0;         // its steps' selections evaluate what is left to the tables, in this many blocks
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

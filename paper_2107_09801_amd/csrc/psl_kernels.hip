@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
 {
     __shared__ CombLds sh;
     const BatchEntry be = batch[blockIdx.y];
-    combine_block<TAIL>(sh, walks[be.slot], be, tabs, G, pure, out, pend, done, margin, b0);
+    combine_block<TAIL, Form::either>(sh, walks[be.slot], be, tabs, G, pure, out, pend, done, margin, b0, gridDim.x);
 }
 
 // The selection of a walk, its ambiguity flags and (pure == 0) its

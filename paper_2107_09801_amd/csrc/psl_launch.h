@@ -66,13 +66,14 @@ hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pen
 hipError_t launch_select(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
                          uint32_t comb_group, const Tables &tabs, int pure, void *out, uint32_t *pend,
                          uint32_t *done, double margin, hipStream_t s);
-// launch_select of a step whose walks are all matrix walks, in small launches
-// (select_takes_left): a walk left to the table evaluation is evaluated here, so
-// that no launch_eval comes before.
-bool select_takes_left(uint32_t nb, uint32_t comb_blocks);
+// launch_select of a step whose walks are all matrix walks, where
+// select_left_blocks (updates: N_lmt x (L-1) of the walk with the most) gives the
+// blocks per walk (grid) and not 0: a walk left to the table evaluation is
+// evaluated here, so that no launch_eval comes before.
+uint32_t select_left_blocks(uint32_t nb, uint32_t comb_blocks, uint64_t updates);
 hipError_t launch_select_left(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
-                              uint32_t comb_group, const Tables &tabs, uint32_t *pend, uint32_t *done, double margin,
-                              hipStream_t s);
+                              uint32_t comb_group, uint32_t grid, const Tables &tabs, uint32_t *pend, uint32_t *done,
+                              double margin, hipStream_t s);
 size_t choice_dev_size();
 bool choice_dev_table(const void *p);
 void choice_dev_unpack(const void *p, uint32_t *i_best, uint32_t *j_best, double *F_best,

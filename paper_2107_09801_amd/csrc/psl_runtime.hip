@@ -713,6 +713,9 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         pl.d_tab = (uint32_t *)(pl.d_mx + p_tab);
         pl.d_segoff = (double *)(pl.d_mx + p_off);
         pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
+        uint64_t updates = 0;
+        for (uint32_t b = 0; b < n; ++b) updates = std::max(updates, (uint64_t)n_l[b] * (Ls[b] - 1));
+        pl.left_blocks = pl.all_split ? select_left_blocks(n, pl.comb_blocks, updates) : 0;
         pl.n_mitems = (uint32_t)mitems.size();
         HIP_TRY(ctx, hipMemcpy(pl.d_mitems, mitems.data(), sizeof(EvalItem) * mitems.size(),
                                hipMemcpyHostToDevice));
@@ -878,11 +881,11 @@ psl_status launch_partials(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs
 psl_status launch_step(psl_ctx *ctx, const BatchPlan &pl, const Tables &tabs, uint32_t n, bool timed)
 {
     psl_status st;
-    const bool left = pl.split && pl.all_split && select_takes_left(n, pl.comb_blocks);
+    const bool left = pl.left_blocks != 0;
     if ((st = launch_partials(ctx, pl, tabs, n, pl.d_pend, timed, EvalCall{}, !left))) return st;
     if (left)
-        HIP_TRY(ctx, launch_select_left(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, pl.d_pend,
-                                        pl.d_done, ctx->amb_margin, ctx->stream));
+        HIP_TRY(ctx, launch_select_left(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, pl.left_blocks, tabs,
+                                        pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));
     else
         HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, n, pl.comb_blocks, pl.comb_group, tabs, 0, nullptr,
                                    pl.d_pend, pl.d_done, ctx->amb_margin, ctx->stream));

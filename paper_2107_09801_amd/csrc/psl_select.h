@@ -337,9 +337,10 @@ __device__ __forceinline__ uint32_t near_peak(const uint32_t *__restrict__ list,
     return (uint32_t)peak;
 }
 
-// F and PSL per candidate from the k-split partials, spread over gridDim.x
-// blocks per walk (blockIdx.y = batch position); each block leaves its
-// smallest F and its first smallest PSL in be.red. A group of G lanes
+// F and PSL per candidate from the partials, for block b of a walk's `blocks`; the
+// block leaves its smallest F and its first smallest PSL in be.red. Form: from
+// ks table partials per candidate, from the matrix sums, or as this step chose.
+// EARLY: the prefix sums are loaded first. A group of G lanes
 // (a power of two, at most 64) shares a candidate: lane g adds splits g,
 // g+G, ... in order, then the group adds its lanes' sums in a fixed order for
 // a given split count and G (G = 1 adds the splits in order). For G <= 4 a
@@ -349,9 +350,6 @@ __device__ __forceinline__ uint32_t near_peak(const uint32_t *__restrict__ list,
 // consecutive partials of each of 64 / cpb splits; the sums go through a
 // butterfly over the wavefront's split lanes, then the four wavefronts' sums
 // are added in wavefront order.
-// With TAIL the walk's last block to finish then makes its selection
-// (finish_walk); b0 = the batch position of
-// blockIdx.y = 0; done holds one zeroed counter per batch position.
 struct CombLds {
     double f[4][32];
     uint32_t m[4][32];
@@ -359,13 +357,12 @@ struct CombLds {
     uint32_t last;
     FinishLds fin;
 };
-template <bool TAIL>
-__device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const BatchEntry &be, const Tables &tabs, int G,
-                                              int pure, ChoiceDev *out, uint32_t *pend, uint32_t *done,
-                                              double margin, uint32_t b0)
+enum class Form { table, matrix, either };
+template <bool EARLY, Form FORM>
+__device__ __forceinline__ void combine_part(CombLds &sh, WalkDev &w, const BatchEntry &be, const Tables &tabs, int G,
+                                             uint32_t blocks, uint32_t b, uint32_t ks)
 {
     const uint32_t n = be.fixed ? be.n_lmt : w.n_lmt;
-    const uint32_t ks = be.ksplit;
     const double *T = tabs.T[w.alpha];
     const uint32_t cpb = kCombThreads / (uint32_t)G;      // candidates per block pass
     const bool wide = G >= 8;
@@ -375,7 +372,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
     static_assert(kCombThreads == 256, "four wavefronts per combine block");
     // matrix path: F_j from the prefix sums and the matrix sums (psl_split.hip),
     // PSL_j from the near-peak shifts here
-    const bool split = be.lsplit != 0 && be.ss->use != 0;
+    const bool split = FORM == Form::matrix || (FORM == Form::either && be.lsplit != 0 && be.ss->use != 0);
     const double U = split ? be.ss->U : 0.0, total = split ? be.ss->total : 0.0;
     const uint32_t start = be.fixed ? be.start : step_start(w);
     const uint32_t L = w.L;
@@ -386,7 +383,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
     int32_t pmin = INT_MAX;
     uint32_t ipmin = UINT_MAX;
     uint32_t lo, hi;
-    comb_range(n, gridDim.x, (uint32_t)G, blockIdx.x, lo, hi);
+    comb_range(n, blocks, (uint32_t)G, b, lo, hi);
     for (uint32_t i0 = lo; i0 < hi; i0 += cpb) {
         const uint32_t i = i0 + ci;
         double f = 0.0;
@@ -408,7 +405,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
         if (split) {
             if (i < hi) {
                 const uint32_t j = (uint32_t)(((uint64_t)start + 1u + i) % L);
-                if (TAIL && g == 0) prefixes();
+                if (EARLY && g == 0) prefixes();
                 const double *part = be.lpart + mx_place(L, j_first, j);
                 for (uint32_t x = g; x <= be.lsplit; x += (uint32_t)G) f += part[(size_t)x * be.lrow];
                 m = near_peak(be.near + 1, n_near, w.C, reinterpret_cast<const uint32_t *>(w.pivot), (int)L, (int)j, g,
@@ -468,7 +465,7 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
             // because |C'_{L-1}| = 1 for every sequence
             const int32_t p = m < 0x3FF00000u ? (int32_t)m : table_inverse(T, tabs.n, m);
             if (split) {
-                if (!TAIL) prefixes();
+                if (!EARLY) prefixes();
                 f = total + ((pv[0] + po[0]) - (pv[1] + po[1])) + U * f;
             }
             be.F[i] = f;
@@ -483,29 +480,46 @@ __device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const Bat
     if (threadIdx.x == 0) {
         SelPart r = sh.r[0];
         for (int x = 1; x < kCombThreads / 64; ++x) sel_merge(r.f, r.p, r.i, sh.r[x].f, sh.r[x].p, sh.r[x].i);
-        be.red[blockIdx.x] = r;
+        be.red[b] = r;
     }
-    if (!TAIL) return;
-    // TAIL: the walk's last block to finish (counted in done[bi], which
-    // it returns to 0 for the next launch) makes the selection and sets the
-    // ambiguity flags. Each block's count is a device-scope release of its F,
-    // P and minimum, and the last block acquires them all.
-    const uint32_t bi = b0 + blockIdx.y;
+}
+
+// Whether the block is the last of the walk's `blocks` to come here (counted in
+// done[bi], which it returns to 0 for the next launch). Each block's count is a
+// device-scope release of what it stored, and the last block acquires it all.
+__device__ __forceinline__ bool last_block(CombLds &sh, uint32_t *done, uint32_t bi, uint32_t blocks)
+{
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t last = 1;
-        if (gridDim.x > 1) {
+        if (blocks > 1) {
             const uint32_t before =
                 __hip_atomic_fetch_add(&done[bi], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            last = before == gridDim.x - 1 ? 1u : 0u;
+            last = before == blocks - 1 ? 1u : 0u;
             if (last) done[bi] = 0;
         }
         sh.last = last;
     }
     __syncthreads();
-    if (!sh.last) return;
-    if (gridDim.x > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    finish_walk<kCombThreads>(sh.fin, w, be, bi, gridDim.x, (uint32_t)G, pure, out, pend, margin);
+    if (!sh.last) return false;
+    if (blocks > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    return true;
+}
+
+// Block blockIdx.x of a walk's `blocks` (blockIdx.y = batch position, b0 that of
+// blockIdx.y = 0). With TAIL the walk's last block to finish then makes its
+// selection (finish_walk) and sets the ambiguity flags; done holds one zeroed
+// counter per batch position.
+template <bool TAIL, Form FORM>
+__device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const BatchEntry &be, const Tables &tabs, int G,
+                                              int pure, ChoiceDev *out, uint32_t *pend, uint32_t *done,
+                                              double margin, uint32_t b0, uint32_t blocks)
+{
+    combine_part<TAIL, FORM>(sh, w, be, tabs, G, blocks, blockIdx.x, be.ksplit);
+    if (!TAIL) return;
+    const uint32_t bi = b0 + blockIdx.y;
+    if (!last_block(sh, done, bi, blocks)) return;
+    finish_walk<kCombThreads>(sh.fin, w, be, bi, blocks, (uint32_t)G, pure, out, pend, margin);
 }
 
 // The launches that make their selection in the last combine blocks.
