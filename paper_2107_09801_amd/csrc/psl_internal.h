@@ -258,7 +258,8 @@ struct PlanMem {
     double *F = nullptr;
     int32_t *P = nullptr;
 };
-// A plan for which the matrix path's memory cannot be had is made without it.
+// A plan for which the matrix path's memory cannot be had is made without it; so is
+// one of a forced shape.
 psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t n, uint32_t n_fixed,
                      uint32_t start_fixed, const EvalShape *force = nullptr, uint32_t force_items = 0,
                      PlanMem *mem = nullptr);

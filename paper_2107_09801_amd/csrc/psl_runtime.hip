@@ -786,7 +786,7 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
         if (mem) mem->used = used;
         return build_plan(ctx, pl, ids, n, n_fixed, start_fixed, force, force_items, mem, matrix);
     };
-    psl_status st = build(true);
+    psl_status st = build(!force);       // a forced shape is the table evaluation's
     if (st != PSL_E_NOMEM) return st;
     // without the matrix path, whose arrays come on top of the others; then in what
     // the other kept layouts hold
@@ -1483,7 +1483,8 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
     hipEvent_t e0, e1;
     HIP_TRY(ctx, hipEventCreate(&e0));
     HIP_TRY(ctx, hipEventCreate(&e1));
-    // mean time of one evaluation launch in a given shape and work-item target
+    // mean time of one launch of the table evaluation in a given shape and work-item
+    // target (the shape is its alone: a step on the matrix path has no use for it)
     auto time_eval = [&](const EvalShape &c, uint32_t items, double &avg) -> psl_status {
         BatchPlan tmp;
         psl_status s2 = make_plan(ctx, tmp, walk_ids, n, UINT32_MAX, 0, &c, items);
@@ -1493,24 +1494,11 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
             plan_free(ctx, tmp);
             return s2;
         }
-        hipError_t e = tmp.split ? launch_near_reset(tmp.d_batch, n, nullptr, nullptr, ctx->stream) : hipSuccess;
         const int reps = 2;
-        // a batch with matrix walks is timed with its preparation (the offsets
-        // are made from its totals); the near-peak lists start empty each time
-        if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-        for (int r = 0; r < reps && e == hipSuccess; ++r) {
-            if (tmp.split) {
-                s2 = launch_partials(ctx, tmp, tabs, n, nullptr, false, EvalCall{}, true);
-                if (!s2) e = launch_near_reset(tmp.d_batch, n, nullptr, nullptr, ctx->stream);
-            } else {
-                e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape, tmp.d_queues,
-                                nullptr, ctx->n_cu, ctx->stream);
-            }
-            if (s2) {
-                plan_free(ctx, tmp);
-                return s2;
-            }
-        }
+        hipError_t e = hipEventRecord(e0, ctx->stream);
+        for (int r = 0; r < reps && e == hipSuccess; ++r)
+            e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape, tmp.d_queues, nullptr,
+                            ctx->n_cu, ctx->stream);
         if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;
