@@ -790,7 +790,9 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     if (st != PSL_E_NOMEM) return st;
     // without the matrix path, whose arrays come on top of the others; then in what
     // the other kept layouts hold
-    if (pl.split) st = build(false);
+    const bool split = pl.split;
+    plan_free(ctx, pl);                  // nothing handed on: the memory is needed
+    if (split) st = build(false);
     if (st == PSL_E_NOMEM && !mem && plans_drop(ctx, &pl)) st = build(false);
     if (!st) ctx->err = err;
     return st;
