@@ -190,9 +190,10 @@ PSL_API psl_status psl_eval_neighbourhood(psl_ctx *ctx, uint32_t walk, uint32_t 
 
 /* psl_eval_neighbourhood for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same evaluation, kernels and results, but every scratch
- * array of the call (work items, k-split partial sums, chunk suffix arrays,
- * near-peak list, combine minima, the choice record) is carved from a fixed
+ * hipMalloc): the same evaluation, kernels and results, to the last bit of F,
+ * but every scratch array of the call (work items, partial sums, the matrix
+ * path's coefficients and prefix sums, chunk suffix arrays, near-peak list,
+ * combine minima, the choice record) is carved from a fixed
  * 64 MiB device array that each device the library runs on holds until the
  * process ends; the call makes no hipMalloc, hipFree or other device
  * allocation. F_dev and psl_dev are required (caller-owned device memory of
@@ -201,8 +202,10 @@ PSL_API psl_status psl_eval_neighbourhood(psl_ctx *ctx, uint32_t walk, uint32_t 
  * and leaves its contents behind (each call clears what must start at zero
  * with a kernel): calls that overlap on one device, from two contexts or two
  * threads, race. Errors: as psl_eval_neighbourhood; PSL_E_INVAL if F_dev or
- * psl_dev is NULL; PSL_E_NOMEM if the evaluation's scratch would exceed the
- * 64 MiB (the message gives the limit), with nothing launched. */
+ * psl_dev is NULL; PSL_E_NOMEM if the table evaluation's scratch would exceed
+ * the 64 MiB (the message gives the limit), with nothing launched. Where only
+ * the matrix path's (PSL_OPT_SPLIT) would, the table evaluation runs, whose F
+ * agree with the matrix path's to its error. */
 PSL_API psl_status psl_eval_neighbourhood_noalloc(psl_ctx *ctx, uint32_t walk, uint32_t start,
                                                   uint32_t n_lmt, double *F_dev, int32_t *psl_dev,
                                                   psl_choice *out);

@@ -646,17 +646,29 @@ hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, c
     return launch_seg_scan(walks, batch, m, s);
 }
 
-__global__ void k_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done)
+// A batch's counters and, of its matrix walks, the records after each
+// coefficient's last: zeros. One block per walk.
+__global__ __launch_bounds__(64) void k_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t *pend, uint32_t *done)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nb) batch[b].near[0] = 0;
-    if (b < nb && done) done[b] = 0;
-    if (b == 0 && pend) pend[0] = 0;
+    const BatchEntry be = batch[blockIdx.x];
+    if (threadIdx.x == 0) {
+        be.near[0] = 0;
+        if (done) done[blockIdx.x] = 0;
+        if (blockIdx.x == 0 && pend) pend[0] = 0;
+    }
+    if (!be.lsplit) return;
+    const uint32_t L = walks[be.slot].L;
+    uint32_t *one = reinterpret_cast<uint32_t *>(be.dig_one + (size_t)split_chunks(L) * kRecBytes);
+    uint32_t *both = reinterpret_cast<uint32_t *>(be.dig_both + (size_t)split_both_chunks(L) * 2 * kRecBytes);
+    for (uint32_t i = threadIdx.x; i < kRecPad * kRecBytes / 4; i += 64) one[i] = 0;
+    for (uint32_t i = threadIdx.x; i < kRecPad * 2 * kRecBytes / 4; i += 64) both[i] = 0;
 }
 
-hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done, hipStream_t s)
+hipError_t launch_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done,
+                              hipStream_t s)
 {
-    k_near_reset<<<(nb + 255) / 256, 256, 0, s>>>(batch, nb, pend, done);
+    if (nb == 0) return hipSuccess;
+    k_batch_reset<<<nb, 64, 0, s>>>(walks, batch, pend, done);
     return hipGetLastError();
 }
 

@@ -51,9 +51,11 @@ hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const Eval
 hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap *map,
                          uint32_t *pend, int scan, const EvalCall &call, hipStream_t s);
 hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const SegMap &map, hipStream_t s);
-// Zero the near-peak counts of a batch, its pending count and its combine
-// counters (done, nb entries; may be null) after its scratch is allocated.
-hipError_t launch_near_reset(const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done, hipStream_t s);
+// Zero the near-peak counts of a batch, its pending count, its combine counters
+// (done, nb entries; may be null) and its matrix walks' zero records after its
+// scratch is allocated.
+hipError_t launch_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done,
+                              hipStream_t s);
 // F and PSL per candidate from the partials, then the selection, its
 // ambiguity flags (margin: their relative margin) and, pure == 0, the step's
 // bookkeeping (pend: the pending list the walks that switch phase join), by
@@ -93,11 +95,10 @@ inline uint64_t pending_units(uint32_t L) { return (L - 1 + kPendUnit - 1) / kPe
 // their suffix values; *pend and *tab zeroed), then the matrix products
 // (items: walk, kMxTile-element tile, k-split), whose first items choose each
 // walk's path; *tab counts the walks left to the table evaluation, launched
-// after them. launch_rec_pad: once per batch layout, the zero records.
+// after them.
 hipError_t launch_prep(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs,
                        const SegMap &map, int scan, uint32_t *pend, uint32_t *tab, const EvalCall &call,
                        hipStream_t s);
-hipError_t launch_rec_pad(const BatchEntry *batch, const WalkDev *walks, uint32_t nb, hipStream_t s);
 hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
                      const Tables &tabs, uint32_t *tab, hipStream_t s);
 

@@ -557,8 +557,8 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         char *p;
         size_t bytes;
         ~Kept() { dev_free(ctx, p, false); }
-    } kept{ctx, pl.carved ? nullptr : pl.d_mx, pl.mx_bytes};
-    pl.d_mx = nullptr;
+    } kept{ctx, mem || pl.carved ? nullptr : pl.d_mx, pl.mx_bytes};
+    if (kept.p) pl.d_mx = nullptr;
     plan_free(ctx, pl);
     pl.ids.assign(ids, ids + n);
     pl.fixed_n = fixed ? n_fixed : 0;
@@ -581,7 +581,7 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     std::vector<EvalItem> &items = lay.items;
     std::vector<uint32_t> lsp(n, 0), nq(n, 0);
     std::vector<EvalItem> mitems;
-    if (matrix && !mem) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, nq, mitems);
+    if (matrix) mx_layout(ctx, Ls.data(), n_l.data(), n, lsp, nq, mitems);
     pl.split = !mitems.empty();
     if (pl.split) {
         // the combine adds a matrix walk's own partials
@@ -609,7 +609,7 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         n_cand += n_l[b];
         n_suf += suffix_len(Ls[b]);
     }
-    const uint64_t n_items = items.size();
+    const uint64_t n_items = items.size() + mitems.size();
     if (n_items >= (1ull << 31)) return fail(ctx, PSL_E_INVAL, "batch too large (%llu work items)",
                                              (unsigned long long)n_items);
     if (mem) {
@@ -627,12 +627,34 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         mem->used += need;
         return PSL_OK;
     };
+    // the matrix path's large arrays
+    size_t n_dig = 0, n_pre = 0, n_lp = 0;
+    for (uint32_t b = 0; b < n; ++b) {
+        if (!lsp[b]) continue;
+        n_dig += dig_bytes(Ls[b]);
+        n_pre += 2 * (size_t)Ls[b];
+        n_lp += (size_t)(lsp[b] + 1) * nq[b] * kMxTile;
+    }
+    auto padded = [](size_t bytes) { return align_up(bytes, 256); };
+    const size_t p_pre = padded(n_dig), p_lp = p_pre + padded(sizeof(double) * n_pre),
+                 large = p_lp + padded(sizeof(double) * n_lp);
     void *p;
     psl_status st;
-    if ((st = get(&p, sizeof(double) * n_part))) return st;
-    pl.d_fpart = (double *)p;
-    if ((st = get(&p, sizeof(uint32_t) * n_part))) return st;
-    pl.d_mpart = (uint32_t *)p;
+    if (mem) {
+        // fixed scratch has one place for the table evaluation's partials and the
+        // matrix path's large arrays: the former are written once the path is known
+        // not to be taken
+        const size_t p_m = padded(sizeof(double) * n_part);
+        if ((st = get(&p, std::max(p_m + sizeof(uint32_t) * n_part, large)))) return st;
+        pl.d_fpart = (double *)p;
+        pl.d_mpart = (uint32_t *)((char *)p + p_m);
+        pl.d_mx = (char *)p;
+    } else {
+        if ((st = get(&p, sizeof(double) * n_part))) return st;
+        pl.d_fpart = (double *)p;
+        if ((st = get(&p, sizeof(uint32_t) * n_part))) return st;
+        pl.d_mpart = (uint32_t *)p;
+    }
     if (mem) {
         pl.d_f = mem->F;
         pl.d_p = mem->P;
@@ -668,9 +690,9 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         pl.seg.tot = pl.d_segtot;
         pl.seg.tmax = pl.d_segmax;
     }
-    // matrix path: per walk of at least kSplitMinL elements (not for plans
-    // carved from fixed scratch, nor for launches with less work than
-    // kSplitMinCand candidates per shift): its digit records, prefix and partial
+    // matrix path: per walk of at least kSplitMinL elements (not for launches
+    // with less work than kSplitMinCand candidates per shift): its digit records,
+    // prefix and partial
     // sums and matrix items (walk, tile, k-split). Workgroup i runs on XCD
     // i mod 8: each walk's items (cost: the chunks of its k-split) form one
     // piece, or several of consecutive items when the walk holds more than
@@ -679,46 +701,36 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     // the queues, so XCD x takes queue x. A batch of many walks keeps each
     // walk's items (and its digits in L2) on one XCD, and one long walk spreads
     // over all eight; short queues are padded with kMxNoWalk items.
-    size_t n_dig = 0, n_pre = 0, n_lp = 0;
-    for (uint32_t b = 0; b < n; ++b) {
-        if (!lsp[b]) continue;
-        n_dig += dig_bytes(Ls[b]);
-        n_pre += 2 * (size_t)Ls[b];
-        n_lp += (size_t)(lsp[b] + 1) * nq[b] * kMxTile;
-    }
     if (pl.split) {
-        size_t at = 0;                  // one allocation, in pieces
+        size_t at = mem ? 0 : large;    // one allocation, in pieces
         auto piece = [&](size_t bytes) {
             const size_t o = at;
-            at += align_up(bytes, 256);
+            at += padded(bytes);
             return o;
         };
-        const size_t p_dig = piece(n_dig), p_pre = piece(sizeof(double) * n_pre), p_lp = piece(sizeof(double) * n_lp),
-                     p_ss = piece(sizeof(SplitState) * n), p_items = piece(sizeof(EvalItem) * mitems.size()),
-                     p_tab = piece(sizeof(uint32_t)), p_off = piece(3 * sizeof(double) * pl.seg.total);
-        if (!mem && kept.p && at <= kept.bytes && at >= kept.bytes / 4) {
-            pl.d_mx = kept.p;
+        const size_t p_ss = piece(sizeof(SplitState) * n), p_tab = piece(sizeof(uint32_t)),
+                     p_off = piece(3 * sizeof(double) * pl.seg.total);
+        char *rest;
+        if (kept.p && at <= kept.bytes && at >= kept.bytes / 4) {
+            rest = pl.d_mx = kept.p;
             pl.mx_bytes = kept.bytes;
             kept.p = nullptr;
         } else {
             if ((st = get(&p, at))) return st;
-            pl.d_mx = (char *)p;
+            rest = (char *)p;
+            if (!mem) pl.d_mx = rest;
             pl.mx_bytes = at;
         }
-        pl.d_dig = (uint8_t *)(pl.d_mx + p_dig);
+        pl.d_dig = (uint8_t *)pl.d_mx;
         pl.d_pre = (double *)(pl.d_mx + p_pre);
         pl.d_lpart = (double *)(pl.d_mx + p_lp);
-        pl.d_ss = (SplitState *)(pl.d_mx + p_ss);
-        pl.d_mitems = (EvalItem *)(pl.d_mx + p_items);
-        pl.d_tab = (uint32_t *)(pl.d_mx + p_tab);
-        pl.d_segoff = (double *)(pl.d_mx + p_off);
+        pl.d_ss = (SplitState *)(rest + p_ss);
+        pl.d_tab = (uint32_t *)(rest + p_tab);
+        pl.d_segoff = (double *)(rest + p_off);
         pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
         uint64_t updates = 0;
         for (uint32_t b = 0; b < n; ++b) updates = std::max(updates, (uint64_t)n_l[b] * (Ls[b] - 1));
         pl.left_blocks = pl.all_split ? select_left_blocks(n, pl.comb_blocks, updates) : 0;
-        pl.n_mitems = (uint32_t)mitems.size();
-        HIP_TRY(ctx, hipMemcpy(pl.d_mitems, mitems.data(), sizeof(EvalItem) * mitems.size(),
-                               hipMemcpyHostToDevice));
     }
     std::vector<BatchEntry> be(n);
     size_t op = 0, oc = 0, os = 0;
@@ -763,17 +775,20 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     }
     if ((st = get(&p, sizeof(BatchEntry) * n))) return st;
     pl.d_batch = (BatchEntry *)p;
+    // the table evaluation's items, then the matrix path's
+    pl.n_items = (uint32_t)items.size();
+    pl.n_mitems = (uint32_t)mitems.size();
+    items.insert(items.end(), mitems.begin(), mitems.end());
     if ((st = get(&p, sizeof(EvalItem) * std::max<size_t>(items.size(), 1)))) return st;
     pl.d_items = (EvalItem *)p;
+    pl.d_mitems = pl.d_items + pl.n_items;
     if ((st = get(&p, sizeof(EvalQueues)))) return st;
     pl.d_queues = (EvalQueues *)p;
     HIP_TRY(ctx, hipMemcpy(pl.d_queues, &lay.queues, sizeof(EvalQueues), hipMemcpyHostToDevice));
     HIP_TRY(ctx, hipMemcpy(pl.d_batch, be.data(), sizeof(BatchEntry) * n, hipMemcpyHostToDevice));
     HIP_TRY(ctx, hipMemcpy(pl.d_items, items.data(), sizeof(EvalItem) * items.size(),
                            hipMemcpyHostToDevice));
-    HIP_TRY(ctx, launch_near_reset(pl.d_batch, n, pl.d_pend, pl.d_done, ctx->stream));
-    if (pl.split) HIP_TRY(ctx, launch_rec_pad(pl.d_batch, ctx->d_walks, n, ctx->stream));
-    pl.n_items = (uint32_t)items.size();
+    HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, pl.d_batch, n, pl.d_pend, pl.d_done, ctx->stream));
     return PSL_OK;
 }
 
@@ -1296,17 +1311,25 @@ psl_status psl_eval_neighbourhood_noalloc(psl_ctx *ctx, uint32_t walk, uint32_t 
         return st;
     }
     const Tables tabs = tables_of(ctx);
-    if ((st = launch_partials(ctx, pl, tabs, 1, nullptr, false, EvalCall{}, true))) {
-        plan_free(ctx, pl);
-        return st;
-    }
-    HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, 1, pl.comb_blocks, pl.comb_group, tabs, 1, d_choice,
-                               nullptr, pl.d_done, ctx->amb_margin, ctx->stream));
     alignas(16) unsigned char host[256];
     if (choice_dev_size() > sizeof host) return fail(ctx, PSL_E_STATE, "choice record too large");
-    HIP_TRY(ctx, hipMemcpyAsync(host, d_choice, choice_dev_size(), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    auto select = [&](int pure) -> psl_status {
+        HIP_TRY(ctx, launch_select(ctx->d_walks, pl.d_batch, 1, pl.comb_blocks, pl.comb_group, tabs, pure, d_choice,
+                                   nullptr, pl.d_done, ctx->amb_margin, ctx->stream));
+        HIP_TRY(ctx, hipMemcpyAsync(host, d_choice, choice_dev_size(), hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        return PSL_OK;
+    };
+    st = launch_partials(ctx, pl, tabs, 1, nullptr, false, EvalCall{}, false);
+    if (!st) st = select(1);
+    if (!st && choice_dev_table(host)) {
+        // the matrix path does not take the walk as it is now
+        HIP_TRY(ctx, launch_eval(ctx->d_walks, pl.d_batch, pl.d_items, pl.n_items, tabs, pl.shape, pl.d_queues, pl.d_tab,
+                                 ctx->n_cu, ctx->stream));
+        st = select(2);
+    }
     plan_free(ctx, pl);
+    if (st) return st;
     if (out) {
         memset(out, 0, sizeof *out);
         choice_dev_unpack(host, &out->i_best, &out->j_best, &out->F_best, &out->F_min, &out->j_psl,

@@ -803,24 +803,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     for (int q = 0; q < 4; ++q) out[q] = v[q];          // rows past L - 1: not read
 }
 
-// The records after each coefficient's last: zeros.
-__global__ void k_rec_pad(const BatchEntry *batch, const WalkDev *walks)
-{
-    const BatchEntry be = batch[blockIdx.x];
-    if (!be.lsplit) return;
-    const uint32_t L = walks[be.slot].L;
-    uint32_t *one = reinterpret_cast<uint32_t *>(be.dig_one + (size_t)split_chunks(L) * kRecBytes);
-    uint32_t *both = reinterpret_cast<uint32_t *>(be.dig_both + (size_t)split_both_chunks(L) * 2 * kRecBytes);
-    for (uint32_t i = threadIdx.x; i < kRecPad * kRecBytes / 4; i += blockDim.x) one[i] = 0;
-    for (uint32_t i = threadIdx.x; i < kRecPad * 2 * kRecBytes / 4; i += blockDim.x) both[i] = 0;
-}
-
-hipError_t launch_rec_pad(const BatchEntry *batch, const WalkDev *walks, uint32_t nb, hipStream_t s)
-{
-    k_rec_pad<<<nb, 256, 0, s>>>(batch, walks);
-    return hipGetLastError();
-}
-
 hipError_t launch_mx(const WalkDev *walks, const BatchEntry *batch, const EvalItem *items, uint32_t n_items,
                      const Tables &tabs, uint32_t *tab, hipStream_t s)
 {

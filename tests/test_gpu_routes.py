@@ -1,7 +1,10 @@
 """Batches that mix matrix and table walks, the table evaluation's launch shapes
-on walks that would take the matrix path, and what the autotuner times."""
+on walks that would take the matrix path, what the autotuner times, and the
+evaluation without allocations."""
 import numpy as np
 import pytest
+
+import seeded_inputs as si
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +83,23 @@ def test_autotune_times_the_table_evaluation(ctx, L, n_lmt):
     b = ctx.autotune(ids)
     for k in ("default_ms", "eval_ms"):
         assert 0.6 < a[k] / b[k] < 1.7, (k, a[k], b[k])
+
+
+@pytest.mark.parametrize("L,alpha,start,n", [(300, 4, 7, 300), (512, 13, 511, 512), (1001, 4, 17, 1001), (2049, 16, 0, 600),
+                                             (16383, 13, 5, 16383), (16383, 4, 16000, 511), (131071, 10, 131000, 6912),
+                                             (131071, 4, 9, 131071), (1048575, 4, 77, 1024)])
+@pytest.mark.parametrize("limit", [-1, 1])
+def test_noalloc_gives_the_same_bits(ctx, L, alpha, start, n, limit):
+    """The call without allocations: the same evaluation, so the same F to the last
+    bit, on either path."""
+    import torch
+    from paper_2107_09801_amd import libpsl
+    ctx.set_option(libpsl.OPT_NEAR_LIMIT, limit)
+    (w,) = ctx.init_walks(L, 1, 1, alpha1=alpha, n_lmt=1, init_bits=[si.random_bits(L, L + alpha)])
+    res = []
+    for call in (ctx.eval_neighbourhood, ctx.eval_neighbourhood_noalloc, ctx.eval_neighbourhood_noalloc):
+        F = torch.empty(n, dtype=torch.float64, device="cuda:0")
+        P = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        res.append((call(w, start, n, F, P), F.cpu().numpy(), P.cpu().numpy()))
+    for ch, F, P in res[1:]:
+        assert np.array_equal(F, res[0][1]) and np.array_equal(P, res[0][2]) and ch == res[0][0]
