@@ -954,6 +954,23 @@ psl_status capture_steps(psl_ctx *ctx, BatchPlan &pl, const Tables &tabs, uint32
     return PSL_OK;
 }
 
+// Whether kernels may store n entries to a caller's array: aligned, and within an
+// allocation of the context's device. (A copy also reaches other memory, and is
+// refused past an allocation's end, where a store would fault or overwrite.)
+static bool kernels_write(const psl_ctx *ctx, const void *p, size_t entry, size_t n)
+{
+    if (!p || (uintptr_t)p % entry) return false;
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != ctx->device ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return n * entry <= size - (size_t)((const char *)p - (const char *)base);
+}
+
 // The context's one-walk batch entry (psl_apply_flip, psl_restore_walk) for
 // walk `slot`, with the arrays of its fitness sums and its block counter,
 // allocated on first use and kept until the context is destroyed.
@@ -1248,8 +1265,9 @@ psl_status psl_eval_neighbourhood(psl_ctx *ctx, uint32_t walk, uint32_t start, u
         const psl_status st = make_plan(ctx, pp, &walk, 1, n_lmt, start);
         if (st) return st;
     }
-    // the kernels write aligned output arrays themselves
-    const bool own_f = !F_dev || (uintptr_t)F_dev % sizeof(double), own_p = !psl_dev || (uintptr_t)psl_dev % sizeof(int32_t);
+    // the kernels write aligned output arrays in this device's memory themselves
+    const bool own_f = !kernels_write(ctx, F_dev, sizeof(double), n_lmt),
+               own_p = !kernels_write(ctx, psl_dev, sizeof(int32_t), n_lmt);
     const EvalCall call{own_f ? pp.d_f : F_dev, own_p ? pp.d_p : psl_dev, start, 1};
     const Tables tabs = tables_of(ctx);
     // the choice record lies in pinned host memory: the kernel that selects

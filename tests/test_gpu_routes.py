@@ -1,6 +1,9 @@
 """Batches that mix matrix and table walks, the table evaluation's launch shapes
 on walks that would take the matrix path, what the autotuner times, and the
-evaluation without allocations."""
+evaluation call's other forms: without allocations, and into memory that kernels
+cannot write."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -103,3 +106,21 @@ def test_noalloc_gives_the_same_bits(ctx, L, alpha, start, n, limit):
         res.append((call(w, start, n, F, P), F.cpu().numpy(), P.cpu().numpy()))
     for ch, F, P in res[1:]:
         assert np.array_equal(F, res[0][1]) and np.array_equal(P, res[0][2]) and ch == res[0][0]
+
+
+@pytest.mark.parametrize("L,n", [(300, 300), (1001, 1001), (16383, 700)])
+def test_evaluation_into_host_memory(ctx, L, n):
+    """Output arrays in pageable host memory, which a kernel cannot write, are copied
+    to; so are pinned ones."""
+    import torch
+    from paper_2107_09801_amd import libpsl
+    (w,) = ctx.init_walks(L, 1, 9, n_lmt=1)
+    F = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    P = torch.empty(n, dtype=torch.int32, device="cuda:0")
+    want = ctx.eval_neighbourhood(w, 3, n, F, P)
+    for pin in (True, False):
+        Fh = torch.zeros(n, dtype=torch.float64, pin_memory=pin)
+        Ph = torch.zeros(n, dtype=torch.int32, pin_memory=pin)
+        ch = libpsl.Choice()
+        ctx._check(libpsl.lib().psl_eval_neighbourhood(ctx._h, w, 3, n, Fh.data_ptr(), Ph.data_ptr(), ctypes.byref(ch)))
+        assert torch.equal(Fh, F.cpu()) and torch.equal(Ph, P.cpu()) and ch.as_dict() == want
