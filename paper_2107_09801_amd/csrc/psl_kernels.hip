@@ -78,9 +78,8 @@ __global__ void k_init_bits(WalkDev *walks, const InitRec *recs, const uint64_t 
 // flip position, and flip f reads elements p_f and p_f +- k; so for every k
 // outside D = {|p_f - p_g| : g < f} the update can read local_best's bits
 // directly, and the shifts in D take the sequential bits.
-__device__ __forceinline__ int32_t switch_flip_delta(const uint64_t *lb, uint32_t L, uint32_t k, uint32_t p)
+__device__ __forceinline__ int32_t switch_flip_delta(const uint64_t *lb, uint32_t L, uint32_t k, uint32_t p, int sp)
 {
-    const int sp = get_bit(lb, p) ? -1 : 1;
     int d = 0;
     if (p + k < L) d += get_bit(lb, p + k) ? -1 : 1;
     if (k <= p) d += get_bit(lb, p - k) ? -1 : 1;
@@ -473,6 +472,7 @@ __device__ __forceinline__ void apply_range(int32_t *__restrict__ C, int32_t *__
 // a launch of its own before: 5 us of a single walk's step, switching or not).
 struct SwitchLds {
     uint32_t fl[kFlipIncremental];
+    int sign[kFlipIncremental];         // of local_best's elements there
     uint32_t in[(1u << kSegShiftMax) / 32];
     PendLds pend;
 };
@@ -481,7 +481,11 @@ __device__ __forceinline__ void switch_range(SwitchLds &sh, WalkDev &w, const Ba
 {
     const uint32_t L = w.L, nf = w.n_flips;
     const uint64_t *lb = w.local_best;
-    if (threadIdx.x < nf) sh.fl[threadIdx.x] = w.flips[threadIdx.x];
+    if (threadIdx.x < nf) {
+        const uint32_t p = w.flips[threadIdx.x];
+        sh.fl[threadIdx.x] = p;
+        sh.sign[threadIdx.x] = get_bit(lb, p) ? -1 : 1;
+    }
     if (threadIdx.x < (1u << kSegShiftMax) / 32) sh.in[threadIdx.x] = 0;
     __syncthreads();
     for (uint32_t pr = threadIdx.x; pr < nf * nf; pr += kApplyThreads) {
@@ -508,7 +512,8 @@ __device__ __forceinline__ void switch_range(SwitchLds &sh, WalkDev &w, const Ba
         if ((sh.in[o >> 5] >> (o & 31u)) & 1u)
             c = switch_corr_seq(lb, c, L, k, sh.fl, nf);
         else
-            for (uint32_t f = 0; f < nf; ++f) c += switch_flip_delta(lb, L, k, sh.fl[f]);
+#pragma unroll 4
+            for (uint32_t f = 0; f < nf; ++f) c += switch_flip_delta(lb, L, k, sh.fl[f], sh.sign[f]);
         w.C[k] = c;
         const uint32_t a = (uint32_t)(c < 0 ? -c : c);
         nsum_add(ts, tc, T[a]);
@@ -520,7 +525,14 @@ __device__ __forceinline__ void switch_range(SwitchLds &sh, WalkDev &w, const Ba
 // Of a walk whose F and PSL are new with this update (a switched phase, a forced
 // flip) the last block to finish, counted in done[bi] (zero between launches),
 // adds up the segments' sums. (A launch of its own for that took 3.6 us of a
-// single walk's step, switching or not, and 4.5 us of a forced flip.)
+// single walk's step, switching or not, and 4.5 us of a forced flip.) Each count
+// is a device-scope release of the stored C, which the blocks of an XCD make one
+// after another (about 40 ns each): with 16 flips at most, about kSwitchBlocks blocks of a
+// launch take switched walks' segments, each several in turn. Steps that switch
+// with 10 flips, N_lmt = 256, us, against a block per segment: one walk at
+// L = 1048575 (2048 segments) 181 -> 141, four 290 -> 261, one at L = 524287
+// 113 -> 100; with 64 flips, whose shifts in D cost most, 512 blocks took 1700 for 527.
+constexpr uint32_t kSwitchBlocks = 1024, kSwitchFew = 16;
 __global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const BatchEntry *batch, Tables tabs,
                                                          int64_t j_fixed, SegMap map, uint32_t *done)
 {
@@ -545,22 +557,28 @@ __global__ __launch_bounds__(kApplyThreads) void k_apply(WalkDev *walks, const B
     const bool lb = moved && (w.flags & STEP_IMPROVED);
     const uint32_t k0 = 1u + (seg << map.shift);
     const uint32_t k1 = min(L, k0 + (1u << map.shift));
+    const uint32_t n = seg_count(L, map.shift);
+    uint32_t blocks = n;                // that count themselves
     double ts = 0.0, tc = 0.0;
     uint32_t tm = 0;
     if (!moved) {
         apply_range<true>(w.C, w.C_lb, b, L, j, sj, lb, k0, k1, tabs.T[w.alpha], ts, tc, tm);
         pend_store(sh.pend, ts, tc, tm, be, seg);
     } else if (switched && w.n_flips <= kFlipIncremental) {
-        switch_range(sh, w, be, tabs.T[w.alpha], j, sj, lb, k0, k1, seg);
+        if (w.n_flips <= kSwitchFew) blocks = min(n, max(kSwitchBlocks / map.nb, 128u));
+        if (seg >= blocks) return;
+        for (uint32_t x = seg; x < n; x += blocks) {
+            const uint32_t x0 = 1u + (x << map.shift);
+            switch_range(sh, w, be, tabs.T[w.alpha], j, sj, lb, x0, min(L, x0 + (1u << map.shift)), x);
+        }
     } else {
         apply_range<false>(w.C, w.C_lb, b, L, j, sj, lb, k0, k1, nullptr, ts, tc, tm);
         return;
     }
-    const uint32_t n = seg_count(L, map.shift);
     if (threadIdx.x == 0) {             // it stored the segment's sums
         s_last = 1;
-        if (n > 1) {
-            s_last = __hip_atomic_fetch_add(&done[bi], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (blocks > 1) {
+            s_last = __hip_atomic_fetch_add(&done[bi], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == blocks - 1;
             if (s_last) done[bi] = 0;
         }
     }
