@@ -510,16 +510,18 @@ void k_eval_strided(const WalkDev *__restrict__ walks, const BatchEntry *__restr
 // The combine of a step of matrix walks, with the table evaluation of a walk that
 // the matrix path does not take in it: the walk's blocks, with those past the
 // first `blocks` that have nothing else to do, share out its tiles of 256
-// candidates, in as many k-splits as give each block an item, and the last to
-// finish adds the partials and makes the selection. A launch that looks and
+// candidates, in as many k-splits as give each block an item; the last to finish a
+// group of tiles (at most kCombMaxBlocks groups, counted in left) adds its
+// partials, and the last group makes the selection. A launch that looks and
 // returns (k_eval_strided) costs every step 3 to 4 us of about 40 (one walk at
 // L = 16383), 1024 blocks here instead of 128 nothing; steps that need it are
 // rare, but those of a walk whose near-peak list overflows tend to follow each
 // other. Such a step, us, here and without the matrix path: L = 131071 N_lmt = 512
-// 97 / 33, L = 1048575 N_lmt = 512 221 / 115, L = 65535 N_lmt = 6912 244 / 77 (with
+// 83 / 33, L = 1048575 N_lmt = 512 189 / 115, L = 65535 N_lmt = 6912 115 / 76 (with
 // every block evaluating the tiles of its own candidates, one k-split after another,
-// 3140, 24900 and 1600), L = 16383 N_lmt = 16383 315 / 63.
-__global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, const BatchEntry *batch, Tables tabs, int G,
+// 3140, 24900 and 1600), L = 16383 N_lmt = 16383 138 / 63. Four wavefronts per SIMD:
+// with three, 1024 blocks do not start at once, and every step takes 2 us more.
+__global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_combine_left(WalkDev *walks, const BatchEntry *batch, Tables tabs, int G,
                                                                uint32_t *pend, uint32_t *done, double margin,
                                                                uint32_t blocks)
 {
@@ -530,23 +532,36 @@ __global__ __launch_bounds__(kCombThreads) void k_combine_left(WalkDev *walks, c
     } sh;
     const BatchEntry be = batch[blockIdx.y];
     WalkDev &w = walks[be.slot];
+    uint32_t parts = blocks;                // the combine blocks of the selection
     if (!be.ss->use) {
         const uint32_t tiles = ((be.fixed ? be.n_lmt : w.n_lmt) + 255) / 256;
         const uint32_t ks = min(be.ksplit, max(1u, gridDim.x / tiles));
+        const uint32_t per = (tiles + kCombMaxBlocks - 1) / kCombMaxBlocks, groups = (tiles + per - 1) / per;
+        parts = 0;
+        uint32_t *left = done + gridDim.y + kCombMaxBlocks * blockIdx.y;
         for (uint32_t x = blockIdx.x; x < tiles * ks; x += gridDim.x) {
             int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
             asm volatile("" : "+v"(tid));
             __builtin_assume(tid >= 0 && tid < 256);
             eval_item<4, true>(sh.eval, walks, batch, EvalItem{blockIdx.y, x % tiles, x / tiles, 0}, tabs, tid, ks);
-            __syncthreads();                // the next item, or the combine, takes the LDS
+            const uint32_t g = x % tiles / per;
+            if (last_block(sh.comb, left, g, min(per, tiles - g * per) * ks)) {
+                combine_part<true, Form::table>(sh.comb, w, be, tabs, 1, groups, g, ks);
+                if (last_block(sh.comb, done, blockIdx.y, groups)) {
+                    parts = groups;
+                    break;
+                }
+            }
+            __syncthreads();                // the next item takes the LDS
         }
-        if (!last_block(sh.comb, done, blockIdx.y, gridDim.x)) return;
-        combine_part<true, Form::table>(sh.comb, w, be, tabs, 1, 1, 0, ks);
-        finish_walk<kCombThreads>(sh.comb.fin, w, be, blockIdx.y, 1, 1, 0, nullptr, pend, margin);
-        return;
+        if (!parts) return;
+        G = 1;
+    } else {
+        if (blockIdx.x >= blocks) return;
+        combine_part<true, Form::matrix>(sh.comb, w, be, tabs, G, blocks, blockIdx.x, 0);
+        if (!last_block(sh.comb, done, blockIdx.y, blocks)) return;
     }
-    if (blockIdx.x < blocks)
-        combine_block<true, Form::matrix>(sh.comb, w, be, tabs, G, 0, nullptr, pend, done, margin, 0, blocks);
+    finish_walk<kCombThreads>(sh.comb.fin, w, be, blockIdx.y, parts, (uint32_t)G, 0, nullptr, pend, margin);
 }
 
 __global__ void k_queue_reset(EvalQueues *queues)
@@ -573,12 +588,13 @@ static void launch_eval_waves(const WalkDev *walks, const BatchEntry *batch, con
 
 // Blocks for items of at least 2^17 updates (smaller ones cost more to add up than
 // they save: L = 131071 N_lmt = 512 97 us in 512 blocks, 132 in 1024), and at most
-// 1024 in all (1536: 2 us of every step). Past 2^31 updates the last block's adding
-// takes too long (L = 131071, all candidates: 6.3 ms, in launches of its own 0.95),
-// and the launch that looks is 2 % of a step.
+// 1024 in all (1536: 2 us of every step). From 2^36 updates on, where the launch
+// that looks is half a per cent of a step, that: blocks of four wavefronts make a
+// table evaluation of all candidates 4 to 8 times as long (L = 131071 9.1 ms, 1.1 in
+// the 16 wavefronts of its own launch).
 uint32_t select_left_blocks(uint32_t nb, uint32_t comb_blocks, uint64_t updates)
 {
-    if (!comb_small(nb, comb_blocks) || updates > 1ull << 31) return 0;
+    if (!comb_small(nb, comb_blocks) || updates >= 1ull << 36) return 0;
     return std::max(comb_blocks, (uint32_t)std::min<uint64_t>(1024 / nb, updates >> 17));
 }
 

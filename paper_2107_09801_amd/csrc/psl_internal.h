@@ -110,7 +110,8 @@ struct BatchPlan {
     int32_t *d_p = nullptr;
     SelPart *d_red = nullptr;
     uint32_t *d_pend = nullptr;       // pending list: count, then batch positions
-    uint32_t *d_done = nullptr;       // per batch position: combine blocks finished (0 between launches)
+    uint32_t *d_done = nullptr;       // per batch position: blocks finished (0 between launches); with left_blocks
+                                      // also of each group of table tiles
     uint32_t fixed_n = 0;             // plans of a fixed neighbourhood: its N_lmt (0: not fixed)
     uint32_t *d_seg = nullptr;        // segment map of the O(L) passes
     double *d_segtot = nullptr;       // per segment: chunk-sum total (suffix pass)

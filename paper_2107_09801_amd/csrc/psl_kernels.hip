@@ -386,6 +386,10 @@ __global__ __launch_bounds__(kSegScanThreads) void k_seg_scan(const WalkDev *wal
 
 // ------------------------------------------------------- selection
 
+// Block blockIdx.x of a walk's gridDim.x (blockIdx.y = batch position, b0 that of
+// blockIdx.y = 0). With TAIL the walk's last block to finish then makes its
+// selection (finish_walk) and sets the ambiguity flags; done holds one zeroed
+// counter per batch position.
 template <bool TAIL>
 __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const BatchEntry *batch, Tables tabs,
                                                           int G, int pure, ChoiceDev *out, uint32_t *pend,
@@ -393,7 +397,11 @@ __global__ __launch_bounds__(kCombThreads) void k_combine(WalkDev *walks, const 
 {
     __shared__ CombLds sh;
     const BatchEntry be = batch[blockIdx.y];
-    combine_block<TAIL, Form::either>(sh, walks[be.slot], be, tabs, G, pure, out, pend, done, margin, b0, gridDim.x);
+    WalkDev &w = walks[be.slot];
+    combine_part<TAIL, Form::either>(sh, w, be, tabs, G, gridDim.x, blockIdx.x, be.ksplit);
+    const uint32_t bi = b0 + blockIdx.y;
+    if (!TAIL || !last_block(sh, done, bi, gridDim.x)) return;
+    finish_walk<kCombThreads>(sh.fin, w, be, bi, gridDim.x, (uint32_t)G, pure, out, pend, margin);
 }
 
 // The selection of a walk, its ambiguity flags and (pure == 0) its
@@ -666,14 +674,17 @@ hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, c
 
 // A batch's counters and, of its matrix walks, the records after each
 // coefficient's last: zeros. One block per walk.
-__global__ __launch_bounds__(64) void k_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t *pend, uint32_t *done)
+__global__ __launch_bounds__(64) void k_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t *pend, uint32_t *done,
+                                                    bool left)
 {
     const BatchEntry be = batch[blockIdx.x];
     if (threadIdx.x == 0) {
         be.near[0] = 0;
-        if (done) done[blockIdx.x] = 0;
-        if (blockIdx.x == 0 && pend) pend[0] = 0;
+        done[blockIdx.x] = 0;
+        if (blockIdx.x == 0) pend[0] = 0;
     }
+    if (left)
+        for (uint32_t i = threadIdx.x; i < kCombMaxBlocks; i += 64) done[gridDim.x + kCombMaxBlocks * blockIdx.x + i] = 0;
     if (!be.lsplit) return;
     const uint32_t L = walks[be.slot].L;
     uint32_t *one = reinterpret_cast<uint32_t *>(be.dig_one + (size_t)split_chunks(L) * kRecBytes);
@@ -683,10 +694,11 @@ __global__ __launch_bounds__(64) void k_batch_reset(const WalkDev *walks, const 
 }
 
 hipError_t launch_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done,
-                              hipStream_t s)
+                              bool left, hipStream_t s)
 {
     if (nb == 0) return hipSuccess;
-    k_batch_reset<<<nb, 64, 0, s>>>(walks, batch, pend, done);
+    if (!pend || !done) return hipErrorInvalidValue;
+    k_batch_reset<<<nb, 64, 0, s>>>(walks, batch, pend, done, left);
     return hipGetLastError();
 }
 

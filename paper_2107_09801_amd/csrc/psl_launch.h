@@ -51,11 +51,11 @@ hipError_t launch_eval(const WalkDev *walks, const BatchEntry *batch, const Eval
 hipError_t launch_suffix(const WalkDev *walks, BatchEntry *batch, uint32_t nb, const Tables &tabs, const SegMap *map,
                          uint32_t *pend, int scan, const EvalCall &call, hipStream_t s);
 hipError_t launch_seg_scan(const WalkDev *walks, const BatchEntry *batch, const SegMap &map, hipStream_t s);
-// Zero the near-peak counts of a batch, its pending count, its combine counters
-// (done, nb entries; may be null) and its matrix walks' zero records after its
-// scratch is allocated.
+// Zero the near-peak counts of a batch, its pending count, its counters (done: nb;
+// with left, kCombMaxBlocks more for each walk) and its matrix walks' zero
+// records after its scratch is allocated.
 hipError_t launch_batch_reset(const WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t *pend, uint32_t *done,
-                              hipStream_t s);
+                              bool left, hipStream_t s);
 // F and PSL per candidate from the partials, then the selection, its
 // ambiguity flags (margin: their relative margin) and, pure == 0, the step's
 // bookkeeping (pend: the pending list the walks that switch phase join), by
@@ -71,7 +71,8 @@ hipError_t launch_select(WalkDev *walks, const BatchEntry *batch, uint32_t nb, u
 // launch_select of a step whose walks are all matrix walks, where
 // select_left_blocks (updates: N_lmt x (L-1) of the walk with the most) gives the
 // blocks per walk (grid) and not 0: a walk left to the table evaluation is
-// evaluated here, so that no launch_eval comes before.
+// evaluated here, so that no launch_eval comes before. done: nb counters, then
+// kCombMaxBlocks for each walk; entries' red: kCombMaxBlocks.
 uint32_t select_left_blocks(uint32_t nb, uint32_t comb_blocks, uint64_t updates);
 hipError_t launch_select_left(WalkDev *walks, const BatchEntry *batch, uint32_t nb, uint32_t comb_blocks,
                               uint32_t comb_group, uint32_t grid, const Tables &tabs, uint32_t *pend, uint32_t *done,

@@ -603,6 +603,14 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     pl.shape = lay.shape;
     pl.comb_blocks = lay.comb_blocks;
     pl.comb_group = lay.comb_group;
+    pl.all_split = pl.split && std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
+    if (pl.all_split && !fixed) {
+        uint64_t updates = 0;
+        for (uint32_t b = 0; b < n; ++b) updates = std::max(updates, (uint64_t)n_l[b] * (Ls[b] - 1));
+        pl.left_blocks = select_left_blocks(n, pl.comb_blocks, updates);
+    }
+    const uint32_t n_red = pl.left_blocks ? kCombMaxBlocks : pl.comb_blocks;
+    const size_t n_done = pl.left_blocks ? (size_t)n * (1 + kCombMaxBlocks) : n;
     size_t n_part = 0, n_cand = 0, n_suf = 0;
     for (uint32_t b = 0; b < n; ++b) {
         n_part += (size_t)ks[b] * n_l[b];
@@ -670,11 +678,11 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     pl.d_m0 = (uint32_t *)p;
     if ((st = get(&p, sizeof(uint32_t) * (kNearCap + 1) * n))) return st;
     pl.d_near = (uint32_t *)p;
-    if ((st = get(&p, sizeof(SelPart) * pl.comb_blocks * n))) return st;
+    if ((st = get(&p, sizeof(SelPart) * n_red * n))) return st;
     pl.d_red = (SelPart *)p;
     if ((st = get(&p, sizeof(uint32_t) * (n + 1)))) return st;
     pl.d_pend = (uint32_t *)p;
-    if ((st = get(&p, sizeof(uint32_t) * n))) return st;
+    if ((st = get(&p, sizeof(uint32_t) * n_done))) return st;
     pl.d_done = (uint32_t *)p;
     std::vector<uint32_t> off(n + 1);
     {
@@ -727,10 +735,6 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         pl.d_ss = (SplitState *)(rest + p_ss);
         pl.d_tab = (uint32_t *)(rest + p_tab);
         pl.d_segoff = (double *)(rest + p_off);
-        pl.all_split = std::find(lsp.begin(), lsp.end(), 0u) == lsp.end();
-        uint64_t updates = 0;
-        for (uint32_t b = 0; b < n; ++b) updates = std::max(updates, (uint64_t)n_l[b] * (Ls[b] - 1));
-        pl.left_blocks = pl.all_split ? select_left_blocks(n, pl.comb_blocks, updates) : 0;
     }
     std::vector<BatchEntry> be(n);
     size_t op = 0, oc = 0, os = 0;
@@ -745,7 +749,7 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         e.S0 = pl.d_s0 + os;
         e.M0 = pl.d_m0 + os;
         e.near = pl.d_near + (size_t)(kNearCap + 1) * b;
-        e.red = pl.d_red + (size_t)pl.comb_blocks * b;
+        e.red = pl.d_red + (size_t)n_red * b;
         os += suffix_len(ctx->walks[ids[b]].L);
         e.slot = ids[b];
         e.ksplit = ks[b];
@@ -788,7 +792,7 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     HIP_TRY(ctx, hipMemcpy(pl.d_batch, be.data(), sizeof(BatchEntry) * n, hipMemcpyHostToDevice));
     HIP_TRY(ctx, hipMemcpy(pl.d_items, items.data(), sizeof(EvalItem) * items.size(),
                            hipMemcpyHostToDevice));
-    HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, pl.d_batch, n, pl.d_pend, pl.d_done, ctx->stream));
+    HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, pl.d_batch, n, pl.d_pend, pl.d_done, pl.left_blocks != 0, ctx->stream));
     return PSL_OK;
 }
 

@@ -484,8 +484,8 @@ __device__ __forceinline__ void combine_part(CombLds &sh, WalkDev &w, const Batc
     }
 }
 
-// Whether the block is the last of the walk's `blocks` to come here (counted in
-// done[bi], which it returns to 0 for the next launch). Each block's count is a
+// Whether the block is the last of `blocks` to come here (counted in done[bi],
+// which it returns to 0 for the next launch). Each block's count is a
 // device-scope release of what it stored, and the last block acquires it all.
 __device__ __forceinline__ bool last_block(CombLds &sh, uint32_t *done, uint32_t bi, uint32_t blocks)
 {
@@ -504,22 +504,6 @@ __device__ __forceinline__ bool last_block(CombLds &sh, uint32_t *done, uint32_t
     if (!sh.last) return false;
     if (blocks > 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     return true;
-}
-
-// Block blockIdx.x of a walk's `blocks` (blockIdx.y = batch position, b0 that of
-// blockIdx.y = 0). With TAIL the walk's last block to finish then makes its
-// selection (finish_walk) and sets the ambiguity flags; done holds one zeroed
-// counter per batch position.
-template <bool TAIL, Form FORM>
-__device__ __forceinline__ void combine_block(CombLds &sh, WalkDev &w, const BatchEntry &be, const Tables &tabs, int G,
-                                              int pure, ChoiceDev *out, uint32_t *pend, uint32_t *done,
-                                              double margin, uint32_t b0, uint32_t blocks)
-{
-    combine_part<TAIL, FORM>(sh, w, be, tabs, G, blocks, blockIdx.x, be.ksplit);
-    if (!TAIL) return;
-    const uint32_t bi = b0 + blockIdx.y;
-    if (!last_block(sh, done, bi, blocks)) return;
-    finish_walk<kCombThreads>(sh.fin, w, be, bi, blocks, (uint32_t)G, pure, out, pend, margin);
 }
 
 // The launches that make their selection in the last combine blocks.

@@ -610,7 +610,7 @@ psl_status Server::upload_layout(char *&sp, char *stage_end)
     seg.tot = d_segtot.p;
     seg.tmax = d_segmax.p;
     HIP_TRY(ctx, hipMemcpyAsync(d_seg.p, off, sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, d_batch.p, n, d_pend.p, d_done.p, ctx->stream));
+    HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, d_batch.p, n, d_pend.p, d_done.p, false, ctx->stream));
     n_items = (uint32_t)items;
     dirty = false;
     return PSL_OK;

@@ -60,7 +60,7 @@ def test_a_left_walk_costs_few_table_steps(ctx, L, n_lmt):
 
 
 @pytest.mark.parametrize("L,n_lmt,n", [(512, 512, 1), (600, 512, 2), (1021, 1021, 1), (4099, 300, 1), (9001, 5000, 3),
-                                       (65535, 512, 1), (65535, 6912, 1), (131071, 700, 2), (65535, 65535, 1)])
+                                       (65535, 512, 1), (65535, 6912, 1), (131071, 700, 2), (65535, 65535, 1), (131071, 131071, 1)])
 @pytest.mark.parametrize("limit", [1, 3])
 def test_left_walks_make_the_table_steps(ctx, L, n_lmt, n, limit):
     """Random pivots, whose lists overflow in some steps, and alike elements, whose
