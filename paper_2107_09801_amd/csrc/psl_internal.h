@@ -134,6 +134,11 @@ struct BatchPlan {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Matrix memory of the last freed layout that a context keeps for the next one, at
+// most: allocating and freeing it cost 270 us of an evaluation of 570 at
+// L = 1048575 (44 MB) that no layout was kept for, and 600 us of a new batch of
+// 1024 walks at L = 600 (37 MB).
+constexpr size_t kSpareMax = (size_t)64 << 20;
 constexpr size_t kInitKeep = (size_t)16 << 20;   // largest start buffer a context keeps
 constexpr size_t kPlanCache = 8;   // step batches whose layout (and graph) is kept
 constexpr uint32_t kEvalItemsDefault = 4096;    // PSL_OPT_EVAL_ITEMS default
@@ -177,6 +182,8 @@ struct psl_ctx {
     BatchPlan pure;                   // single-walk plan of psl_eval_neighbourhood (kept for the next call)
     psl::BatchEntry *d_one = nullptr; // psl_apply_flip's batch entry and its sums (allocated on first use)
     uint32_t one_slot = UINT32_MAX;   // the walk slot it holds
+    char *spare = nullptr;            // matrix memory of a freed layout, at most kSpareMax
+    size_t spare_bytes = 0;
     char *d_init = nullptr;           // psl_init_walks' records, entries and staged bits (kept while small)
     size_t init_cap = 0;
     void *d_choice = nullptr;         // choice record of psl_eval_neighbourhood (pinned host memory)
@@ -214,7 +221,8 @@ psl_status dev_alloc(psl_ctx *ctx, void **p, size_t bytes, bool from_arena);
 void dev_free(psl_ctx *ctx, void *p, bool from_arena);
 void plan_free(psl_ctx *ctx, BatchPlan &pl);
 void plans_clear(psl_ctx *ctx);
-// Frees what the kept layouts hold, but for one of them; true if there was any.
+// Frees what the kept layouts hold, but for one of them, and the spare memory; true
+// if there was any.
 bool plans_drop(psl_ctx *ctx, const BatchPlan *but);
 psl_status ensure_tables(psl_ctx *ctx, uint32_t L);
 Tables tables_of(const psl_ctx *ctx);

@@ -118,6 +118,15 @@ psl_status timing_mark(psl_ctx *ctx)
     return PSL_OK;
 }
 
+static bool spare_drop(psl_ctx *ctx)
+{
+    const bool any = ctx->spare != nullptr;
+    dev_free(ctx, ctx->spare, false);
+    ctx->spare = nullptr;
+    ctx->spare_bytes = 0;
+    return any;
+}
+
 void plan_free(psl_ctx *ctx, BatchPlan &pl)
 {
     if (pl.gexec) (void)hipGraphExecDestroy(pl.gexec);
@@ -142,7 +151,14 @@ void plan_free(psl_ctx *ctx, BatchPlan &pl)
     dev_free(ctx, pl.d_segmax, false);
     dev_free(ctx, pl.d_near, false);
     dev_free(ctx, pl.d_queues, false);
-    dev_free(ctx, pl.d_mx, false);
+    // (the context's stream runs whatever writes it, this plan's work and the next's)
+    if (pl.mx_bytes > ctx->spare_bytes && pl.mx_bytes <= kSpareMax) {
+        spare_drop(ctx);
+        ctx->spare = pl.d_mx;
+        ctx->spare_bytes = pl.mx_bytes;
+    } else {
+        dev_free(ctx, pl.d_mx, false);
+    }
     pl = BatchPlan();
 }
 
@@ -164,7 +180,7 @@ bool plans_drop(psl_ctx *ctx, const BatchPlan *but)
     };
     for (auto &pl : ctx->plans) drop(pl);
     drop(ctx->pure);
-    return any;
+    return spare_drop(ctx) || any;
 }
 
 // dev_alloc of what outlives a call, in memory that kept layouts hold if there is
@@ -549,16 +565,6 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
 {
     const bool fixed = n_fixed != UINT32_MAX;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    // the matrix path's memory of the layout that this one replaces serves again if
-    // it is large enough: at L = 1048575 its 44 MB cost 270 us of every evaluation of
-    // another walk or N_lmt than the last (300 us in all without them)
-    struct Kept {
-        psl_ctx *ctx;
-        char *p;
-        size_t bytes;
-        ~Kept() { dev_free(ctx, p, false); }
-    } kept{ctx, mem || pl.carved ? nullptr : pl.d_mx, pl.mx_bytes};
-    if (kept.p) pl.d_mx = nullptr;
     plan_free(ctx, pl);
     pl.ids.assign(ids, ids + n);
     pl.fixed_n = fixed ? n_fixed : 0;
@@ -719,10 +725,11 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         const size_t p_ss = piece(sizeof(SplitState) * n), p_tab = piece(sizeof(uint32_t)),
                      p_off = piece(3 * sizeof(double) * pl.seg.total);
         char *rest;
-        if (kept.p && at <= kept.bytes && at >= kept.bytes / 4) {
-            rest = pl.d_mx = kept.p;
-            pl.mx_bytes = kept.bytes;
-            kept.p = nullptr;
+        if (!mem && ctx->spare && at <= ctx->spare_bytes && at >= ctx->spare_bytes / 4) {
+            rest = pl.d_mx = ctx->spare;
+            pl.mx_bytes = ctx->spare_bytes;
+            ctx->spare = nullptr;
+            ctx->spare_bytes = 0;
         } else {
             if ((st = get(&p, at))) return st;
             rest = (char *)p;
@@ -810,8 +817,9 @@ psl_status make_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, uint32_t 
     // without the matrix path, whose arrays come on top of the others; then in what
     // the other kept layouts hold
     const bool split = pl.split;
-    plan_free(ctx, pl);                  // nothing handed on: the memory is needed
-    if (split) st = build(false);
+    plan_free(ctx, pl);
+    const bool spare = !mem && spare_drop(ctx);
+    if (split || spare) st = build(false);
     if (st == PSL_E_NOMEM && !mem && plans_drop(ctx, &pl)) st = build(false);
     if (!st) ctx->err = err;
     return st;
@@ -1077,6 +1085,7 @@ void psl_ctx_destroy(psl_ctx *ctx)
         dev_free(ctx, h.trace, false);
     }
     plans_clear(ctx);
+    spare_drop(ctx);
     for (uint32_t a = 1; a <= PSL_ALPHA_MAX; ++a) dev_free(ctx, ctx->d_T[a], false);
     dev_free(ctx, ctx->d_walks, false);
     if (ctx->d_choice) (void)hipHostFree(ctx->d_choice);

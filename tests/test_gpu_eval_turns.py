@@ -1,6 +1,6 @@
-"""Evaluations that cannot use the layout of the one before (another N_lmt, another
-walk): right, and not much slower than without the matrix path, whose memory a
-layout hands to the next."""
+"""Evaluations and batches that cannot use the layout of the one before (another
+N_lmt, other walks): right, and not much slower than without the matrix path, whose
+memory a layout hands to the next."""
 import time
 
 import numpy as np
@@ -58,3 +58,18 @@ def test_a_new_layout_costs_what_the_tables_do(ctx):
                 ctx.eval_neighbourhood(w, 5, n)
             best[mode] = min(best[mode], time.perf_counter() - t)
     assert best[-1] <= 1.4 * best[0], best
+
+
+def test_a_new_batch_costs_what_the_tables_do(ctx):
+    """Layouts of 1024 short walks, one after another, each with a step."""
+    from paper_2107_09801_amd import libpsl
+    ids = ctx.init_walks(600, 1024, 3)
+    best = {}
+    for mode in (-1, 0):
+        best[mode] = 1e9
+        for _ in range(12):
+            t = time.perf_counter()
+            ctx.set_option(libpsl.OPT_SPLIT, mode)          # drops the kept layouts
+            ctx.step_batch(ids, 1)
+            best[mode] = min(best[mode], time.perf_counter() - t)
+    assert best[-1] <= 1.6 * best[0], best
