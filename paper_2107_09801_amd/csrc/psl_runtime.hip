@@ -725,7 +725,7 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         const size_t p_ss = piece(sizeof(SplitState) * n), p_tab = piece(sizeof(uint32_t)),
                      p_off = piece(3 * sizeof(double) * pl.seg.total);
         char *rest;
-        if (!mem && ctx->spare && at <= ctx->spare_bytes && at >= ctx->spare_bytes / 4) {
+        if (!mem && ctx->spare && at <= ctx->spare_bytes) {
             rest = pl.d_mx = ctx->spare;
             pl.mx_bytes = ctx->spare_bytes;
             ctx->spare = nullptr;
