@@ -2,7 +2,7 @@
 // for every shift, O(L^2), at init, at a restore and after a Rand_flip too
 // large for the one-flip rebuild.
 //
-// Long sequences: on the matrix cores, as products of two +-1 matrices made
+// Long sequences, and many: on the matrix cores, as products of two +-1 matrices made
 // from the sequence's bits in FP4. One block takes kCorrTile = 4096
 // consecutive shifts and a range of the positions i, in 32-position chunks.
 // The 16 rows of v_mfma_f32_16x16x128_f8f6f4 hold s at i + K0 + 32 n + 16 p + r
@@ -18,8 +18,8 @@
 // about 40 vector instructions (4 cycles each): away from the sequence's ends the
 // matrices need no masks, which took 30 more. 1024 walks at L = 131071 take 3.7
 // ms, 14 ns per product and SIMD; alone, a product takes 7 to 10. One XOR
-// and popcount per 32 products, the form that short sequences keep, is bound by
-// vector issue.
+// and popcount per 32 products, the form of short sequences and small launches, is
+// bound by vector issue, in small launches by the length of a block's sweep.
 #include "psl_dev_util.h"
 #include "psl_device.h"
 #include "psl_launch.h"
@@ -28,7 +28,7 @@
 
 namespace psl {
 
-// Shortest walk of the matrix form: its column words reach 120 words before the
+// Shortest walk that the matrix form can take: its column words reach 120 words before the
 // sequence, inside the guards from L = 3712 on.
 constexpr uint32_t kCorrMxMinL = 4096;
 
@@ -44,12 +44,13 @@ __device__ __forceinline__ bool corr_takes(const WalkDev &w, int mode)
 // of two staged words) give 32 products per XOR and popcount.
 constexpr int kCorrThreads = 256;
 constexpr int kCorrSeg = 1024;        // staged 32-bit words per segment
-__global__ __launch_bounds__(kCorrThreads) void k_corr(WalkDev *walks, const BatchEntry *batch, int mode)
+__global__ __launch_bounds__(kCorrThreads) void k_corr(WalkDev *walks, const BatchEntry *batch, int mode,
+                                                       uint32_t mx_L)
 {
     WalkDev &w = walks[batch[blockIdx.y].slot];
     const uint32_t L = w.L;
     const uint32_t k0 = blockIdx.x * kCorrThreads;
-    if (k0 >= L || L >= kCorrMxMinL || !corr_takes(w, mode)) return;
+    if (k0 >= L || L >= mx_L || !corr_takes(w, mode)) return;
     __shared__ uint32_t A[kCorrSeg];
     __shared__ uint32_t B[kCorrSeg + 16];
     const uint32_t *s32 = reinterpret_cast<const uint32_t *>(w.pivot);
@@ -123,14 +124,14 @@ __device__ __forceinline__ void pm1_nibbles(uint32_t x, uint32_t (&o)[4])
 // L = 65535 took 133 us (now 80). One part: C (and C_lb in mode 0) is stored;
 // several: added into C, which is zero.
 __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_corr_mx(
-    WalkDev *walks, const BatchEntry *batch, int mode, int splits, int Q)
+    WalkDev *walks, const BatchEntry *batch, int mode, uint32_t mx_L, int splits, int Q)
 {
     WalkDev &w = walks[batch[(blockIdx.x + blockIdx.y) % gridDim.x].slot];
     if (!corr_takes(w, mode)) return;
     const int L = (int)w.L;
     const int tiles = (int)(gridDim.y / (uint32_t)splits);
     const int K0 = (int)kCorrTile * ((int)blockIdx.y % tiles);
-    if (K0 >= L || L < (int)kCorrMxMinL) return;
+    if (K0 >= L || L < (int)mx_L) return;
     // the block's chunks (those with a position i below L - K0), a quarter for each wavefront
     const int p0 = Q * ((int)blockIdx.y / tiles), p1 = min(p0 + Q, (L - K0 + 31) >> 5);
     if (p0 >= p1) return;
@@ -233,12 +234,12 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(3)))
 }
 
 // Before and after the parts of k_corr_mx are added into C: C = 0; C_lb = C.
-__global__ void k_corr_edge(WalkDev *walks, const BatchEntry *batch, int mode, int after)
+__global__ void k_corr_edge(WalkDev *walks, const BatchEntry *batch, int mode, uint32_t mx_L, int after)
 {
     WalkDev &w = walks[batch[blockIdx.y].slot];
     if (!corr_takes(w, mode)) return;
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= w.L || w.L < kCorrMxMinL) return;
+    if (k >= w.L || w.L < mx_L) return;
     if (after) w.C_lb[k] = w.C[k];
     else       w.C[k] = 0;
 }
@@ -256,17 +257,26 @@ hipError_t launch_corr(WalkDev *walks, const BatchEntry *batch, uint32_t nb, con
     const uint32_t most = (d.max_L + 31) / 32;
     const uint32_t Q = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(kMinPart, (d.chunks + kBlocks - 1) / kBlocks));
     const uint32_t splits = (most + Q - 1) / Q, tiles = (d.max_L + kCorrTile - 1) / kCorrTile;
+    // the shortest walk on the matrix cores: none in a launch with little work of
+    // walks of moderate length, whose few tiles leave most compute units idle, where
+    // a block of the popcount form has 256 shifts and no zeroed C to add to. Starts,
+    // matrix / popcount, us: one walk at L = 4097 39 / 32, 16383 47 / 38, 32767
+    // 48 / 45, 40009 48 / 50, 65535 47 / 61; 4 at 32767 (16384 chunks) 51 / 49, 8 at
+    // 32767 51 / 62; 16 at 16383 (16384) 51 / 48, 32 54 / 64; 64 at 8193 (16448)
+    // 62 / 55, at 12001 65 / 67; 256 at 4097 (16640) 77 / 79.
+    constexpr uint32_t kMaxPopL = 36864, kMaxPopChunks = 16384;
+    const uint32_t mx_L = d.max_L < kMaxPopL && d.chunks <= kMaxPopChunks ? UINT32_MAX : kCorrMxMinL;
     for (uint32_t b0 = 0; b0 < nb; b0 += kMaxY) {
         const uint32_t ny = std::min(kMaxY, nb - b0);
-        if (d.min_L < kCorrMxMinL) {
-            const uint32_t len = std::min(d.max_L, kCorrMxMinL - 1);
-            k_corr<<<dim3((len + kCorrThreads - 1) / kCorrThreads, ny), kCorrThreads, 0, s>>>(walks, batch + b0, mode);
+        if (d.min_L < mx_L) {
+            const uint32_t len = std::min(d.max_L, mx_L - 1);
+            k_corr<<<dim3((len + kCorrThreads - 1) / kCorrThreads, ny), kCorrThreads, 0, s>>>(walks, batch + b0, mode, mx_L);
         }
-        if (d.max_L >= kCorrMxMinL) {
+        if (d.max_L >= mx_L) {
             const dim3 all((d.max_L + 255) / 256, ny);
-            if (splits > 1) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, 0);
-            k_corr_mx<<<dim3(ny, tiles * splits), kMxThreads, 0, s>>>(walks, batch + b0, mode, (int)splits, (int)Q);
-            if (splits > 1 && mode == 0) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, 1);
+            if (splits > 1) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, mx_L, 0);
+            k_corr_mx<<<dim3(ny, tiles * splits), kMxThreads, 0, s>>>(walks, batch + b0, mode, mx_L, (int)splits, (int)Q);
+            if (splits > 1 && mode == 0) k_corr_edge<<<all, 256, 0, s>>>(walks, batch + b0, mode, mx_L, 1);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
