@@ -187,11 +187,11 @@ bool plans_drop(psl_ctx *ctx, const BatchPlan *but)
 // no other.
 psl_status dev_alloc_kept(psl_ctx *ctx, void **p, size_t bytes, bool from_arena)
 {
-    const std::string err = ctx->err;
-    psl_status st = dev_alloc(ctx, p, bytes, from_arena);
-    if (st != PSL_E_NOMEM || (from_arena && ctx->arena.active()) || !plans_drop(ctx, nullptr)) return st;
-    if (!(st = dev_alloc(ctx, p, bytes, from_arena))) ctx->err = err;
-    return st;
+    if (from_arena && ctx->arena.active()) return dev_alloc(ctx, p, bytes, true);
+    if (hipMalloc(p, bytes ? bytes : 256) == hipSuccess) return PSL_OK;
+    (void)hipGetLastError();
+    (void)plans_drop(ctx, nullptr);
+    return dev_alloc(ctx, p, bytes, false);
 }
 
 // Power tables for every exponent, |c| up to L_max + 4.
