@@ -48,20 +48,6 @@ __device__ __forceinline__ void copy_words(uint64_t *__restrict__ dst, const uin
     for (; x < n; x += nthreads) dst[x] = x == flip_word ? src[x] ^ flip_mask : src[x];
 }
 
-// Bits [pos, pos+32) of a packed sequence held as nw32 32-bit words; bits
-// outside the words read as 0.
-__device__ __forceinline__ uint32_t bits32_at(const uint32_t *__restrict__ w32, int nw32,
-                                              int pos)
-{
-    int wi = pos >> 5;
-    uint32_t sh = (uint32_t)pos & 31u;
-    uint32_t lo = (wi >= 0 && wi < nw32) ? w32[wi] : 0u;
-    uint32_t hi = (wi + 1 >= 0 && wi + 1 < nw32) ? w32[wi + 1] : 0u;
-    return __builtin_amdgcn_alignbit(hi, lo, sh);
-}
-
-__device__ __forceinline__ double dmax(double a, double b) { return a > b ? a : b; }
-
 // High 32 bits of a non-negative double. Over the power table they are
 // strictly increasing in |c| (consecutive entries differ by a factor of at
 // least 1 + 2^-19 for alpha >= 2 and |c| <= 2^20 + 8; for alpha = 1 the

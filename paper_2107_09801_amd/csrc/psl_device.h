@@ -16,8 +16,6 @@ constexpr int kEvalWavesMax = 16;    // wavefronts per evaluation block: 16, 8 o
 constexpr int kEvalWaves = 8;        // the default below 256 x 1024 candidates per batch
 constexpr int kEvalWavesSmall = 4;   // blocks for batches of small neighbourhoods
 constexpr int kTileK = 256;          // shifts staged per LDS tile
-constexpr int kChunks = kTileK / 32; // 32-shift windows per tile
-constexpr int kPairs = kTileK / 2;   // shift pairs per tile
 constexpr int kRowStride = 5;        // T(|C_k + 2m|), m = -2..2
 constexpr int kNearCap = 4096;       // capacity of the near-peak shift list
 constexpr uint32_t kFlipIncremental = 64;  // Rand_flip sizes rebuilt by one-flip updates

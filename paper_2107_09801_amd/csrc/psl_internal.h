@@ -90,7 +90,6 @@ struct WalkHost {
 // A batch as laid out on the device; cached by its walk list.
 struct BatchPlan {
     std::vector<uint32_t> ids;
-    uint32_t max_L = 0, max_nw = 0;
     CorrDims corr;                    // of its walks
     bool big_flips = false;           // some walk's Rand_flip exceeds the one-flip rebuild
     uint64_t pend_units = 0;          // work units of the pending-walk rebuild (all walks)

@@ -576,8 +576,6 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         pl.big_flips |= h.flip_lmt > kFlipIncremental;
         pl.corr.add(h.L);
         pl.pend_units += pending_units(h.L);
-        pl.max_L = std::max(pl.max_L, h.L);
-        pl.max_nw = std::max(pl.max_nw, h.nw);
     }
     EvalLayout lay;
     const EvalShape shape = force ? *force : pick_shape(ctx, Ls.data(), n_l.data(), n);

@@ -166,7 +166,7 @@ struct Server {
     DevBuf<uint32_t> d_adm_m0;
     uint32_t comb_blocks = 1, comb_group = 1;
     DevBuf<int32_t> d_p;
-    uint32_t n_items = 0, max_L = 0;
+    uint32_t n_items = 0;
     EvalShape shape;
     DevBuf<EvalQueues> d_queues;
     bool dirty = true;
@@ -530,11 +530,9 @@ psl_status Server::upload_layout(char *&sp, char *stage_end)
 {
     const uint32_t n = (uint32_t)active.size();
     std::vector<uint32_t> Ls(n), nls(n);
-    max_L = 0;
     for (uint32_t b = 0; b < n; ++b) {
         Ls[b] = active[b].cfg.L;
         nls[b] = active[b].cfg.n_lmt ? active[b].cfg.n_lmt : active[b].cfg.L;
-        max_L = std::max(max_L, Ls[b]);
     }
     EvalLayout lay;
     eval_layout(Ls.data(), nls.data(), n, pick_shape(ctx, Ls.data(), nls.data(), n),
