@@ -356,7 +356,8 @@ typedef struct {
 
 /* Time every candidate launch shape of the table evaluation on these walks
  * (their state is not changed; steps on the matrix path, PSL_OPT_SPLIT, do not
- * depend on it), then, in the fastest shape, the work-item targets
+ * depend on it; of launches that take 100 ms and more, only the largest
+ * persistent grids), then, in the fastest shape, the work-item targets
  * half, twice and four times PSL_OPT_EVAL_ITEMS; keep the fastest pair for
  * every later batch with the same key (log2 of the largest L, of the median
  * N_lmt and of the walk count, and whether the L differ by more than 4x),

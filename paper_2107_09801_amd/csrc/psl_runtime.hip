@@ -1543,23 +1543,25 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
         BatchPlan tmp;
         psl_status s2 = make_plan(ctx, tmp, walk_ids, n, UINT32_MAX, 0, &c, items);
         if (s2) return s2;
-        s2 = launch_partials(ctx, tmp, tabs, n, nullptr, false, EvalCall{}, true);      // warm-up
-        if (s2) {
-            plan_free(ctx, tmp);
-            return s2;
-        }
-        const int reps = 2;
-        hipError_t e = hipEventRecord(e0, ctx->stream);
-        for (int r = 0; r < reps && e == hipSuccess; ++r)
-            e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape, tmp.d_queues, nullptr,
-                            ctx->n_cu, ctx->stream);
-        if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(e1);
-        float ms = 0.f;
-        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        auto launches = [&](int reps) {
+            hipError_t e = hipEventRecord(e0, ctx->stream);
+            for (int r = 0; r < reps && e == hipSuccess; ++r)
+                e = launch_eval(ctx->d_walks, tmp.d_batch, tmp.d_items, tmp.n_items, tabs, tmp.shape, tmp.d_queues, nullptr,
+                                ctx->n_cu, ctx->stream);
+            if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            float ms = 0.f;
+            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+            avg = ms / reps;
+            return e;
+        };
+        hipError_t e = launch_suffix(ctx->d_walks, tmp.d_batch, n, tabs, &tmp.seg, nullptr,
+                                     tmp.shape.waves >= kEvalWavesMax, EvalCall{}, ctx->stream);
+        // the first launch warms up, but for one so long that nothing warms it
+        if (e == hipSuccess) e = launches(1);
+        if (e == hipSuccess && avg < 20.0) e = launches(2);
         plan_free(ctx, tmp);
         if (e != hipSuccess) return fail(ctx, PSL_E_HIP, "autotune: %s", hipGetErrorString(e));
-        avg = ms / reps;
         return PSL_OK;
     };
     double best_ms = 1e300, def_ms = 0.0;
@@ -1567,6 +1569,9 @@ psl_status psl_autotune(psl_ctx *ctx, const uint32_t *walk_ids, uint32_t n, psl_
     uint32_t best_items = ctx->eval_items;
     psl_status st = PSL_OK;
     for (const EvalShape &c : cands) {
+        // long launches gain from every block that fits (1024 walks at L = 131071, 16
+        // wavefronts: 866 ms with one block per CU, 581 with two)
+        if (best_ms >= 100.0 && c.persistent && c.grid < max_blocks_per_cu(c.waves) * ctx->n_cu) continue;
         double avg = 0.0;
         if ((st = time_eval(c, ctx->eval_items, avg))) break;
         if (c.waves == def.waves && c.persistent == def.persistent && c.grid == def.grid) def_ms = avg;
