@@ -530,24 +530,26 @@ __global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(4)
         CombLds comb;
         __device__ Lds() {}
     } sh;
-    const BatchEntry be = batch[blockIdx.y];
+    // walks fastest, so that the blocks with something to do come first
+    const uint32_t bi = blockIdx.x, b = blockIdx.y;
+    const BatchEntry be = batch[bi];
     WalkDev &w = walks[be.slot];
     uint32_t parts = blocks;                // the combine blocks of the selection
     if (!be.ss->use) {
         const uint32_t tiles = ((be.fixed ? be.n_lmt : w.n_lmt) + 255) / 256;
-        const uint32_t ks = min(be.ksplit, max(1u, gridDim.x / tiles));
+        const uint32_t ks = min(be.ksplit, max(1u, gridDim.y / tiles));
         const uint32_t per = (tiles + kCombMaxBlocks - 1) / kCombMaxBlocks, groups = (tiles + per - 1) / per;
         parts = 0;
-        uint32_t *left = done + gridDim.y + kCombMaxBlocks * blockIdx.y;
-        for (uint32_t x = blockIdx.x; x < tiles * ks; x += gridDim.x) {
+        uint32_t *left = done + gridDim.x + kCombMaxBlocks * bi;
+        for (uint32_t x = b; x < tiles * ks; x += gridDim.y) {
             int tid = (int)threadIdx.x;     // opaque per item, as in k_eval_persistent
             asm volatile("" : "+v"(tid));
             __builtin_assume(tid >= 0 && tid < 256);
-            eval_item<4, true>(sh.eval, walks, batch, EvalItem{blockIdx.y, x % tiles, x / tiles, 0}, tabs, tid, ks);
+            eval_item<4, true>(sh.eval, walks, batch, EvalItem{bi, x % tiles, x / tiles, 0}, tabs, tid, ks);
             const uint32_t g = x % tiles / per;
             if (last_block(sh.comb, left, g, min(per, tiles - g * per) * ks)) {
                 combine_part<true, Form::table>(sh.comb, w, be, tabs, 1, groups, g, ks);
-                if (last_block(sh.comb, done, blockIdx.y, groups)) {
+                if (last_block(sh.comb, done, bi, groups)) {
                     parts = groups;
                     break;
                 }
@@ -557,11 +559,11 @@ __global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(4)
         if (!parts) return;
         G = 1;
     } else {
-        if (blockIdx.x >= blocks) return;
-        combine_part<true, Form::matrix>(sh.comb, w, be, tabs, G, blocks, blockIdx.x, 0);
-        if (!last_block(sh.comb, done, blockIdx.y, blocks)) return;
+        if (b >= blocks) return;
+        combine_part<true, Form::matrix>(sh.comb, w, be, tabs, G, blocks, b, 0);
+        if (!last_block(sh.comb, done, bi, blocks)) return;
     }
-    finish_walk<kCombThreads>(sh.comb.fin, w, be, blockIdx.y, parts, (uint32_t)G, 0, nullptr, pend, margin);
+    finish_walk<kCombThreads>(sh.comb.fin, w, be, bi, parts, (uint32_t)G, 0, nullptr, pend, margin);
 }
 
 __global__ void k_queue_reset(EvalQueues *queues)
@@ -605,7 +607,7 @@ hipError_t launch_select_left(WalkDev *walks, const BatchEntry *batch, uint32_t 
     if (grid < comb_blocks || comb_blocks < 1 || comb_blocks > kCombMaxBlocks || !comb_small(nb, comb_blocks) || !done) return hipErrorInvalidValue;
     if (comb_group < 1 || comb_group > 64 || (comb_group & (comb_group - 1))) return hipErrorInvalidValue;
     if (nb == 0) return hipSuccess;
-    k_combine_left<<<dim3(grid, nb), kCombThreads, 0, s>>>(walks, batch, tabs, (int)comb_group, pend, done, margin,
+    k_combine_left<<<dim3(nb, grid), kCombThreads, 0, s>>>(walks, batch, tabs, (int)comb_group, pend, done, margin,
                                                            comb_blocks);
     return hipGetLastError();
 }
