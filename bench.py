@@ -35,8 +35,8 @@ PEAK_LANE_OPS = 256 * 64 * 2.4e9
 PEAK_FP4_OPS = 1.0e16
 # FLOPs of the matrix path per nominal C_k-update: an element j takes two products per
 # both-neighbour shift and one per one-neighbour shift, 2 min(j, L-1-j) + |L-1-2j| = L-1 in
-# all, each with 16 digit columns.
-MX_OPS_PER_UPDATE = 2 * 16
+# all, each with 14 digits (two of the instruction's 16 columns hold zeros).
+MX_OPS_PER_UPDATE = 2 * 14
 # Shortest walk the matrix path takes, and the fewest candidates per shift (on
 # average over its walks) of a launch that takes it by default.
 SPLIT_MIN_L = 512
@@ -679,7 +679,7 @@ def main():
                     "peak": PEAK_FP4_OPS / 1e12, "unit": "TFLOP/s", "frac": ops / lin_avg_s / PEAK_FP4_OPS,
                     "traffic": measured_traffic(tag, "k_mx"), "traffic_unit": "B/launch",
                     "ops_per_launch": ops,
-                    "basis": "32 FLOPs (16 digit multiply-adds) per element and coefficient / the launch "
+                    "basis": "28 FLOPs (14 digit multiply-adds) per element and coefficient / the launch "
                              "time measured here, against the dense FP4/FP6 peak"}
     roofline = roof_eval if roof_lin is None or eval_avg_s >= lin_avg_s else roof_lin
     eval_s = eval_avg_s + lin_avg_s       # table evaluation and matrix products

@@ -396,9 +396,10 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
 /* PSL_OPT_AMBIG_MARGIN: the relative margin m of the ambiguity flags
  * (PSL_CHOICE_AMBIGUOUS_ARGMIN, PSL_STEP_AMBIG_*), in units of 1e-15:
  * 0 .. 10^15 (m = 0 .. 1); -1 restores the default 500 (m = 5e-13, which
- * covers the FP64 rounding of this library's F, at most about 3e-14
- * relative, and of an exact summation). Only the flags change: the moves are
- * the band rule's whatever the margin. Errors: PSL_E_INVAL outside the range. */
+ * covers the FP64 rounding of this library's F, at most about 3e-14 relative
+ * from the tables and 1.3e-13 on the matrix path (PSL_OPT_SPLIT; 4e-15 and
+ * 7e-16 have been seen), and of an exact summation). Only the flags change: the
+ * moves are the band rule's whatever the margin. Errors: PSL_E_INVAL outside the range. */
 #define PSL_OPT_AMBIG_MARGIN 3
 /* PSL_OPT_SPLIT: the matrix path of the evaluation (Eq. (5) over the
  * neighbours as 0/1 matrices, the XNOR and AND of the two neighbours of
@@ -409,9 +410,10 @@ PSL_API psl_status psl_tune_load(psl_ctx *ctx, const char *path);
  * batches and evaluations whose walks of L >= 512 evaluate at least 512
  * candidates on average (N_lmt weighted by L-1), below which its preparation
  * of every shift costs more than it saves; 1: in every batch and evaluation;
- * 0: never (every step takes the table evaluation). Moves and PSL are the same
- * either way (F agrees to about 1e-14 relative); errors: PSL_E_INVAL outside
- * -1..2. */
+ * 0: never (every step takes the table evaluation). Batches and evaluations
+ * for whose matrix scratch (about 40 bytes per shift) there is no device memory
+ * take the table evaluation too. Moves and PSL are the same either way (F agrees
+ * to about 1e-14 relative); errors: PSL_E_INVAL outside -1..2. */
 #define PSL_OPT_SPLIT 4
 /* PSL_OPT_TEST_FAIL_ADMIT: a test hook of the request loop. With n >= 1, the
  * n-th admission (counted per psl_serve_start, admissions that take at least

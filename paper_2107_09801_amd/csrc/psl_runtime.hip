@@ -9,8 +9,9 @@ using namespace psl;
 using namespace psl_rt;
 
 // Fixed scratch of psl_eval_neighbourhood_noalloc: the evaluation plan's
-// arrays of one walk (work items, k-split partials, chunk suffix arrays,
-// near-peak list, combine minima, segment map, choice record), carved per
+// arrays of one walk (work items, partial sums, the matrix path's digits and
+// prefix sums, chunk suffix arrays, near-peak list, combine minima, segment map,
+// choice record), carved per
 // call. Every device the library runs on holds one copy until the process
 // ends, and every call on that device shares it. Host code reaches it only
 // through the address hipGetSymbolAddress returns for the device (kept per

@@ -87,12 +87,13 @@ __device__ __forceinline__ void split_digits(double v, uint32_t (&out)[4])
 // the order in which the matrix kernel's masks leave the bits of a word. The
 // threads leave the codes of a tile in LDS (one word per shift and four
 // columns); then one thread per (coefficient, chunk, four columns, half the
-// slots) packs them. All values of a prefix are non-negative and go through
-// about 16 roundings within a segment.
+// slots) packs them. The values of a prefix have either sign, and each goes
+// through about 16 roundings within a segment (split_offsets says what F's
+// rounding comes to).
 //
 // One pass instead of three (chunk sums, coefficients, a serial scan per walk
 // that took 0.94 ms of a step at L = 1048575 and 0.21 ms for 64 walks at
-// L = 131071). Prefixes, 16 of the 44 bytes written per shift, are scanned and
+// L = 131071). Prefixes, 16 of the 40 bytes written per shift, are scanned and
 // stored only in tiles that hold some candidate's m_j or M_j; the others' values
 // stay in their threads until the next such tile. The next tile's C is loaded
 // while a tile's digits are made, and the scans go through lane permutations of
@@ -306,6 +307,12 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const WalkDev *walks, Bat
 // every neighbour's F (T(P-4) for the pivot's PSL P, and at least 1); a walk
 // that does not take it is counted in *tab, which the table evaluation looks
 // at first.
+// FP64 rounding comes on top, of sums whose terms have both signs: with fewer than
+// 64 rounded additions between a term and F_j, at most 64 x 2^-53 times the sum of
+// the terms' absolute values, which is 1.7 F_j (alpha = 1) to 17 F_j (alpha = 16,
+// L = 512 to 600, where 4 is most against |C_k|): 1.2e-13 of F_j at the most. Seen
+// over L = 512 to 9001, random and low-PSL pivots, alpha = 1 to 16: 6.7e-16 (the
+// table evaluation's F: 4.0e-15).
 __device__ __forceinline__ void split_offsets(const WalkDev &w, const BatchEntry &be, const Tables &tabs, uint32_t *tab,
                                               int x, int lane)
 {
