@@ -33,7 +33,10 @@ def _fill(leave):
     torch.cuda.empty_cache()
     hold = []
     while _free() > leave + 32 * MB:
-        hold.append(torch.empty(_free() - leave, dtype=torch.uint8, device="cuda:0"))
+        try:
+            hold.append(torch.empty(_free() - leave, dtype=torch.uint8, device="cuda:0"))
+        except torch.OutOfMemoryError:      # less is free than is reported
+            break
     return hold
 
 
