@@ -56,6 +56,19 @@ psl_status fail(psl_ctx *ctx, psl_status st, const char *fmt, ...)
 
 
 
+// Host copies go through the context's stream: one on the legacy stream fails, and
+// breaks the capture, while another thread captures a graph on a blocking stream.
+// copy returns with the copy done; queue_copy needs a synchronisation before the
+// host memory goes.
+static hipError_t queue_copy(psl_ctx *ctx, void *dst, const void *src, size_t bytes, hipMemcpyKind kind)
+{
+    return hipMemcpyAsync(dst, src, bytes, kind, ctx->stream);
+}
+static hipError_t copy(psl_ctx *ctx, void *dst, const void *src, size_t bytes, hipMemcpyKind kind)
+{
+    return hipMemcpyWithStream(dst, src, bytes, kind, ctx->stream);
+}
+
 psl_status dev_alloc(psl_ctx *ctx, void **p, size_t bytes, bool from_arena)
 {
     *p = nullptr;
@@ -239,8 +252,7 @@ psl_status ensure_walk_cap(psl_ctx *ctx, uint32_t cap)
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     plans_clear(ctx);            // captured launches name the old walk array
     if (ctx->d_walks) {
-        HIP_TRY(ctx, hipMemcpy(p, ctx->d_walks, sizeof(WalkDev) * ctx->walk_cap,
-                               hipMemcpyDeviceToDevice));
+        HIP_TRY(ctx, copy(ctx, p, ctx->d_walks, sizeof(WalkDev) * ctx->walk_cap, hipMemcpyDeviceToDevice));
         dev_free(ctx, ctx->d_walks, false);
     }
     ctx->d_walks = (WalkDev *)p;
@@ -695,7 +707,6 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
         if ((st = get(&p, sizeof(uint32_t) * (n + 1)))) return st;
         pl.d_seg = (uint32_t *)p;
         pl.seg.off = pl.d_seg;
-        HIP_TRY(ctx, hipMemcpy(pl.d_seg, off.data(), sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice));
         if ((st = get(&p, sizeof(double) * pl.seg.total))) return st;
         pl.d_segtot = (double *)p;
         if ((st = get(&p, sizeof(uint32_t) * pl.seg.total))) return st;
@@ -794,10 +805,15 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     pl.d_mitems = pl.d_items + pl.n_items;
     if ((st = get(&p, sizeof(EvalQueues)))) return st;
     pl.d_queues = (EvalQueues *)p;
-    HIP_TRY(ctx, hipMemcpy(pl.d_queues, &lay.queues, sizeof(EvalQueues), hipMemcpyHostToDevice));
-    HIP_TRY(ctx, hipMemcpy(pl.d_batch, be.data(), sizeof(BatchEntry) * n, hipMemcpyHostToDevice));
-    HIP_TRY(ctx, hipMemcpy(pl.d_items, items.data(), sizeof(EvalItem) * items.size(),
-                           hipMemcpyHostToDevice));
+    {
+        hipError_t e = queue_copy(ctx, pl.d_seg, off.data(), sizeof(uint32_t) * (n + 1), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = queue_copy(ctx, pl.d_queues, &lay.queues, sizeof(EvalQueues), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = queue_copy(ctx, pl.d_batch, be.data(), sizeof(BatchEntry) * n, hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = queue_copy(ctx, pl.d_items, items.data(), sizeof(EvalItem) * items.size(), hipMemcpyHostToDevice);
+        const hipError_t f = hipStreamSynchronize(ctx->stream);
+        HIP_TRY(ctx, e != hipSuccess ? e : f);
+    }
     HIP_TRY(ctx, launch_batch_reset(ctx->d_walks, pl.d_batch, n, pl.d_pend, pl.d_done, pl.left_blocks != 0, ctx->stream));
     return PSL_OK;
 }
@@ -1010,7 +1026,7 @@ psl_status one_entry(psl_ctx *ctx, uint32_t slot)
     ctx->one_slot = UINT32_MAX;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     memcpy(head, &e, sizeof e);
-    HIP_TRY(ctx, hipMemcpy(ctx->d_one, head, sizeof head, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, copy(ctx, ctx->d_one, head, sizeof head, hipMemcpyHostToDevice));
     ctx->one_slot = slot;
     return PSL_OK;
 }
@@ -1441,14 +1457,13 @@ psl_status psl_read_walk(psl_ctx *ctx, uint32_t walk, psl_walk_state *out, uint6
     if (serve_active(ctx)) return fail(ctx, PSL_E_STATE, "the context is serving");
     if (!walk_ok(ctx, walk)) return fail(ctx, PSL_E_STATE, "unknown walk %u", walk);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     WalkDev w;
-    HIP_TRY(ctx, hipMemcpy(&w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
-    if (pivot_bits) HIP_TRY(ctx, hipMemcpy(pivot_bits, w.pivot, 8 * w.nw, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, copy(ctx, &w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
+    if (pivot_bits) HIP_TRY(ctx, copy(ctx, pivot_bits, w.pivot, 8 * w.nw, hipMemcpyDeviceToHost));
     if (local_best_bits)
-        HIP_TRY(ctx, hipMemcpy(local_best_bits, w.local_best, 8 * w.nw, hipMemcpyDeviceToHost));
-    if (best_bits) HIP_TRY(ctx, hipMemcpy(best_bits, w.best, 8 * w.nw, hipMemcpyDeviceToHost));
-    if (C) HIP_TRY(ctx, hipMemcpy(C, w.C, sizeof(int32_t) * w.L, hipMemcpyDeviceToHost));
+        HIP_TRY(ctx, copy(ctx, local_best_bits, w.local_best, 8 * w.nw, hipMemcpyDeviceToHost));
+    if (best_bits) HIP_TRY(ctx, copy(ctx, best_bits, w.best, 8 * w.nw, hipMemcpyDeviceToHost));
+    if (C) HIP_TRY(ctx, copy(ctx, C, w.C, sizeof(int32_t) * w.L, hipMemcpyDeviceToHost));
     if (out) {
         memset(out, 0, sizeof *out);
         out->L = w.L;
@@ -1706,10 +1721,10 @@ psl_status psl_trace_enable(psl_ctx *ctx, uint32_t walk, uint32_t capacity)
         if (st) return st;
     }
     WalkDev w;
-    HIP_TRY(ctx, hipMemcpy(&w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, copy(ctx, &w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
     w.trace = (TraceEntry *)ring;
     w.trace_cap = capacity;
-    HIP_TRY(ctx, hipMemcpy(ctx->d_walks + walk, &w, sizeof w, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, copy(ctx, ctx->d_walks + walk, &w, sizeof w, hipMemcpyHostToDevice));
     dev_free(ctx, h.trace, false);
     h.trace = ring;
     return PSL_OK;
@@ -1724,10 +1739,10 @@ psl_status psl_trace_read(psl_ctx *ctx, uint32_t walk, psl_trace_entry *out, uin
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     WalkDev w;
-    HIP_TRY(ctx, hipMemcpy(&w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, copy(ctx, &w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
     if (!w.trace_cap) return fail(ctx, PSL_E_STATE, "walk %u has no trace", walk);
     std::vector<TraceEntry> ring(w.trace_cap);
-    HIP_TRY(ctx, hipMemcpy(ring.data(), w.trace, sizeof(TraceEntry) * w.trace_cap, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, copy(ctx, ring.data(), w.trace, sizeof(TraceEntry) * w.trace_cap, hipMemcpyDeviceToHost));
     const uint64_t have = std::min<uint64_t>(w.t, w.trace_cap);
     const uint64_t n = std::min<uint64_t>(have, max_entries);
     for (uint64_t x = 0; x < n; ++x) {
@@ -1775,7 +1790,7 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     WalkDev w;
-    HIP_TRY(ctx, hipMemcpy(&w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
+    HIP_TRY(ctx, copy(ctx, &w, ctx->d_walks + walk, sizeof w, hipMemcpyDeviceToHost));
     w.seed = st->seed;
     w.alpha1 = st->alpha1;
     w.alpha2 = st->alpha2;
@@ -1792,21 +1807,21 @@ psl_status psl_restore_walk(psl_ctx *ctx, uint32_t walk, const psl_walk_state *s
     w.pending = 0;
     w.n_flips = 0;
     w.flags = 0;
-    HIP_TRY(ctx, hipMemcpy(ctx->d_walks + walk, &w, sizeof w, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, copy(ctx, ctx->d_walks + walk, &w, sizeof w, hipMemcpyHostToDevice));
     h.n_lmt = w.n_lmt;
     h.flip_lmt = w.flip_lmt;
     plans_clear(ctx);            // N_lmt may differ
     // C of local_best (and C) from local_best's bits, then C from the pivot's
     if (const psl_status rs = one_entry(ctx, walk)) return rs;
     const Tables tabs = tables_of(ctx);
-    hipError_t r = hipMemcpy(w.pivot, local_best, 8ull * nw, hipMemcpyHostToDevice);
+    hipError_t r = copy(ctx, w.pivot, local_best, 8ull * nw, hipMemcpyHostToDevice);
     CorrDims cd;
     cd.add(L);
     if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 0, ctx->stream);
     if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
-    if (r == hipSuccess) r = hipMemcpy(w.pivot, pivot, 8ull * nw, hipMemcpyHostToDevice);
-    if (r == hipSuccess) r = hipMemcpy(w.local_best, local_best, 8ull * nw, hipMemcpyHostToDevice);
-    if (r == hipSuccess) r = hipMemcpy(w.best, best, 8ull * nw, hipMemcpyHostToDevice);
+    if (r == hipSuccess) r = copy(ctx, w.pivot, pivot, 8ull * nw, hipMemcpyHostToDevice);
+    if (r == hipSuccess) r = copy(ctx, w.local_best, local_best, 8ull * nw, hipMemcpyHostToDevice);
+    if (r == hipSuccess) r = copy(ctx, w.best, best, 8ull * nw, hipMemcpyHostToDevice);
     if (r == hipSuccess) r = launch_corr(ctx->d_walks, ctx->d_one, 1, cd, 2, ctx->stream);
     if (r == hipSuccess)
         r = launch_fit(ctx->d_walks, ctx->d_one, 1, tabs, seg_uniform(1, L), kFitPivot, ctx->stream);
