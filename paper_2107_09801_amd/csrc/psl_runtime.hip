@@ -11,8 +11,7 @@ using namespace psl_rt;
 // Fixed scratch of psl_eval_neighbourhood_noalloc: the evaluation plan's
 // arrays of one walk (work items, partial sums, the matrix path's digits and
 // prefix sums, chunk suffix arrays, near-peak list, combine minima, segment map,
-// choice record), carved per
-// call. Every device the library runs on holds one copy until the process
+// choice record), carved per call. Every device the library runs on holds one copy until the process
 // ends, and every call on that device shares it. Host code reaches it only
 // through the address hipGetSymbolAddress returns for the device (kept per
 // device below); the array's own name is a host-side stand-in.
@@ -716,9 +715,8 @@ static psl_status build_plan(psl_ctx *ctx, BatchPlan &pl, const uint32_t *ids, u
     }
     // matrix path: per walk of at least kSplitMinL elements (not for launches
     // with less work than kSplitMinCand candidates per shift): its digit records,
-    // prefix and partial
-    // sums and matrix items (walk, tile, k-split). Workgroup i runs on XCD
-    // i mod 8: each walk's items (cost: the chunks of its k-split) form one
+    // prefix and partial sums and matrix items (walk, tile, k-split). Workgroup i
+    // runs on XCD i mod 8: each walk's items (cost: the chunks of its k-split) form one
     // piece, or several of consecutive items when the walk holds more than
     // 1/16 of the launch's cost; the pieces are dealt to 8 queues (costliest
     // first, each to the least loaded queue) and the launch order interleaves
